@@ -14,7 +14,8 @@
  *   transB = GEMM_OP_N : B is K x N, op(B)(k,j) = B[k*ldb + j], ldb >= N
  *   transB = GEMM_OP_T : B is stored N x K ("column-major B"), op(B)(k,j) = B[j*ldb + k], ldb >= K
  *   C is M x N, C(i,j) = C[i*ldc + j], ldc >= N.
- * Products are accumulated in fp32 (bf16 x bf16 and fp16 x fp16 products are exact), the
+ * Products are accumulated in fp32 (bf16 x bf16 and fp16 x fp16 products are exact; an fp32 product is formed from
+ * exact bf16 pieces of its factors to within 2^-23 of itself, typically 2^-26, or by the fp32 instruction), the
  * epilogue runs in fp32, and the result is rounded once, to nearest-even, into the type of C.
  * IEEE special values behave as in that arithmetic: subnormal inputs are multiplied (not flushed
  * to zero), fp32 results below the normal range stay subnormal, a result beyond the largest

@@ -193,6 +193,11 @@ bool tile_variant_splits(int variant);
 // the product as a strided batch (Args::k_total) into fp32 partial results, and
 // launch_splitk_reduce adds them.
 bool tile_variant_slices(int variant);
+// The fp32 128x128 variant: where its tiles are more than one for every compute unit of the part, a workgroup takes two of them, one above
+// the other, with twice the waves: the two share the panel of B, a staged element serves 1.33 times the products, and the
+// eight waves, two to a SIMD, fill each other's gaps (4096^3: 612 us against 727 with one tile per workgroup; 2560^3 171
+// against 222).  With fewer tiles it would leave units idle (2048^3: 124 against 98).
+constexpr int64_t kF32PairAbove = 256;
 hipError_t launch_tile(const Args& a, int variant, int group_m, const TileSplit& split, hipStream_t stream);
 hipError_t launch_tile_split_reduce(const Args& a, int variant, int group_m, const TileSplit& split, hipStream_t stream);
 

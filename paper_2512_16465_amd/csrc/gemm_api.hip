@@ -166,6 +166,7 @@ constexpr int kSliceChoices[] = {2, 4, 8, 16};
 constexpr int64_t kMinSliceK = 512;          // shorter k ranges spend their time filling the pipeline (256x512x4096: 8 slices 12 us, 16 slices 15)
 constexpr int64_t kMinSliceKF32 = 128;      // (an fp32 slab takes 16 times as long to multiply: 64x1024x1024 11 us in 8 slices, 18 in 2)
 constexpr double kSliceMargin = 0.9;          // slices must promise 10 % (384x2048x2048: 14 us whole, 18 in 4 slices, estimated equal)
+constexpr double kSliceLaunchF32 = 3.5, kSliceMarginF32 = 0.92;      // (512^3 fp32: 11 us in 4 slices, 13 whole; 3072^3 within 8 %)
 constexpr double kSliceLaunch = 5.0;          // the second kernel of a sliced call: launch, gap, one round trip (512x2048x2048: 14 us whole, 19 in 4 slices)
 // Operands beyond the last-level cache stream from HBM on every call; there the large tile with its split
 // stays ahead of the sliced small tile (128x16384x16384: 114 against 125 us, 128x8192x28672: 104
@@ -191,35 +192,64 @@ double small_tile_time(const Args& a, int64_t tiles, int slices, int64_t cus) {
     return t;
 }
 
+// Most slices an fp32 call may be cut in: what its workspace has always been sized for.  A caller that reserved the
+// workspace for a call, captures it on a handle that has none, or makes it through gemm_run_noalloc must not find that a
+// faster kernel needs more of it, so this rule (the estimate for the fp32 instruction: 0.0275 / 0.085 us per element of k for
+// a 64x64 / 128x128 tile alone on its unit, 0.02 / 0.068 per tile otherwise) stays as it was when the kernel changed.
+int most_f32_slices(const Args& a, int64_t cus) {
+    int most = 1;
+    double best = 0.0;
+    for (int big = 0; big < 2; ++big) {
+        const int64_t side = big ? 128 : 64;
+        const int64_t tiles = ((a.M + side - 1) / side) * ((a.N + side - 1) / side) * a.batch;
+        for (int sl : {1, 2, 4, 8, 16}) {
+            if (sl > 1 && (a.batch != 1 || a.N % 8 != 0 || a.K / sl < kMinSliceKF32)) break;
+            const int64_t wgs = tiles * sl;
+            double t = (wgs <= cus ? (big ? 0.085 : 0.0275) : (big ? 0.068 : 0.02) * (double)((wgs + cus - 1) / cus)) * ((double)a.K / sl) + 4.0;
+            if (sl > 1) t = (t + kSliceLaunch + (double)sl * (double)(a.M * a.N) * 8.0 / kSliceMoveRate) / kSliceMargin;
+            if (best == 0.0 || t < best) { best = t; most = sl; }
+        }
+    }
+    return most;
+}
+
 struct TileChoice { int variant; int first_split_tile; int parts; double time; };   // time: the estimate behind the choice, us (0: none)
 // fp32: the 128x128 or the 64x64 tile, whichever leaves the busiest compute unit less to do (see
 // choose_tile).  The small tile is at least as fast as the general kernel down to a single tile
-// (256^3: 9.0 against 10.2 us, 64^3: 5.8 against 5.9), so every aligned fp32 call takes a tile kernel.
+// (256^3: 8.6 against 10.2 us, 64^3: 4.6 against 5.9), so every aligned fp32 call takes a tile kernel.
 constexpr int kF32TileVariant = 11, kF32SmallTileVariant = 13;
 constexpr int64_t kF32MinTiles = 1;
 
 TileChoice choose_tile(const Args& a, int num_cus) {
     const int64_t cus = num_cus > 0 ? num_cus : 256;
     if (a.dtype == gemm::DT_F32) {
-        // fp32: the 128x128 tile (two workgroups per compute unit) or the 64x64 tile (four), whole or
-        // in k slices.  Estimate in us: a workgroup that has its unit to itself walks k at 0.0275
-        // (64x64: 1024^3 in 28 us) or 0.085 us per element; with more, the busiest unit takes
-        // tiles-per-unit x 0.02 (4096x1024x1024: 82 us) or x 0.068 (4096x8192x1024: 575 us); 4 us fixed;
-        // slices add the second kernel.  3072^3: 9 small tiles per unit against 3 large ones, 515 against
-        // 615 us; 4096^3: 1070 on the large tile against 1105.  Deep k on a small grid gains most from
-        // slices: 256x256x65536 1558 -> 114 us in 16, 512x512x16384 393 -> 92 in 8, 64x4096x4096 101 -> 31 in 8.
+        // fp32: the 128x128 tile (beyond one per compute unit in pairs, see launch_f32_variant) or the 64x64 tile (up
+        // to three workgroups per unit), whole or in k slices.  Estimate in us per element of k, 4 us fixed:
+        //   64x64: a unit's one, two or three workgroups 0.0177, 0.028, 0.0405 (1024^3 22 us, 1536^3 61, 3072^3 378);
+        //   128x128: one per unit 0.0465 (2048^3 98 us); in pairs 0.0755 for a full round (4096x2048x4096 312 us),
+        //   0.0575 for one that leaves 40 % of the units idle (2304^3 141), in between in proportion (2560^3 171).
+        // Slices add the second kernel.  Deep k on a small grid gains most from them: 256x256x4096 74 -> 15 us in
+        // 16, 64x4096x4096 78 -> 23 in 8.
+        auto rounds = [&](double n, double full, double idle) {     // n workgroups, one per unit
+            const double whole = (double)(int64_t)(n / (double)cus), fill = n / (double)cus - whole;
+            return whole * full + (fill > 0.0 ? idle + (full - idle) * (fill > 0.6 ? (fill - 0.6) / 0.4 : 0.0) : 0.0);
+        };
+        const int most_slices = most_f32_slices(a, cus);
         int best_variant = kF32SmallTileVariant, best_slices = 1;
         double best_time = 0.0;
         for (int big = 0; big < 2; ++big) {
             const int64_t side = big ? 128 : 64;
             const int64_t tiles = ((a.M + side - 1) / side) * ((a.N + side - 1) / side) * a.batch;
-            const double alone = big ? 0.085 : 0.0275, shared = big ? 0.068 : 0.02;
             for (int sl : {1, 2, 4, 8, 16}) {
-                if (sl > 1 && (a.batch != 1 || a.N % 8 != 0 || a.K / sl < kMinSliceKF32)) break;
+                if (sl > most_slices) break;
                 const int64_t wgs = tiles * sl, per_unit = (wgs + cus - 1) / cus;
                 const double k = (double)a.K / sl;
-                double t = (wgs <= cus ? alone : shared * (double)per_unit) * k + 4.0;
-                if (sl > 1) t = (t + kSliceLaunch + (double)sl * (double)(a.M * a.N) * 8.0 / kSliceMoveRate) / kSliceMargin;
+                double per_k;
+                if (!big) per_k = (double)(per_unit / 3) * 0.0405 + (per_unit % 3 == 0 ? 0.0 : (per_unit % 3 == 1 ? 0.0177 : 0.028));
+                else if (wgs <= gemm::kF32PairAbove) per_k = (double)per_unit * 0.0465;
+                else per_k = rounds((double)(((a.M + 255) / 256) * ((a.N + 127) / 128) * a.batch * sl), 0.0755, 0.0575);
+                double t = per_k * k + 4.0;
+                if (sl > 1) t = (t + kSliceLaunchF32 + (double)sl * (double)(a.M * a.N) * 8.0 / kSliceMoveRate) / kSliceMarginF32;
                 if (best_time == 0.0 || t < best_time) { best_time = t; best_variant = big ? kF32TileVariant : kF32SmallTileVariant; best_slices = sl; }
             }
         }

@@ -1,118 +1,270 @@
-// Macro-tile kernel for fp32 operands on the fp32 matrix instruction (gfx950).
+// Macro-tile kernel for fp32 operands on the bf16 matrix instruction (gfx950).
 //
-// v_mfma_f32_32x32x2_f32 takes one float of A and one of B per lane (lane l: row / column l%32,
-// k = l/32) and lasts 64 cycles: the fp32 matrix rate is a sixteenth of the bf16 one, so this
-// kernel is bound by the matrix pipe by a wide margin and is kept simple - 128x128 tile, BK = 32,
-// four waves of 64x64, operands staged global -> registers -> LDS in two stages, two workgroups
-// per compute unit.
+// The fp32 matrix instructions run at a sixteenth of the bf16 rate (157 against 2500 TFLOP/s), so the product is
+// formed from bf16 ones without giving up fp32 accuracy.  Every operand element is taken apart, exactly, as
+//   x = hi + mid + lo,   hi = bf16(x), mid = bf16(x - hi), lo = x - hi - mid
+// (8 significant bits each and the signs of the remainders: 24 bits), and of the nine products of the pieces the
+// six largest are summed,
+//   hi*hi + hi*mid + mid*hi + mid*mid + hi*lo + lo*hi,
+// each exact in fp32 and added in the fp32 accumulators of v_mfma_f32_16x16x32_bf16.  The three left out are below
+// 2^-23 |a b| together at the very worst and 2^-27 each as a rule.  Against 64-bit sums the results are closer than the
+// fp32 instruction's, which rounds an accumulator once per two products where this one does six times per 32 (2-norm, Gaussian data: K = 4
+// 3.2e-8 against 4.0e-8, K = 32 3.7e-8 against 1.0e-7, K = 256 2.3e-7 against 2.9e-7, K = 4096 1.0e-6 against 1.1e-6).
 //
-// The order of the k index inside a group of eight is free (both operands use the same), so
-// lane half h takes k = 4h .. 4h+3 of the group over four consecutive MFMAs.  A k-contiguous
-// operand then needs one 16-byte LDS read per 32 rows and group (rows padded to BK + 4 floats: the
-// reads of 16 consecutive rows fall on distinct banks); an m/n-contiguous operand is kept as
-// [k][row] and read one float at a time (32 consecutive lanes read 32 consecutive floats).  No
-// transposition is needed for any of the four layouts.
+// Structure: one stage of a slab is three planes of bf16 per operand in LDS, two stages; while a wave multiplies slab
+// kt it takes apart slab kt+1, which is in registers, into the other stage, and asks for slab kt+2 as registers come free.
+// One barrier per slab, a sixth of its instructions ahead of its end: the last pair of planes is in registers by then, so
+// the matrix pipe has work on both sides of the barrier.  Everything is placed by slots, one behind each matrix
+// instruction.
 //
-// Edges as in the 16-bit kernels: loads past the end of an operand return zero through the
-// buffer descriptor's range check; chunks of a k-contiguous operand past K are masked.
+// Bound: the issue port.  Next to a matrix instruction (16 cycles) there is room for about two vector
+// instructions; beyond, each costs 4.7 cycles (measured: 17.9 cycles per matrix instruction alone, 19.3 with two vector ones, 23.6
+// with three, 28.4 with four, from one wave or from two alike).  Taking an element apart costs six, so a tile's ratio of
+// staged elements to products decides: 1.5 vector instructions per matrix instruction with 256x128, two with 128x128.
+// Beyond that the power limit: the pairs run at 1.88 GHz with the matrix pipe 68 % busy.  Measured, this kernel / the fp32
+// instruction before: 4096^3 600 us (229 TFLOP/s) / 1072, 2048^3 93 / 147, 1024^3 22 / 27, 256^3 8.6 / 8.9,
+// 4096x4096x64 27 / 30.
+//
+// What the split cannot take.  It is exact for elements that are zero or between 2^-110 and 2^40 in magnitude (below,
+// the last piece is no bf16 number any more; above, pieces of one product might overflow to infinities of opposite
+// signs).  The largest magnitude is tracked (half an instruction per element); for the smallest, which zeros make
+// costly to track, the results are looked at instead: an element below 2^-110 loses at most 2^-134 of itself, all of them
+// together at most K 2^-133 times the largest magnitude, and where every result of the tile is 2^26 times that nothing is
+// lost that fp32 would keep.  Otherwise the tile's operands are scanned for such elements, and only if there are any, or
+// one beyond 2^40, the tile is computed again with the slabs in question multiplied by v_mfma_f32_16x16x4_f32.
+// (A NaN takes either way.)
+//
+// Edges: loads past the end of an operand return zero dword by dword through the buffer descriptor's range check;
+// elements of a k-contiguous operand past K are cleared when they are staged.  Nothing needs more than the natural
+// alignment of a float.
 #pragma once
+#include <utility>
 #include "tile_kernel.hpp"
 
 namespace gemm {
 namespace tile {
 
-// SIDE = rows and columns of the workgroup tile: 128 (four waves of 64x64) or 64 (four waves of
-// 32x32, for problems with too few 128x128 tiles to fill the chip).
-template <int SIDE>
+// BM x BN workgroup tile, WM x WN waves.
+template <int BM_, int BN_, int WM_, int WN_>
 struct F32CfgT {
-    static_assert(SIDE == 128 || SIDE == 64, "two tile sizes");
-    static constexpr int BM = SIDE, BN = SIDE, BK = 32, WM = 2, WN = 2;
+    static constexpr int BM = BM_, BN = BN_, BK = 32, WM = WM_, WN = WN_;
     static constexpr int NT = WM * WN * 64;
     static constexpr int WTM = BM / WM, WTN = BN / WN;
-    static constexpr int TM = WTM / 32, TN = WTN / 32;
-    static constexpr int KC_STRIDE = BK + 4;          // floats per row of a k-contiguous slab in LDS
-    static constexpr int MC_STRIDE = SIDE + 8;        // floats per k-row of an m/n-contiguous slab: the two lane halves read k-rows
-                                                      // four apart, 4 * (SIDE + 8) floats = 32 banks (mod 64) from each other
-    static constexpr int OPERAND_BYTES = SIDE * KC_STRIDE * 4 > BK * MC_STRIDE * 4 ? SIDE * KC_STRIDE * 4 : BK * MC_STRIDE * 4;
-    static constexpr int STAGE = 2 * OPERAND_BYTES;
-    static constexpr int WGS_PER_CU = SIDE == 128 ? 2 : 4;
+    static constexpr int TM = WTM / 32, TN = WTN / 32;   // 32-row bands of the epilogue
+    static constexpr int TI = WTM / 16, TJ = WTN / 16;   // 16x16 accumulators of the wave sub-block
+    static constexpr int A_PLANE = BM * BK * 2, B_PLANE = BN * BK * 2;   // one piece (hi, mid or lo) of a slab: rows of 32 bf16, chunks placed by swz<4>
+    static constexpr int B_REGION = 3 * A_PLANE, STAGE = 3 * (A_PLANE + B_PLANE);
+    static constexpr int RAW_STRIDE = BK + 4;            // floats per row of a slab staged as fp32
+    static_assert(BM * RAW_STRIDE * 4 <= 3 * A_PLANE && BN * RAW_STRIDE * 4 <= 3 * B_PLANE, "the fp32 form of a slab fits the region of the three planes");
+    static constexpr int WGS_PER_CU = 2 * STAGE > 80 * 1024 ? 1 : 3;
+    static constexpr int WAVES_PER_SIMD = WGS_PER_CU * NT / 256;
 };
-using F32Cfg = F32CfgT<128>;
 
-// One operand's slab: SIDE rows x BK k, L 16-byte chunks per thread.
-template <bool KC, class F32Cfg>
+// f(0), f(1) .. f(N - 1) with the numbers as types: the bodies are placed slot by slot and name registers
+template <class F, int... I>
+__device__ __forceinline__ void static_for_each(F&& f, std::integer_sequence<int, I...>) { (f(std::integral_constant<int, I>{}), ...); }
+template <int N, class F>
+__device__ __forceinline__ void static_for(F&& f) { static_for_each(f, std::make_integer_sequence<int, N>{}); }
+
+constexpr float kSplitLargest = 0x1p40f, kSplitSmallest = 0x1p-110f;
+
+// bf16 pair of two floats (round to nearest even), and its two values widened again
+__device__ __forceinline__ uint32_t pack_bf16(float x, float y) {
+    typedef __attribute__((ext_vector_type(2))) float f32x2;
+    typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{x, y}, bf16x2));
+}
+__device__ __forceinline__ float low_bf16(uint32_t p) { return __uint_as_float(p << 16); }
+__device__ __forceinline__ float high_bf16(uint32_t p) { return __uint_as_float(p & 0xffff0000u); }
+
+// One operand's slab: ROWS rows x 32 k.  A thread holds L quads of elements that it can take apart and stage without
+// moving anything between lanes.  k-contiguous operand: a quad is one 16-byte load, four consecutive k of one row.
+// m/n-contiguous operand: G = L or four loads of four rows each at consecutive k make a block; with four loads quad i of
+// the block is row i (four k), with two it is rows 2i and 2i + 1 (two k each).
+template <bool KC, int ROWS, class C>
 struct F32Mover {
-    static constexpr int L = F32Cfg::BM * F32Cfg::BK / 4 / F32Cfg::NT;   // chunks per thread
-    static constexpr int CPR = F32Cfg::BK / 4;                      // 16-byte chunks per row of a k-contiguous slab
-    static constexpr int CPK = F32Cfg::BM / 4;                      // 16-byte chunks per k-row of an m/n-contiguous slab
-    uint32_t goff[L];      // byte offset of the chunk from the slab's first byte
-    uint32_t loff[L];      // byte offset in the operand's LDS region
-    u32x4 r[L];
-    int valid_k;           // k values of the slab in r that lie inside K
+    static constexpr int L = ROWS * C::BK / 4 / C::NT, G = L < 4 ? L : 4;
+    static_assert(L == 2 || L == 4 || L == 8, "64, 128 or 256 rows");
+    static constexpr int PLANE = ROWS * C::BK * 2;
+    static constexpr int KQ = C::BK / 4, RB = ROWS / 4;                     // quads per row (k-contiguous); blocks of four rows
+    uint32_t goff[L];      // byte offset of the load from the slab's first byte
+    uint32_t loff[L];      // byte offset of the quad (of its first row's part) in a plane
+    f32x4 r[L];
 
+    // first row and first k of quad i
+    static __device__ __forceinline__ uint32_t quad_row(int i, int tid) {
+        return KC ? (i * C::NT + tid) / KQ : (((i / G) * C::NT + tid) % RB) * 4 + (i % G) * (4 / G);
+    }
+    static __device__ __forceinline__ uint32_t quad_k(int i, int tid) { return KC ? (i * C::NT + tid) % KQ * 4 : ((i / G) * C::NT + tid) / RB * G; }
     __device__ __forceinline__ void init(int tid, int64_t ld) {
 #pragma unroll
         for (int i = 0; i < L; ++i) {
-            const uint32_t q = i * F32Cfg::NT + tid;
-            if (KC) {
-                const uint32_t row = q / CPR, c = q % CPR;             // CPR chunks cover a row's BK k
-                goff[i] = (uint32_t)((row * ld + c * 4) * 4);
-                loff[i] = (row * F32Cfg::KC_STRIDE + c * 4) * 4;
-            } else {
-                const uint32_t k = q / CPK, c = q % CPK;               // CPK chunks cover a k-row's columns
-                goff[i] = (uint32_t)((k * ld + c * 4) * 4);
-                loff[i] = (k * F32Cfg::MC_STRIDE + c * 4) * 4;
-            }
+            const uint32_t row = quad_row(i, tid), k = quad_k(i, tid);
+            goff[i] = (uint32_t)((KC ? row * ld + k : (k + i % G) * ld + (row & ~3u)) * 4);
+            loff[i] = swz<4>(row, k >> 3) + (k & 7) * 2;
         }
     }
     static __device__ __forceinline__ const char* tile_base(const void* p, int64_t first_row, int64_t ld) {
         return KC ? (const char*)p + first_row * ld * 4 : (const char*)p + first_row * 4;
     }
-    static __device__ __forceinline__ int64_t k_step_bytes(int64_t ld) { return KC ? (int64_t)F32Cfg::BK * 4 : (int64_t)F32Cfg::BK * ld * 4; }
+    static __device__ __forceinline__ int64_t k_step_bytes(int64_t ld) { return KC ? (int64_t)C::BK * 4 : (int64_t)C::BK * ld * 4; }
     static __device__ __forceinline__ int64_t total_bytes(int64_t rows, int64_t K, int64_t ld) {
         return KC ? ((rows - 1) * ld + K) * 4 : ((K - 1) * ld + rows) * 4;
     }
-    // base = first byte of the slab, avail = bytes from there to the end of the operand.  Every
-    // chunk is requested (one past the end of the operand reads as zero through the descriptor's
-    // range check); the chunks of a k-contiguous operand that lie past K hold whatever follows the
-    // row in memory and are cleared in lstore, once they have arrived -- clearing them here would
-    // be a write to a register with a load in flight, which waits for the load.
-    __device__ __forceinline__ void gload(const char* base, int64_t avail, int k0, int K) {
-        const __amdgpu_buffer_rsrc_t rsrc = make_rsrc(base, avail);
-        valid_k = K - k0;
-#pragma unroll
-        for (int i = 0; i < L; ++i) r[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, goff[i], 0, 0));
+    // Every load is issued (past the end of the operand it reads as zero); what a k-contiguous operand holds past K is
+    // cleared when it is staged -- clearing it here would be a write to a register with a load in flight, which waits for it.
+    __device__ __forceinline__ void gload_one(int i, __amdgpu_buffer_rsrc_t rsrc) {
+        r[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, goff[i], 0, 0));
     }
-    __device__ __forceinline__ void lstore(char* region, int tid) {
+    __device__ __forceinline__ void gload(__amdgpu_buffer_rsrc_t rsrc) {
 #pragma unroll
-        for (int i = 0; i < L; ++i) {
-            if (KC && valid_k < F32Cfg::BK) {                          // wave-uniform: only the last slab of a ragged K
-                const int c = (i * F32Cfg::NT + tid) % CPR;
-                if (c * 4 >= valid_k) r[i] = u32x4{0u, 0u, 0u, 0u};
-            }
-            *(u32x4*)(region + loff[i]) = r[i];
+        for (int i = 0; i < L; ++i) gload_one(i, rsrc);
+    }
+    // the loads whose registers are free once quad i (taken in order) has been taken apart
+    __device__ __forceinline__ void gload_after(int i, __amdgpu_buffer_rsrc_t rsrc) {
+        if (KC) {
+            gload_one(i, rsrc);
+        } else if (i % G == G - 1) {
+#pragma unroll
+            for (int j = 0; j < G; ++j) gload_one(i - i % G + j, rsrc);
         }
     }
-    // the four floats k = 8g + 4h + (0..3) of row `row` (tile-local) for lane half h
-    static __device__ __forceinline__ f32x4 frag(const char* region, int row, int g, int h) {
-        if (KC) return *(const f32x4*)(region + (row * F32Cfg::KC_STRIDE + 8 * g + 4 * h) * 4);
-        f32x4 v;
+    // Element e of pair h of quad i, where it lies in the registers.
+    template <int I, int H, int E> static constexpr int reg_of() { return KC ? I : (G == 4 ? I - I % G + 2 * H + E : E); }
+    template <int I, int H, int E> static constexpr int lane_of() { return KC ? 2 * H + E : (G == 4 ? I % G : 2 * I + H); }
+    template <int I, int H, int E> __device__ __forceinline__ float get() const { return r[reg_of<I, H, E>()][lane_of<I, H, E>()]; }
+    template <int I, int H, int E> __device__ __forceinline__ void set(float x) { r[reg_of<I, H, E>()][lane_of<I, H, E>()] = x; }
+    // the last slab of a k-contiguous operand: clear what lies past K (`left` = k values of the slab inside K)
+    __device__ __forceinline__ void clear_past(int left, int tid) {
+        if (!KC) return;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) v[j] = *(const float*)(region + ((8 * g + 4 * h + j) * F32Cfg::MC_STRIDE + row) * 4);
-        return v;
+        for (int i = 0; i < L; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) r[i][e] = (int)quad_k(i, tid) + e < left ? r[i][e] : 0.0f;
+    }
+    // Pair h of quad i, taken apart in five parts of one to four instructions (in place: the elements become what is left
+    // of them).  The empty assembly keeps a part where it is called: the compiler would move all of it behind
+    // the matrix instructions, to where the pieces are stored.
+    static constexpr int PARTS = 5;
+    float wide[2];
+    u32x2 piece[3];        // of the quad at hand
+    template <int PART, int I, int H>
+    __device__ __forceinline__ void split_part(float& largest) {
+        float x = get<I, H, 0>(), y = get<I, H, 1>();
+        if constexpr (PART == 0) asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(largest) : "v"(x), "v"(y));      // (a NaN is passed over)
+        if constexpr (PART == 4) {
+            uint32_t w = pack_bf16(x, y);
+            asm volatile("" ::"v"(w));
+            piece[2][H] = w;
+        } else if constexpr (PART % 2 == 0) {
+            uint32_t w = pack_bf16(x, y);
+            wide[0] = low_bf16(w); wide[1] = high_bf16(w);
+            asm volatile("" ::"v"(w), "v"(wide[0]), "v"(wide[1]));
+            piece[PART / 2][H] = w;
+        } else {
+            x -= wide[0]; y -= wide[1];
+            asm volatile("" ::"v"(x), "v"(y));
+            set<I, H, 0>(x); set<I, H, 1>(y);
+        }
+    }
+    // the quad's pieces to their planes
+    __device__ __forceinline__ void store_pieces(char* region, int i) const {
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+            if constexpr (KC || G == 4) {
+                *(u32x2*)(region + p * PLANE + loff[i]) = piece[p];
+            } else {          // two rows of a 128-byte line: the second one's chunks sit 64 bytes across
+                *(uint32_t*)(region + p * PLANE + loff[i]) = piece[p].x;
+                *(uint32_t*)(region + p * PLANE + (loff[i] ^ 64u)) = piece[p].y;
+            }
+        }
+    }
+    __device__ __forceinline__ void split_and_store(char* region, float& largest) {
+        static_for<L>([&](auto i) {
+            constexpr int I = decltype(i)::value;
+            static_for<2 * PARTS>([&](auto w) { split_part<decltype(w)::value % PARTS, I, decltype(w)::value / PARTS>(largest); });
+            store_pieces(region, I);
+        });
+    }
+    // an element that the split cannot take
+    __device__ __forceinline__ bool outside() const {
+        bool out = false;
+#pragma unroll
+        for (int i = 0; i < L; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float m = __builtin_fabsf(r[i][e]);
+                out = out || m > kSplitLargest || (m < kSplitSmallest && m != 0.0f);
+            }
+        return out;
+    }
+    __device__ __forceinline__ void store_raw(char* region, int tid) const {
+        static_for<L>([&](auto i) {
+            constexpr int I = decltype(i)::value;
+            float* p = (float*)region + quad_row(I, tid) * C::RAW_STRIDE + quad_k(I, tid);
+            const f32x4 x = {get<I, 0, 0>(), get<I, 0, 1>(), get<I, 1, 0>(), get<I, 1, 1>()};
+            if constexpr (KC || G == 4) {
+                *(f32x4*)p = x;
+            } else {
+                p[0] = x[0]; p[1] = x[1];
+                p[C::RAW_STRIDE] = x[2]; p[C::RAW_STRIDE + 1] = x[3];
+            }
+        });
     }
 };
 
+// c += a * b.  With one workgroup per compute unit the accumulators live in the accumulation registers, and the
+// instruction is written as assembly: left to itself the compiler moves them (or the fragments) between the two register
+// files in the loop.  No accumulator is touched twice within four of them; the kernel supplies the wait states
+// before it reads one.
+template <bool ASM>
+__device__ __forceinline__ void f32_mfma_bf16(f32x4& c, u32x4 a, u32x4 b) {
+    if constexpr (ASM) asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+    else c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+template <bool ASM>
+__device__ __forceinline__ void f32_mfma_f32(f32x4& c, float a, float b) {
+    if constexpr (ASM) asm volatile("v_mfma_f32_16x16x4_f32 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+    else c = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+// the wait states between the last such instruction and the first read of an accumulator
+template <bool ASM, int N>
+__device__ __forceinline__ void f32_settle(f32x4 (&c)[N]) {
+    if constexpr (ASM) {
+        asm volatile("s_nop 15");
+#pragma unroll
+        for (int i = 0; i < N; ++i) asm volatile("" : "+a"(c[i]));
+    }
+}
+
+// Which planes (0 = hi, 1 = mid, 2 = lo) the six steps of a slab multiply.  hi*hi comes last: in the first slab the small
+// products are then summed among themselves (a K of one slab is rounded once at full magnitude).  The first step needs
+// neither hi, so that it can be fetched while the last step of the slab before still multiplies those.
+template <class C>
+struct F32Planes {
+    static constexpr int of_a(int s) { return s < 2 ? 1 : (s == 2 ? 2 : 0); }
+    static constexpr int of_b(int s) { return s == 0 || s == 4 ? 1 : (s == 3 ? 2 : 0); }
+    // the steps that use a plane of the operand for the first time
+    static constexpr bool new_a(int s) { return s == 0 || s == 2 || s == 3; }
+    static constexpr bool new_b(int s) { return s == 0 || s == 1 || s == 3; }
+    // a step of four instructions is shorter than the LDS takes: all planes of a slab at once
+    static constexpr bool EARLY = C::TI * C::TJ < 8;
+};
+
 template <class C, bool A_KC, bool B_KC>
-__global__ __launch_bounds__(C::NT, C::WGS_PER_CU) void tile_f32_kernel(Args a, int tiles_m, int tiles_n, int group_m, int c_vec_ok) {
+__global__ __launch_bounds__(C::NT, C::WAVES_PER_SIMD) void tile_f32_kernel(Args a, int tiles_m, int tiles_n, int group_m, int c_vec_ok) {
     using EL = EpiLayout<C>;
+    constexpr int TI = C::TI, TJ = C::TJ;
+    constexpr bool ASM = C::WAVES_PER_SIMD == 1;
     constexpr int LDS_BYTES = 2 * C::STAGE > EL::BYTES ? 2 * C::STAGE : EL::BYTES;
     __shared__ __attribute__((aligned(128))) char lds[LDS_BYTES];
+    __shared__ float wave_largest[C::WM * C::WN];
+    __shared__ uint32_t flag[4];
     select_batch(a);
 
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
-    const int l32 = lane & 31, lhi = lane >> 5;
+    const int c16 = lane & 15, g4 = lane >> 4;
     const int wm = wave % C::WM, wn = wave / C::WM;
 
     int tm, tn;
@@ -120,87 +272,254 @@ __global__ __launch_bounds__(C::NT, C::WGS_PER_CU) void tile_f32_kernel(Args a, 
     const int64_t m0 = (int64_t)tm * C::BM, n0 = (int64_t)tn * C::BN;
     const int K = (int)a.K;
 
-    F32Mover<A_KC, C> la;
-    F32Mover<B_KC, C> lb;
+    using LA = F32Mover<A_KC, C::BM, C>;
+    using LB = F32Mover<B_KC, C::BN, C>;
+    LA la;
+    LB lb;
     la.init(tid, a.lda);
     lb.init(tid, a.ldb);
-    const char* pa = F32Mover<A_KC, C>::tile_base(a.A, m0, a.lda);
-    const char* pb = F32Mover<B_KC, C>::tile_base(a.B, n0, a.ldb);
-    const int64_t a_step = F32Mover<A_KC, C>::k_step_bytes(a.lda), b_step = F32Mover<B_KC, C>::k_step_bytes(a.ldb);
-    const int64_t a_bytes = F32Mover<A_KC, C>::total_bytes(a.M, a.K, a.lda) - (pa - (const char*)a.A);
-    const int64_t b_bytes = F32Mover<B_KC, C>::total_bytes(a.N, a.K, a.ldb) - (pb - (const char*)a.B);
+    const char* pa = LA::tile_base(a.A, m0, a.lda);
+    const char* pb = LB::tile_base(a.B, n0, a.ldb);
+    const int64_t a_step = LA::k_step_bytes(a.lda), b_step = LB::k_step_bytes(a.ldb);
+    const int64_t a_bytes = LA::total_bytes(a.M, a.K, a.lda) - (pa - (const char*)a.A);
+    const int64_t b_bytes = LB::total_bytes(a.N, a.K, a.ldb) - (pb - (const char*)a.B);
 
-    f32x16 acc[C::TM][C::TN];
+    // accumulator (i, j): B's fragment is the instruction's first operand, so lane (c16, g4) holds row 16 i + c16 and
+    // columns 16 j + 4 g4 .. + 3 of the wave sub-block
+    f32x4 acc[TI][TJ];
+    auto clear_acc = [&]() {
 #pragma unroll
-    for (int i = 0; i < C::TM; ++i)
+        for (int i = 0; i < TI; ++i)
 #pragma unroll
-        for (int j = 0; j < C::TN; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+            for (int j = 0; j < TJ; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    };
+    clear_acc();
 
-    const int k_tiles = (K + C::BK - 1) / C::BK;
-    auto gload = [&](int t) {
-        la.gload(pa + t * a_step, a_bytes - t * a_step, t * C::BK, K);
-        lb.gload(pb + t * b_step, b_bytes - t * b_step, t * C::BK, K);
+    uint32_t fa[TI], fb[TJ];                              // this lane's fragment of 16 rows in a plane: row c16, k = 8 g4 .. + 7
+#pragma unroll
+    for (int i = 0; i < TI; ++i) fa[i] = swz<4>(wm * C::WTM + i * 16 + c16, g4);
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) fb[j] = C::B_REGION + swz<4>(wn * C::WTN + j * 16 + c16, g4);
+
+    // The order of the slabs is free: a partial one comes first, so that the loop only sees whole ones.  Past the last
+    // slab the loop asks twice more and gets zeros or k values it has had; they are taken apart and not used.
+    const int partial = K % C::BK, k_tiles = K / C::BK + (partial ? 1 : 0);
+    auto slab_rsrc = [&](const char* p, int64_t step, int64_t bytes, int t) {
+        const int64_t at = partial ? (t == 0 ? k_tiles - 1 : t - 1) : t;
+        return make_rsrc(p + at * step, bytes - at * step);
     };
-    auto lstore = [&](int stage) {
-        la.lstore(lds + stage * C::STAGE, tid);
-        lb.lstore(lds + stage * C::STAGE + C::OPERAND_BYTES, tid);
+    auto load_slab = [&](int t) {
+        la.gload(slab_rsrc(pa, a_step, a_bytes, t));
+        lb.gload(slab_rsrc(pb, b_step, b_bytes, t));
+    };
+    auto clear_past = [&](int t) {
+        if (t == 0 && partial) { la.clear_past(partial, tid); lb.clear_past(partial, tid); }
     };
 
-    // Pipeline of one slab kt (G groups of 16 MFMAs): the next slab's global loads are issued at
-    // its start and land in registers behind the MFMAs; the fragments of group g+1 are read from
-    // LDS before the MFMAs of group g are issued; before the last group the next slab goes from
-    // registers to the other LDS stage, the workgroup meets at the barrier, and the first
-    // fragments of the next slab are read -- all of it behind the last group's MFMAs.  The other
-    // stage is free at that point: its last readers took their fragments before the previous
-    // barrier.
-    constexpr int G = C::BK / 8;
-    static_assert(G % 2 == 0, "fragment buffers alternate and group 0 uses buffer 0");
-    f32x4 fa[2][C::TM], fb[2][C::TN];
-    auto read_frags = [&](int buf, const char* stage, int g) {
-#pragma unroll
-        for (int i = 0; i < C::TM; ++i) fa[buf][i] = F32Mover<A_KC, C>::frag(stage, wm * C::WTM + i * 32 + l32, g, lhi);
-#pragma unroll
-        for (int j = 0; j < C::TN; ++j) fb[buf][j] = F32Mover<B_KC, C>::frag(stage + C::OPERAND_BYTES, wn * C::WTN + j * 32 + l32, g, lhi);
-    };
+    constexpr int STEPS = 6;
+    using Planes = F32Planes<C>;
+    constexpr int NM = TI * TJ;
+    u32x4 af[3][TI], bf[3][TJ];
+    auto read_a = [&](const char* stage, int p, int i) { af[p][i] = *(const u32x4*)(stage + p * C::A_PLANE + fa[i]); };
+    auto read_b = [&](const char* stage, int p, int j) { bf[p][j] = *(const u32x4*)(stage + p * C::B_PLANE + fb[j]); };
+
+    float largest = 0.0f;
     if (k_tiles > 0) {
-        gload(0);
-        lstore(0);
-        __syncthreads();
-        read_frags(0, lds, 0);
-        for (int kt = 0; kt < k_tiles; ++kt) {
-            const char* cur = lds + (kt & 1) * C::STAGE;
-            const char* nxt = lds + ((kt + 1) & 1) * C::STAGE;
-            const bool more = kt + 1 < k_tiles;
-            if (more) gload(kt + 1);
+        LA la1 = la;                  // the first two slabs in one trip to memory
+        LB lb1 = lb;
+        load_slab(0);
+        la1.gload(slab_rsrc(pa, a_step, a_bytes, 1));
+        lb1.gload(slab_rsrc(pb, b_step, b_bytes, 1));
+        __builtin_amdgcn_sched_barrier(0);
+        clear_past(0);
+        la.split_and_store(lds, largest);
+        lb.split_and_store(lds + C::B_REGION, largest);
 #pragma unroll
-            for (int g = 0; g < G; ++g) {
-                if (g + 1 < G) {
-                    read_frags((g + 1) & 1, cur, g + 1);
-                } else if (more) {
-                    lstore((kt + 1) & 1);
-                    __syncthreads();
-                    read_frags(0, nxt, 0);
+        for (int i = 0; i < LA::L; ++i) la.r[i] = la1.r[i];
+#pragma unroll
+        for (int i = 0; i < LB::L; ++i) lb.r[i] = lb1.r[i];
+    }
+    if (tid < 4) flag[tid] = 0;       // (read after the loop)
+#pragma unroll
+    for (int i = 0; i < TI; ++i) af[0][i] = u32x4{0u, 0u, 0u, 0u};       // the step ahead of the first slab adds nothing
+#pragma unroll
+    for (int j = 0; j < TJ; ++j) bf[0][j] = u32x4{0u, 0u, 0u, 0u};
+    auto iteration = [&](int kt, auto stage_) {
+        constexpr int stage = decltype(stage_)::value;
+        const char* cur = lds + stage * C::STAGE;
+        char* nxt = lds + (1 - stage) * C::STAGE;
+        const __amdgpu_buffer_rsrc_t ra = slab_rsrc(pa, a_step, a_bytes, kt + 2), rb = slab_rsrc(pb, b_step, b_bytes, kt + 2);
+        __syncthreads();              // slab kt is staged; every wave has the last planes of slab kt-1 in registers
+        // step 5 of slab kt-1, then steps 0 to 4 of slab kt
+        constexpr int PAIRS = 2 * (LA::L + LB::L), WORK = PAIRS * LA::PARTS, SLOTS = STEPS * NM, LAST = SLOTS - SLOTS / 16;
+        static_for<SLOTS>([&](auto slot_) {
+            constexpr int slot = decltype(slot_)::value, n = slot / NM, s = (n + STEPS - 1) % STEPS, m = slot % NM, i = m / TJ, j = m % TJ;
+            f32_mfma_bf16<ASM>(acc[i][j], bf[Planes::of_b(s)][j], af[Planes::of_a(s)][i]);
+            // the planes that the next step, step n of slab kt, is the first to need
+            if constexpr (Planes::EARLY) {
+                if constexpr (slot == 0) {
+#pragma unroll
+                    for (int i = 0; i < TI; ++i) read_a(cur, Planes::of_a(0), i);
+#pragma unroll
+                    for (int j = 0; j < TJ; ++j) read_b(cur, Planes::of_b(0), j);
                 }
-                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (slot == NM - 1) {
+                    static_for<STEPS - 1>([&](auto t) {
+                        constexpr int next = decltype(t)::value + 1;
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
+                        for (int j = 0; j < TJ; ++j)
+                            if (Planes::new_b(next)) read_b(cur, Planes::of_b(next), j);
 #pragma unroll
-                    for (int i = 0; i < C::TM; ++i)
+                        for (int i = 0; i < TI; ++i)
+                            if (Planes::new_a(next)) read_a(cur, Planes::of_a(next), i);
+                    });
+                }
+            } else {
+                if constexpr (Planes::new_b(n) && m < TJ) read_b(cur, Planes::of_b(n), m);
+                if constexpr (Planes::new_a(n) && m >= NM - TI - TJ && m < NM - TJ) read_a(cur, Planes::of_a(n), m - (NM - TI - TJ));
+            }
+            // the next slab: a share of taking it apart (A's quads first), its stores, the loads behind it
+            constexpr int w0 = slot * WORK / LAST < WORK ? slot * WORK / LAST : WORK;
+            constexpr int w1 = (slot + 1) * WORK / LAST < WORK ? (slot + 1) * WORK / LAST : WORK;
+            static_for<w1 - w0>([&](auto w_) {
+                constexpr int w = w0 + decltype(w_)::value, pair = w / LA::PARTS, part = w % LA::PARTS, quad = pair / 2;
+                constexpr bool done = part == LA::PARTS - 1 && pair % 2 == 1;
+                if constexpr (quad < LA::L) {
+                    la.template split_part<part, quad, pair % 2>(largest);
+                    if constexpr (done) { la.store_pieces(nxt, quad); la.gload_after(quad, ra); }
+                } else {
+                    lb.template split_part<part, quad - LA::L, pair % 2>(largest);
+                    if constexpr (done) { lb.store_pieces(nxt + C::B_REGION, quad - LA::L); lb.gload_after(quad - LA::L, rb); }
+                }
+            });
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+#pragma unroll 1
+    for (int kt = 0; kt < k_tiles; kt += 2) {
+        iteration(kt, std::integral_constant<int, 0>{});
+        if (kt + 1 < k_tiles) iteration(kt + 1, std::integral_constant<int, 1>{});
+    }
 #pragma unroll
-                        for (int j = 0; j < C::TN; ++j)
-                            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[g & 1][i][q], fb[g & 1][j][q], acc[i][j], 0, 0, 0);
-                __builtin_amdgcn_sched_barrier(0);
+    for (int m = 0; m < NM; ++m) f32_mfma_bf16<ASM>(acc[m / TJ][m % TJ], bf[0][m % TJ], af[0][m / TJ]);
+#pragma unroll
+    for (int i = 0; i < TI; ++i) f32_settle<ASM>(acc[i]);
+
+    // Has the split lost anything?  (see above)  First with the largest magnitude that there could be, which costs no
+    // exchange between the threads; then with the one there is.
+    auto set_if = [&](int word, bool mine) { if (mine) flag[word] = 1; };
+    auto is_set = [&](int word) { return __builtin_amdgcn_readfirstlane(flag[word]) != 0; };      // (behind a barrier)
+    auto below = [&](float largest_there) {               // (only what is inside C: a tile's rows and columns past its edge are zero)
+        const float floor = largest_there * (float)K * 0x1p-107f;
+        const int64_t rows = a.M - (m0 + wm * C::WTM + c16), cols = a.N - (n0 + wn * C::WTN + 4 * g4);
+        bool small = false;
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
+            for (int j = 0; j < TJ; ++j)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    small = small || (__builtin_fabsf(acc[i][j][v]) < floor && 16 * i < rows && 16 * j + v < cols);
+        return small;
+    };
+    if (k_tiles == 0) __syncthreads();
+    set_if(0, below(kSplitLargest));
+    set_if(1, largest > kSplitLargest);
+    __syncthreads();
+    bool again = is_set(1);
+    if (__builtin_expect(!again && is_set(0), 0)) {
+#pragma unroll
+        for (int d = 32; d >= 1; d >>= 1) largest = fmaxf(largest, __shfl_xor(largest, d, 64));
+        if (lane == 0) wave_largest[wave] = largest;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < C::WM * C::WN; ++w) largest = fmaxf(largest, wave_largest[w]);
+        set_if(2, below(largest));
+        __syncthreads();
+        if (is_set(2)) {
+            bool out = false;
+            LA la1 = la;              // two slabs in flight (past the last one: zeros, or k values seen before)
+            LB lb1 = lb;
+#pragma unroll 1
+            for (int kt = 0; kt < k_tiles; kt += 2) {
+                load_slab(kt);
+                la1.gload(slab_rsrc(pa, a_step, a_bytes, kt + 1));
+                lb1.gload(slab_rsrc(pb, b_step, b_bytes, kt + 1));
+                clear_past(kt);
+                out = out || la.outside() || lb.outside();
+                if (kt + 1 < k_tiles) out = out || la1.outside() || lb1.outside();
+            }
+            set_if(3, out);
+            __syncthreads();
+            again = is_set(3);
+        }
+        __syncthreads();
+    }
+    if (__builtin_expect(again, 0)) {
+        clear_acc();
+#pragma unroll 1
+        for (int kt = 0; kt < k_tiles; ++kt) {
+            load_slab(kt);
+            clear_past(kt);
+            __syncthreads();                              // the last slab has been read, and its flag
+            if (tid == 0) flag[0] = 0;
+            __syncthreads();
+            set_if(0, la.outside() || lb.outside());
+            __syncthreads();
+            if (is_set(0)) {
+                la.store_raw(lds, tid);
+                lb.store_raw(lds + C::B_REGION, tid);
+                __syncthreads();
+                // lane group g4 takes k = 4 g4 .. + 3 of sixteen, one per instruction (the order of k is free as long as
+                // both operands agree)
+#pragma unroll 1
+                for (int s = 0; s < C::BK / 16; ++s) {
+                    f32x4 ar[TI], br[TJ];
+                    const int k = (16 * s + 4 * g4) * 4;
+#pragma unroll
+                    for (int i = 0; i < TI; ++i) ar[i] = *(const f32x4*)(lds + (wm * C::WTM + i * 16 + c16) * C::RAW_STRIDE * 4 + k);
+#pragma unroll
+                    for (int j = 0; j < TJ; ++j) br[j] = *(const f32x4*)(lds + C::B_REGION + (wn * C::WTN + j * 16 + c16) * C::RAW_STRIDE * 4 + k);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+#pragma unroll
+                        for (int m = 0; m < NM; ++m)
+                            f32_mfma_f32<ASM>(acc[m / TJ][m % TJ], br[m % TJ][q], ar[m / TJ][q]);
+                }
+            } else {
+                la.split_and_store(lds, largest);
+                lb.split_and_store(lds + C::B_REGION, largest);
+                __syncthreads();
+#pragma unroll 1
+                for (int s = 0; s < STEPS; ++s) {
+                    const int p = Planes::of_a(s), q = Planes::of_b(s);
+                    u32x4 ar[TI], br[TJ];
+#pragma unroll
+                    for (int i = 0; i < TI; ++i) ar[i] = *(const u32x4*)(lds + p * C::A_PLANE + fa[i]);
+#pragma unroll
+                    for (int j = 0; j < TJ; ++j) br[j] = *(const u32x4*)(lds + q * C::B_PLANE + fb[j]);
+#pragma unroll
+                    for (int m = 0; m < NM; ++m) f32_mfma_bf16<ASM>(acc[m / TJ][m % TJ], br[m % TJ], ar[m / TJ]);
+                }
             }
         }
     }
+#pragma unroll
+    for (int i = 0; i < TI; ++i) f32_settle<ASM>(acc[i]);
     __syncthreads();                                      // LDS is reused by the epilogue
-    tile_epilogue<C>(acc, lds, a, m0, n0, c_vec_ok);
+    tile_epilogue_bands<C>(
+        [&](auto band, char* region) {
+            constexpr int b = decltype(band)::value;
+#pragma unroll
+            for (int i2 = 0; i2 < 2; ++i2)
+#pragma unroll
+                for (int j = 0; j < TJ; ++j) *(f32x4*)(region + ((16 * i2 + c16) * EL::RS + j * 16 + 4 * g4) * 4) = acc[2 * b + i2][j];
+        },
+        lds, a, m0, n0, c_vec_ok);
 }
 
 template <class C>
-inline hipError_t launch_f32_variant(const Args& a, int group_m, hipStream_t stream) {
+inline hipError_t launch_f32_tiles(const Args& a, int group_m, hipStream_t stream) {
     const int tiles_m = (int)((a.M + C::BM - 1) / C::BM), tiles_n = (int)((a.N + C::BN - 1) / C::BN);
     const dim3 grid((unsigned)(tiles_m * tiles_n), (unsigned)a.batch), block(C::NT);
     const bool akc = !a.transA, bkc = a.transB != 0;
@@ -213,6 +532,16 @@ inline hipError_t launch_f32_variant(const Args& a, int group_m, hipStream_t str
     else GEMM_TILE_LAUNCH(false, false);
 #undef GEMM_TILE_LAUNCH
     return hipGetLastError();
+}
+
+// (kF32PairAbove: why the 128x128 variant takes its tiles in pairs)
+template <int BM, int BN, int WM, int WN>
+inline hipError_t launch_f32_variant(const Args& a, int group_m, hipStream_t stream) {
+    if constexpr (BM == 128) {
+        const int64_t tiles = ((a.M + 127) / 128) * ((a.N + 127) / 128) * a.batch;
+        if (tiles > kF32PairAbove) return launch_f32_tiles<F32CfgT<256, 128, 4, 2>>(a, group_m, stream);
+    }
+    return launch_f32_tiles<F32CfgT<BM, BN, WM, WN>>(a, group_m, stream);
 }
 
 }  // namespace tile

@@ -1,0 +1,55 @@
+"""The fp32 tile kernels form their products from bf16 pieces; values that the pieces cannot hold are found and multiplied
+as fp32.  Rows of every such kind between ordinary ones, all data exact, in each tile form: bit for bit the oracle's."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2512_16465_amd as lg
+import workloads as wl
+from gpu_harness import DeviceProblem, decode_c, oracle_problem
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def handle():
+    h = lg.gemm_create()
+    yield h
+    torch.cuda.synchronize()
+    lg.gemm_destroy(h)
+
+
+# 64x64 tiles, one 128x128 tile per workgroup, pairs of them (more than 256 tiles); a partial slab, ragged edges
+@pytest.mark.parametrize("ta,tb", [(0, 1), (1, 0), (0, 0), (1, 1)])
+@pytest.mark.parametrize("variant,M,N,K", [(13, 196, 132, 100), (11, 196, 260, 100), (11, 2100, 2068, 72)])
+def test_values_outside_the_split(handle, variant, M, N, K, ta, tb):
+    rng = np.random.default_rng([7, M])
+    a = rng.integers(-7, 8, (M, K)).astype(np.float64)
+    b = rng.integers(-3, 4, (K, N)).astype(np.float64)
+    a[0] = 0.0
+    a[1] = rng.integers(-7, 8, K) * 2.0 ** -149                 # subnormals: lost by every piece
+    a[2] = rng.integers(-7, 8, K) * 2.0 ** -130
+    a[3] *= 2.0 ** -108                                          # just inside
+    a[4, K - 1] = np.inf
+    a[5, 0] = np.nan
+    a[6] *= 2.0 ** 80                                            # (every partial sum: at most 100 * 7 * 3 * 2^(80 + 30) < 2^122, no order of addition overflows)
+    a[7, 3], a[7, 4] = 2.0 ** -149, 0.0                          # one lost element among ordinary ones: below rounding
+    a[M - 1] = rng.integers(-7, 8, K) * 2.0 ** -140
+    b[:, 1] *= 2.0 ** 24
+    b[:, N - 1] *= 2.0 ** 30
+    b[:, 2] = 0.0
+    cfg = wl.Config("split", M, N, K, ta, tb, wl.F32, wl.F32)
+    inp = {"A": wl.to_bits(np.ascontiguousarray(a.T if ta else a, dtype=np.float32).reshape(-1), wl.F32),
+           "B": wl.to_bits(np.ascontiguousarray(b.T if tb else b, dtype=np.float32).reshape(-1), wl.F32), "C": None, "bias": None}
+    with np.errstate(invalid="ignore"):
+        want = oracle.decode(wl.F32, oracle.encode(wl.F32, oracle.gemm_full(oracle_problem(cfg, inp))))
+    assert np.any(want[1] != 0) and np.all(np.isnan(want[5])) and np.any(np.isinf(want[4]))
+    lg.gemm_set_plan(handle, lg.GEMM_KERNEL_MFMA_TILE, variant, 1)
+    p = DeviceProblem(cfg, inp)
+    p.run(handle)
+    lg.gemm_set_plan(handle)
+    got = decode_c(cfg, p.result_bits())
+    bad = ~((got == want) | (np.isnan(got) & np.isnan(want)))
+    # row 7: its lost element is a rounding away from every sum (|sum| >= 1 against 2^-149 * 2^31)
+    assert not bad.any(), (variant, sorted(set(np.argwhere(bad)[:, 0]))[:8], int(bad.sum()))
