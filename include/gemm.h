@@ -121,10 +121,12 @@ gemm_status_t gemm_workspace_size(gemm_handle_t h, size_t* bytes);
  *                   B or bias.
  *   epilogue        see gemm_epilogue_t; may be NULL.
  *
- * Any shape, leading dimension and alignment is accepted for all three types.  The fast
+ * Any shape, leading dimension and alignment is accepted for all three types.  The fastest
  * matrix-core kernels need 16-byte aligned A and B, leading dimensions that are multiples of
- * 8 elements and a contiguous dimension that is a multiple of 8 (bf16/fp16); other calls run
- * a slower general kernel with the same result contract.
+ * 8 elements and a contiguous dimension that is a multiple of 8 (bf16/fp16; 4 for fp32); other calls run
+ * the general family with the same result contract (matrix cores too, but for the smallest calls).
+ * Such a call may be cut in k slices, with at most GEMM_NOALLOC_SCRATCH_BYTES of workspace; where none is to be had (the
+ * handle has not enough and the stream is being captured, or memory is out) it runs whole, in another order of summation.
  *
  * Errors (C is untouched in every error case detected before launch):
  *   GEMM_ERR_INVALID_ARG  null handle; negative size; ld smaller than the stored row; a null
@@ -208,7 +210,9 @@ const char* gemm_status_string(gemm_status_t s);
 
 typedef enum {
     GEMM_KERNEL_AUTO = 0,      /* let the library choose (default) */
-    GEMM_KERNEL_GENERAL = 1,   /* one thread per output element, any shape/alignment */
+    GEMM_KERNEL_GENERAL = 1,   /* any shape and alignment.  Variant 0: one thread per output element.  Variant 1 (bf16 / fp16):
+                                  128x128 MFMA tiles; variants 2, 3 (fp32): the fp32 tiles.  A forced variant that
+                                  cannot serve the call (and -1) falls back to 0 */
     GEMM_KERNEL_MFMA_TILE = 2, /* LDS-staged macro-tile kernel on MFMA */
     GEMM_KERNEL_SKINNY = 3     /* streaming kernels with split-K for few rows of C.  bf16 / fp16, M <= 64: variant 0
                                   for a row-major B (K x N), variant 1 for B stored N x K (an A stored K x M is first
@@ -230,7 +234,8 @@ typedef struct {
                              * the tiles of the last, partly filled round of workgroups (all tiles when
                              * there are fewer tiles than compute units) are cut, each into that many
                              * shares of the k range (at most one share per 32-element slab).
-                             * Every other tile variant: the whole product is cut into that many
+                             * Every other tile variant, and the general family's variants but 0 (without the
+                             * condition on N): the whole product is cut into that many
                              * ranges of K (whole 32-element slabs; fewer if K has not enough of
                              * them), computed side by side into fp32 partial results and added by a
                              * second kernel; this needs N to be a multiple of 8.  Batched calls, and

@@ -42,21 +42,18 @@ __device__ __forceinline__ void select_batch(Args& a) {
     }
 }
 
-// Rows of C can be read and written with vectors of four elements (16 bytes of fp32, 8 bytes of a
-// 16-bit type) in every matrix of the batch.
-inline int c_rows_take_vec4(const Args& a) {
-    const int64_t align = a.out_dtype == DT_F32 ? 16 : 8;
-    if (a.ldc % 4 != 0 || (uintptr_t)a.C % align != 0) return 0;
-    if (a.batch > 1 && (a.strideC * elem_bytes(a.out_dtype)) % align != 0) return 0;
-    return 1;
-}
-
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
+
+// The same vectors at the alignment of an element: global loads and stores of 8 and 16 bytes need no more (a C whose rows
+// start on any element is then written like an aligned one).
+typedef f32x4 f32x4_any __attribute__((aligned(4)));
+typedef u32x4 u32x4_any __attribute__((aligned(2)));
+typedef u32x2 u32x2_any __attribute__((aligned(2)));
 
 // ---- scalar conversions (round to nearest even on the way down) ----
 
@@ -213,8 +210,8 @@ int skinny_max_split(const Args& a, int variant = -1);
 size_t skinny_workspace_bytes(const Args& a, int split_k);
 int skinny_default_split(const Args& a, int num_cus, int variant = -1);
 hipError_t launch_skinny(const Args& a, int split_k, float* workspace, hipStream_t stream, int variant = -1);
-// Adds `split_k` fp32 partial results `partials[s][M][N]` (rows N apart) in the order of s and applies
-// the epilogue of `a` into C.  N must be a multiple of 8.
+// Adds `split_k` fp32 partial results `partials[s][M][P]` in the order of s and applies the epilogue of `a` into C; the
+// rows of a partial result are P = N rounded up to a multiple of 8 apart.
 hipError_t launch_splitk_reduce(const Args& a, int split_k, const float* partials, hipStream_t stream);
 
 // fp32 operands, at most 8 rows: the streaming kernels on the vector ALUs (part of the skinny family)
@@ -230,6 +227,13 @@ int gemv16_max_split(const Args& a);
 int gemv16_default_split(const Args& a, int num_cus);
 hipError_t launch_gemv16(const Args& a, int split_k, float* workspace, hipStream_t stream);
 
-hipError_t launch_general(const Args& a, hipStream_t stream);
+// Operands off the 16-byte grid (any base address that suits the element type, any leading dimension, any sizes): the
+// general family.  Variant 0 takes everything; the others are the register-staged 128x128 macro-tile kernel with movers
+// that need no alignment (1, 16-bit operands) and the fp32 tile kernels, which need none (2: 128x128, 3: 64x64).
+constexpr int kGeneralVariants = 4;
+const char* general_variant_name(int variant);
+bool general_variant_supports(const Args& a, int variant);
+hipError_t launch_general(const Args& a, int variant, int group_m, hipStream_t stream);
+hipError_t launch_any_tile(const Args& a, int group_m, hipStream_t stream);
 
 }  // namespace gemm

@@ -220,36 +220,40 @@ struct TileChoice { int variant; int first_split_tile; int parts; double time; }
 constexpr int kF32TileVariant = 11, kF32SmallTileVariant = 13;
 constexpr int64_t kF32MinTiles = 1;
 
+// fp32: the 128x128 tile (beyond one per compute unit in pairs, see kF32PairAbove) or the 64x64 tile (up to three
+// workgroups per unit), whole or in `slices` of k.  Estimate in us per element of k, 4 us fixed:
+//   64x64: a unit's one, two or three workgroups 0.0177, 0.028, 0.0405 (1024^3 22 us, 1536^3 60, 3072^3 364);
+//   128x128: one per unit 0.0465 (2048^3 95 us); in pairs 0.0755 for a full round (4096x2048x4096 297 us),
+//   0.0575 for one that leaves 40 % of the units idle (2304^3 140), in between in proportion (2560^3 161).
+// Slices add the second kernel.  Deep k on a small grid gains most from them: 256x256x4096 74 -> 15 us in
+// 16, 64x4096x4096 78 -> 23 in 8.
+double f32_time(const Args& a, bool big, int slices, int64_t cus) {
+    const int64_t side = big ? 128 : 64;
+    const int64_t wgs = ((a.M + side - 1) / side) * ((a.N + side - 1) / side) * a.batch * slices, per_unit = (wgs + cus - 1) / cus;
+    double per_k;
+    if (!big) {
+        per_k = (double)(per_unit / 3) * 0.0405 + (per_unit % 3 == 0 ? 0.0 : (per_unit % 3 == 1 ? 0.0177 : 0.028));
+    } else if (wgs <= gemm::kF32PairAbove) {
+        per_k = (double)per_unit * 0.0465;
+    } else {
+        const double n = (double)(((a.M + 255) / 256) * ((a.N + 127) / 128) * a.batch * slices) / (double)cus;
+        const double whole = (double)(int64_t)n, fill = n - whole;
+        per_k = whole * 0.0755 + (fill > 0.0 ? 0.0575 + 0.018 * (fill > 0.6 ? (fill - 0.6) / 0.4 : 0.0) : 0.0);
+    }
+    const double t = per_k * ((double)a.K / slices) + 4.0;
+    return slices > 1 ? (t + kSliceLaunchF32 + (double)slices * (double)(a.M * a.N) * 8.0 / kSliceMoveRate) / kSliceMarginF32 : t;
+}
+
 TileChoice choose_tile(const Args& a, int num_cus) {
     const int64_t cus = num_cus > 0 ? num_cus : 256;
     if (a.dtype == gemm::DT_F32) {
-        // fp32: the 128x128 tile (beyond one per compute unit in pairs, see launch_f32_variant) or the 64x64 tile (up
-        // to three workgroups per unit), whole or in k slices.  Estimate in us per element of k, 4 us fixed:
-        //   64x64: a unit's one, two or three workgroups 0.0177, 0.028, 0.0405 (1024^3 22 us, 1536^3 61, 3072^3 378);
-        //   128x128: one per unit 0.0465 (2048^3 98 us); in pairs 0.0755 for a full round (4096x2048x4096 312 us),
-        //   0.0575 for one that leaves 40 % of the units idle (2304^3 141), in between in proportion (2560^3 171).
-        // Slices add the second kernel.  Deep k on a small grid gains most from them: 256x256x4096 74 -> 15 us in
-        // 16, 64x4096x4096 78 -> 23 in 8.
-        auto rounds = [&](double n, double full, double idle) {     // n workgroups, one per unit
-            const double whole = (double)(int64_t)(n / (double)cus), fill = n / (double)cus - whole;
-            return whole * full + (fill > 0.0 ? idle + (full - idle) * (fill > 0.6 ? (fill - 0.6) / 0.4 : 0.0) : 0.0);
-        };
         const int most_slices = most_f32_slices(a, cus);
         int best_variant = kF32SmallTileVariant, best_slices = 1;
         double best_time = 0.0;
         for (int big = 0; big < 2; ++big) {
-            const int64_t side = big ? 128 : 64;
-            const int64_t tiles = ((a.M + side - 1) / side) * ((a.N + side - 1) / side) * a.batch;
             for (int sl : {1, 2, 4, 8, 16}) {
                 if (sl > most_slices) break;
-                const int64_t wgs = tiles * sl, per_unit = (wgs + cus - 1) / cus;
-                const double k = (double)a.K / sl;
-                double per_k;
-                if (!big) per_k = (double)(per_unit / 3) * 0.0405 + (per_unit % 3 == 0 ? 0.0 : (per_unit % 3 == 1 ? 0.0177 : 0.028));
-                else if (wgs <= gemm::kF32PairAbove) per_k = (double)per_unit * 0.0465;
-                else per_k = rounds((double)(((a.M + 255) / 256) * ((a.N + 127) / 128) * a.batch * sl), 0.0755, 0.0575);
-                double t = per_k * k + 4.0;
-                if (sl > 1) t = (t + kSliceLaunchF32 + (double)sl * (double)(a.M * a.N) * 8.0 / kSliceMoveRate) / kSliceMarginF32;
+                const double t = f32_time(a, big != 0, sl, cus);
                 if (best_time == 0.0 || t < best_time) { best_time = t; best_variant = big ? kF32TileVariant : kF32SmallTileVariant; best_slices = sl; }
             }
         }
@@ -372,6 +376,13 @@ struct Workspace {
         if (fixed) return bytes <= kScratchBytes ? GEMM_OK : GEMM_ERR_SCRATCH_LIMIT;
         return ensure_workspace(h, bytes);
     }
+    // the same for a plan that can do without: false where there is nothing to be had
+    bool obtain(size_t bytes, hipStream_t stream) const {
+        if (fixed || bytes <= h->workspace_bytes) return ensure(bytes) == GEMM_OK;
+        hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(stream, &capturing) != hipSuccess) { (void)hipGetLastError(); return false; }
+        return capturing == hipStreamCaptureStatusNone && ensure(bytes) == GEMM_OK;
+    }
 };
 
 gemm_status_t free_retired(gemm_handle_s* h) {
@@ -478,12 +489,25 @@ GEMM_EXPORT const char* gemm_variant_name(gemm_kernel_t kernel, int32_t variant)
         const gemm::TileVariantInfo* info = gemm::tile_variant_info(variant);
         return info ? info->name : nullptr;
     }
-    if (kernel == GEMM_KERNEL_GENERAL) return variant == 0 ? "general_16x16" : nullptr;
+    if (kernel == GEMM_KERNEL_GENERAL) return gemm::general_variant_name(variant);
     if (kernel == GEMM_KERNEL_SKINNY) return gemm::skinny_variant_name(variant);
     return nullptr;
 }
 
 namespace {
+
+// The product `a` as a strided batch of `slices` ranges of k, `len` elements each but the last, into fp32 partial results
+// whose rows are `ld` apart.
+Args slices_of(const Args& a, int slices, int64_t len, float* partials, int64_t ld) {
+    Args p = a;
+    p.K = len; p.k_total = a.K;
+    p.batch = slices;
+    p.strideA = a.transA ? len * a.lda : len;
+    p.strideB = a.transB ? len : len * a.ldb;
+    p.C = partials; p.ldc = ld; p.strideC = a.M * ld;
+    p.out_dtype = gemm::DT_F32; p.alpha = 1.0f; p.beta = 0.0f; p.bias = nullptr; p.act = gemm::ACT_NONE;
+    return p;
+}
 
 // Launches the kernels of a plan for the (validated) call `a`; may lower plan.split_k to what the
 // call can take.  split_first: first tile of a split trailing round (macro-tile family).
@@ -524,16 +548,9 @@ gemm_status_t launch_plan(const Workspace& ws, const Args& a, gemm_plan_t& plan,
             plan.split_k = (int)((K + slice_len - 1) / slice_len);
         }
         if (plan.split_k > 1 && slice_len > 0) {
-            const int64_t len = slice_len;
             const gemm_status_t st = ws.ensure((size_t)plan.split_k * (size_t)M * (size_t)N * sizeof(float));
             if (st != GEMM_OK) return st;
-            Args p = a;
-            p.K = len; p.k_total = K;
-            p.batch = plan.split_k;
-            p.strideA = a.transA ? len * a.lda : len;
-            p.strideB = a.transB ? len : len * a.ldb;
-            p.C = ws.ptr(); p.ldc = N; p.strideC = M * N;
-            p.out_dtype = gemm::DT_F32; p.alpha = 1.0f; p.beta = 0.0f; p.bias = nullptr; p.act = gemm::ACT_NONE;
+            const Args p = slices_of(a, plan.split_k, slice_len, ws.ptr(), N);
             if (!allocate_only) e = gemm::launch_tile(p, plan.variant, kTileBandRows, split, stream);
             if (!allocate_only && e == hipSuccess) e = gemm::launch_splitk_reduce(a, plan.split_k, ws.ptr(), stream);
         } else if (plan.split_k > 1) {
@@ -548,8 +565,21 @@ gemm_status_t launch_plan(const Workspace& ws, const Args& a, gemm_plan_t& plan,
         } else if (!allocate_only) {
             e = gemm::launch_tile(a, plan.variant, kTileBandRows, split, stream);
         }
-    } else if (!allocate_only) {
-        e = gemm::launch_general(a, stream);
+    } else {
+        if (plan.split_k > 1) {
+            // k slices, as above; a call of this family has never needed a workspace, so where there is none to be had (the
+            // stream is being captured, memory is out) it runs whole
+            const int64_t slabs = (K + 31) / 32, len = ((slabs + plan.split_k - 1) / plan.split_k) * 32, P = (N + 7) / 8 * 8;
+            plan.split_k = (int)((K + len - 1) / len);
+            if (plan.split_k < 2 || !ws.obtain((size_t)plan.split_k * (size_t)M * (size_t)P * sizeof(float), stream)) plan.split_k = 1;
+            if (plan.split_k > 1) {
+                if (allocate_only) return GEMM_OK;
+                e = gemm::launch_general(slices_of(a, plan.split_k, len, ws.ptr(), P), plan.variant, kTileBandRows, stream);
+                if (e == hipSuccess) e = gemm::launch_splitk_reduce(a, plan.split_k, ws.ptr(), stream);
+                return e == hipSuccess ? GEMM_OK : GEMM_ERR_HIP;
+            }
+        }
+        if (!allocate_only) e = gemm::launch_general(a, plan.variant, kTileBandRows, stream);
     }
     return e == hipSuccess ? GEMM_OK : GEMM_ERR_HIP;
 }
@@ -641,6 +671,40 @@ struct AutoPlan {
     int rest_split_first;
 };
 
+// Operands off the 16-byte grid: the general kernel for the smallest calls, the matrix cores for the rest, in k slices where
+// the tiles leave the chip idle.  Slices have to fit the static scratch, so that every entry point takes the same ones.
+// 16-bit operands, the 128x128 tile: 10 us fixed and per element of k 0.0175 us for up to 128 workgroups, 0.021 for one on
+// every unit, 0.0305 per round of two (1023^3 25 to 29 us, 2049x2051x2045 53, 4095x4097x4093 245 to 270; 16x8191x4095 83 whole,
+// 27 in 8 slices; 1201x1203x4095 78 whole, 49 in 4).  The general kernel: 4.5 us and, per step of 16 along k, 0.35 us and
+// 0.25 ns per block at least (65x67x129 6.8 us against 12, 255x1023x255 14 against 20; 129x257x511 19 against 14.5,
+// 2049x2051x2045 1245).  fp32 operands: the fp32 tiles, which are ahead down to a single tile.
+constexpr int64_t kGeneralMinSliceK = 64;
+
+gemm_plan_t general_plan(const Args& a, int num_cus) {
+    const int64_t cus = num_cus > 0 ? num_cus : 256;
+    gemm_plan_t plan{GEMM_KERNEL_GENERAL, 0, 1};
+    const bool f32 = a.dtype == gemm::DT_F32;
+    if (!gemm::general_variant_supports(a, f32 ? 3 : 1)) return plan;
+    const double blocks = (double)((a.M + 15) / 16) * (double)((a.N + 15) / 16) * (double)a.batch;
+    double best = f32 ? 0.0 : 4.5 + (double)((a.K + 15) / 16) * (0.35 + 0.00025 * blocks);
+    for (int variant = f32 ? 2 : 1; variant <= (f32 ? 3 : 1); ++variant)
+        for (int sl : {1, 2, 4, 8, 16}) {
+            const int64_t P = (a.N + 7) / 8 * 8;
+            if (sl > 1 && (a.batch != 1 || a.K / sl < kGeneralMinSliceK || (int64_t)sl * a.M * P * 4 > (int64_t)kScratchBytes)) break;
+            double t;
+            if (f32) {
+                t = f32_time(a, variant == 2, sl, cus);
+            } else {
+                const int64_t wgs = ((a.M + 127) / 128) * ((a.N + 127) / 128) * a.batch * sl;
+                const double per_k = wgs <= cus / 2 ? 0.0175 : (wgs <= cus ? 0.021 : 0.0305 * (double)((wgs + 2 * cus - 1) / (2 * cus)));
+                t = 10.0 + per_k * ((double)a.K / sl);
+                if (sl > 1) t = (t + kSliceLaunchF32 + (double)sl * (double)(a.M * P) * 8.0 / kSliceMoveRate) / kSliceMarginF32;
+            }
+            if (best == 0.0 || t < best) { best = t; plan.variant = variant; plan.split_k = sl; }
+        }
+    return plan;
+}
+
 AutoPlan automatic_plan(const Args& a, int num_cus, bool batch_aligned) {
     AutoPlan ap;
     ap.plan = gemm_plan_t{GEMM_KERNEL_GENERAL, 0, 1};
@@ -681,6 +745,8 @@ AutoPlan automatic_plan(const Args& a, int num_cus, bool batch_aligned) {
             ap.rest_plan = gemm_plan_t{GEMM_KERNEL_MFMA_TILE, cr.variant, cr.parts};
             ap.rest_split_first = cr.first_split_tile;
         }
+    } else {
+        ap.plan = general_plan(a, num_cus);
     }
     return ap;
 }
@@ -782,8 +848,10 @@ gemm_status_t run_batch(gemm_handle_t h, bool fixed_scratch, int64_t batch, int6
             if (!gemm::skinny_variant_serves(a, plan.variant)) return GEMM_ERR_UNSUPPORTED;
             if (plan.variant < 0) plan.variant = gemm::skinny_variant_of(a);
             if (plan.split_k == 0) plan.split_k = gemm::skinny_default_split(a, h->num_cus, plan.variant);
-        } else {
-            plan = gemm_plan_t{GEMM_KERNEL_GENERAL, 0, 1};
+        } else if (plan.variant < 1 || !gemm::general_variant_supports(a, plan.variant) || plan.variant >= gemm::kGeneralVariants) {
+            plan = gemm_plan_t{GEMM_KERNEL_GENERAL, 0, 1};      // (the one that takes everything)
+        } else if (plan.split_k < 1 || batch > 1) {
+            plan.split_k = 1;
         }
     } else {
         const AutoPlan ap = automatic_plan(a, h->num_cus, batch_aligned);

@@ -1,7 +1,7 @@
-// The general kernel: one thread per output element, any shape, leading dimension, alignment
-// and element type.  It is the correctness floor under the matrix-core kernels (calls whose
-// operands are not 16-byte aligned, or whose contiguous dimension is not a multiple of 8,
-// land here), and it also serves K == 0 and alpha == 0 where only the epilogue is left.
+// The general family: calls whose operands are not on the 16-byte grid, or whose contiguous dimension is not a
+// multiple of 8.  Most of them go on to matrix-core kernels that need no alignment; the general kernel proper, one
+// thread per output element, any shape, leading dimension, alignment and element type, is the correctness floor under
+// them, and it also serves K == 0 and alpha == 0 where only the epilogue is left.
 #include "common.hpp"
 
 namespace gemm {
@@ -59,7 +59,29 @@ __global__ __launch_bounds__(GT * GT) void general_kernel(Args a) {
 
 }  // namespace
 
-hipError_t launch_general(const Args& a, hipStream_t stream) {
+const char* general_variant_name(int variant) {
+    static const char* const names[kGeneralVariants] = {"general_16x16", "general_128x128x64_w2x2",
+                                                        "general_f32_128x128x32_w2x2", "general_f32_64x64x32_w2x2"};
+    return variant >= 0 && variant < kGeneralVariants ? names[variant] : nullptr;
+}
+
+bool general_variant_supports(const Args& a, int variant) {
+    if (variant == 0) return true;
+    if (variant < 0 || variant >= kGeneralVariants) return false;
+    if ((a.dtype == DT_F32) != (variant >= 2) || a.M < 1 || a.N < 1 || a.K < 1) return false;
+    const uintptr_t off = a.dtype == DT_F32 ? 3 : 1;                    // elements at their natural alignment
+    if (((uintptr_t)a.A & off) || ((uintptr_t)a.B & off)) return false;
+    // 32-bit byte offsets inside a slab, a 32-bit workgroup count
+    if (a.lda > (1 << 22) || a.ldb > (1 << 22) || a.K > (1 << 30)) return false;
+    if (((a.M + 63) / 64) * ((a.N + 63) / 64) > (int64_t)1 << 30) return false;
+    // the 16-bit mover of an m/n-contiguous operand fetches eight rows at a time
+    return a.dtype == DT_F32 || ((!a.transA || a.M >= 8) && (a.transB || a.N >= 8));
+}
+
+hipError_t launch_general(const Args& a, int variant, int group_m, hipStream_t stream) {
+    if (!general_variant_supports(a, variant)) return hipErrorInvalidValue;
+    if (variant == 1) return launch_any_tile(a, group_m, stream);
+    if (variant >= 2) return launch_tile(a, variant == 2 ? 11 : 13, group_m, TileSplit{0, 1, nullptr}, stream);
     const int64_t tiles = ((a.M + GT - 1) / GT) * ((a.N + GT - 1) / GT);
     if (tiles == 0) return hipSuccess;
     const int64_t grid = tiles < (1 << 20) ? tiles : (1 << 20);

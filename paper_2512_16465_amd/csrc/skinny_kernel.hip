@@ -80,29 +80,29 @@ __device__ __forceinline__ void sk_unpack16(u32x4 u, int dtype, float (&out)[8])
     }
 }
 
-__device__ __forceinline__ void sk_load_row_inputs(const Args& a, int64_t row, int64_t col, bool vec_ok, SkRowInputs& in) {
+__device__ __forceinline__ void sk_load_row_inputs(const Args& a, int64_t row, int64_t col, bool vec_ok, SkRowInputs& in, int count = 8) {
     const int64_t idx = row * a.ldc + col;
     if (a.beta != 0.0f) {
         if (vec_ok && a.out_dtype != DT_F32) {
-            sk_unpack16(*(const u32x4*)((const uint16_t*)a.C + idx), a.out_dtype, in.c_in);
+            sk_unpack16(*(const u32x4_any*)((const uint16_t*)a.C + idx), a.out_dtype, in.c_in);
         } else if (vec_ok) {
-            const f32x4 lo = *(const f32x4*)((const float*)a.C + idx), hi = *(const f32x4*)((const float*)a.C + idx + 4);
+            const f32x4 lo = *(const f32x4_any*)((const float*)a.C + idx), hi = *(const f32x4_any*)((const float*)a.C + idx + 4);
 #pragma unroll
             for (int e = 0; e < 4; ++e) { in.c_in[e] = lo[e]; in.c_in[4 + e] = hi[e]; }
         } else {
 #pragma unroll
-            for (int e = 0; e < 8; ++e) in.c_in[e] = load_elem(a.C, a.out_dtype, idx + e);
+            for (int e = 0; e < 8; ++e) in.c_in[e] = e < count ? load_elem(a.C, a.out_dtype, idx + e) : 0.0f;
         }
     } else {
 #pragma unroll
         for (int e = 0; e < 8; ++e) in.c_in[e] = 0.0f;
     }
 #pragma unroll
-    for (int e = 0; e < 8; ++e) in.bias[e] = a.bias ? load_elem(a.bias, a.bias_dtype, col + e) : 0.0f;
+    for (int e = 0; e < 8; ++e) in.bias[e] = a.bias && e < count ? load_elem(a.bias, a.bias_dtype, col + e) : 0.0f;
 }
 
 // Stores 8 consecutive outputs of one row, after the epilogue, in the type of C.
-__device__ __forceinline__ void sk_store_row(const Args& a, int64_t row, int64_t col, const float (&x)[8], const SkRowInputs& in, bool vec_ok) {
+__device__ __forceinline__ void sk_store_row(const Args& a, int64_t row, int64_t col, const float (&x)[8], const SkRowInputs& in, bool vec_ok, int count = 8) {
     float o[8];
     const int64_t idx = row * a.ldc + col;
 #pragma unroll
@@ -110,11 +110,12 @@ __device__ __forceinline__ void sk_store_row(const Args& a, int64_t row, int64_t
     if (a.out_dtype == DT_F32) {
         float* p = (float*)a.C + idx;
         if (vec_ok) {
-            *(f32x4*)p = f32x4{o[0], o[1], o[2], o[3]};
-            *(f32x4*)(p + 4) = f32x4{o[4], o[5], o[6], o[7]};
+            *(f32x4_any*)p = f32x4{o[0], o[1], o[2], o[3]};
+            *(f32x4_any*)(p + 4) = f32x4{o[4], o[5], o[6], o[7]};
         } else {
 #pragma unroll
-            for (int e = 0; e < 8; ++e) p[e] = o[e];
+            for (int e = 0; e < 8; ++e)
+                if (e < count) p[e] = o[e];
         }
     } else {
         uint16_t h[8];
@@ -125,10 +126,11 @@ __device__ __forceinline__ void sk_store_row(const Args& a, int64_t row, int64_t
             u32x4 u;
 #pragma unroll
             for (int e = 0; e < 4; ++e) u[e] = (uint32_t)h[2 * e] | ((uint32_t)h[2 * e + 1] << 16);
-            *(u32x4*)p = u;
+            *(u32x4_any*)p = u;
         } else {
 #pragma unroll
-            for (int e = 0; e < 8; ++e) p[e] = h[e];
+            for (int e = 0; e < 8; ++e)
+                if (e < count) p[e] = h[e];
         }
     }
 }
@@ -650,13 +652,15 @@ __global__ __launch_bounds__(ST_WAVES * 64) void skinny_nt_narrow_kernel(Args a,
 // anything is used: S > 0 fixes the number of slices at compile time (all their loads are issued
 // back to back, together with those of C_in and bias); S == 0 takes any number.
 template <int S>
-__global__ __launch_bounds__(256) void splitk_reduce_kernel(Args a, int split_k, const float* ws, int c_vec_ok) {
-    const int64_t groups_per_row = a.N / 8;
+__global__ __launch_bounds__(256) void splitk_reduce_kernel(Args a, int split_k, const float* ws) {
+    const int64_t groups_per_row = (a.N + 7) / 8;       // rows of a partial result are whole groups of eight
     const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (g >= a.M * groups_per_row) return;
     const int64_t row = g / groups_per_row, col = (g % groups_per_row) * 8;
-    const int64_t slice = a.M * a.N;
-    const float* p = ws + row * a.N + col;
+    const int64_t slice = a.M * groups_per_row * 8;
+    const float* p = ws + row * groups_per_row * 8 + col;
+    const int count = a.N - col < 8 ? (int)(a.N - col) : 8;
+    const bool vec_ok = count == 8;
     SkRowInputs in;
     float x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     if constexpr (S > 0) {
@@ -666,20 +670,20 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(Args a, int split_k,
             lo[s] = *(const f32x4*)(p + s * slice);
             hi[s] = *(const f32x4*)(p + s * slice + 4);
         }
-        sk_load_row_inputs(a, row, col, c_vec_ok != 0, in);
+        sk_load_row_inputs(a, row, col, vec_ok, in, count);
 #pragma unroll
         for (int s = 0; s < S; ++s)
 #pragma unroll
             for (int e = 0; e < 4; ++e) { x[e] += lo[s][e]; x[4 + e] += hi[s][e]; }
     } else {
-        sk_load_row_inputs(a, row, col, c_vec_ok != 0, in);
+        sk_load_row_inputs(a, row, col, vec_ok, in, count);
         for (int s = 0; s < split_k; ++s) {
             const f32x4 lo = *(const f32x4*)(p + s * slice), hi = *(const f32x4*)(p + s * slice + 4);
 #pragma unroll
             for (int e = 0; e < 4; ++e) { x[e] += lo[e]; x[4 + e] += hi[e]; }
         }
     }
-    sk_store_row(a, row, col, x, in, c_vec_ok != 0);
+    sk_store_row(a, row, col, x, in, vec_ok, count);
 }
 
 // A stored K x M (transA): the few rows of op(A) are gathered once into a row-major M x K copy in the
@@ -879,16 +883,15 @@ hipError_t launch_skinny(const Args& call, int split_k, float* workspace, hipStr
 }
 
 hipError_t launch_splitk_reduce(const Args& a, int split_k, const float* partials, hipStream_t stream) {
-    if (split_k < 1 || partials == nullptr || (a.N & 7)) return hipErrorInvalidValue;
-    const int c_vec_ok = (a.ldc % 8 == 0) && ((uintptr_t)a.C % 16 == 0);
-    const int64_t threads = a.M * (a.N / 8);
+    if (split_k < 1 || partials == nullptr) return hipErrorInvalidValue;
+    const int64_t threads = a.M * ((a.N + 7) / 8);
     const dim3 rgrid((unsigned)((threads + 255) / 256)), rblock(256);
     switch (split_k) {
-        case 2: hipLaunchKernelGGL(splitk_reduce_kernel<2>, rgrid, rblock, 0, stream, a, split_k, partials, c_vec_ok); break;
-        case 4: hipLaunchKernelGGL(splitk_reduce_kernel<4>, rgrid, rblock, 0, stream, a, split_k, partials, c_vec_ok); break;
-        case 8: hipLaunchKernelGGL(splitk_reduce_kernel<8>, rgrid, rblock, 0, stream, a, split_k, partials, c_vec_ok); break;
-        case 16: hipLaunchKernelGGL(splitk_reduce_kernel<16>, rgrid, rblock, 0, stream, a, split_k, partials, c_vec_ok); break;
-        default: hipLaunchKernelGGL(splitk_reduce_kernel<0>, rgrid, rblock, 0, stream, a, split_k, partials, c_vec_ok); break;
+        case 2: hipLaunchKernelGGL(splitk_reduce_kernel<2>, rgrid, rblock, 0, stream, a, split_k, partials); break;
+        case 4: hipLaunchKernelGGL(splitk_reduce_kernel<4>, rgrid, rblock, 0, stream, a, split_k, partials); break;
+        case 8: hipLaunchKernelGGL(splitk_reduce_kernel<8>, rgrid, rblock, 0, stream, a, split_k, partials); break;
+        case 16: hipLaunchKernelGGL(splitk_reduce_kernel<16>, rgrid, rblock, 0, stream, a, split_k, partials); break;
+        default: hipLaunchKernelGGL(splitk_reduce_kernel<0>, rgrid, rblock, 0, stream, a, split_k, partials); break;
     }
     return hipGetLastError();
 }

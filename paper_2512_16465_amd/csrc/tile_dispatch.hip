@@ -91,7 +91,7 @@ namespace {
 // number, four at a time) and of C_in and bias are issued before the first use.
 template <int P>
 __global__ __launch_bounds__(256) void tile_split_reduce_kernel(Args a, int tiles_m, int tiles_n, int group_m, int first_tile,
-                                                                int parts, const float* partials, int BM, int BN, int c_vec_ok) {
+                                                                int parts, const float* partials, int BM, int BN) {
     int tm, tn;
     tile::tile_of_workgroup(first_tile + (int)blockIdx.x, tiles_m, tiles_n, group_m, tm, tn);
     const int idx = (int)blockIdx.y * 256 + (int)threadIdx.x;          // one of BM * BN / 4 vectors
@@ -102,7 +102,7 @@ __global__ __launch_bounds__(256) void tile_split_reduce_kernel(Args a, int tile
     const float* p = partials + ((size_t)blockIdx.x * parts) * tile_floats + (size_t)r * BN + c;
     float c_in[4] = {0.0f, 0.0f, 0.0f, 0.0f}, bj[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     auto load_inputs = [&]() {
-        const bool vec = c_vec_ok && col + 3 < a.N;
+        const bool vec = col + 3 < a.N;
         if (vec && a.beta != 0.0f) {
             const int64_t ci = row * a.ldc + col;
             f32x4 v;
@@ -144,7 +144,7 @@ __global__ __launch_bounds__(256) void tile_split_reduce_kernel(Args a, int tile
     f32x4 o;
 #pragma unroll
     for (int e = 0; e < 4; ++e) o[e] = epilogue_value(s[e], a.alpha, a.beta, c_in[e], bj[e], a.act);
-    if (c_vec_ok && col + 3 < a.N) {          // four outputs in one store
+    if (col + 3 < a.N) {          // four outputs in one store
         const int64_t ci = row * a.ldc + col;
         if (a.out_dtype == DT_F32) tile::OutVec<DT_F32>::store4((float*)a.C + ci, o);
         else if (a.out_dtype == DT_BF16) tile::OutVec<DT_BF16>::store4((uint16_t*)a.C + ci, o);
@@ -168,10 +168,9 @@ hipError_t launch_tile_split_reduce(const Args& a, int variant, int group_m, con
     if (tail <= 0) return hipSuccess;
     const dim3 grid((unsigned)tail, (unsigned)(BM * BN / 4 / 256)), block(256);
     const int gm = group_m < 1 ? 1 : group_m;
-    const int c_vec_ok = c_rows_take_vec4(a);
 #define GEMM_REDUCE_LAUNCH(P)                                                                                       \
     hipLaunchKernelGGL(tile_split_reduce_kernel<P>, grid, block, 0, stream, a, tiles_m, tiles_n, gm, split.first_tile, \
-                       split.parts, (const float*)split.partials, BM, BN, c_vec_ok)
+                       split.parts, (const float*)split.partials, BM, BN)
     switch (split.parts) {
         case 2: GEMM_REDUCE_LAUNCH(2); break;
         case 3: GEMM_REDUCE_LAUNCH(3); break;

@@ -132,7 +132,7 @@ __device__ __forceinline__ void wait_raw8(Frag16RawMC (&r)[8]) {
 // a workgroup runs the same pipeline over its share of the k slabs and stores its accumulators,
 // unscaled, as an fp32 tile in `partials`.
 template <class C, bool IS_BF16, bool A_KC, bool B_KC, bool DIRECT = false>
-__global__ __launch_bounds__(C::NT) void tile_dma16_kernel(Args a, int tiles_m, int tiles_n, int group_m, int c_vec_ok,
+__global__ __launch_bounds__(C::NT) void tile_dma16_kernel(Args a, int tiles_m, int tiles_n, int group_m,
                                                            int split_first, int split_parts, float* partials, int rotate) {
     constexpr int BM = C::BM, BN = C::BN, BK = C::BK, NT = C::NT, NS = C::NS;
     constexpr int TM = C::WTM / 16, TN = C::WTN / 16;        // 16x16 accumulators per wave
@@ -448,7 +448,7 @@ __global__ __launch_bounds__(C::NT) void tile_dma16_kernel(Args a, int tiles_m, 
         e.C = partials + ((size_t)(pid - split_first) * split_parts + part) * (BM * BN);
         e.ldc = BN; e.M = BM; e.N = BN;
         e.out_dtype = DT_F32; e.alpha = 1.0f; e.beta = 0.0f; e.bias = nullptr; e.act = ACT_NONE;
-        em0 = 0; en0 = 0; c_vec_ok = 1;
+        em0 = 0; en0 = 0;
     }
     // The MFMAs took B's fragment as their first operand, so each 16x16 accumulator holds its block
     // of C transposed: register v of lane l is row l%16, column 4*(l/16) + v, and a lane's four
@@ -513,7 +513,7 @@ __global__ __launch_bounds__(C::NT) void tile_dma16_kernel(Args a, int tiles_m, 
                 for (int j = 0; j < TN; ++j)
                     *(f32x4*)(region + ((16 * i2 + c16) * EL::RS + j * 16 + 4 * g4) * 4) = acc[2 * b + i2][j];
         },
-        lds, e, em0, en0, c_vec_ok, live_rows);
+        lds, e, em0, en0, live_rows);
 }
 
 template <class C>
@@ -525,7 +525,6 @@ hipError_t launch_dma16_variant(const Args& a, int group_m, const TileSplit& spl
     const dim3 grid((unsigned)(split_first + (tiles - split_first) * split_parts), (unsigned)a.batch), block(C::NT);
     const bool bf = a.dtype == DT_BF16;
     const bool akc = !a.transA, bkc = a.transB != 0;
-    const int c_vec_ok = c_rows_take_vec4(a);
     // A split call streams its operands (few tiles, long k), and so does a single row or column of
     // tiles whose operands exceed the last-level cache: rotate the k walk when a k-contiguous
     // operand has its rows a multiple of 4 KiB apart (see the kernel).  With more than four shares
@@ -546,11 +545,11 @@ hipError_t launch_dma16_variant(const Args& a, int group_m, const TileSplit& spl
         if constexpr (HAS_DIRECT) {                                                                                             \
             if (direct) {                                                                                                       \
                 hipLaunchKernelGGL((tile_dma16_kernel<C, BF, AKC, BKC, true>), grid, block, 0, stream, a, tiles_m, tiles_n, group_m, \
-                                   c_vec_ok, split_first, split_parts, split.partials, rotate);                                 \
+                                   split_first, split_parts, split.partials, rotate);                                 \
                 break;                                                                                                          \
             }                                                                                                                   \
         }                                                                                                                       \
-        hipLaunchKernelGGL((tile_dma16_kernel<C, BF, AKC, BKC>), grid, block, 0, stream, a, tiles_m, tiles_n, group_m, c_vec_ok, \
+        hipLaunchKernelGGL((tile_dma16_kernel<C, BF, AKC, BKC>), grid, block, 0, stream, a, tiles_m, tiles_n, group_m, \
                            split_first, split_parts, split.partials, rotate);                                                   \
     } while (0)
     if (bf) {

@@ -214,7 +214,7 @@ __device__ __forceinline__ void wait_raw(u32x4 (&)[2]) {}
 __device__ __forceinline__ void wait_raw(u32x4 (&)[4]) {}
 
 template <class C, bool IS_BF16, bool A_KC, bool B_KC, bool PLAIN>
-__global__ __launch_bounds__(C::NT) void tile_dma_kernel(Args a, int tiles_m, int tiles_n, int group_m, int c_vec_ok, int rotate) {
+__global__ __launch_bounds__(C::NT) void tile_dma_kernel(Args a, int tiles_m, int tiles_n, int group_m, int rotate) {
     constexpr int BM = C::BM, BN = C::BN, BK = C::BK, NT = C::NT, TM = C::TM, TN = C::TN, NS = C::NS;
     using EL = EpiLayout<C>;
     constexpr int RING = NS * C::STAGE;
@@ -410,7 +410,7 @@ __global__ __launch_bounds__(C::NT) void tile_dma_kernel(Args a, int tiles_m, in
 #undef GEMM_WAIT_VM_BARRIER
 
     if constexpr (PLAIN) tile_epilogue_plain<C>(acc, a, m0, n0);
-    else tile_epilogue<C>(acc, lds, a, m0, n0, c_vec_ok);
+    else tile_epilogue<C>(acc, lds, a, m0, n0);
 }
 
 template <class C>
@@ -419,7 +419,6 @@ hipError_t launch_dma_variant(const Args& a, int group_m, hipStream_t stream) {
     const dim3 grid((unsigned)(tiles_m * tiles_n), (unsigned)a.batch), block(C::NT);
     const bool bf = a.dtype == DT_BF16;
     const bool akc = !a.transA, bkc = a.transB != 0;
-    const int c_vec_ok = c_rows_take_vec4(a);
     const bool plain = plain_epilogue_applies<C>(a);
     // a single row or column of tiles, operands beyond the last-level cache, one of them k-contiguous with
     // rows a multiple of 4 KiB apart (65536x128x4096: 125 -> 119 us, 128x28672x8192 with B stored N x K:
@@ -431,10 +430,10 @@ hipError_t launch_dma_variant(const Args& a, int group_m, hipStream_t stream) {
     do {                                                                                                       \
         if (plain)                                                                                             \
             hipLaunchKernelGGL((tile_dma_kernel<C, BF, AKC, BKC, true>), grid, block, 0, stream, a, tiles_m,   \
-                               tiles_n, group_m, c_vec_ok, rotate);                                            \
+                               tiles_n, group_m, rotate);                                            \
         else                                                                                                   \
             hipLaunchKernelGGL((tile_dma_kernel<C, BF, AKC, BKC, false>), grid, block, 0, stream, a, tiles_m,  \
-                               tiles_n, group_m, c_vec_ok, rotate);                                            \
+                               tiles_n, group_m, rotate);                                            \
     } while (0)
     if (bf) {
         if (akc && bkc) GEMM_TILE_LAUNCH(true, true, true);

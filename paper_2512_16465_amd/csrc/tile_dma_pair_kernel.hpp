@@ -23,7 +23,7 @@ namespace gemm {
 namespace tile {
 
 template <class C, bool IS_BF16, bool A_KC, bool B_KC, bool PLAIN>
-__global__ __launch_bounds__(C::NT) void tile_dma_pair_kernel(Args a, int tiles_m, int tiles_n, int group_m, int c_vec_ok) {
+__global__ __launch_bounds__(C::NT) void tile_dma_pair_kernel(Args a, int tiles_m, int tiles_n, int group_m) {
     constexpr int BM = C::BM, BN = C::BN, BK = C::BK, NT = C::NT, TM = C::TM, TN = C::TN, NS = C::NS;
     static_assert(NS == 5, "the pairing schedule is written for a ring of five stages");
     using EL = EpiLayout<C>;
@@ -252,7 +252,7 @@ __global__ __launch_bounds__(C::NT) void tile_dma_pair_kernel(Args a, int tiles_
 #undef GEMM_WAIT_LDS_BARRIER
 
     if constexpr (PLAIN) tile_epilogue_plain<C>(acc, a, m0, n0);
-    else tile_epilogue<C>(acc, lds, a, m0, n0, c_vec_ok);
+    else tile_epilogue<C>(acc, lds, a, m0, n0);
 }
 
 template <class C>
@@ -261,16 +261,15 @@ hipError_t launch_dma_pair_variant(const Args& a, int group_m, hipStream_t strea
     const dim3 grid((unsigned)(tiles_m * tiles_n), (unsigned)a.batch), block(C::NT);
     const bool bf = a.dtype == DT_BF16;
     const bool akc = !a.transA, bkc = a.transB != 0;
-    const int c_vec_ok = c_rows_take_vec4(a);
     const bool plain = plain_epilogue_applies<C>(a);
 #define GEMM_TILE_LAUNCH(BF, AKC, BKC)                                                                             \
     do {                                                                                                           \
         if (plain)                                                                                                 \
             hipLaunchKernelGGL((tile_dma_pair_kernel<C, BF, AKC, BKC, true>), grid, block, 0, stream, a, tiles_m,  \
-                               tiles_n, group_m, c_vec_ok);                                                        \
+                               tiles_n, group_m);                                                        \
         else                                                                                                       \
             hipLaunchKernelGGL((tile_dma_pair_kernel<C, BF, AKC, BKC, false>), grid, block, 0, stream, a, tiles_m, \
-                               tiles_n, group_m, c_vec_ok);                                                        \
+                               tiles_n, group_m);                                                        \
     } while (0)
     if (bf) {
         if (akc && bkc) GEMM_TILE_LAUNCH(true, true, true);

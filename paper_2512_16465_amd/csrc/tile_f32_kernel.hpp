@@ -252,7 +252,7 @@ struct F32Planes {
 };
 
 template <class C, bool A_KC, bool B_KC>
-__global__ __launch_bounds__(C::NT, C::WAVES_PER_SIMD) void tile_f32_kernel(Args a, int tiles_m, int tiles_n, int group_m, int c_vec_ok) {
+__global__ __launch_bounds__(C::NT, C::WAVES_PER_SIMD) void tile_f32_kernel(Args a, int tiles_m, int tiles_n, int group_m) {
     using EL = EpiLayout<C>;
     constexpr int TI = C::TI, TJ = C::TJ;
     constexpr bool ASM = C::WAVES_PER_SIMD == 1;
@@ -515,7 +515,7 @@ __global__ __launch_bounds__(C::NT, C::WAVES_PER_SIMD) void tile_f32_kernel(Args
 #pragma unroll
                 for (int j = 0; j < TJ; ++j) *(f32x4*)(region + ((16 * i2 + c16) * EL::RS + j * 16 + 4 * g4) * 4) = acc[2 * b + i2][j];
         },
-        lds, a, m0, n0, c_vec_ok);
+        lds, a, m0, n0);
 }
 
 template <class C>
@@ -523,9 +523,8 @@ inline hipError_t launch_f32_tiles(const Args& a, int group_m, hipStream_t strea
     const int tiles_m = (int)((a.M + C::BM - 1) / C::BM), tiles_n = (int)((a.N + C::BN - 1) / C::BN);
     const dim3 grid((unsigned)(tiles_m * tiles_n), (unsigned)a.batch), block(C::NT);
     const bool akc = !a.transA, bkc = a.transB != 0;
-    const int c_vec_ok = c_rows_take_vec4(a);
 #define GEMM_TILE_LAUNCH(AKC, BKC) \
-    hipLaunchKernelGGL((tile_f32_kernel<C, AKC, BKC>), grid, block, 0, stream, a, tiles_m, tiles_n, group_m, c_vec_ok)
+    hipLaunchKernelGGL((tile_f32_kernel<C, AKC, BKC>), grid, block, 0, stream, a, tiles_m, tiles_n, group_m)
     if (akc && bkc) GEMM_TILE_LAUNCH(true, true);
     else if (akc && !bkc) GEMM_TILE_LAUNCH(true, false);
     else if (!akc && bkc) GEMM_TILE_LAUNCH(false, true);

@@ -25,6 +25,7 @@ struct Cfg {
     static constexpr int CPR = BK / 8;                 // 16-byte chunks per LDS row
     static constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2;
     static constexpr int STAGE = A_BYTES + B_BYTES;
+    static constexpr int WAVES_PER_SIMD = 4 * STAGE <= 160 * 1024 && TM * TN <= 4 ? 2 : 1;      // (two workgroups of the 128x128 tile share a unit's LDS)
     static_assert(BK == 32 || BK == 64, "the swizzle below is written for 64- or 128-byte rows");
     static_assert(WTM % 32 == 0 && WTN % 32 == 0, "wave sub-block must be whole 32x32 tiles");
 };
@@ -52,16 +53,20 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const char* base, in
     return __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (int)n, 0x00020000);
 }
 
+// The movers come in two forms.  ANY = false: every chunk starts on a 16-byte boundary and the contiguous dimension is whole
+// chunks.  ANY = true: rows start on any element and end anywhere (16-byte buffer loads need no alignment; the range
+// check drops a dword that straddles the end of the operand, so no such dword is ever asked for).
+
 // Operand whose k index is contiguous in memory: tile row r, k-chunk c is 16 bytes at
 // base + r*ld + 8c.  Each thread moves L chunks.
-template <int ROWS, int BK, int NT>
+template <int ROWS, int BK, int NT, bool ANY = false>
 struct LoaderKC {
     static constexpr int CPR = BK / 8, CHUNKS = ROWS * CPR, L = CHUNKS / NT;
     static_assert(CHUNKS % NT == 0, "chunks must divide evenly over the threads");
     u32x4 r[L];
     uint32_t goff[L];
 
-    __device__ __forceinline__ void init(int tid, int valid_rows, int64_t ld) {
+    __device__ __forceinline__ void init(int tid, int valid_rows, int64_t ld, int /*ahead*/ = 0) {
 #pragma unroll
         for (int i = 0; i < L; ++i) {
             const int id = i * NT + tid, row = id / CPR, c = id % CPR;
@@ -76,8 +81,27 @@ struct LoaderKC {
 #pragma unroll
         for (int i = 0; i < L; ++i) {
             const int c = (i * NT + tid) % CPR;
-            if (!MASKED || k0 + c * 8 < K) r[i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, goff[i], 0, 0);
+            if (!MASKED || k0 + c * 8 + (ANY ? 7 : 0) < K) r[i] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, goff[i], 0, 0);
             else r[i] = u32x4{0u, 0u, 0u, 0u};
+        }
+        if (ANY && MASKED && (K & 7)) {
+            // the chunks that hold a row's last k, element by element: all loads first (a lane without such a chunk reads the
+            // slab's first element and drops it), then the elements put in their places
+            uint32_t x[L][7];
+            const int rest = K & 7;
+#pragma unroll
+            for (int i = 0; i < L; ++i) {
+                const bool last = K - rest == k0 + (i * NT + tid) % CPR * 8;
+#pragma unroll
+                for (int e = 0; e < 7; ++e)
+                    x[i][e] = (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rsrc, last && e < rest ? goff[i] + 2 * e : 0u, 0, 0);
+            }
+#pragma unroll
+            for (int i = 0; i < L; ++i) {
+                const bool last = K - rest == k0 + (i * NT + tid) % CPR * 8;
+#pragma unroll
+                for (int e = 0; e < 7; ++e) r[i][e / 2] |= last && e < rest ? x[i][e] << (16 * (e & 1)) : 0u;
+            }
         }
     }
     __device__ __forceinline__ void lstore(char* lds, int tid) const {
@@ -102,19 +126,24 @@ struct LoaderKC {
 // Operand whose m (or n) index is contiguous in memory: element (k, r) is at base + k*ld + r.
 // A thread unit is 8 k-rows x 8 r: eight 16-byte loads, an 8x8 transposition of 16-bit values
 // in registers (one v_perm_b32 per output dword), eight 16-byte LDS stores.
-template <int ROWS, int BK, int NT>
+// ANY: the chunk with the edge of the matrix in it, and those past it, start 8 elements ahead of the edge instead, and
+// their rows go where they belong; the first row of a later tile's base is moved 8 elements ahead for that (the matrix has
+// at least 8 rows).
+template <int ROWS, int BK, int NT, bool ANY = false>
 struct LoaderMC {
     static constexpr int CPR = BK / 8, RC = ROWS / 8, UNITS = RC * CPR, U = (UNITS + NT - 1) / NT;
     static_assert(UNITS % 64 == 0, "whole waves must be active or idle");
     u32x4 r[U][8];
     uint32_t goff[U];
+    int row0[ANY ? U : 1];       // first row of the unit in the tile (negative: ahead of it)
 
-    __device__ __forceinline__ void init(int tid, int valid_rows, int64_t ld) {
+    __device__ __forceinline__ void init(int tid, int valid_rows, int64_t ld, int ahead = 0) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int unit = u * NT + tid, c = unit % RC, g = unit / RC;
             const int c8 = (c * 8 + 8 <= valid_rows) ? c * 8 : valid_rows - 8;   // stay inside the matrix
-            goff[u] = (uint32_t)((g * 8 * ld + c8) * 2);
+            goff[u] = (uint32_t)((g * 8 * ld + c8 + (ANY ? ahead : 0)) * 2);
+            if (ANY) row0[u] = c8;
         }
     }
     template <bool MASKED>
@@ -147,15 +176,16 @@ struct LoaderMC {
         const int u = q / 8, n = q % 8;
         const int unit = u * NT + tid, c = unit % RC, g = unit / RC;
         if (UNITS % NT != 0 && unit >= UNITS) return;
+        const int row = ANY ? row0[ANY ? u : 0] + n : c * 8 + n;
         u32x4 o;
         const uint32_t sel = (n & 1) ? 0x07060302u : 0x05040100u;   // high or low halves of both sources
 #pragma unroll
         for (int kp = 0; kp < 4; ++kp)
             o[kp] = __builtin_amdgcn_perm(r[u][2 * kp + 1][n >> 1], r[u][2 * kp][n >> 1], sel);
-        *(u32x4*)(lds + swz<CPR>(c * 8 + n, g)) = o;
+        if (!ANY || row >= 0) *(u32x4*)(lds + swz<CPR>(row, g)) = o;
     }
     static __device__ __forceinline__ const char* tile_base(const void* p, int64_t first_row, int64_t /*ld*/) {
-        return (const char*)p + first_row * 2;
+        return (const char*)p + (first_row - (ANY && first_row > 0 ? 8 : 0)) * 2;
     }
     static __device__ __forceinline__ int64_t k_step_bytes(int64_t ld) { return (int64_t)BK * ld * 2; }
 };
@@ -190,34 +220,35 @@ __device__ __forceinline__ void tile_of_workgroup(int pid, int tiles_m, int tile
 template <int OUT> struct OutVec;
 template <> struct OutVec<DT_F32> {
     typedef float elem;
-    static __device__ __forceinline__ f32x4 load4(const elem* p) { return *(const f32x4*)p; }
+    static __device__ __forceinline__ f32x4 load4(const elem* p) { return *(const f32x4_any*)p; }
     static __device__ __forceinline__ float load1(const elem* p) { return *p; }
-    static __device__ __forceinline__ void store4(elem* p, f32x4 v) { __builtin_nontemporal_store(v, (f32x4*)p); }
+    static __device__ __forceinline__ void store4(elem* p, f32x4 v) { __builtin_nontemporal_store(v, (f32x4_any*)p); }
     static __device__ __forceinline__ void store1(elem* p, float v) { *p = v; }
 };
 template <> struct OutVec<DT_BF16> {
     typedef uint16_t elem;
     static __device__ __forceinline__ f32x4 load4(const elem* p) {
-        const uint2 u = *(const uint2*)p;
+        const u32x2 u = *(const u32x2_any*)p;
         return f32x4{__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u),
                      __uint_as_float(u.y << 16), __uint_as_float(u.y & 0xffff0000u)};
     }
     static __device__ __forceinline__ float load1(const elem* p) { return bf16_bits_to_f32(*p); }
     static __device__ __forceinline__ void store4(elem* p, f32x4 v) {
         typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
-        __builtin_nontemporal_store(__builtin_bit_cast(u32x2, __builtin_convertvector(v, bf16x4)), (u32x2*)p);   // v_cvt_pk_bf16_f32, nearest even
+        __builtin_nontemporal_store(__builtin_bit_cast(u32x2, __builtin_convertvector(v, bf16x4)), (u32x2_any*)p);   // v_cvt_pk_bf16_f32, nearest even
     }
     static __device__ __forceinline__ void store1(elem* p, float v) { *p = __builtin_bit_cast(uint16_t, (__bf16)v); }
 };
 template <> struct OutVec<DT_F16> {
     typedef uint16_t elem;
     static __device__ __forceinline__ f32x4 load4(const elem* p) {
-        return f32x4{f16_bits_to_f32(p[0]), f16_bits_to_f32(p[1]), f16_bits_to_f32(p[2]), f16_bits_to_f32(p[3])};
+        const u32x2 u = *(const u32x2_any*)p;
+        return f32x4{f16_bits_to_f32((uint16_t)u.x), f16_bits_to_f32((uint16_t)(u.x >> 16)), f16_bits_to_f32((uint16_t)u.y), f16_bits_to_f32((uint16_t)(u.y >> 16))};
     }
     static __device__ __forceinline__ float load1(const elem* p) { return f16_bits_to_f32(*p); }
     static __device__ __forceinline__ void store4(elem* p, f32x4 v) {
         typedef __attribute__((ext_vector_type(4))) _Float16 f16x4;
-        __builtin_nontemporal_store(__builtin_bit_cast(u32x2, __builtin_convertvector(v, f16x4)), (u32x2*)p);    // v_cvt_f16_f32, nearest even
+        __builtin_nontemporal_store(__builtin_bit_cast(u32x2, __builtin_convertvector(v, f16x4)), (u32x2_any*)p);    // v_cvt_f16_f32, nearest even
     }
     static __device__ __forceinline__ void store1(elem* p, float v) { *p = f32_to_f16_bits(v); }
 };
@@ -244,7 +275,7 @@ struct EpiLayout {
 // that wave's accumulators, to region[(row * EL::RS + column) * 4]; `band` is an
 // std::integral_constant, so the accumulator registers it names are static.
 template <class C, class Dump>
-__device__ __forceinline__ void tile_epilogue_bands(Dump dump, char* lds, const Args& a, int64_t m0, int64_t n0, int c_vec_ok,
+__device__ __forceinline__ void tile_epilogue_bands(Dump dump, char* lds, const Args& a, int64_t m0, int64_t n0,
                                                     int64_t live_rows = INT64_MAX) {
     constexpr int TM = C::TM;
     using EL = EpiLayout<C>;
@@ -269,7 +300,7 @@ __device__ __forceinline__ void tile_epilogue_bands(Dump dump, char* lds, const 
     // needs static register numbers; the bands are walked by a real loop that picks the dump with
     // a compare chain, and the read-back/store part exists once.
     static_assert(TM <= 4, "the band switch below lists four cases");
-    const bool interior = c_vec_ok && (m0 + C::BM <= a.M) && (n0 + C::BN <= a.N);
+    const bool interior = (m0 + C::BM <= a.M) && (n0 + C::BN <= a.N);
     auto run_epilogue = [&](auto tag) {
         using OV = OutVec<decltype(tag)::value>;
         typename OV::elem* Cp = (typename OV::elem*)a.C;
@@ -323,7 +354,7 @@ __device__ __forceinline__ void tile_epilogue_bands(Dump dump, char* lds, const 
                     const int64_t row = m0 + wm * C::WTM + i * 32 + rl;
                     if (row < a.M && col < a.N) {
                         typename OV::elem* p = Cp + row * a.ldc + col;
-                        if (c_vec_ok && col + 3 < a.N) {
+                        if (col + 3 < a.N) {
                             f32x4 cin = {0.0f, 0.0f, 0.0f, 0.0f};
                             if (beta != 0.0f) cin = OV::load4(p);
                             f32x4 o;
@@ -352,7 +383,7 @@ __device__ __forceinline__ void tile_epilogue_bands(Dump dump, char* lds, const 
 // The staged epilogue for accumulators of the 32x32x16 MFMA.
 template <class C>
 __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[C::TM][C::TN], char* lds, const Args& a,
-                                              int64_t m0, int64_t n0, int c_vec_ok) {
+                                              int64_t m0, int64_t n0) {
     using EL = EpiLayout<C>;
     const int lane = threadIdx.x & 63;
     const int l32 = lane & 31, lhi = lane >> 5;
@@ -365,7 +396,7 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[C::TM][C::TN], char*
                 for (int v = 0; v < 16; ++v)
                     *(float*)(region + ((8 * (v >> 2) + 4 * lhi + (v & 3)) * EL::RS + j * 32 + l32) * 4) = acc[b][j][v];
         },
-        lds, a, m0, n0, c_vec_ok);
+        lds, a, m0, n0);
 }
 
 // The plainest epilogue, C = alpha*A*B on a problem made of whole tiles (beta == 0, no bias, no
@@ -407,8 +438,8 @@ inline bool plain_epilogue_applies(const Args& a) {
            a.ldc < (1 << 26);
 }
 
-template <class C, bool IS_BF16, bool A_KC, bool B_KC>
-__global__ __launch_bounds__(C::NT) void tile_kernel(Args a, int tiles_m, int tiles_n, int group_m, int c_vec_ok) {
+template <class C, bool IS_BF16, bool A_KC, bool B_KC, bool ANY = false>
+__global__ __launch_bounds__(C::NT, C::NT / 256 * C::WAVES_PER_SIMD) void tile_kernel(Args a, int tiles_m, int tiles_n, int group_m) {
     constexpr int BM = C::BM, BN = C::BN, BK = C::BK, NT = C::NT, TM = C::TM, TN = C::TN, CPR = C::CPR;
     using EL = EpiLayout<C>;
     constexpr int LDS_BYTES = 2 * C::STAGE > EL::BYTES ? 2 * C::STAGE : EL::BYTES;
@@ -427,12 +458,12 @@ __global__ __launch_bounds__(C::NT) void tile_kernel(Args a, int tiles_m, int ti
     const int valid_n = (a.N - n0) < BN ? (int)(a.N - n0) : BN;
     const int K = (int)a.K;
 
-    using LA = typename std::conditional<A_KC, LoaderKC<BM, BK, NT>, LoaderMC<BM, BK, NT>>::type;
-    using LB = typename std::conditional<B_KC, LoaderKC<BN, BK, NT>, LoaderMC<BN, BK, NT>>::type;
+    using LA = typename std::conditional<A_KC, LoaderKC<BM, BK, NT, ANY>, LoaderMC<BM, BK, NT, ANY>>::type;
+    using LB = typename std::conditional<B_KC, LoaderKC<BN, BK, NT, ANY>, LoaderMC<BN, BK, NT, ANY>>::type;
     LA la;
     LB lb;
-    la.init(tid, valid_m, a.lda);
-    lb.init(tid, valid_n, a.ldb);
+    la.init(tid, valid_m, a.lda, m0 > 0 ? 8 : 0);
+    lb.init(tid, valid_n, a.ldb, n0 > 0 ? 8 : 0);
     const char* pa = LA::tile_base(a.A, m0, a.lda);
     const char* pb = LB::tile_base(a.B, n0, a.ldb);
     const int64_t a_step = LA::k_step_bytes(a.lda), b_step = LB::k_step_bytes(a.ldb);
@@ -573,21 +604,18 @@ __global__ __launch_bounds__(C::NT) void tile_kernel(Args a, int tiles_m, int ti
         __syncthreads();                 // every wave is done with the operand stages: LDS is reused below
     }
 
-    tile_epilogue<C>(acc, lds, a, m0, n0, c_vec_ok);
+    tile_epilogue<C>(acc, lds, a, m0, n0);
 }
 
 // One translation unit per variant instantiates this with its Cfg.
-template <class C>
+template <class C, bool ANY = false>
 hipError_t launch_variant(const Args& a, int group_m, hipStream_t stream) {
     const int tiles_m = (int)((a.M + C::BM - 1) / C::BM), tiles_n = (int)((a.N + C::BN - 1) / C::BN);
     const dim3 grid((unsigned)(tiles_m * tiles_n), (unsigned)a.batch), block(C::NT);
     const bool bf = a.dtype == DT_BF16;
     const bool akc = !a.transA, bkc = a.transB != 0;
-    // vector access to C needs 16-byte (fp32) or 8-byte (16-bit types) aligned rows
-    const int c_vec_ok = c_rows_take_vec4(a);
-#define GEMM_TILE_LAUNCH(BF, AKC, BKC)                                                                       \
-    hipLaunchKernelGGL((tile_kernel<C, BF, AKC, BKC>), grid, block, 0, stream, a, tiles_m, tiles_n, group_m, \
-                       c_vec_ok)
+#define GEMM_TILE_LAUNCH(BF, AKC, BKC)                                                                            \
+    hipLaunchKernelGGL((tile_kernel<C, BF, AKC, BKC, ANY>), grid, block, 0, stream, a, tiles_m, tiles_n, group_m)
     if (bf) {
         if (akc && bkc) GEMM_TILE_LAUNCH(true, true, true);
         else if (akc && !bkc) GEMM_TILE_LAUNCH(true, true, false);

@@ -1,0 +1,71 @@
+"""Calls off the 16-byte grid on the matrix-core kernels of the general family: odd sizes, leading dimensions and base
+addresses in every layout and type, around the edges of tiles, slabs and chunks, whole and in k slices.  Integer data, so every
+element is exact; what lies behind a row (NaN) reaches no result and the padding of C keeps its contents."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2512_16465_amd as lg
+import workloads as wl
+from gpu_harness import BatchedDeviceProblem, DeviceProblem, c_bits_as_uint, decode_c, expected_bits_exact
+
+pytestmark = pytest.mark.gpu
+SHAPES = [(8, 8, 1), (9, 15, 7), (127, 129, 63), (131, 9, 65), (257, 263, 191), (264, 13, 200), (40, 521, 1031)]
+
+
+@pytest.fixture(scope="module")
+def handle():
+    h = lg.gemm_create()
+    yield h
+    torch.cuda.synchronize()
+    lg.gemm_destroy(h)
+
+
+def poisoned(inp, key, rows, cols, ld, dtype):
+    x = inp[key].reshape(rows, ld).copy()
+    x[:, cols:] = wl.to_bits(np.full((1,), np.nan, dtype=np.float32), dtype)[0]
+    return x.reshape(-1)
+
+
+@pytest.mark.parametrize("dtype", [wl.BF16, wl.F16, wl.F32])
+@pytest.mark.parametrize("ta,tb", [(0, 1), (0, 0), (1, 1), (1, 0)])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_every_variant(handle, shape, ta, tb, dtype):
+    M, N, K = shape
+    cfg = wl.Config("any", M, N, K, ta, tb, dtype, wl.F32 if (M + N) % 2 else dtype, alpha=1.0, beta=-1.0, bias_dist=("normal", 1.0),
+                    bias_dtype=wl.F32, lda=(M if ta else K) + 3, ldb=(K if tb else N) + 1, ldc=N + 2)
+    inp, _ = wl.make_integer_inputs(cfg, 7 * M + N, -2, 2)
+    want = oracle.decode(cfg.out_dtype, expected_bits_exact(cfg, inp)).reshape(M, N)
+    a_rows, a_cols = cfg.a_shape()
+    b_rows, b_cols = cfg.b_shape()
+    inp["A"], inp["B"] = poisoned(inp, "A", a_rows, a_cols, cfg.ld_a(), dtype), poisoned(inp, "B", b_rows, b_cols, cfg.ld_b(), dtype)
+    plans = [None] + [(v, s) for v in ((2, 3) if dtype == wl.F32 else (1,)) for s in (1, 3)] + [(0, 1)]
+    for plan in plans:
+        print(shape, ta, tb, dtype, plan, flush=True)
+        if plan is None:
+            lg.gemm_set_plan(handle)
+        else:
+            lg.gemm_set_plan(handle, lg.GEMM_KERNEL_GENERAL, *plan)
+        p = DeviceProblem(cfg, inp, a_offset_elems=1, b_offset_elems=3)
+        before = p.result_bits().copy()
+        p.run(handle)
+        got_plan = lg.gemm_get_last_plan(handle)
+        lg.gemm_set_plan(handle)
+        assert got_plan[0] == lg.GEMM_KERNEL_GENERAL and (plan is None or got_plan[1] == plan[0]), (plan, got_plan)
+        after = p.result_bits()
+        got = oracle.decode(cfg.out_dtype, c_bits_as_uint(cfg, after))
+        assert np.array_equal(got, want), f"{plan}: {np.argwhere(got != want)[:4]} of {int((got != want).sum())}"
+        if M > 1:
+            assert np.array_equal(before[:-1, N:].view(np.uint8), after[:-1, N:].view(np.uint8)), "padding of C written"
+
+
+@pytest.mark.parametrize("dtype,variant", [(wl.BF16, 1), (wl.F32, 2), (wl.F32, 3)])
+def test_odd_batch(handle, dtype, variant):
+    cfg = wl.Config("any", 170, 245, 133, 0, 0, dtype, wl.F32)
+    p = BatchedDeviceProblem(cfg, 5, cfg.stride_a() + 1, cfg.stride_b() + 3, cfg.stride_c() + 1, seed=3, integer=True)
+    lg.gemm_set_plan(handle, lg.GEMM_KERNEL_GENERAL, variant, 1)
+    p.run(handle)
+    lg.gemm_set_plan(handle)
+    assert lg.gemm_get_last_plan(handle) == (lg.GEMM_KERNEL_GENERAL, variant, 1)
+    p.check("odd batch", exact=True)
