@@ -730,7 +730,12 @@ AutoPlan automatic_plan(const Args& a, int num_cus, bool batch_aligned) {
     // MFMA kernel with 16 columns per workgroup (8 x 4096 x 4096 8.7 us against 12.3)
     const bool few_rows = a.dtype != gemm::DT_F32 && a.batch == 1 && gemm::skinny_supports(a) &&
                           (gemm::skinny_variant_of(a) == 4 || gemm::skinny_variant_of(a) == 5);
-    if (may_stream && (long_stream || only_stream || few_rows)) {
+    // ... the same two kernels where only the number of stored rows (columns of C) is no multiple of 8: without a split
+    // nothing in them works on groups of columns
+    const int ragged = batch_aligned && roof.cls != GEMM_COMPUTE_BOUND ? gemm::skinny_ragged_columns_variant(a) : -1;
+    if (ragged >= 0) {
+        ap.plan = gemm_plan_t{GEMM_KERNEL_SKINNY, ragged, 1};
+    } else if (may_stream && (long_stream || only_stream || few_rows)) {
         ap.plan = gemm_plan_t{GEMM_KERNEL_SKINNY, gemm::skinny_variant_of(a), gemm::skinny_default_split(a, num_cus)};
     } else if (gemm::tile_supports(a) && batch_aligned &&
                (a.dtype != gemm::DT_F32 || ((a.M + 63) / 64) * ((a.N + 63) / 64) * a.batch >= kF32MinTiles)) {

@@ -192,7 +192,7 @@ int gemv16_default_split(const Args& a, int num_cus) {
 }
 
 hipError_t launch_gemv16(const Args& a, int split_k, float* workspace, hipStream_t stream) {
-    if (!gemv16_supports(a)) return hipErrorInvalidValue;
+    if (!gemv16_supports(a) && (split_k > 1 || skinny_ragged_columns_variant(a) != 4)) return hipErrorInvalidValue;
     if (split_k < 1) split_k = 1;
     const int64_t trips = g16_trips(a);
     if (split_k > trips) split_k = (int)trips;

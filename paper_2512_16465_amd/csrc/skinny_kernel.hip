@@ -753,6 +753,24 @@ int skinny_variant_of(const Args& a) {
     return (a.dtype == DT_F32 ? 2 : 0) + (a.transB ? 1 : 0);
 }
 
+// A wave of either kernel stores its own columns one by one; only the reduction of a split works on groups of eight.  One
+// launch against split quarter tiles with their second one: 1 x 4097 x 4096 5.3 us against 12.8, 4 x 4097 x 4096 8.0 / 13.3,
+// 1 x 32003 x 4096 36.5 / 44.3, 8 x 1031 x 4096 8.1 / 13.5, 16 x 4095 x 4096 9.6 / 13.1, 8 x 9001 x 4096 18.0 / 18.6.
+// Without a split a wave walks all of k, which is as long as k whatever the number of columns.  It ends even with the
+// tiles at K = 8192 (16 x 515 x 7936 13.2 / 14.0) and loses beyond (16 x 515 x 16384 22.1 / 17.4, 4 x 259 x 16384 16.3 / 15.4,
+// 4 x 259 x 32768 29.0 / 18.1), with a single row, whose trips cost a third, at twice that (1 x 31 x 16384 8.1 / 14.3,
+// 1 x 31 x 65536 25.4 / 20.9).
+constexpr int64_t SK_RAGGED_MAX_K = 8192, SK_RAGGED_MAX_K_ONE_ROW = 16384;
+int skinny_ragged_columns_variant(const Args& a) {
+    if (a.N % 8 == 0 || a.batch != 1 || !a.transB || a.transA || a.dtype == DT_F32) return -1;
+    if (a.K > (a.M == 1 ? SK_RAGGED_MAX_K_ONE_ROW : SK_RAGGED_MAX_K)) return -1;
+    Args r = a;
+    r.N = (a.N + 7) / 8 * 8;
+    if (!skinny_supports(r)) return -1;
+    const int v = skinny_variant_of(r);
+    return v == 4 || v == 5 ? v : -1;
+}
+
 bool skinny_variant_serves(const Args& a, int variant) {
     if (variant < 0 || variant == skinny_variant_of(a)) return true;
     if (variant == 4) return gemv16_supports(a);

@@ -69,3 +69,25 @@ def test_odd_batch(handle, dtype, variant):
     lg.gemm_set_plan(handle)
     assert lg.gemm_get_last_plan(handle) == (lg.GEMM_KERNEL_GENERAL, variant, 1)
     p.check("odd batch", exact=True)
+
+
+@pytest.mark.parametrize("dtype", [wl.BF16, wl.F16])
+@pytest.mark.parametrize("M,N,K", [(1, 9, 8), (1, 4097, 520), (3, 1031, 1032), (4, 12301, 264), (5, 4095, 256), (8, 4099, 1288), (16, 1025, 776)])
+def test_few_rows_and_columns_that_are_no_multiple_of_eight(handle, M, N, K, dtype):
+    cfg = wl.Config("ragged", M, N, K, 0, 1, dtype, wl.F32 if N % 4 == 1 else dtype, alpha=1.0, beta=1.0, bias_dist=("normal", 1.0),
+                    bias_dtype=wl.F32, lda=K + 8, ldb=K + 24, ldc=N + 3)
+    inp, _ = wl.make_integer_inputs(cfg, M + N, -2, 2)
+    want = oracle.decode(cfg.out_dtype, expected_bits_exact(cfg, inp)).reshape(M, N)
+    inp["A"], inp["B"] = poisoned(inp, "A", M, K, cfg.ld_a(), dtype), poisoned(inp, "B", N, K, cfg.ld_b(), dtype)
+    p = DeviceProblem(cfg, inp)
+    before = p.result_bits().copy()
+    p.run(handle)
+    assert lg.gemm_get_last_plan(handle) == (lg.GEMM_KERNEL_SKINNY, 4 if M <= 4 else 5, 1)
+    after = p.result_bits()
+    assert np.array_equal(oracle.decode(cfg.out_dtype, c_bits_as_uint(cfg, after)), want)
+    if M > 1:
+        assert np.array_equal(before[:-1, N:].view(np.uint8), after[:-1, N:].view(np.uint8)), "padding of C written"
+    # a forced plan of the family is refused as it always was
+    lg.gemm_set_plan(handle, lg.GEMM_KERNEL_SKINNY, -1, 0)
+    assert p.run(handle, check=False) == lg.GEMM_ERR_UNSUPPORTED
+    lg.gemm_set_plan(handle)
