@@ -211,7 +211,7 @@ const char* gemm_status_string(gemm_status_t s);
 typedef enum {
     GEMM_KERNEL_AUTO = 0,      /* let the library choose (default) */
     GEMM_KERNEL_GENERAL = 1,   /* any shape and alignment.  Variant 0: one thread per output element.  Variant 1 (bf16 / fp16):
-                                  128x128 MFMA tiles; variants 2, 3 (fp32): the fp32 tiles.  A forced variant that
+                                  128x128 MFMA tiles; variant 2 (fp32): 64x64 fp32 tiles.  A forced variant that
                                   cannot serve the call (and -1) falls back to 0 */
     GEMM_KERNEL_MFMA_TILE = 2, /* LDS-staged macro-tile kernel on MFMA */
     GEMM_KERNEL_SKINNY = 3     /* streaming kernels with split-K for few rows of C.  bf16 / fp16, M <= 64: variant 0

@@ -232,11 +232,12 @@ hipError_t launch_gemv16(const Args& a, int split_k, float* workspace, hipStream
 
 // Operands off the 16-byte grid (any base address that suits the element type, any leading dimension, any sizes): the
 // general family.  Variant 0 takes everything; the others are the register-staged 128x128 macro-tile kernel with movers
-// that need no alignment (1, 16-bit operands) and the fp32 tile kernels, which need none (2: 128x128, 3: 64x64).
-constexpr int kGeneralVariants = 4;
+// that need no alignment (1, 16-bit operands) and the 64x64 fp32 tile kernel, which needs none (2).
+constexpr int kGeneralVariants = 3;
 const char* general_variant_name(int variant);
 bool general_variant_supports(const Args& a, int variant);
 hipError_t launch_general(const Args& a, int variant, int group_m, hipStream_t stream);
 hipError_t launch_any_tile(const Args& a, int group_m, hipStream_t stream);
+hipError_t launch_any_f32_tile(const Args& a, int group_m, hipStream_t stream);
 
 }  // namespace gemm

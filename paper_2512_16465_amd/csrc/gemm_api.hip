@@ -677,31 +677,33 @@ struct AutoPlan {
 // every unit, 0.0305 per round of two (1023^3 25 to 29 us, 2049x2051x2045 53, 4095x4097x4093 245 to 270; 16x8191x4095 83 whole,
 // 27 in 8 slices; 1201x1203x4095 78 whole, 49 in 4).  The general kernel: 4.5 us and, per step of 16 along k, 0.35 us and
 // 0.25 ns per block at least (65x67x129 6.8 us against 12, 255x1023x255 14 against 20; 129x257x511 19 against 14.5,
-// 2049x2051x2045 1245).  fp32 operands: the fp32 tiles, which are ahead down to a single tile.
+// 2049x2051x2045 1245).  fp32 operands: the 64x64 tiles with folded sums, 1.5 us and 3 ns per element of k behind the plain
+// ones, against the same general kernel (33x35x31 5.8 us against 4.8, 65x67x129 8.7 / 6.9, 255x1023x255 12.7 / 14.7,
+// 129x257x511 10.8 in 4 slices / 18.6, 2049x2051x2045 146 / 1336, 4095x4097x4093 958 / about 10 ms).
 constexpr int64_t kGeneralMinSliceK = 64;
 
 gemm_plan_t general_plan(const Args& a, int num_cus) {
     const int64_t cus = num_cus > 0 ? num_cus : 256;
     gemm_plan_t plan{GEMM_KERNEL_GENERAL, 0, 1};
     const bool f32 = a.dtype == gemm::DT_F32;
-    if (!gemm::general_variant_supports(a, f32 ? 3 : 1)) return plan;
+    if (!gemm::general_variant_supports(a, f32 ? 2 : 1)) return plan;
     const double blocks = (double)((a.M + 15) / 16) * (double)((a.N + 15) / 16) * (double)a.batch;
-    double best = f32 ? 0.0 : 4.5 + (double)((a.K + 15) / 16) * (0.35 + 0.00025 * blocks);
-    for (int variant = f32 ? 2 : 1; variant <= (f32 ? 3 : 1); ++variant)
-        for (int sl : {1, 2, 4, 8, 16}) {
-            const int64_t P = (a.N + 7) / 8 * 8;
-            if (sl > 1 && (a.batch != 1 || a.K / sl < kGeneralMinSliceK || (int64_t)sl * a.M * P * 4 > (int64_t)kScratchBytes)) break;
-            double t;
-            if (f32) {
-                t = f32_time(a, variant == 2, sl, cus);
-            } else {
-                const int64_t wgs = ((a.M + 127) / 128) * ((a.N + 127) / 128) * a.batch * sl;
-                const double per_k = wgs <= cus / 2 ? 0.0175 : (wgs <= cus ? 0.021 : 0.0305 * (double)((wgs + 2 * cus - 1) / (2 * cus)));
-                t = 10.0 + per_k * ((double)a.K / sl);
-                if (sl > 1) t = (t + kSliceLaunchF32 + (double)sl * (double)(a.M * P) * 8.0 / kSliceMoveRate) / kSliceMarginF32;
-            }
-            if (best == 0.0 || t < best) { best = t; plan.variant = variant; plan.split_k = sl; }
+    double best = 4.5 + (double)((a.K + 15) / 16) * (0.35 + 0.00025 * blocks);
+    const int variant = f32 ? 2 : 1;
+    for (int sl : {1, 2, 4, 8, 16}) {
+        const int64_t P = (a.N + 7) / 8 * 8;
+        if (sl > 1 && (a.batch != 1 || a.K / sl < kGeneralMinSliceK || (int64_t)sl * a.M * P * 4 > (int64_t)kScratchBytes)) break;
+        double t;
+        if (f32) {
+            t = f32_time(a, false, sl, cus) + 1.5 + 0.003 * ((double)a.K / sl);
+        } else {
+            const int64_t wgs = ((a.M + 127) / 128) * ((a.N + 127) / 128) * a.batch * sl;
+            const double per_k = wgs <= cus / 2 ? 0.0175 : (wgs <= cus ? 0.021 : 0.0305 * (double)((wgs + 2 * cus - 1) / (2 * cus)));
+            t = 10.0 + per_k * ((double)a.K / sl);
+            if (sl > 1) t = (t + kSliceLaunchF32 + (double)sl * (double)(a.M * P) * 8.0 / kSliceMoveRate) / kSliceMarginF32;
         }
+        if (t < best) { best = t; plan.variant = variant; plan.split_k = sl; }
+    }
     return plan;
 }
 

@@ -61,14 +61,14 @@ __global__ __launch_bounds__(GT * GT) void general_kernel(Args a) {
 
 const char* general_variant_name(int variant) {
     static const char* const names[kGeneralVariants] = {"general_16x16", "general_128x128x64_w2x2",
-                                                        "general_f32_128x128x32_w2x2", "general_f32_64x64x32_w2x2"};
+                                                        "general_f32_64x64x32_w2x2"};
     return variant >= 0 && variant < kGeneralVariants ? names[variant] : nullptr;
 }
 
 bool general_variant_supports(const Args& a, int variant) {
     if (variant == 0) return true;
     if (variant < 0 || variant >= kGeneralVariants) return false;
-    if ((a.dtype == DT_F32) != (variant >= 2) || a.M < 1 || a.N < 1 || a.K < 1) return false;
+    if ((a.dtype == DT_F32) != (variant == 2) || a.M < 1 || a.N < 1 || a.K < 1) return false;
     const uintptr_t off = a.dtype == DT_F32 ? 3 : 1;                    // elements at their natural alignment
     if (((uintptr_t)a.A & off) || ((uintptr_t)a.B & off)) return false;
     // 32-bit byte offsets inside a slab, a 32-bit workgroup count
@@ -81,7 +81,7 @@ bool general_variant_supports(const Args& a, int variant) {
 hipError_t launch_general(const Args& a, int variant, int group_m, hipStream_t stream) {
     if (!general_variant_supports(a, variant)) return hipErrorInvalidValue;
     if (variant == 1) return launch_any_tile(a, group_m, stream);
-    if (variant >= 2) return launch_tile(a, variant == 2 ? 11 : 13, group_m, TileSplit{0, 1, nullptr}, stream);
+    if (variant == 2) return launch_any_f32_tile(a, group_m, stream);
     const int64_t tiles = ((a.M + GT - 1) / GT) * ((a.N + GT - 1) / GT);
     if (tiles == 0) return hipSuccess;
     const int64_t grid = tiles < (1 << 20) ? tiles : (1 << 20);

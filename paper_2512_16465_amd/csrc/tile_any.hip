@@ -1,6 +1,8 @@
-// The register-staged 128x128 macro-tile kernel for 16-bit operands of any alignment.
-#include "tile_kernel.hpp"
+// The kernels of the general family on the matrix cores: the register-staged 128x128 macro-tile kernel for 16-bit operands
+// of any alignment, and the 64x64 fp32 tile with the sums of each slab folded.
+#include "tile_f32_kernel.hpp"
 
 namespace gemm {
 hipError_t launch_any_tile(const Args& a, int group_m, hipStream_t stream) { return tile::launch_variant<tile::Cfg<128, 128, 64, 2, 2>, true>(a, group_m, stream); }
+hipError_t launch_any_f32_tile(const Args& a, int group_m, hipStream_t stream) { return tile::launch_f32_tiles<tile::F32CfgT<64, 64, 2, 2, true>>(a, group_m, stream); }
 }  // namespace gemm

@@ -44,9 +44,14 @@
 namespace gemm {
 namespace tile {
 
-// BM x BN workgroup tile, WM x WN waves.
-template <int BM_, int BN_, int WM_, int WN_>
+// BM x BN workgroup tile, WM x WN waves.  FOLD: each slab is summed by itself and added to the accumulators by the vector
+// ALUs, which rounds a sum once per 32 elements of k at full magnitude (without: six times, on the matrix unit).  The general
+// family takes it, whose plain kernel sums sixteen at a time: 2-norm error against 64 bits, Gaussian data, K = 128 / 1024 /
+// 4095, plain kernel 9.3e-8 / 1.65e-7 / 2.98e-7, folded 5.6e-8 / 1.18e-7 / 2.21e-7, not folded 1.5e-7 / 4.9e-7 / 1.0e-6
+// (the fp32 instruction is behind all three).  2049x2051x2045 145 us against 120 without the folds.
+template <int BM_, int BN_, int WM_, int WN_, bool FOLD_ = false>
 struct F32CfgT {
+    static constexpr bool FOLD = FOLD_;
     static constexpr int BM = BM_, BN = BN_, BK = 32, WM = WM_, WN = WN_;
     static constexpr int NT = WM * WN * 64;
     static constexpr int WTM = BM / WM, WTN = BN / WN;
@@ -58,6 +63,7 @@ struct F32CfgT {
     static_assert(BM * RAW_STRIDE * 4 <= 3 * A_PLANE && BN * RAW_STRIDE * 4 <= 3 * B_PLANE, "the fp32 form of a slab fits the region of the three planes");
     static constexpr int WGS_PER_CU = 2 * STAGE > 80 * 1024 ? 1 : 3;
     static constexpr int WAVES_PER_SIMD = WGS_PER_CU * NT / 256;
+    static_assert(!FOLD || WAVES_PER_SIMD > 1, "the additions need matrix instructions whose wait states the compiler supplies");
 };
 
 // f(0), f(1) .. f(N - 1) with the numbers as types: the bodies are placed slot by slot and name registers
@@ -294,6 +300,20 @@ __global__ __launch_bounds__(C::NT, C::WAVES_PER_SIMD) void tile_f32_kernel(Args
             for (int j = 0; j < TJ; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     };
     clear_acc();
+    // what the matrix instructions add to: the accumulators, or the sums of one slab
+    constexpr bool FOLD = C::FOLD;
+    f32x4 slab_sum[FOLD ? TI : 1][FOLD ? TJ : 1];
+    auto sum = [&](int m) -> f32x4& {
+        if constexpr (FOLD) return slab_sum[m / TJ][m % TJ];
+        else return acc[m / TJ][m % TJ];
+    };
+    auto fold = [&](int m) {
+        if constexpr (FOLD) acc[m / TJ][m % TJ] += slab_sum[m / TJ][m % TJ];
+    };
+    auto clear_sum = [&](int m) {
+        if constexpr (FOLD) slab_sum[m / TJ][m % TJ] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    };
+    if constexpr (FOLD) static_for<TI * TJ>([&](auto m) { clear_sum(decltype(m)::value); });
 
     uint32_t fa[TI], fb[TJ];                              // this lane's fragment of 16 rows in a plane: row c16, k = 8 g4 .. + 7
 #pragma unroll
@@ -354,7 +374,10 @@ __global__ __launch_bounds__(C::NT, C::WAVES_PER_SIMD) void tile_f32_kernel(Args
         constexpr int PAIRS = 2 * (LA::L + LB::L), WORK = PAIRS * LA::PARTS, SLOTS = STEPS * NM, LAST = SLOTS - SLOTS / 16;
         static_for<SLOTS>([&](auto slot_) {
             constexpr int slot = decltype(slot_)::value, n = slot / NM, s = (n + STEPS - 1) % STEPS, m = slot % NM, i = m / TJ, j = m % TJ;
-            f32_mfma_bf16<ASM>(acc[i][j], bf[Planes::of_b(s)][j], af[Planes::of_a(s)][i]);
+            // (the sums of slab kt-1 are added NM - 1 instructions after their last product, just before slab kt needs them)
+            if constexpr (slot >= NM - 1 && slot < 2 * NM - 1) fold(slot - (NM - 1));
+            if constexpr (n == 1) clear_sum(m);
+            f32_mfma_bf16<ASM>(sum(m), bf[Planes::of_b(s)][j], af[Planes::of_a(s)][i]);
             // the planes that the next step, step n of slab kt, is the first to need
             if constexpr (Planes::EARLY) {
                 if constexpr (slot == 0) {
@@ -401,7 +424,9 @@ __global__ __launch_bounds__(C::NT, C::WAVES_PER_SIMD) void tile_f32_kernel(Args
         if (kt + 1 < k_tiles) iteration(kt + 1, std::integral_constant<int, 1>{});
     }
 #pragma unroll
-    for (int m = 0; m < NM; ++m) f32_mfma_bf16<ASM>(acc[m / TJ][m % TJ], bf[0][m % TJ], af[0][m / TJ]);
+    for (int m = 0; m < NM; ++m) f32_mfma_bf16<ASM>(sum(m), bf[0][m % TJ], af[0][m / TJ]);
+#pragma unroll
+    for (int m = 0; m < NM; ++m) fold(m);
 #pragma unroll
     for (int i = 0; i < TI; ++i) f32_settle<ASM>(acc[i]);
 
@@ -461,6 +486,8 @@ __global__ __launch_bounds__(C::NT, C::WAVES_PER_SIMD) void tile_f32_kernel(Args
         for (int kt = 0; kt < k_tiles; ++kt) {
             load_slab(kt);
             clear_past(kt);
+#pragma unroll
+            for (int m = 0; m < NM; ++m) clear_sum(m);
             __syncthreads();                              // the last slab has been read, and its flag
             if (tid == 0) flag[0] = 0;
             __syncthreads();
@@ -484,7 +511,7 @@ __global__ __launch_bounds__(C::NT, C::WAVES_PER_SIMD) void tile_f32_kernel(Args
                     for (int q = 0; q < 4; ++q)
 #pragma unroll
                         for (int m = 0; m < NM; ++m)
-                            f32_mfma_f32<ASM>(acc[m / TJ][m % TJ], br[m % TJ][q], ar[m / TJ][q]);
+                            f32_mfma_f32<ASM>(sum(m), br[m % TJ][q], ar[m / TJ][q]);
                 }
             } else {
                 la.split_and_store(lds, largest);
@@ -499,9 +526,11 @@ __global__ __launch_bounds__(C::NT, C::WAVES_PER_SIMD) void tile_f32_kernel(Args
 #pragma unroll
                     for (int j = 0; j < TJ; ++j) br[j] = *(const u32x4*)(lds + q * C::B_PLANE + fb[j]);
 #pragma unroll
-                    for (int m = 0; m < NM; ++m) f32_mfma_bf16<ASM>(acc[m / TJ][m % TJ], br[m % TJ], ar[m / TJ]);
+                    for (int m = 0; m < NM; ++m) f32_mfma_bf16<ASM>(sum(m), br[m % TJ], ar[m / TJ]);
                 }
             }
+#pragma unroll
+            for (int m = 0; m < NM; ++m) fold(m);
         }
     }
 #pragma unroll

@@ -40,7 +40,7 @@ def test_every_variant(handle, shape, ta, tb, dtype):
     a_rows, a_cols = cfg.a_shape()
     b_rows, b_cols = cfg.b_shape()
     inp["A"], inp["B"] = poisoned(inp, "A", a_rows, a_cols, cfg.ld_a(), dtype), poisoned(inp, "B", b_rows, b_cols, cfg.ld_b(), dtype)
-    plans = [None] + [(v, s) for v in ((2, 3) if dtype == wl.F32 else (1,)) for s in (1, 3)] + [(0, 1)]
+    plans = [None] + [(v, s) for v in ((2,) if dtype == wl.F32 else (1,)) for s in (1, 3)] + [(0, 1)]
     for plan in plans:
         print(shape, ta, tb, dtype, plan, flush=True)
         if plan is None:
@@ -60,7 +60,7 @@ def test_every_variant(handle, shape, ta, tb, dtype):
             assert np.array_equal(before[:-1, N:].view(np.uint8), after[:-1, N:].view(np.uint8)), "padding of C written"
 
 
-@pytest.mark.parametrize("dtype,variant", [(wl.BF16, 1), (wl.F32, 2), (wl.F32, 3)])
+@pytest.mark.parametrize("dtype,variant", [(wl.BF16, 1), (wl.F32, 2)])
 def test_odd_batch(handle, dtype, variant):
     cfg = wl.Config("any", 170, 245, 133, 0, 0, dtype, wl.F32)
     p = BatchedDeviceProblem(cfg, 5, cfg.stride_a() + 1, cfg.stride_b() + 3, cfg.stride_c() + 1, seed=3, integer=True)
@@ -91,3 +91,21 @@ def test_few_rows_and_columns_that_are_no_multiple_of_eight(handle, M, N, K, dty
     lg.gemm_set_plan(handle, lg.GEMM_KERNEL_SKINNY, -1, 0)
     assert p.run(handle, check=False) == lg.GEMM_ERR_UNSUPPORTED
     lg.gemm_set_plan(handle)
+
+
+@pytest.mark.parametrize("K", [40, 65, 129, 1025])
+def test_fp32_error_is_no_larger_than_that_of_the_plain_kernel(handle, K):
+    M, N = 261, 131
+    g = torch.Generator(device="cuda").manual_seed(K)
+    A, B = torch.randn(M, K, generator=g, device="cuda"), torch.randn(K, N, generator=g, device="cuda")
+    want, errors = A.double() @ B.double(), {}
+    for plan in ((2, 1), (0, 1)):
+        lg.gemm_set_plan(handle, lg.GEMM_KERNEL_GENERAL, *plan)
+        C = torch.empty(M, N, device="cuda")
+        lg.gemm_run(handle, M, N, K, 0, 0, wl.F32, 1.0, A.data_ptr(), K, B.data_ptr(), N, 0.0, C.data_ptr(), N, lg.make_epilogue(wl.F32),
+                    torch.cuda.current_stream().cuda_stream)
+        assert lg.gemm_get_last_plan(handle) == (lg.GEMM_KERNEL_GENERAL, *plan)
+        errors[plan[0]] = ((C.double() - want).norm() / want.norm()).item()
+    lg.gemm_set_plan(handle)
+    # one rounding per 32 elements of k at the sum's magnitude against one per 16
+    assert errors[2] <= errors[0], errors
