@@ -388,7 +388,8 @@ def main():
             roof = None          # launch-latency bound: no roofline is meaningful
         elif bound == "mfma":
             ach = cfg.flops() / (ev_mean * 1e-3) / 1e12
-            peak = FP32_MFMA_PEAK_TFLOPS if cfg.dtype == wl.F32 else MFMA_BF16_PEAK_TFLOPS    # the contraction's own type
+            # fp32 products are sums of six bf16 ones on the same matrix cores
+            peak = MFMA_BF16_PEAK_TFLOPS / (6 if cfg.dtype == wl.F32 else 1)
             roof = {"bound": "mfma", "achieved": ach, "peak": peak, "unit": "TFLOP/s",
                     "frac": ach / peak, "traffic": measured_traffic(name), "kernel": kname}
         else:

@@ -220,9 +220,9 @@ typedef enum {
                                   variants 2 and 3, the same two layouts on the vector ALUs.  B stored N x K, bf16 /
                                   fp16, A row-major, has two one-launch forms besides variant 1: variant 4 on the vector
                                   ALUs (M <= 8; automatic up to 4 rows) and variant 5, variant 1 with 16 columns per
-                                  workgroup (M <= 16; automatic for 5 to 16 rows on weights of 128 MiB at most).  N is a
-                                  multiple of 8 in forced plans; the automatic choice takes variants 4 and 5 in one
-                                  slice for any other N too (K <= 8192; 16384 with one row).  The layout and type of the call decide among them; variant -1 takes the automatic one, a
+                                  workgroup (M <= 16; automatic for 5 to 16 rows on weights of 128 MiB at most).  Variants 4
+                                  and 5 in one slice also serve the N that are no multiple of 8 in the calls that the
+                                  automatic choice gives them (K <= 8192; 16384 with one row).  The layout and type of the call decide among them; variant -1 takes the automatic one, a
                                   variant forced against the call is GEMM_ERR_UNSUPPORTED */
 } gemm_kernel_t;
 

@@ -192,11 +192,13 @@ double small_tile_time(const Args& a, int64_t tiles, int slices, int64_t cus) {
     return t;
 }
 
-// Most slices an fp32 call may be cut in: what its workspace has always been sized for.  A caller that reserved the
+// The slices an fp32 call is cut in: what its workspace has always been sized for.  A caller that reserved the
 // workspace for a call, captures it on a handle that has none, or makes it through gemm_run_noalloc must not find that a
-// faster kernel needs more of it, so this rule (the estimate for the fp32 instruction: 0.0275 / 0.085 us per element of k for
-// a 64x64 / 128x128 tile alone on its unit, 0.02 / 0.068 per tile otherwise) stays as it was when the kernel changed.
-int most_f32_slices(const Args& a, int64_t cus) {
+// faster kernel needs more of it, and fewer of them would round longer sums (532x1296x1296 3.3e-7 of the result's norm in
+// 4, 5.5e-7 whole), so this rule (the estimate for the fp32 instruction: 0.0275 / 0.085 us per element of k for a 64x64 /
+// 128x128 tile alone on its unit, 0.02 / 0.068 per tile otherwise) stays as it was when the kernel changed.  Its counts are
+// still good ones: 532x1296x1296 25.1 us in 4 slices against 30.6 whole, 3072x312x1984 37.9 in 2 against 44.1.
+int f32_slices(const Args& a, int64_t cus) {
     int most = 1;
     double best = 0.0;
     for (int big = 0; big < 2; ++big) {
@@ -247,17 +249,9 @@ double f32_time(const Args& a, bool big, int slices, int64_t cus) {
 TileChoice choose_tile(const Args& a, int num_cus) {
     const int64_t cus = num_cus > 0 ? num_cus : 256;
     if (a.dtype == gemm::DT_F32) {
-        const int most_slices = most_f32_slices(a, cus);
-        int best_variant = kF32SmallTileVariant, best_slices = 1;
-        double best_time = 0.0;
-        for (int big = 0; big < 2; ++big) {
-            for (int sl : {1, 2, 4, 8, 16}) {
-                if (sl > most_slices) break;
-                const double t = f32_time(a, big != 0, sl, cus);
-                if (best_time == 0.0 || t < best_time) { best_time = t; best_variant = big ? kF32TileVariant : kF32SmallTileVariant; best_slices = sl; }
-            }
-        }
-        return TileChoice{best_variant, 0, best_slices, 0.0};
+        const int slices = f32_slices(a, cus);
+        const bool big = f32_time(a, true, slices, cus) < f32_time(a, false, slices, cus);
+        return TileChoice{big ? kF32TileVariant : kF32SmallTileVariant, 0, slices, 0.0};
     }
     // a batch multiplies the number of workgroups; its trailing round is never split along K
     const int64_t small = ((a.M + 127) / 128) * ((a.N + 127) / 128) * a.batch;
@@ -850,6 +844,9 @@ gemm_status_t run_batch(gemm_handle_t h, bool fixed_scratch, int64_t batch, int6
                 split_first = (int)(tiles - tiles % cus);
                 if (split_first == tiles) plan.split_k = 1;
             }
+        } else if (plan.kernel == GEMM_KERNEL_SKINNY && plan.variant >= 4 && plan.split_k == 1 && batch_aligned &&
+                   plan.variant == gemm::skinny_ragged_columns_variant(a)) {
+            // (a plan that the automatic choice reported can be forced)
         } else if (plan.kernel == GEMM_KERNEL_SKINNY) {
             if (!gemm::skinny_supports(a) || !batch_aligned) return GEMM_ERR_UNSUPPORTED;
             if (!gemm::skinny_variant_serves(a, plan.variant)) return GEMM_ERR_UNSUPPORTED;

@@ -87,7 +87,11 @@ def test_few_rows_and_columns_that_are_no_multiple_of_eight(handle, M, N, K, dty
     assert np.array_equal(oracle.decode(cfg.out_dtype, c_bits_as_uint(cfg, after)), want)
     if M > 1:
         assert np.array_equal(before[:-1, N:].view(np.uint8), after[:-1, N:].view(np.uint8)), "padding of C written"
-    # a forced plan of the family is refused as it always was
+    # the reported plan can be forced, any other of the family is refused as it always was
+    lg.gemm_set_plan(handle, *lg.gemm_get_last_plan(handle))
+    again = DeviceProblem(cfg, inp)
+    again.run(handle)
+    assert np.array_equal(again.result_bits().view(np.uint8), after.view(np.uint8))
     lg.gemm_set_plan(handle, lg.GEMM_KERNEL_SKINNY, -1, 0)
     assert p.run(handle, check=False) == lg.GEMM_ERR_UNSUPPORTED
     lg.gemm_set_plan(handle)
