@@ -673,7 +673,7 @@ struct AutoPlan {
 // 0.25 ns per block at least (65x67x129 6.8 us against 12, 255x1023x255 14 against 20; 129x257x511 19 against 14.5,
 // 2049x2051x2045 1245).  fp32 operands: the 64x64 tiles with folded sums, 1.5 us and 3 ns per element of k behind the plain
 // ones, against the same general kernel (33x35x31 5.8 us against 4.8, 65x67x129 8.7 / 6.9, 255x1023x255 12.7 / 14.7,
-// 129x257x511 10.8 in 4 slices / 18.6, 2049x2051x2045 146 / 1336, 4095x4097x4093 958 / about 10 ms).
+// 129x257x511 10.8 in 4 slices / 18.6, 2049x2051x2045 147 to 156 / 1280 to 1330, 4095x4097x4093 958 / about 10 ms).
 constexpr int64_t kGeneralMinSliceK = 64;
 
 gemm_plan_t general_plan(const Args& a, int num_cus) {
