@@ -654,7 +654,7 @@ __global__ __launch_bounds__(ST_WAVES * 64) void skinny_nt_narrow_kernel(Args a,
 template <int S>
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(Args a, int split_k, const float* ws) {
     const int64_t groups_per_row = (a.N + 7) / 8;       // rows of a partial result are whole groups of eight
-    const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (g >= a.M * groups_per_row) return;
     const int64_t row = g / groups_per_row, col = (g % groups_per_row) * 8;
     const int64_t slice = a.M * groups_per_row * 8;
@@ -900,10 +900,16 @@ hipError_t launch_skinny(const Args& call, int split_k, float* workspace, hipStr
     return launch_splitk_reduce(a, split_k, workspace, stream);
 }
 
+// The kernel is one trip to memory long.  Few threads are spread over the chip, a wave per workgroup: with 256 threads
+// each, 8 x 8192 gave 32 workgroups on 256 units (8 x 8192 x 8192 34.5 -> 33.7 to 34.2 us, fp32 64 x 264 x 2504 in 16 slices 14.4 ->
+// 12.3); from 256 such workgroups on every unit has one either way.
+constexpr int64_t kReduceSpread = 65536;
+
 hipError_t launch_splitk_reduce(const Args& a, int split_k, const float* partials, hipStream_t stream) {
     if (split_k < 1 || partials == nullptr) return hipErrorInvalidValue;
     const int64_t threads = a.M * ((a.N + 7) / 8);
-    const dim3 rgrid((unsigned)((threads + 255) / 256)), rblock(256);
+    const int64_t per_block = threads <= kReduceSpread ? 64 : 256;
+    const dim3 rgrid((unsigned)((threads + per_block - 1) / per_block)), rblock((unsigned)per_block);
     switch (split_k) {
         case 2: hipLaunchKernelGGL(splitk_reduce_kernel<2>, rgrid, rblock, 0, stream, a, split_k, partials); break;
         case 4: hipLaunchKernelGGL(splitk_reduce_kernel<4>, rgrid, rblock, 0, stream, a, split_k, partials); break;
