@@ -32,7 +32,8 @@
 // together at most K 2^-133 times the largest magnitude, and where every result of the tile is 2^26 times that nothing is
 // lost that fp32 would keep.  Otherwise the tile's operands are scanned for such elements, and only if there are any, or
 // one beyond 2^40, the tile is computed again with the slabs in question multiplied by v_mfma_f32_16x16x4_f32.
-// (A NaN takes either way.)
+// (A NaN takes either way.)  Only elements of the operands count, not what lies past their edges and is loaded with them: the
+// magnitudes are kept by row, at no cost since a thread takes the same rows of every slab.
 //
 // Edges: loads past the end of an operand return zero dword by dword through the buffer descriptor's range check;
 // elements of a k-contiguous operand past K are cleared when they are staged.  Nothing needs more than the natural
@@ -93,8 +94,12 @@ struct F32Mover {
     static_assert(L == 2 || L == 4 || L == 8, "64, 128 or 256 rows");
     static constexpr int PLANE = ROWS * C::BK * 2;
     static constexpr int KQ = C::BK / 4, RB = ROWS / 4;                     // quads per row (k-contiguous); blocks of four rows
+    // Rows that the thread takes elements of, the same ones in every slab: a quad holds one of them, or two rows' pairs.
+    static constexpr bool PAIR_ROWS = !KC && G == 2;
+    static constexpr int LINES = PAIR_ROWS ? 2 * L : L;
     uint32_t goff[L];      // byte offset of the load from the slab's first byte
     uint32_t loff[L];      // byte offset of the quad (of its first row's part) in a plane
+    float largest[LINES];  // largest magnitude seen in each row
     f32x4 r[L];
 
     // first row and first k of quad i
@@ -102,7 +107,12 @@ struct F32Mover {
         return KC ? (i * C::NT + tid) / KQ : (((i / G) * C::NT + tid) % RB) * 4 + (i % G) * (4 / G);
     }
     static __device__ __forceinline__ uint32_t quad_k(int i, int tid) { return KC ? (i * C::NT + tid) % KQ * 4 : ((i / G) * C::NT + tid) / RB * G; }
+    static __device__ __forceinline__ int line_row(int line, int tid) {
+        return PAIR_ROWS ? (int)quad_row(line / 2, tid) + line % 2 : (int)quad_row(line, tid);
+    }
     __device__ __forceinline__ void init(int tid, int64_t ld) {
+#pragma unroll
+        for (int i = 0; i < LINES; ++i) largest[i] = 0.0f;
 #pragma unroll
         for (int i = 0; i < L; ++i) {
             const uint32_t row = quad_row(i, tid), k = quad_k(i, tid);
@@ -114,10 +124,11 @@ struct F32Mover {
         return KC ? (const char*)p + first_row * ld * 4 : (const char*)p + first_row * 4;
     }
     static __device__ __forceinline__ int64_t k_step_bytes(int64_t ld) { return KC ? (int64_t)C::BK * 4 : (int64_t)C::BK * ld * 4; }
-    static __device__ __forceinline__ int64_t total_bytes(int64_t rows, int64_t K, int64_t ld) {
-        return KC ? ((rows - 1) * ld + K) * 4 : ((K - 1) * ld + rows) * 4;
+    // bytes of the operand from the first element of a slab of k elements of a tile with `rows` rows of it to the last one
+    static __device__ __forceinline__ uint32_t slab_bytes(int rows, int k, int64_t ld) {
+        return (uint32_t)((KC ? (rows - 1) * ld + k : (k - 1) * ld + rows) * 4);
     }
-    // Every load is issued (past the end of the operand it reads as zero); what a k-contiguous operand holds past K is
+    // Every load is issued (past the end of the slab it reads as zero); what a k-contiguous operand holds past K is
     // cleared when it is staged -- clearing it here would be a write to a register with a load in flight, which waits for it.
     __device__ __forceinline__ void gload_one(int i, __amdgpu_buffer_rsrc_t rsrc) {
         r[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, goff[i], 0, 0));
@@ -155,9 +166,9 @@ struct F32Mover {
     float wide[2];
     u32x2 piece[3];        // of the quad at hand
     template <int PART, int I, int H>
-    __device__ __forceinline__ void split_part(float& largest) {
+    __device__ __forceinline__ void split_part() {
         float x = get<I, H, 0>(), y = get<I, H, 1>();
-        if constexpr (PART == 0) asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(largest) : "v"(x), "v"(y));      // (a NaN is passed over)
+        if constexpr (PART == 0) asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(largest[PAIR_ROWS ? 2 * I + H : I]) : "v"(x), "v"(y));      // (a NaN is passed over)
         if constexpr (PART == 4) {
             uint32_t w = pack_bf16(x, y);
             asm volatile("" ::"v"(w));
@@ -185,22 +196,29 @@ struct F32Mover {
             }
         }
     }
-    __device__ __forceinline__ void split_and_store(char* region, float& largest) {
+    __device__ __forceinline__ void split_and_store(char* region) {
         static_for<L>([&](auto i) {
             constexpr int I = decltype(i)::value;
-            static_for<2 * PARTS>([&](auto w) { split_part<decltype(w)::value % PARTS, I, decltype(w)::value / PARTS>(largest); });
+            static_for<2 * PARTS>([&](auto w) { split_part<decltype(w)::value % PARTS, I, decltype(w)::value / PARTS>(); });
             store_pieces(region, I);
         });
     }
-    // an element that the split cannot take
-    __device__ __forceinline__ bool outside() const {
+    // largest magnitude among the thread's rows of the operand (the tile's first `rows`)
+    __device__ __forceinline__ float largest_of(int rows, int tid) const {
+        float m = 0.0f;
+#pragma unroll
+        for (int i = 0; i < LINES; ++i) m = fmaxf(m, line_row(i, tid) < rows ? largest[i] : 0.0f);
+        return m;
+    }
+    // an element of the operand that the split cannot take (an m/n-contiguous one is loaded past its edge as well)
+    __device__ __forceinline__ bool outside(int rows, int tid) const {
         bool out = false;
 #pragma unroll
         for (int i = 0; i < L; ++i)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const float m = __builtin_fabsf(r[i][e]);
-                out = out || m > kSplitLargest || (m < kSplitSmallest && m != 0.0f);
+                out = out || ((m > kSplitLargest || (m < kSplitSmallest && m != 0.0f)) && (KC || ((int)quad_row(i, tid) & ~3) + e < rows));
             }
         return out;
     }
@@ -276,6 +294,7 @@ __global__ __launch_bounds__(C::NT, C::WAVES_PER_SIMD) void tile_f32_kernel(Args
     int tm, tn;
     tile_of_workgroup(blockIdx.x, tiles_m, tiles_n, group_m, tm, tn);
     const int64_t m0 = (int64_t)tm * C::BM, n0 = (int64_t)tn * C::BN;
+    const int rows_a = (int)(a.M - m0 < C::BM ? a.M - m0 : C::BM), rows_b = (int)(a.N - n0 < C::BN ? a.N - n0 : C::BN);
     const int K = (int)a.K;
 
     using LA = F32Mover<A_KC, C::BM, C>;
@@ -287,8 +306,6 @@ __global__ __launch_bounds__(C::NT, C::WAVES_PER_SIMD) void tile_f32_kernel(Args
     const char* pa = LA::tile_base(a.A, m0, a.lda);
     const char* pb = LB::tile_base(a.B, n0, a.ldb);
     const int64_t a_step = LA::k_step_bytes(a.lda), b_step = LB::k_step_bytes(a.ldb);
-    const int64_t a_bytes = LA::total_bytes(a.M, a.K, a.lda) - (pa - (const char*)a.A);
-    const int64_t b_bytes = LB::total_bytes(a.N, a.K, a.ldb) - (pb - (const char*)a.B);
 
     // accumulator (i, j): B's fragment is the instruction's first operand, so lane (c16, g4) holds row 16 i + c16 and
     // columns 16 j + 4 g4 .. + 3 of the wave sub-block
@@ -322,15 +339,15 @@ __global__ __launch_bounds__(C::NT, C::WAVES_PER_SIMD) void tile_f32_kernel(Args
     for (int j = 0; j < TJ; ++j) fb[j] = C::B_REGION + swz<4>(wn * C::WTN + j * 16 + c16, g4);
 
     // The order of the slabs is free: a partial one comes first, so that the loop only sees whole ones.  Past the last
-    // slab the loop asks twice more and gets zeros or k values it has had; they are taken apart and not used.
+    // slab the loop asks twice more and gets zeros (what lies there in memory is not the operand's).
     const int partial = K % C::BK, k_tiles = K / C::BK + (partial ? 1 : 0);
-    auto slab_rsrc = [&](const char* p, int64_t step, int64_t bytes, int t) {
-        const int64_t at = partial ? (t == 0 ? k_tiles - 1 : t - 1) : t;
-        return make_rsrc(p + at * step, bytes - at * step);
-    };
+    auto slab_of = [&](int t) { return (int64_t)(partial ? (t == 0 ? k_tiles - 1 : t - 1) : t); };
+    auto slab_k = [&](int t) { return partial && t == 0 ? partial : C::BK; };
+    auto slab_a = [&](int t) { return make_rsrc(pa + slab_of(t) * a_step, t < k_tiles ? LA::slab_bytes(rows_a, slab_k(t), a.lda) : 0); };
+    auto slab_b = [&](int t) { return make_rsrc(pb + slab_of(t) * b_step, t < k_tiles ? LB::slab_bytes(rows_b, slab_k(t), a.ldb) : 0); };
     auto load_slab = [&](int t) {
-        la.gload(slab_rsrc(pa, a_step, a_bytes, t));
-        lb.gload(slab_rsrc(pb, b_step, b_bytes, t));
+        la.gload(slab_a(t));
+        lb.gload(slab_b(t));
     };
     auto clear_past = [&](int t) {
         if (t == 0 && partial) { la.clear_past(partial, tid); lb.clear_past(partial, tid); }
@@ -343,17 +360,16 @@ __global__ __launch_bounds__(C::NT, C::WAVES_PER_SIMD) void tile_f32_kernel(Args
     auto read_a = [&](const char* stage, int p, int i) { af[p][i] = *(const u32x4*)(stage + p * C::A_PLANE + fa[i]); };
     auto read_b = [&](const char* stage, int p, int j) { bf[p][j] = *(const u32x4*)(stage + p * C::B_PLANE + fb[j]); };
 
-    float largest = 0.0f;
     if (k_tiles > 0) {
         LA la1 = la;                  // the first two slabs in one trip to memory
         LB lb1 = lb;
         load_slab(0);
-        la1.gload(slab_rsrc(pa, a_step, a_bytes, 1));
-        lb1.gload(slab_rsrc(pb, b_step, b_bytes, 1));
+        la1.gload(slab_a(1));
+        lb1.gload(slab_b(1));
         __builtin_amdgcn_sched_barrier(0);
         clear_past(0);
-        la.split_and_store(lds, largest);
-        lb.split_and_store(lds + C::B_REGION, largest);
+        la.split_and_store(lds);
+        lb.split_and_store(lds + C::B_REGION);
 #pragma unroll
         for (int i = 0; i < LA::L; ++i) la.r[i] = la1.r[i];
 #pragma unroll
@@ -364,11 +380,15 @@ __global__ __launch_bounds__(C::NT, C::WAVES_PER_SIMD) void tile_f32_kernel(Args
     for (int i = 0; i < TI; ++i) af[0][i] = u32x4{0u, 0u, 0u, 0u};       // the step ahead of the first slab adds nothing
 #pragma unroll
     for (int j = 0; j < TJ; ++j) bf[0][j] = u32x4{0u, 0u, 0u, 0u};
+    const char *next_a = pa + slab_of(2) * a_step, *next_b = pb + slab_of(2) * b_step;      // slab kt+2: a whole one
+    const uint32_t whole_a = LA::slab_bytes(rows_a, C::BK, a.lda), whole_b = LB::slab_bytes(rows_b, C::BK, a.ldb);
     auto iteration = [&](int kt, auto stage_) {
         constexpr int stage = decltype(stage_)::value;
         const char* cur = lds + stage * C::STAGE;
         char* nxt = lds + (1 - stage) * C::STAGE;
-        const __amdgpu_buffer_rsrc_t ra = slab_rsrc(pa, a_step, a_bytes, kt + 2), rb = slab_rsrc(pb, b_step, b_bytes, kt + 2);
+        const __amdgpu_buffer_rsrc_t ra = make_rsrc(next_a, kt + 2 < k_tiles ? whole_a : 0), rb = make_rsrc(next_b, kt + 2 < k_tiles ? whole_b : 0);
+        next_a += a_step;
+        next_b += b_step;
         __syncthreads();              // slab kt is staged; every wave has the last planes of slab kt-1 in registers
         // step 5 of slab kt-1, then steps 0 to 4 of slab kt
         constexpr int PAIRS = 2 * (LA::L + LB::L), WORK = PAIRS * LA::PARTS, SLOTS = STEPS * NM, LAST = SLOTS - SLOTS / 16;
@@ -408,10 +428,10 @@ __global__ __launch_bounds__(C::NT, C::WAVES_PER_SIMD) void tile_f32_kernel(Args
                 constexpr int w = w0 + decltype(w_)::value, pair = w / LA::PARTS, part = w % LA::PARTS, quad = pair / 2;
                 constexpr bool done = part == LA::PARTS - 1 && pair % 2 == 1;
                 if constexpr (quad < LA::L) {
-                    la.template split_part<part, quad, pair % 2>(largest);
+                    la.template split_part<part, quad, pair % 2>();
                     if constexpr (done) { la.store_pieces(nxt, quad); la.gload_after(quad, ra); }
                 } else {
-                    lb.template split_part<part, quad - LA::L, pair % 2>(largest);
+                    lb.template split_part<part, quad - LA::L, pair % 2>();
                     if constexpr (done) { lb.store_pieces(nxt + C::B_REGION, quad - LA::L); lb.gload_after(quad - LA::L, rb); }
                 }
             });
@@ -434,7 +454,7 @@ __global__ __launch_bounds__(C::NT, C::WAVES_PER_SIMD) void tile_f32_kernel(Args
     // exchange between the threads; then with the one there is.
     auto set_if = [&](int word, bool mine) { if (mine) flag[word] = 1; };
     auto is_set = [&](int word) { return __builtin_amdgcn_readfirstlane(flag[word]) != 0; };      // (behind a barrier)
-    auto below = [&](float largest_there) {               // (only what is inside C: a tile's rows and columns past its edge are zero)
+    auto below = [&](float largest_there) {               // (only what is inside C: past its edge there are products of what lies past an operand's edge)
         const float floor = largest_there * (float)K * 0x1p-107f;
         const int64_t rows = a.M - (m0 + wm * C::WTM + c16), cols = a.N - (n0 + wn * C::WTN + 4 * g4);
         bool small = false;
@@ -448,6 +468,7 @@ __global__ __launch_bounds__(C::NT, C::WAVES_PER_SIMD) void tile_f32_kernel(Args
         return small;
     };
     if (k_tiles == 0) __syncthreads();
+    float largest = fmaxf(la.largest_of(rows_a, tid), lb.largest_of(rows_b, tid));
     set_if(0, below(kSplitLargest));
     set_if(1, largest > kSplitLargest);
     __syncthreads();
@@ -463,16 +484,15 @@ __global__ __launch_bounds__(C::NT, C::WAVES_PER_SIMD) void tile_f32_kernel(Args
         __syncthreads();
         if (is_set(2)) {
             bool out = false;
-            LA la1 = la;              // two slabs in flight (past the last one: zeros, or k values seen before)
+            LA la1 = la;              // two slabs in flight (past the last one: zeros)
             LB lb1 = lb;
 #pragma unroll 1
             for (int kt = 0; kt < k_tiles; kt += 2) {
                 load_slab(kt);
-                la1.gload(slab_rsrc(pa, a_step, a_bytes, kt + 1));
-                lb1.gload(slab_rsrc(pb, b_step, b_bytes, kt + 1));
+                la1.gload(slab_a(kt + 1));
+                lb1.gload(slab_b(kt + 1));
                 clear_past(kt);
-                out = out || la.outside() || lb.outside();
-                if (kt + 1 < k_tiles) out = out || la1.outside() || lb1.outside();
+                out = out || la.outside(rows_a, tid) || lb.outside(rows_b, tid) || la1.outside(rows_a, tid) || lb1.outside(rows_b, tid);
             }
             set_if(3, out);
             __syncthreads();
@@ -491,7 +511,7 @@ __global__ __launch_bounds__(C::NT, C::WAVES_PER_SIMD) void tile_f32_kernel(Args
             __syncthreads();                              // the last slab has been read, and its flag
             if (tid == 0) flag[0] = 0;
             __syncthreads();
-            set_if(0, la.outside() || lb.outside());
+            set_if(0, la.outside(rows_a, tid) || lb.outside(rows_b, tid));
             __syncthreads();
             if (is_set(0)) {
                 la.store_raw(lds, tid);
@@ -514,8 +534,8 @@ __global__ __launch_bounds__(C::NT, C::WAVES_PER_SIMD) void tile_f32_kernel(Args
                             f32_mfma_f32<ASM>(sum(m), br[m % TJ][q], ar[m / TJ][q]);
                 }
             } else {
-                la.split_and_store(lds, largest);
-                lb.split_and_store(lds + C::B_REGION, largest);
+                la.split_and_store(lds);
+                lb.split_and_store(lds + C::B_REGION);
                 __syncthreads();
 #pragma unroll 1
                 for (int s = 0; s < STEPS; ++s) {

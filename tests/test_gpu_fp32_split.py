@@ -53,3 +53,28 @@ def test_values_outside_the_split(handle, variant, M, N, K, ta, tb):
     bad = ~((got == want) | (np.isnan(got) & np.isnan(want)))
     # row 7: its lost element is a rounding away from every sum (|sum| >= 1 against 2^-149 * 2^31)
     assert not bad.any(), (variant, sorted(set(np.argwhere(bad)[:, 0]))[:8], int(bad.sum()))
+
+
+# what lies behind the rows of an operand (padding, or the neighbouring columns of a larger matrix) decides nothing: the bits
+# are those of a run with zeros there
+@pytest.mark.parametrize("ta,tb", [(0, 1), (1, 0), (0, 0), (1, 1)])
+@pytest.mark.parametrize("kernel,variant,M,N,K,pad", [(lg.GEMM_KERNEL_MFMA_TILE, 13, 100, 68, 96, 60), (lg.GEMM_KERNEL_MFMA_TILE, 13, 196, 132, 100, 36),
+                                                      (lg.GEMM_KERNEL_MFMA_TILE, 11, 196, 260, 128, 60), (lg.GEMM_KERNEL_MFMA_TILE, 11, 2100, 2068, 72, 60),
+                                                      (lg.GEMM_KERNEL_GENERAL, 2, 99, 69, 96, 59), (lg.GEMM_KERNEL_GENERAL, 2, 130, 67, 101, 61)])
+def test_memory_outside_the_operands_decides_nothing(handle, kernel, variant, M, N, K, pad, ta, tb):
+    rng = np.random.default_rng([11, M, K])
+    a_shape, b_shape = ((K, M) if ta else (M, K)), ((N, K) if tb else (K, N))
+    a, b = (np.zeros((s[0], s[1] + pad), np.float32) for s in (a_shape, b_shape))
+    a[:, :a_shape[1]], b[:, :b_shape[1]] = rng.standard_normal(a_shape), rng.standard_normal(b_shape)
+    cfg = wl.Config("padding", M, N, K, ta, tb, wl.F32, wl.F32, lda=a.shape[1], ldb=b.shape[1])
+    results = []
+    for outside in (0.0, np.inf, 1e30, 1e-40):
+        a[:, a_shape[1]:], b[:, b_shape[1]:] = outside, outside
+        lg.gemm_set_plan(handle, kernel, variant, 1)
+        p = DeviceProblem(cfg, {"A": wl.to_bits(a.reshape(-1), wl.F32), "B": wl.to_bits(b.reshape(-1), wl.F32), "C": None, "bias": None})
+        p.run(handle)
+        lg.gemm_set_plan(handle)
+        assert lg.gemm_get_last_plan(handle) == (kernel, variant, 1)
+        results.append(p.result_bits().copy())
+    for outside, got in zip((np.inf, 1e30, 1e-40), results[1:]):
+        assert np.array_equal(got.view(np.uint32), results[0].view(np.uint32)), (outside, int((got != results[0]).sum()))
