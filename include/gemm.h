@@ -96,7 +96,8 @@ gemm_status_t gemm_create(gemm_handle_t* out);
  * set aside.  This is the one call besides gemm_destroy that frees device memory, and it may block:
  * the caller must have synchronised every stream that used the handle.  The skinny family needs
  * split_k * M * N * 4 bytes; the macro-tile family needs, for a split last round, (tiles in that
- * round) * split_k * (tile rows * tile columns) * 4, and for k slices split_k * M * N * 4;
+ * round) * split_k * (tile rows * tile columns) * 4, and for k slices split_k * M * N * 4; the
+ * general family split_k * M * (N rounded up to a multiple of 8) * 4, at most 32 MiB in an automatic plan;
  * 256 MiB covers every shape of the bench.  bytes == 0 only frees the set-aside buffers.
  * Errors: GEMM_ERR_INVALID_ARG for a null handle or another current device; GEMM_ERR_ALLOC if the
  * allocation failed (the old workspace stays); GEMM_ERR_HIP if freeing failed.
@@ -126,7 +127,8 @@ gemm_status_t gemm_workspace_size(gemm_handle_t h, size_t* bytes);
  * 8 elements and a contiguous dimension that is a multiple of 8 (bf16/fp16; 4 for fp32); other calls run
  * the general family with the same result contract (matrix cores too, but for the smallest calls).
  * Such a call may be cut in k slices, with at most GEMM_NOALLOC_SCRATCH_BYTES of workspace; where none is to be had (the
- * handle has not enough and the stream is being captured, or memory is out) it runs whole, in another order of summation.
+ * handle has not enough and the stream is being captured, or memory is out) its slices are computed one after another, which
+ * takes longer and gives the same bits.
  *
  * Errors (C is untouched in every error case detected before launch):
  *   GEMM_ERR_INVALID_ARG  null handle; negative size; ld smaller than the stored row; a null

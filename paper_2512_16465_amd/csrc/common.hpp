@@ -236,8 +236,10 @@ hipError_t launch_gemv16(const Args& a, int split_k, float* workspace, hipStream
 constexpr int kGeneralVariants = 3;
 const char* general_variant_name(int variant);
 bool general_variant_supports(const Args& a, int variant);
-hipError_t launch_general(const Args& a, int variant, int group_m, hipStream_t stream);
-hipError_t launch_any_tile(const Args& a, int group_m, hipStream_t stream);
-hipError_t launch_any_f32_tile(const Args& a, int group_m, hipStream_t stream);
+// slice_len: 0, or the length of the k slices in which variants 1 and 2 then compute the call without any workspace, one
+// after another, to the same bits as the slices side by side and launch_splitk_reduce behind them.
+hipError_t launch_general(const Args& a, int variant, int group_m, hipStream_t stream, int64_t slice_len = 0);
+hipError_t launch_any_tile(const Args& a, int group_m, hipStream_t stream, int64_t slice_len);
+hipError_t launch_any_f32_tile(const Args& a, int group_m, hipStream_t stream, int64_t slice_len);
 
 }  // namespace gemm

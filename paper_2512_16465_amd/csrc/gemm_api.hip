@@ -370,7 +370,7 @@ struct Workspace {
         if (fixed) return bytes <= kScratchBytes ? GEMM_OK : GEMM_ERR_SCRATCH_LIMIT;
         return ensure_workspace(h, bytes);
     }
-    // the same for a plan that can do without: false where there is nothing to be had
+    // the same for a plan that can do without: false where there is nothing to be had (never: the static scratch)
     bool obtain(size_t bytes, hipStream_t stream) const {
         if (fixed || bytes <= h->workspace_bytes) return ensure(bytes) == GEMM_OK;
         hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
@@ -561,13 +561,19 @@ gemm_status_t launch_plan(const Workspace& ws, const Args& a, gemm_plan_t& plan,
         }
     } else {
         if (plan.split_k > 1) {
-            // k slices, as above; a call of this family has never needed a workspace, so where there is none to be had (the
-            // stream is being captured, memory is out) it runs whole
+            // k slices, as above; a call of this family has never failed for want of a workspace, so where there is none to
+            // be had (the stream is being captured, memory is out) its slices are computed one after another, to the same bits
             const int64_t slabs = (K + 31) / 32, len = ((slabs + plan.split_k - 1) / plan.split_k) * 32, P = (N + 7) / 8 * 8;
             plan.split_k = (int)((K + len - 1) / len);
-            if (plan.split_k < 2 || !ws.obtain((size_t)plan.split_k * (size_t)M * (size_t)P * sizeof(float), stream)) plan.split_k = 1;
             if (plan.split_k > 1) {
+                const size_t need = (size_t)plan.split_k * (size_t)M * (size_t)P * sizeof(float);
+                if (ws.fixed && need > kScratchBytes) return GEMM_ERR_SCRATCH_LIMIT;
+                const bool side_by_side = ws.obtain(need, stream);
                 if (allocate_only) return GEMM_OK;
+                if (!side_by_side) {
+                    e = gemm::launch_general(a, plan.variant, kTileBandRows, stream, len);
+                    return e == hipSuccess ? GEMM_OK : GEMM_ERR_HIP;
+                }
                 e = gemm::launch_general(slices_of(a, plan.split_k, len, ws.ptr(), P), plan.variant, kTileBandRows, stream);
                 if (e == hipSuccess) e = gemm::launch_splitk_reduce(a, plan.split_k, ws.ptr(), stream);
                 return e == hipSuccess ? GEMM_OK : GEMM_ERR_HIP;

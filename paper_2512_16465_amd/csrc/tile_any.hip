@@ -3,6 +3,12 @@
 #include "tile_f32_kernel.hpp"
 
 namespace gemm {
-hipError_t launch_any_tile(const Args& a, int group_m, hipStream_t stream) { return tile::launch_variant<tile::Cfg<128, 128, 64, 2, 2>, true>(a, group_m, stream); }
-hipError_t launch_any_f32_tile(const Args& a, int group_m, hipStream_t stream) { return tile::launch_f32_tiles<tile::F32CfgT<64, 64, 2, 2, true>>(a, group_m, stream); }
+hipError_t launch_any_tile(const Args& a, int group_m, hipStream_t stream, int64_t slice_len) {
+    using C = tile::Cfg<128, 128, 64, 2, 2>;
+    return slice_len ? tile::launch_variant<C, true, true>(a, group_m, stream, slice_len) : tile::launch_variant<C, true>(a, group_m, stream);
+}
+hipError_t launch_any_f32_tile(const Args& a, int group_m, hipStream_t stream, int64_t slice_len) {
+    using C = tile::F32CfgT<64, 64, 2, 2, true>;
+    return slice_len ? tile::launch_f32_tiles<C, true>(a, group_m, stream, slice_len) : tile::launch_f32_tiles<C>(a, group_m, stream);
+}
 }  // namespace gemm

@@ -275,25 +275,18 @@ struct F32Planes {
     static constexpr bool EARLY = C::TI * C::TJ < 8;
 };
 
+// The accumulators of one tile of op(A) * op(B); every wave is done with `lds` when it returns.
+// Accumulator (i, j): B's fragment is the instruction's first operand, so lane (c16, g4) holds row 16 i + c16 and
+// columns 16 j + 4 g4 .. + 3 of the wave sub-block.
 template <class C, bool A_KC, bool B_KC>
-__global__ __launch_bounds__(C::NT, C::WAVES_PER_SIMD) void tile_f32_kernel(Args a, int tiles_m, int tiles_n, int group_m) {
-    using EL = EpiLayout<C>;
+__device__ __forceinline__ void f32_tile_product(const Args& a, int64_t m0, int64_t n0, char* lds, float* wave_largest, uint32_t* flag,
+                                                 f32x4 (&acc)[C::TI][C::TJ]) {
     constexpr int TI = C::TI, TJ = C::TJ;
     constexpr bool ASM = C::WAVES_PER_SIMD == 1;
-    constexpr int LDS_BYTES = 2 * C::STAGE > EL::BYTES ? 2 * C::STAGE : EL::BYTES;
-    __shared__ __attribute__((aligned(128))) char lds[LDS_BYTES];
-    __shared__ float wave_largest[C::WM * C::WN];
-    __shared__ uint32_t flag[4];
-    select_batch(a);
-
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int c16 = lane & 15, g4 = lane >> 4;
     const int wm = wave % C::WM, wn = wave / C::WM;
-
-    int tm, tn;
-    tile_of_workgroup(blockIdx.x, tiles_m, tiles_n, group_m, tm, tn);
-    const int64_t m0 = (int64_t)tm * C::BM, n0 = (int64_t)tn * C::BN;
     const int rows_a = (int)(a.M - m0 < C::BM ? a.M - m0 : C::BM), rows_b = (int)(a.N - n0 < C::BN ? a.N - n0 : C::BN);
     const int K = (int)a.K;
 
@@ -307,9 +300,6 @@ __global__ __launch_bounds__(C::NT, C::WAVES_PER_SIMD) void tile_f32_kernel(Args
     const char* pb = LB::tile_base(a.B, n0, a.ldb);
     const int64_t a_step = LA::k_step_bytes(a.lda), b_step = LB::k_step_bytes(a.ldb);
 
-    // accumulator (i, j): B's fragment is the instruction's first operand, so lane (c16, g4) holds row 16 i + c16 and
-    // columns 16 j + 4 g4 .. + 3 of the wave sub-block
-    f32x4 acc[TI][TJ];
     auto clear_acc = [&]() {
 #pragma unroll
         for (int i = 0; i < TI; ++i)
@@ -556,6 +546,37 @@ __global__ __launch_bounds__(C::NT, C::WAVES_PER_SIMD) void tile_f32_kernel(Args
 #pragma unroll
     for (int i = 0; i < TI; ++i) f32_settle<ASM>(acc[i]);
     __syncthreads();                                      // LDS is reused by the epilogue
+}
+
+// IN_TURN: as for the 16-bit tile_kernel, the k slices of the call one after another
+template <class C, bool A_KC, bool B_KC, bool IN_TURN>
+__global__ __launch_bounds__(C::NT, C::WAVES_PER_SIMD) void tile_f32_kernel(Args a, int tiles_m, int tiles_n, int group_m, int64_t slice_len) {
+    using EL = EpiLayout<C>;
+    constexpr int TI = C::TI, TJ = C::TJ;
+    constexpr int LDS_BYTES = 2 * C::STAGE > EL::BYTES ? 2 * C::STAGE : EL::BYTES;
+    __shared__ __attribute__((aligned(128))) char lds[LDS_BYTES];
+    __shared__ float wave_largest[C::WM * C::WN];
+    __shared__ uint32_t flag[4];
+    select_batch(a);
+    int tm, tn;
+    tile_of_workgroup(blockIdx.x, tiles_m, tiles_n, group_m, tm, tn);
+    const int64_t m0 = (int64_t)tm * C::BM, n0 = (int64_t)tn * C::BN;
+    f32x4 acc[TI][TJ];
+    if constexpr (IN_TURN) {
+        f32x4 part[TI][TJ];
+        for_each_slice(a, slice_len, [&](const Args& s, bool first) {
+            f32_tile_product<C, A_KC, B_KC>(s, m0, n0, lds, wave_largest, flag, part);
+#pragma unroll
+            for (int i = 0; i < TI; ++i)
+#pragma unroll
+                for (int j = 0; j < TJ; ++j)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) acc[i][j][v] = (first ? 0.0f : acc[i][j][v]) + part[i][j][v];
+        });
+    } else {
+        f32_tile_product<C, A_KC, B_KC>(a, m0, n0, lds, wave_largest, flag, acc);
+    }
+    const int lane = threadIdx.x & 63, c16 = lane & 15, g4 = lane >> 4;
     tile_epilogue_bands<C>(
         [&](auto band, char* region) {
             constexpr int b = decltype(band)::value;
@@ -564,16 +585,16 @@ __global__ __launch_bounds__(C::NT, C::WAVES_PER_SIMD) void tile_f32_kernel(Args
 #pragma unroll
                 for (int j = 0; j < TJ; ++j) *(f32x4*)(region + ((16 * i2 + c16) * EL::RS + j * 16 + 4 * g4) * 4) = acc[2 * b + i2][j];
         },
-        lds, a, m0, n0);
+        lds, a, m0, n0, INT64_MAX, !IN_TURN);
 }
 
-template <class C>
-inline hipError_t launch_f32_tiles(const Args& a, int group_m, hipStream_t stream) {
+template <class C, bool IN_TURN = false>
+inline hipError_t launch_f32_tiles(const Args& a, int group_m, hipStream_t stream, int64_t slice_len = 0) {
     const int tiles_m = (int)((a.M + C::BM - 1) / C::BM), tiles_n = (int)((a.N + C::BN - 1) / C::BN);
     const dim3 grid((unsigned)(tiles_m * tiles_n), (unsigned)a.batch), block(C::NT);
     const bool akc = !a.transA, bkc = a.transB != 0;
 #define GEMM_TILE_LAUNCH(AKC, BKC) \
-    hipLaunchKernelGGL((tile_f32_kernel<C, AKC, BKC>), grid, block, 0, stream, a, tiles_m, tiles_n, group_m)
+    hipLaunchKernelGGL((tile_f32_kernel<C, AKC, BKC, IN_TURN>), grid, block, 0, stream, a, tiles_m, tiles_n, group_m, slice_len)
     if (akc && bkc) GEMM_TILE_LAUNCH(true, true);
     else if (akc && !bkc) GEMM_TILE_LAUNCH(true, false);
     else if (!akc && bkc) GEMM_TILE_LAUNCH(false, true);

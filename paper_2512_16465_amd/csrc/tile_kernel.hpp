@@ -271,12 +271,14 @@ struct EpiLayout {
 // read and written with full-width vector accesses.  Every wave of the workgroup must be done
 // with the operand stages in LDS before this is called.
 //
+// `vectors` = false: every element goes the way of a ragged tile's, whose arithmetic is that of splitk_reduce_kernel to the bit.
+//
 // `dump(band, region)` writes rows 32*band .. 32*band+31 of the wave's sub-block, as held in
 // that wave's accumulators, to region[(row * EL::RS + column) * 4]; `band` is an
 // std::integral_constant, so the accumulator registers it names are static.
 template <class C, class Dump>
 __device__ __forceinline__ void tile_epilogue_bands(Dump dump, char* lds, const Args& a, int64_t m0, int64_t n0,
-                                                    int64_t live_rows = INT64_MAX) {
+                                                    int64_t live_rows = INT64_MAX, bool vectors = true) {
     constexpr int TM = C::TM;
     using EL = EpiLayout<C>;
     const int tid = threadIdx.x;
@@ -300,7 +302,7 @@ __device__ __forceinline__ void tile_epilogue_bands(Dump dump, char* lds, const 
     // needs static register numbers; the bands are walked by a real loop that picks the dump with
     // a compare chain, and the read-back/store part exists once.
     static_assert(TM <= 4, "the band switch below lists four cases");
-    const bool interior = (m0 + C::BM <= a.M) && (n0 + C::BN <= a.N);
+    const bool interior = vectors && (m0 + C::BM <= a.M) && (n0 + C::BN <= a.N);
     auto run_epilogue = [&](auto tag) {
         using OV = OutVec<decltype(tag)::value>;
         typename OV::elem* Cp = (typename OV::elem*)a.C;
@@ -383,7 +385,7 @@ __device__ __forceinline__ void tile_epilogue_bands(Dump dump, char* lds, const 
 // The staged epilogue for accumulators of the 32x32x16 MFMA.
 template <class C>
 __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[C::TM][C::TN], char* lds, const Args& a,
-                                              int64_t m0, int64_t n0) {
+                                              int64_t m0, int64_t n0, bool vectors = true) {
     using EL = EpiLayout<C>;
     const int lane = threadIdx.x & 63;
     const int l32 = lane & 31, lhi = lane >> 5;
@@ -396,7 +398,7 @@ __device__ __forceinline__ void tile_epilogue(f32x16 (&acc)[C::TM][C::TN], char*
                 for (int v = 0; v < 16; ++v)
                     *(float*)(region + ((8 * (v >> 2) + 4 * lhi + (v & 3)) * EL::RS + j * 32 + l32) * 4) = acc[b][j][v];
         },
-        lds, a, m0, n0);
+        lds, a, m0, n0, INT64_MAX, vectors);
 }
 
 // The plainest epilogue, C = alpha*A*B on a problem made of whole tiles (beta == 0, no bias, no
@@ -438,22 +440,28 @@ inline bool plain_epilogue_applies(const Args& a) {
            a.ldc < (1 << 26);
 }
 
-template <class C, bool IS_BF16, bool A_KC, bool B_KC, bool ANY = false>
-__global__ __launch_bounds__(C::NT, C::NT / 256 * C::WAVES_PER_SIMD) void tile_kernel(Args a, int tiles_m, int tiles_n, int group_m) {
-    constexpr int BM = C::BM, BN = C::BN, BK = C::BK, NT = C::NT, TM = C::TM, TN = C::TN, CPR = C::CPR;
-    using EL = EpiLayout<C>;
-    constexpr int LDS_BYTES = 2 * C::STAGE > EL::BYTES ? 2 * C::STAGE : EL::BYTES;
-    __shared__ __attribute__((aligned(128))) char lds[LDS_BYTES];
-    select_batch(a);
+// The k slices of a call, one after another in one workgroup: `product(args, first)` is called with the operands and the k
+// extent of each, in order.
+template <class F>
+__device__ __forceinline__ void for_each_slice(const Args& a, int64_t slice_len, F&& product) {
+    Args s = a;
+#pragma unroll 1
+    for (int64_t k0 = 0; k0 < a.K; k0 += slice_len) {
+        s.K = a.K - k0 < slice_len ? a.K - k0 : slice_len;
+        product(s, k0 == 0);
+        s.A = (const char*)s.A + (a.transA ? slice_len * a.lda : slice_len) * elem_bytes(a.dtype);
+        s.B = (const char*)s.B + (a.transB ? slice_len : slice_len * a.ldb) * elem_bytes(a.dtype);
+    }
+}
 
+// The accumulators of one tile of op(A) * op(B); every wave is done with `lds` when it returns.
+template <class C, bool IS_BF16, bool A_KC, bool B_KC, bool ANY>
+__device__ __forceinline__ void tile_product(const Args& a, int64_t m0, int64_t n0, char* lds, f32x16 (&acc)[C::TM][C::TN]) {
+    constexpr int BM = C::BM, BN = C::BN, BK = C::BK, NT = C::NT, TM = C::TM, TN = C::TN, CPR = C::CPR;
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
     const int l32 = lane & 31, lhi = lane >> 5;
     const int wm = wave % C::WM, wn = wave / C::WM;
-
-    int tm, tn;
-    tile_of_workgroup(blockIdx.x, tiles_m, tiles_n, group_m, tm, tn);
-    const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
     const int valid_m = (a.M - m0) < BM ? (int)(a.M - m0) : BM;
     const int valid_n = (a.N - n0) < BN ? (int)(a.N - n0) : BN;
     const int K = (int)a.K;
@@ -480,7 +488,6 @@ __global__ __launch_bounds__(C::NT, C::NT / 256 * C::WAVES_PER_SIMD) void tile_k
 #pragma unroll
     for (int j = 0; j < TN; ++j) fb[j] = C::A_BYTES + swz<CPR>(wn * C::WTN + j * 32 + l32, lhi);
 
-    f32x16 acc[TM][TN];
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -603,19 +610,46 @@ __global__ __launch_bounds__(C::NT, C::NT / 256 * C::WAVES_PER_SIMD) void tile_k
         }
         __syncthreads();                 // every wave is done with the operand stages: LDS is reused below
     }
+}
 
-    tile_epilogue<C>(acc, lds, a, m0, n0);
+// IN_TURN: the k slices of the call are computed one after another and added in the order and the arithmetic of
+// splitk_reduce_kernel, for a call that is cut in slices but has no workspace for their partial results.
+template <class C, bool IS_BF16, bool A_KC, bool B_KC, bool ANY = false, bool IN_TURN = false>
+__global__ __launch_bounds__(C::NT, IN_TURN ? 1 : C::NT / 256 * C::WAVES_PER_SIMD) void tile_kernel(Args a, int tiles_m, int tiles_n, int group_m, int64_t slice_len) {
+    using EL = EpiLayout<C>;
+    constexpr int LDS_BYTES = 2 * C::STAGE > EL::BYTES ? 2 * C::STAGE : EL::BYTES;
+    __shared__ __attribute__((aligned(128))) char lds[LDS_BYTES];
+    select_batch(a);
+    int tm, tn;
+    tile_of_workgroup(blockIdx.x, tiles_m, tiles_n, group_m, tm, tn);
+    const int64_t m0 = (int64_t)tm * C::BM, n0 = (int64_t)tn * C::BN;
+    f32x16 acc[C::TM][C::TN];
+    if constexpr (IN_TURN) {
+        f32x16 part[C::TM][C::TN];
+        for_each_slice(a, slice_len, [&](const Args& s, bool first) {
+            tile_product<C, IS_BF16, A_KC, B_KC, ANY>(s, m0, n0, lds, part);
+#pragma unroll
+            for (int i = 0; i < C::TM; ++i)
+#pragma unroll
+                for (int j = 0; j < C::TN; ++j)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) acc[i][j][v] = (first ? 0.0f : acc[i][j][v]) + part[i][j][v];
+        });
+    } else {
+        tile_product<C, IS_BF16, A_KC, B_KC, ANY>(a, m0, n0, lds, acc);
+    }
+    tile_epilogue<C>(acc, lds, a, m0, n0, !IN_TURN);
 }
 
 // One translation unit per variant instantiates this with its Cfg.
-template <class C, bool ANY = false>
-hipError_t launch_variant(const Args& a, int group_m, hipStream_t stream) {
+template <class C, bool ANY = false, bool IN_TURN = false>
+hipError_t launch_variant(const Args& a, int group_m, hipStream_t stream, int64_t slice_len = 0) {
     const int tiles_m = (int)((a.M + C::BM - 1) / C::BM), tiles_n = (int)((a.N + C::BN - 1) / C::BN);
     const dim3 grid((unsigned)(tiles_m * tiles_n), (unsigned)a.batch), block(C::NT);
     const bool bf = a.dtype == DT_BF16;
     const bool akc = !a.transA, bkc = a.transB != 0;
 #define GEMM_TILE_LAUNCH(BF, AKC, BKC)                                                                            \
-    hipLaunchKernelGGL((tile_kernel<C, BF, AKC, BKC, ANY>), grid, block, 0, stream, a, tiles_m, tiles_n, group_m)
+    hipLaunchKernelGGL((tile_kernel<C, BF, AKC, BKC, ANY, IN_TURN>), grid, block, 0, stream, a, tiles_m, tiles_n, group_m, slice_len)
     if (bf) {
         if (akc && bkc) GEMM_TILE_LAUNCH(true, true, true);
         else if (akc && !bkc) GEMM_TILE_LAUNCH(true, true, false);

@@ -113,3 +113,65 @@ def test_fp32_error_is_no_larger_than_that_of_the_plain_kernel(handle, K):
     lg.gemm_set_plan(handle)
     # one rounding per 32 elements of k at the sum's magnitude against one per 16
     assert errors[2] <= errors[0], errors
+
+
+def run_problem(p, handle, noalloc=False, check=True):
+    c = p.cfg
+    return (lg.gemm_run_noalloc if noalloc else lg.gemm_run)(
+        handle, c.M, c.N, c.K, c.transA, c.transB, c.dtype, c.alpha, p.A.data_ptr(), c.ld_a(), p.B.data_ptr(), c.ld_b(), c.beta,
+        p.C.data_ptr(), c.ld_c(), p.epilogue(), torch.cuda.current_stream().cuda_stream, check=check)
+
+
+# A call that is cut in slices gives the same bits wherever its partial results go: the handle's workspace, the static scratch,
+# or nowhere (captured on a handle without a workspace: the slices one after another).
+@pytest.mark.parametrize("dtype,out", [(wl.BF16, wl.BF16), (wl.F16, wl.F32), (wl.F32, wl.F32)])
+@pytest.mark.parametrize("ta,tb", [(0, 1), (1, 0), (0, 0), (1, 1)])
+@pytest.mark.parametrize("M,N,K,plan", [(16, 2047, 4095, None), (131, 257, 1001, (5,)), (130, 141, 333, (3,))])
+@pytest.mark.parametrize("beta,act", [(0.0, wl.ACT_SILU), (-1.3, wl.ACT_NONE)])
+def test_slices_give_the_same_bits_with_and_without_a_workspace(M, N, K, plan, ta, tb, dtype, out, beta, act):
+    if dtype != wl.F32 and ta and M % 8:
+        M += 8 - M % 8
+    cfg = wl.Config("slices", M, N, K, ta, tb, dtype, out, alpha=0.7, beta=beta, a_dist=("normal", 1.0), b_dist=("normal", 0.05), c_dist=("normal", 1.0),
+                    bias_dist=("normal", 0.1), bias_dtype=wl.F32, act=act, lda=(M if ta else K) + 1, ldb=(K if tb else N) + 3, ldc=N + 1)
+    inputs = wl.make_inputs(cfg, M + K)
+    handles = [lg.gemm_create() for _ in range(3)]
+    problems = [DeviceProblem(cfg, inputs) for _ in range(3)]
+    try:
+        if plan:
+            for h in handles:
+                lg.gemm_set_plan(h, lg.GEMM_KERNEL_GENERAL, 2 if dtype == wl.F32 else 1, plan[0])
+        run_problem(problems[0], handles[0])
+        run_problem(problems[1], handles[1], noalloc=True)
+        torch.cuda.synchronize()
+        assert lg.gemm_get_last_plan(handles[0])[2] > 1 and lg.gemm_workspace_size(handles[0]) > 0 and lg.gemm_workspace_size(handles[1]) == 0
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            run_problem(problems[2], handles[2])
+        assert lg.gemm_workspace_size(handles[2]) == 0
+        plans = [lg.gemm_get_last_plan(h) for h in handles]
+        assert plans[0] == plans[1] == plans[2]
+        want = problems[0].result_bits()
+        assert np.array_equal(problems[1].result_bits().view(np.uint8), want.view(np.uint8)), "static scratch"
+        for replay in range(3):
+            problems[2].reset_c()
+            graph.replay()
+            got = problems[2].result_bits()
+            assert np.array_equal(got.view(np.uint8), want.view(np.uint8)), (replay, int((got != want).sum()))
+            problems[0].reset_c()
+            run_problem(problems[0], handles[0])          # eager work between the replays
+            assert np.array_equal(problems[0].result_bits().view(np.uint8), want.view(np.uint8))
+    finally:
+        torch.cuda.synchronize()
+        for h in handles:
+            lg.gemm_destroy(h)
+
+
+def test_a_forced_split_beyond_the_static_scratch_is_refused(handle):
+    cfg = wl.Config("limit", 1025, 1027, 1029, 0, 1, wl.BF16, wl.F32)
+    p = DeviceProblem(cfg, wl.make_integer_inputs(cfg, 1, -2, 2)[0])
+    before = p.result_bits().copy()
+    lg.gemm_set_plan(handle, lg.GEMM_KERNEL_GENERAL, 1, 16)
+    assert run_problem(p, handle, noalloc=True, check=False) == lg.GEMM_ERR_SCRATCH_LIMIT
+    assert np.array_equal(p.result_bits().view(np.uint8), before.view(np.uint8))
+    assert run_problem(p, handle) == lg.GEMM_OK and lg.gemm_get_last_plan(handle) == (lg.GEMM_KERNEL_GENERAL, 1, 11)
+    lg.gemm_set_plan(handle)
