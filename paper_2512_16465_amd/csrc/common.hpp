@@ -238,8 +238,11 @@ const char* general_variant_name(int variant);
 bool general_variant_supports(const Args& a, int variant);
 // slice_len: 0, or the length of the k slices in which variants 1 and 2 then compute the call without any workspace, one
 // after another, to the same bits as the slices side by side and launch_splitk_reduce behind them.
-hipError_t launch_general(const Args& a, int variant, int group_m, hipStream_t stream, int64_t slice_len = 0);
-hipError_t launch_any_tile(const Args& a, int group_m, hipStream_t stream, int64_t slice_len);
+// fold: for a call (or the slices of one) whose result keeps 32 bits.  Variant 1 then adds each slab's sums by the vector ALUs,
+// for an error no larger than that of variant 0, which adds sixteen elements at a time (a 16-bit result's own rounding is
+// three orders of magnitude above either).
+hipError_t launch_general(const Args& a, int variant, int group_m, hipStream_t stream, bool fold, int64_t slice_len = 0);
+hipError_t launch_any_tile(const Args& a, int group_m, hipStream_t stream, int64_t slice_len, bool fold);
 hipError_t launch_any_f32_tile(const Args& a, int group_m, hipStream_t stream, int64_t slice_len);
 
 }  // namespace gemm

@@ -560,6 +560,7 @@ gemm_status_t launch_plan(const Workspace& ws, const Args& a, gemm_plan_t& plan,
             e = gemm::launch_tile(a, plan.variant, kTileBandRows, split, stream);
         }
     } else {
+        const bool fold = a.out_dtype == gemm::DT_F32;
         if (plan.split_k > 1) {
             // k slices, as above; a call of this family has never failed for want of a workspace, so where there is none to
             // be had (the stream is being captured, memory is out) its slices are computed one after another, to the same bits
@@ -571,15 +572,15 @@ gemm_status_t launch_plan(const Workspace& ws, const Args& a, gemm_plan_t& plan,
                 const bool side_by_side = ws.obtain(need, stream);
                 if (allocate_only) return GEMM_OK;
                 if (!side_by_side) {
-                    e = gemm::launch_general(a, plan.variant, kTileBandRows, stream, len);
+                    e = gemm::launch_general(a, plan.variant, kTileBandRows, stream, fold, len);
                     return e == hipSuccess ? GEMM_OK : GEMM_ERR_HIP;
                 }
-                e = gemm::launch_general(slices_of(a, plan.split_k, len, ws.ptr(), P), plan.variant, kTileBandRows, stream);
+                e = gemm::launch_general(slices_of(a, plan.split_k, len, ws.ptr(), P), plan.variant, kTileBandRows, stream, fold);
                 if (e == hipSuccess) e = gemm::launch_splitk_reduce(a, plan.split_k, ws.ptr(), stream);
                 return e == hipSuccess ? GEMM_OK : GEMM_ERR_HIP;
             }
         }
-        if (!allocate_only) e = gemm::launch_general(a, plan.variant, kTileBandRows, stream);
+        if (!allocate_only) e = gemm::launch_general(a, plan.variant, kTileBandRows, stream, fold);
     }
     return e == hipSuccess ? GEMM_OK : GEMM_ERR_HIP;
 }

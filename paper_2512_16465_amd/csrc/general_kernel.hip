@@ -78,9 +78,9 @@ bool general_variant_supports(const Args& a, int variant) {
     return a.dtype == DT_F32 || ((!a.transA || a.M >= 8) && (a.transB || a.N >= 8));
 }
 
-hipError_t launch_general(const Args& a, int variant, int group_m, hipStream_t stream, int64_t slice_len) {
+hipError_t launch_general(const Args& a, int variant, int group_m, hipStream_t stream, bool fold, int64_t slice_len) {
     if (!general_variant_supports(a, variant)) return hipErrorInvalidValue;
-    if (variant == 1) return launch_any_tile(a, group_m, stream, slice_len);
+    if (variant == 1) return launch_any_tile(a, group_m, stream, slice_len, fold);
     if (variant == 2) return launch_any_f32_tile(a, group_m, stream, slice_len);
     const int64_t tiles = ((a.M + GT - 1) / GT) * ((a.N + GT - 1) / GT);
     if (tiles == 0) return hipSuccess;

@@ -454,9 +454,10 @@ __device__ __forceinline__ void for_each_slice(const Args& a, int64_t slice_len,
     }
 }
 
-// The accumulators of one tile of op(A) * op(B); every wave is done with `lds` when it returns.
-template <class C, bool IS_BF16, bool A_KC, bool B_KC, bool ANY>
-__device__ __forceinline__ void tile_product(const Args& a, int64_t m0, int64_t n0, char* lds, f32x16 (&acc)[C::TM][C::TN]) {
+// The sums of one tile of op(A) * op(B); every wave is done with `lds` when it returns.  FOLD: two instructions' products, 32
+// elements of k, are summed by themselves and added by the vector ALUs, which rounds a sum half as often at full magnitude.
+template <class C, bool IS_BF16, bool A_KC, bool B_KC, bool ANY, bool FOLD>
+__device__ __forceinline__ void tile_product(const Args& a, int64_t m0, int64_t n0, char* lds, f32x16 (&sums)[C::TM][C::TN]) {
     constexpr int BM = C::BM, BN = C::BN, BK = C::BK, NT = C::NT, TM = C::TM, TN = C::TN, CPR = C::CPR;
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
@@ -488,12 +489,24 @@ __device__ __forceinline__ void tile_product(const Args& a, int64_t m0, int64_t 
 #pragma unroll
     for (int j = 0; j < TN; ++j) fb[j] = C::A_BYTES + swz<CPR>(wn * C::WTN + j * 32 + l32, lhi);
 
+    f32x16 slab_sums[FOLD ? TM : 1][FOLD ? TN : 1];       // what the matrix instructions add to, with FOLD
+    auto acc = [&](int i, int j) -> f32x16& {
+        if constexpr (FOLD) return slab_sums[i][j];
+        else return sums[i][j];
+    };
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+            for (int v = 0; v < 16; ++v) sums[i][j][v] = acc(i, j)[v] = 0.0f;
+    // ahead of the first product of every 32 elements of k: the sums of those before, finished by then
+    auto fold = [&](int i, int j) {
+        if constexpr (FOLD) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) { sums[i][j][v] += slab_sums[i][j][v]; slab_sums[i][j][v] = 0.0f; }
+        }
+    };
 
     const int k_tiles = (K + BK - 1) / BK;
     const int full_tiles = K / BK;      // k tiles that need no mask; at most one masked tile follows
@@ -512,7 +525,13 @@ __device__ __forceinline__ void tile_product(const Args& a, int64_t m0, int64_t 
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int j = 0; j < TN; ++j) acc[i][j] = mfma32<IS_BF16>(af[buf][i], bf[buf][j], acc[i][j]);
+            for (int j = 0; j < TN; ++j) acc(i, j) = mfma32<IS_BF16>(af[buf][i], bf[buf][j], acc(i, j));
+    };
+    auto fold_all = [&]() {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) fold(i, j);
     };
     auto lstore = [&](int stage) {
         la.lstore(lds + stage * C::STAGE, tid);
@@ -553,7 +572,8 @@ __device__ __forceinline__ void tile_product(const Args& a, int64_t m0, int64_t 
             const bool last = ks == NKS - 1;
 #pragma unroll
             for (int m = 0; m < NM; ++m) {
-                acc[m / TN][m % TN] = mfma32<IS_BF16>(af[cur][m / TN], bf[cur][m % TN], acc[m / TN][m % TN]);
+                if (ks % 2 == 0) fold(m / TN, m % TN);
+                acc(m / TN, m % TN) = mfma32<IS_BF16>(af[cur][m / TN], bf[cur][m % TN], acc(m / TN, m % TN));
 #pragma unroll
                 for (int q = (m * NR) / NM; q < ((m + 1) * NR) / NM; ++q)
                     read_one(nxt, last ? stage ^ 1 : stage, last ? 0 : ks + 1, q);
@@ -581,6 +601,7 @@ __device__ __forceinline__ void tile_product(const Args& a, int64_t m0, int64_t 
 #pragma unroll
         for (int ks = 0; ks < NKS; ++ks) {
             const int cur = ks & 1, nxt = cur ^ 1;
+            if (ks % 2 == 0) fold_all();
             if (ks < NKS - 1) {
                 read_frags(nxt, stage, ks + 1);
                 if (ks == NKS - 2 && have_next) lstore(stage ^ 1);
@@ -609,13 +630,14 @@ __device__ __forceinline__ void tile_product(const Args& a, int64_t m0, int64_t 
             step(kt, kt + 1 < k_tiles, nn < full_tiles ? 1 : (nn < k_tiles ? 2 : 0));
         }
         __syncthreads();                 // every wave is done with the operand stages: LDS is reused below
+        fold_all();
     }
 }
 
 // IN_TURN: the k slices of the call are computed one after another and added in the order and the arithmetic of
 // splitk_reduce_kernel, for a call that is cut in slices but has no workspace for their partial results.
-template <class C, bool IS_BF16, bool A_KC, bool B_KC, bool ANY = false, bool IN_TURN = false>
-__global__ __launch_bounds__(C::NT, IN_TURN ? 1 : C::NT / 256 * C::WAVES_PER_SIMD) void tile_kernel(Args a, int tiles_m, int tiles_n, int group_m, int64_t slice_len) {
+template <class C, bool IS_BF16, bool A_KC, bool B_KC, bool ANY = false, bool FOLD = false, bool IN_TURN = false>
+__global__ __launch_bounds__(C::NT, FOLD || IN_TURN ? 1 : C::NT / 256 * C::WAVES_PER_SIMD) void tile_kernel(Args a, int tiles_m, int tiles_n, int group_m, int64_t slice_len) {
     using EL = EpiLayout<C>;
     constexpr int LDS_BYTES = 2 * C::STAGE > EL::BYTES ? 2 * C::STAGE : EL::BYTES;
     __shared__ __attribute__((aligned(128))) char lds[LDS_BYTES];
@@ -627,7 +649,7 @@ __global__ __launch_bounds__(C::NT, IN_TURN ? 1 : C::NT / 256 * C::WAVES_PER_SIM
     if constexpr (IN_TURN) {
         f32x16 part[C::TM][C::TN];
         for_each_slice(a, slice_len, [&](const Args& s, bool first) {
-            tile_product<C, IS_BF16, A_KC, B_KC, ANY>(s, m0, n0, lds, part);
+            tile_product<C, IS_BF16, A_KC, B_KC, ANY, FOLD>(s, m0, n0, lds, part);
 #pragma unroll
             for (int i = 0; i < C::TM; ++i)
 #pragma unroll
@@ -636,20 +658,20 @@ __global__ __launch_bounds__(C::NT, IN_TURN ? 1 : C::NT / 256 * C::WAVES_PER_SIM
                     for (int v = 0; v < 16; ++v) acc[i][j][v] = (first ? 0.0f : acc[i][j][v]) + part[i][j][v];
         });
     } else {
-        tile_product<C, IS_BF16, A_KC, B_KC, ANY>(a, m0, n0, lds, acc);
+        tile_product<C, IS_BF16, A_KC, B_KC, ANY, FOLD>(a, m0, n0, lds, acc);
     }
     tile_epilogue<C>(acc, lds, a, m0, n0, !IN_TURN);
 }
 
 // One translation unit per variant instantiates this with its Cfg.
-template <class C, bool ANY = false, bool IN_TURN = false>
+template <class C, bool ANY = false, bool FOLD = false, bool IN_TURN = false>
 hipError_t launch_variant(const Args& a, int group_m, hipStream_t stream, int64_t slice_len = 0) {
     const int tiles_m = (int)((a.M + C::BM - 1) / C::BM), tiles_n = (int)((a.N + C::BN - 1) / C::BN);
     const dim3 grid((unsigned)(tiles_m * tiles_n), (unsigned)a.batch), block(C::NT);
     const bool bf = a.dtype == DT_BF16;
     const bool akc = !a.transA, bkc = a.transB != 0;
 #define GEMM_TILE_LAUNCH(BF, AKC, BKC)                                                                            \
-    hipLaunchKernelGGL((tile_kernel<C, BF, AKC, BKC, ANY, IN_TURN>), grid, block, 0, stream, a, tiles_m, tiles_n, group_m, slice_len)
+    hipLaunchKernelGGL((tile_kernel<C, BF, AKC, BKC, ANY, FOLD, IN_TURN>), grid, block, 0, stream, a, tiles_m, tiles_n, group_m, slice_len)
     if (bf) {
         if (akc && bkc) GEMM_TILE_LAUNCH(true, true, true);
         else if (akc && !bkc) GEMM_TILE_LAUNCH(true, true, false);

@@ -175,3 +175,29 @@ def test_a_forced_split_beyond_the_static_scratch_is_refused(handle):
     assert np.array_equal(p.result_bits().view(np.uint8), before.view(np.uint8))
     assert run_problem(p, handle) == lg.GEMM_OK and lg.gemm_get_last_plan(handle) == (lg.GEMM_KERNEL_GENERAL, 1, 11)
     lg.gemm_set_plan(handle)
+
+
+def error_of(handle, M, N, K, ta, tb, A, B, dtype, plan):
+    lg.gemm_set_plan(handle, *plan)
+    C = torch.empty(M, N, device="cuda")
+    lg.gemm_run(handle, M, N, K, ta, tb, dtype, 1.0, A.data_ptr(), M if ta else K, B.data_ptr(), K if tb else N, 0.0, C.data_ptr(), N,
+                lg.make_epilogue(wl.F32), torch.cuda.current_stream().cuda_stream)
+    lg.gemm_set_plan(handle)
+    want = (A.t() if ta else A).double() @ (B.t() if tb else B).double()
+    return lg.gemm_get_last_plan(handle), ((C.double() - want).norm() / want.norm()).item()
+
+
+@pytest.mark.parametrize("dtype", [wl.BF16, wl.F16])
+@pytest.mark.parametrize("ta,tb", [(0, 1), (1, 0), (0, 0), (1, 1)])
+@pytest.mark.parametrize("K", [41, 65, 129, 257, 513, 1025, 4095])
+def test_error_of_16_bit_products_with_an_fp32_result_is_no_larger_than_that_of_the_plain_kernel(handle, K, ta, tb, dtype):
+    M, N = 261, 517
+    g = torch.Generator(device="cuda").manual_seed(K)
+    t = torch.bfloat16 if dtype == wl.BF16 else torch.float16
+    A, B = (torch.randn(*s, generator=g, device="cuda").to(t) for s in ((K, M) if ta else (M, K), (N, K) if tb else (K, N)))
+    plain = error_of(handle, M, N, K, ta, tb, A, B, dtype, (lg.GEMM_KERNEL_GENERAL, 0, 1))[1]
+    for slices in (1, 3):
+        plan, error = error_of(handle, M, N, K, ta, tb, A, B, dtype, (lg.GEMM_KERNEL_GENERAL, 1, slices))
+        assert plan[:2] == (lg.GEMM_KERNEL_GENERAL, 1)
+        # a sum rounded at full magnitude once per 32 elements of k (and slice) against one per 16
+        assert error <= plain, (slices, error, plain)
