@@ -495,7 +495,12 @@ __global__ __launch_bounds__(ST_WAVES * 64) void skinny_nt_kernel(Args a, int sp
 // kernel shares them over four column blocks) into the registers of its ring slot, as many bytes through the
 // caches as B brings from memory.  Four visits in flight per wave (the waits count the wave's younger loads,
 // 16 per visit, and the counter ends at 63).
-template <bool IS_BF16, int H, int D>
+//
+// FOLD: half a visit is summed by itself and added by the vector ALUs (eight instructions per visit), which rounds a wave's sum
+// once per 128 elements of k at full magnitude instead of once per 32.  For the N that are no multiple of 8: those calls come from
+// the split quarter tiles, whose shares are shorter than a wave's walk here (2-norm error against 64 bits, Gaussian data, fp32 C:
+// 14 x 821 x 4504 1.4e-7 there, 2.2e-7 unfolded; 11 x 33 x 5184 1.3e-7, 2.3e-7).
+template <bool IS_BF16, int H, int D, bool FOLD>
 __global__ __launch_bounds__(ST_WAVES * 64) void skinny_nt_narrow_kernel(Args a, int split_k, float* ws) {
     static_assert(H == 1, "16 rows of C (a second row block needs the registers of a visit in flight)");
     static_assert(D == 2 || D == 4, "visits in flight per wave: four, or two with two workgroups per compute unit");
@@ -552,6 +557,7 @@ __global__ __launch_bounds__(ST_WAVES * 64) void skinny_nt_narrow_kernel(Args a,
 #pragma unroll
     for (int h = 0; h < H; ++h) acc[h] = f32x4{0.f, 0.f, 0.f, 0.f};
 
+    f32x4 half[2][H];                    // the sums of the halves of one visit, with FOLD
     u32x4 aq[D][H][ST_RUN];              // the pieces of A of the visit in each ring slot
 
     // Every visit slot of the loop below issues its loads whether the visit exists or not (a visit past
@@ -594,10 +600,17 @@ __global__ __launch_bounds__(ST_WAVES * 64) void skinny_nt_narrow_kernel(Args a,
 #pragma unroll
         for (int t = 0; t < ST_RUN; ++t)
 #pragma unroll
-            for (int h = 0; h < H; ++h) acc[h] = st_mfma<IS_BF16>(aq[slot][h][t], cur[t], acc[h]);
+            for (int h = 0; h < H; ++h) {
+                if constexpr (FOLD) half[t / 4][h] = st_mfma<IS_BF16>(aq[slot][h][t], cur[t], t % 4 == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : half[t / 4][h]);
+                else acc[h] = st_mfma<IS_BF16>(aq[slot][h][t], cur[t], acc[h]);
+            }
         __builtin_amdgcn_sched_barrier(0);
         load_visit(slot_c, v + D);
         __builtin_amdgcn_sched_barrier(0);
+        if constexpr (FOLD) {
+#pragma unroll
+            for (int h = 0; h < H; ++h) { acc[h] += half[0][h]; acc[h] += half[1][h]; }
+        }
     };
 
     load_visit(std::integral_constant<int, 0>{}, 0);
@@ -878,13 +891,14 @@ hipError_t launch_skinny(const Args& call, int split_k, float* workspace, hipStr
         if (a.M > SK_NARROW_ROWS) return hipErrorInvalidValue;
         const dim3 ngrid((unsigned)((a.N + 15) / 16), (unsigned)split_k), nblock(ST_WAVES * 64);
         // one round of workgroups at most: four visits in flight per wave; more: two, and two workgroups per compute unit
-        if (a.N <= SK_NARROW_MAX_N) {
-            if (a.dtype == DT_BF16) hipLaunchKernelGGL((skinny_nt_narrow_kernel<true, 1, 4>), ngrid, nblock, 0, stream, a, split_k, workspace);
-            else hipLaunchKernelGGL((skinny_nt_narrow_kernel<false, 1, 4>), ngrid, nblock, 0, stream, a, split_k, workspace);
-        } else {
-            if (a.dtype == DT_BF16) hipLaunchKernelGGL((skinny_nt_narrow_kernel<true, 1, 2>), ngrid, nblock, 0, stream, a, split_k, workspace);
-            else hipLaunchKernelGGL((skinny_nt_narrow_kernel<false, 1, 2>), ngrid, nblock, 0, stream, a, split_k, workspace);
-        }
+        const auto kernel = [&](auto depth, auto fold) {
+            constexpr int D = decltype(depth)::value;
+            constexpr bool FOLD = decltype(fold)::value;
+            return a.dtype == DT_BF16 ? skinny_nt_narrow_kernel<true, 1, D, FOLD> : skinny_nt_narrow_kernel<false, 1, D, FOLD>;
+        };
+        const auto of_depth = [&](auto depth) { return a.N % 8 ? kernel(depth, std::true_type{}) : kernel(depth, std::false_type{}); };
+        hipLaunchKernelGGL((a.N <= SK_NARROW_MAX_N ? of_depth(std::integral_constant<int, 4>{}) : of_depth(std::integral_constant<int, 2>{})),
+                           ngrid, nblock, 0, stream, a, split_k, workspace);
     } else if (a.transB) {
         if (a.dtype == DT_BF16) launch_nt<true>(a, grid, split_k, workspace, stream);
         else launch_nt<false>(a, grid, split_k, workspace, stream);

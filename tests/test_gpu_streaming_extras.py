@@ -229,3 +229,23 @@ def test_mfma_kernel_with_16_columns_refusals_and_automatic_choice(handle):
         assert ((kernel, variant) == (lg.GEMM_KERNEL_SKINNY, 5)) == expect, (M, N, K)
         ref, _, mag = oracle.gemm_full(oracle_problem(cfg, inp), want_bounds=True)
         assert_close(cfg, decode_c(cfg, p.result_bits()), ref, mag, f"automatic plan {M}x{N}x{K}")
+
+
+@pytest.mark.parametrize("M,N,K,shares", [(14, 821, 4504, 12), (8, 113, 2728, 8), (5, 109, 1936, 8), (11, 33, 5184, 12), (14, 2027, 1192, 6), (7, 5003, 8184, 6), (5, 413, 1016, 6), (15, 135, 864, 4)])
+@pytest.mark.parametrize("dtype", [wl.BF16, wl.F16])
+def test_error_of_few_rows_on_a_ragged_weight_is_no_larger_than_that_of_the_split_tiles(handle, M, N, K, shares, dtype):
+    """N no multiple of 8: a wave of the one-launch kernel walks a longer range of k than a share of the split quarter tiles, and
+    folds its sums per 128 elements for it."""
+    g = torch.Generator(device="cuda").manual_seed(K)
+    t = torch.bfloat16 if dtype == wl.BF16 else torch.float16
+    A, B = (torch.randn(*s, generator=g, device="cuda").to(t) for s in ((M, K), (N, K)))
+    want, errors = A.double() @ B.t().double(), []
+    for plan in (None, (lg.GEMM_KERNEL_MFMA_TILE, 16, shares)):
+        lg.gemm_set_plan(handle, *(plan or ()))
+        C = torch.empty(M, N, device="cuda")
+        lg.gemm_run(handle, M, N, K, 0, 1, dtype, 1.0, A.data_ptr(), K, B.data_ptr(), K, 0.0, C.data_ptr(), N, lg.make_epilogue(wl.F32),
+                    torch.cuda.current_stream().cuda_stream)
+        assert lg.gemm_get_last_plan(handle) == (plan or (lg.GEMM_KERNEL_SKINNY, 5, 1))
+        errors.append(((C.double() - want).norm() / want.norm()).item())
+    lg.gemm_set_plan(handle)
+    assert errors[0] <= errors[1], errors
