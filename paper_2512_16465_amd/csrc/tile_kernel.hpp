@@ -356,20 +356,28 @@ __device__ __forceinline__ void tile_epilogue_bands(Dump dump, char* lds, const 
                     const int64_t row = m0 + wm * C::WTM + i * 32 + rl;
                     if (row < a.M && col < a.N) {
                         typename OV::elem* p = Cp + row * a.ldc + col;
-                        if (col + 3 < a.N) {
-                            f32x4 cin = {0.0f, 0.0f, 0.0f, 0.0f};
-                            if (beta != 0.0f) cin = OV::load4(p);
-                            f32x4 o;
+                        // (a lane with the edge in its columns loads and stores one by one; the arithmetic is there once, since
+                        // code run for the first time waits for the instruction cache: 571x55x40 fp16 14.0 us with two copies)
+                        const bool whole = col + 3 < a.N;
+                        f32x4 cin = {0.0f, 0.0f, 0.0f, 0.0f};
+                        if (beta != 0.0f) {
+                            if (whole) {
+                                cin = OV::load4(p);
+                            } else {
 #pragma unroll
-                            for (int e = 0; e < 4; ++e) o[e] = epilogue_value(s[e], alpha, beta, cin[e], bias4[e], act);
+                                for (int e = 0; e < 3; ++e)
+                                    if (col + e < a.N) cin[e] = OV::load1(p + e);
+                            }
+                        }
+                        f32x4 o;
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) o[e] = epilogue_value(s[e], alpha, beta, cin[e], bias4[e], act);
+                        if (whole) {
                             OV::store4(p, o);
                         } else {
 #pragma unroll
-                            for (int e = 0; e < 4; ++e)
-                                if (col + e < a.N) {
-                                    const float c1 = (beta != 0.0f) ? OV::load1(p + e) : 0.0f;
-                                    OV::store1(p + e, epilogue_value(s[e], alpha, beta, c1, bias4[e], act));
-                                }
+                            for (int e = 0; e < 3; ++e)
+                                if (col + e < a.N) OV::store1(p + e, o[e]);
                         }
                     }
                 }
