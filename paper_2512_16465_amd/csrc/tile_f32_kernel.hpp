@@ -25,15 +25,14 @@
 // instruction before: 4096^3 600 us (229 TFLOP/s) / 1072, 2048^3 93 / 147, 1024^3 22 / 27, 256^3 8.6 / 8.9,
 // 4096x4096x64 27 / 30.
 //
-// What the split cannot take.  It is exact for elements that are zero or between 2^-110 and 2^40 in magnitude (below,
-// the last piece is no bf16 number any more; above, pieces of one product might overflow to infinities of opposite
-// signs).  The largest magnitude is tracked (half an instruction per element); for the smallest, which zeros make
-// costly to track, the results are looked at instead: an element below 2^-110 loses at most 2^-134 of itself, all of them
-// together at most K 2^-133 times the largest magnitude, and where every result of the tile is 2^26 times that nothing is
-// lost that fp32 would keep.  Otherwise the tile's operands are scanned for such elements, and only if there are any, or
-// one beyond 2^40, the tile is computed again with the slabs in question multiplied by v_mfma_f32_16x16x4_f32.
-// (A NaN takes either way.)  Only elements of the operands count, not what lies past their edges and is loaded with them: the
-// magnitudes are kept by row, at no cost since a thread takes the same rows of every slab.
+// What the split cannot take.  The pieces of an element are multiples of its last bit, 2^-149 for the smallest floats, and a bf16
+// number's last bit is 2^-133 at least: both operands are multiplied by 2^16 first (one instruction per element, exact), which
+// makes the split exact for every float down to the subnormal ones, and the sums by 2^-32 in the end.  Zeros, tiny elements and
+// sums that cancel cost nothing.  Left are values so large that something overflows: a scaled element, a product of two or a sum
+// (results from 2^96 on), and infinities and NaN themselves.  All of these end in a sum that is not finite, whatever comes
+// after, so a tile with such a sum is computed again, unscaled, the slabs that hold an element above 2^40 or below
+// 2^-110 by v_mfma_f32_16x16x4_f32.  Only elements of the operands count there, not what lies past their edges and is
+// loaded with them.
 //
 // Edges: loads past the end of an operand return zero dword by dword through the buffer descriptor's range check;
 // elements of a k-contiguous operand past K are cleared when they are staged.  Nothing needs more than the natural
@@ -73,7 +72,8 @@ __device__ __forceinline__ void static_for_each(F&& f, std::integer_sequence<int
 template <int N, class F>
 __device__ __forceinline__ void static_for(F&& f) { static_for_each(f, std::make_integer_sequence<int, N>{}); }
 
-constexpr float kSplitLargest = 0x1p40f, kSplitSmallest = 0x1p-110f;
+constexpr float kSplitScale = 0x1p16f, kSplitUnscale = 0x1p-32f;          // of each operand, of a product
+constexpr float kSplitLargest = 0x1p40f, kSplitSmallest = 0x1p-110f;      // what the split takes without the scale
 
 // bf16 pair of two floats (round to nearest even), and its two values widened again
 __device__ __forceinline__ uint32_t pack_bf16(float x, float y) {
@@ -94,12 +94,8 @@ struct F32Mover {
     static_assert(L == 2 || L == 4 || L == 8, "64, 128 or 256 rows");
     static constexpr int PLANE = ROWS * C::BK * 2;
     static constexpr int KQ = C::BK / 4, RB = ROWS / 4;                     // quads per row (k-contiguous); blocks of four rows
-    // Rows that the thread takes elements of, the same ones in every slab: a quad holds one of them, or two rows' pairs.
-    static constexpr bool PAIR_ROWS = !KC && G == 2;
-    static constexpr int LINES = PAIR_ROWS ? 2 * L : L;
     uint32_t goff[L];      // byte offset of the load from the slab's first byte
     uint32_t loff[L];      // byte offset of the quad (of its first row's part) in a plane
-    float largest[LINES];  // largest magnitude seen in each row
     f32x4 r[L];
 
     // first row and first k of quad i
@@ -107,12 +103,7 @@ struct F32Mover {
         return KC ? (i * C::NT + tid) / KQ : (((i / G) * C::NT + tid) % RB) * 4 + (i % G) * (4 / G);
     }
     static __device__ __forceinline__ uint32_t quad_k(int i, int tid) { return KC ? (i * C::NT + tid) % KQ * 4 : ((i / G) * C::NT + tid) / RB * G; }
-    static __device__ __forceinline__ int line_row(int line, int tid) {
-        return PAIR_ROWS ? (int)quad_row(line / 2, tid) + line % 2 : (int)quad_row(line, tid);
-    }
     __device__ __forceinline__ void init(int tid, int64_t ld) {
-#pragma unroll
-        for (int i = 0; i < LINES; ++i) largest[i] = 0.0f;
 #pragma unroll
         for (int i = 0; i < L; ++i) {
             const uint32_t row = quad_row(i, tid), k = quad_k(i, tid);
@@ -159,27 +150,27 @@ struct F32Mover {
 #pragma unroll
             for (int e = 0; e < 4; ++e) r[i][e] = (int)quad_k(i, tid) + e < left ? r[i][e] : 0.0f;
     }
-    // Pair h of quad i, taken apart in five parts of one to four instructions (in place: the elements become what is left
-    // of them).  The empty assembly keeps a part where it is called: the compiler would move all of it behind
+    // Pair h of quad i, scaled and taken apart in six parts of one to three instructions (in place: the elements become what is
+    // left of them).  The empty assembly keeps a part where it is called: the compiler would move all of it behind
     // the matrix instructions, to where the pieces are stored.
-    static constexpr int PARTS = 5;
+    static constexpr int PARTS = 6;
     float wide[2];
     u32x2 piece[3];        // of the quad at hand
     template <int PART, int I, int H>
-    __device__ __forceinline__ void split_part() {
+    __device__ __forceinline__ void split_part(float scale) {
         float x = get<I, H, 0>(), y = get<I, H, 1>();
-        if constexpr (PART == 0) asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(largest[PAIR_ROWS ? 2 * I + H : I]) : "v"(x), "v"(y));      // (a NaN is passed over)
-        if constexpr (PART == 4) {
+        if constexpr (PART == 5) {
             uint32_t w = pack_bf16(x, y);
             asm volatile("" ::"v"(w));
             piece[2][H] = w;
-        } else if constexpr (PART % 2 == 0) {
+        } else if constexpr (PART % 2 == 1) {
             uint32_t w = pack_bf16(x, y);
             wide[0] = low_bf16(w); wide[1] = high_bf16(w);
             asm volatile("" ::"v"(w), "v"(wide[0]), "v"(wide[1]));
             piece[PART / 2][H] = w;
         } else {
-            x -= wide[0]; y -= wide[1];
+            if constexpr (PART == 0) { x *= scale; y *= scale; }
+            else { x -= wide[0]; y -= wide[1]; }
             asm volatile("" ::"v"(x), "v"(y));
             set<I, H, 0>(x); set<I, H, 1>(y);
         }
@@ -196,21 +187,15 @@ struct F32Mover {
             }
         }
     }
-    __device__ __forceinline__ void split_and_store(char* region) {
+    __device__ __forceinline__ void split_and_store(char* region, float scale) {
         static_for<L>([&](auto i) {
             constexpr int I = decltype(i)::value;
-            static_for<2 * PARTS>([&](auto w) { split_part<decltype(w)::value % PARTS, I, decltype(w)::value / PARTS>(); });
+            static_for<2 * PARTS>([&](auto w) { split_part<decltype(w)::value % PARTS, I, decltype(w)::value / PARTS>(scale); });
             store_pieces(region, I);
         });
     }
-    // largest magnitude among the thread's rows of the operand (the tile's first `rows`)
-    __device__ __forceinline__ float largest_of(int rows, int tid) const {
-        float m = 0.0f;
-#pragma unroll
-        for (int i = 0; i < LINES; ++i) m = fmaxf(m, line_row(i, tid) < rows ? largest[i] : 0.0f);
-        return m;
-    }
-    // an element of the operand that the split cannot take (an m/n-contiguous one is loaded past its edge as well)
+    // an element of the operand that the split cannot take as it is, not scaled (an m/n-contiguous operand is loaded past its
+    // edge as well: `rows` = rows of the tile inside it)
     __device__ __forceinline__ bool outside(int rows, int tid) const {
         bool out = false;
 #pragma unroll
@@ -279,7 +264,7 @@ struct F32Planes {
 // Accumulator (i, j): B's fragment is the instruction's first operand, so lane (c16, g4) holds row 16 i + c16 and
 // columns 16 j + 4 g4 .. + 3 of the wave sub-block.
 template <class C, bool A_KC, bool B_KC>
-__device__ __forceinline__ void f32_tile_product(const Args& a, int64_t m0, int64_t n0, char* lds, float* wave_largest, uint32_t* flag,
+__device__ __forceinline__ void f32_tile_product(const Args& a, int64_t m0, int64_t n0, char* lds, uint32_t* flag,
                                                  f32x4 (&acc)[C::TI][C::TJ]) {
     constexpr int TI = C::TI, TJ = C::TJ;
     constexpr bool ASM = C::WAVES_PER_SIMD == 1;
@@ -358,20 +343,22 @@ __device__ __forceinline__ void f32_tile_product(const Args& a, int64_t m0, int6
         lb1.gload(slab_b(1));
         __builtin_amdgcn_sched_barrier(0);
         clear_past(0);
-        la.split_and_store(lds);
-        lb.split_and_store(lds + C::B_REGION);
+        la.split_and_store(lds, kSplitScale);
+        lb.split_and_store(lds + C::B_REGION, kSplitScale);
 #pragma unroll
         for (int i = 0; i < LA::L; ++i) la.r[i] = la1.r[i];
 #pragma unroll
         for (int i = 0; i < LB::L; ++i) lb.r[i] = lb1.r[i];
     }
-    if (tid < 4) flag[tid] = 0;       // (read after the loop)
+    if (tid < 2) flag[tid] = 0;       // (read after the loop)
 #pragma unroll
     for (int i = 0; i < TI; ++i) af[0][i] = u32x4{0u, 0u, 0u, 0u};       // the step ahead of the first slab adds nothing
 #pragma unroll
     for (int j = 0; j < TJ; ++j) bf[0][j] = u32x4{0u, 0u, 0u, 0u};
     const char *next_a = pa + slab_of(2) * a_step, *next_b = pb + slab_of(2) * b_step;      // slab kt+2: a whole one
     const uint32_t whole_a = LA::slab_bytes(rows_a, C::BK, a.lda), whole_b = LB::slab_bytes(rows_b, C::BK, a.ldb);
+    float scale = kSplitScale;
+    asm("" : "+s"(scale));                                // (in a register: the instruction is half as long)
     auto iteration = [&](int kt, auto stage_) {
         constexpr int stage = decltype(stage_)::value;
         const char* cur = lds + stage * C::STAGE;
@@ -418,10 +405,10 @@ __device__ __forceinline__ void f32_tile_product(const Args& a, int64_t m0, int6
                 constexpr int w = w0 + decltype(w_)::value, pair = w / LA::PARTS, part = w % LA::PARTS, quad = pair / 2;
                 constexpr bool done = part == LA::PARTS - 1 && pair % 2 == 1;
                 if constexpr (quad < LA::L) {
-                    la.template split_part<part, quad, pair % 2>();
+                    la.template split_part<part, quad, pair % 2>(scale);
                     if constexpr (done) { la.store_pieces(nxt, quad); la.gload_after(quad, ra); }
                 } else {
-                    lb.template split_part<part, quad - LA::L, pair % 2>();
+                    lb.template split_part<part, quad - LA::L, pair % 2>(scale);
                     if constexpr (done) { lb.store_pieces(nxt + C::B_REGION, quad - LA::L); lb.gload_after(quad - LA::L, rb); }
                 }
             });
@@ -440,73 +427,60 @@ __device__ __forceinline__ void f32_tile_product(const Args& a, int64_t m0, int6
 #pragma unroll
     for (int i = 0; i < TI; ++i) f32_settle<ASM>(acc[i]);
 
-    // Has the split lost anything?  (see above)  First with the largest magnitude that there could be, which costs no
-    // exchange between the threads; then with the one there is.
+#pragma unroll
+    for (int i = 0; i < TI; ++i)
+#pragma unroll
+        for (int j = 0; j < TJ; ++j) acc[i][j] *= kSplitUnscale;
+
+    // Has anything overflowed?  (see above; only what is inside C counts: past its edge there are products of what lies past an
+    // operand's edge)
     auto set_if = [&](int word, bool mine) { if (mine) flag[word] = 1; };
     auto is_set = [&](int word) { return __builtin_amdgcn_readfirstlane(flag[word]) != 0; };      // (behind a barrier)
-    auto below = [&](float largest_there) {               // (only what is inside C: past its edge there are products of what lies past an operand's edge)
-        const float floor = largest_there * (float)K * 0x1p-107f;
-        const int64_t rows = a.M - (m0 + wm * C::WTM + c16), cols = a.N - (n0 + wn * C::WTN + 4 * g4);
-        bool small = false;
+    float nan = 0.0f;                                     // not a number as soon as it has met one that is not finite
+    if (rows_a == C::BM && rows_b == C::BN) {
 #pragma unroll
         for (int i = 0; i < TI; ++i)
 #pragma unroll
             for (int j = 0; j < TJ; ++j)
 #pragma unroll
-                for (int v = 0; v < 4; ++v)
-                    small = small || (__builtin_fabsf(acc[i][j][v]) < floor && 16 * i < rows && 16 * j + v < cols);
-        return small;
-    };
-    if (k_tiles == 0) __syncthreads();
-    float largest = fmaxf(la.largest_of(rows_a, tid), lb.largest_of(rows_b, tid));
-    set_if(0, below(kSplitLargest));
-    set_if(1, largest > kSplitLargest);
-    __syncthreads();
-    bool again = is_set(1);
-    if (__builtin_expect(!again && is_set(0), 0)) {
+                for (int v = 0; v < 4; ++v) nan = fmaf(acc[i][j][v], 0.0f, nan);
+    } else {
+        const int rows = rows_a - (wm * C::WTM + c16), cols = rows_b - (wn * C::WTN + 4 * g4);
 #pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) largest = fmaxf(largest, __shfl_xor(largest, d, 64));
-        if (lane == 0) wave_largest[wave] = largest;
-        __syncthreads();
+        for (int i = 0; i < TI; ++i)
 #pragma unroll
-        for (int w = 0; w < C::WM * C::WN; ++w) largest = fmaxf(largest, wave_largest[w]);
-        set_if(2, below(largest));
-        __syncthreads();
-        if (is_set(2)) {
-            bool out = false;
-            LA la1 = la;              // two slabs in flight (past the last one: zeros)
-            LB lb1 = lb;
-#pragma unroll 1
-            for (int kt = 0; kt < k_tiles; kt += 2) {
-                load_slab(kt);
-                la1.gload(slab_a(kt + 1));
-                lb1.gload(slab_b(kt + 1));
-                clear_past(kt);
-                out = out || la.outside(rows_a, tid) || lb.outside(rows_b, tid) || la1.outside(rows_a, tid) || lb1.outside(rows_b, tid);
-            }
-            set_if(3, out);
-            __syncthreads();
-            again = is_set(3);
-        }
-        __syncthreads();
+            for (int j = 0; j < TJ; ++j)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) nan = fmaf(16 * i < rows && 16 * j + v < cols ? acc[i][j][v] : 0.0f, 0.0f, nan);
     }
-    if (__builtin_expect(again, 0)) {
+    if (k_tiles == 0) __syncthreads();
+    set_if(0, nan != nan);
+    __syncthreads();
+    if (__builtin_expect(is_set(0), 0)) {
         clear_acc();
+        __syncthreads();
+        if (tid == 0) flag[0] = 0;
+        __syncthreads();
+        load_slab(0);
 #pragma unroll 1
         for (int kt = 0; kt < k_tiles; ++kt) {
-            load_slab(kt);
             clear_past(kt);
 #pragma unroll
             for (int m = 0; m < NM; ++m) clear_sum(m);
-            __syncthreads();                              // the last slab has been read, and its flag
-            if (tid == 0) flag[0] = 0;
-            __syncthreads();
-            set_if(0, la.outside(rows_a, tid) || lb.outside(rows_b, tid));
-            __syncthreads();
-            if (is_set(0)) {
+            set_if(kt & 1, la.outside(rows_a, tid) || lb.outside(rows_b, tid));
+            __syncthreads();                              // (the last slab has been read as well)
+            const bool as_fp32 = is_set(kt & 1);
+            if (as_fp32) {
                 la.store_raw(lds, tid);
                 lb.store_raw(lds + C::B_REGION, tid);
-                __syncthreads();
+            } else {
+                la.split_and_store(lds, 1.0f);
+                lb.split_and_store(lds + C::B_REGION, 1.0f);
+            }
+            load_slab(kt + 1);
+            __syncthreads();
+            if (tid == 0) flag[kt & 1] = 0;
+            if (as_fp32) {
                 // lane group g4 takes k = 4 g4 .. + 3 of sixteen, one per instruction (the order of k is free as long as
                 // both operands agree)
 #pragma unroll 1
@@ -524,9 +498,6 @@ __device__ __forceinline__ void f32_tile_product(const Args& a, int64_t m0, int6
                             f32_mfma_f32<ASM>(sum(m), br[m % TJ][q], ar[m / TJ][q]);
                 }
             } else {
-                la.split_and_store(lds);
-                lb.split_and_store(lds + C::B_REGION);
-                __syncthreads();
 #pragma unroll 1
                 for (int s = 0; s < STEPS; ++s) {
                     const int p = Planes::of_a(s), q = Planes::of_b(s);
@@ -555,8 +526,7 @@ __global__ __launch_bounds__(C::NT, C::WAVES_PER_SIMD) void tile_f32_kernel(Args
     constexpr int TI = C::TI, TJ = C::TJ;
     constexpr int LDS_BYTES = 2 * C::STAGE > EL::BYTES ? 2 * C::STAGE : EL::BYTES;
     __shared__ __attribute__((aligned(128))) char lds[LDS_BYTES];
-    __shared__ float wave_largest[C::WM * C::WN];
-    __shared__ uint32_t flag[4];
+    __shared__ uint32_t flag[2];
     select_batch(a);
     int tm, tn;
     tile_of_workgroup(blockIdx.x, tiles_m, tiles_n, group_m, tm, tn);
@@ -565,7 +535,7 @@ __global__ __launch_bounds__(C::NT, C::WAVES_PER_SIMD) void tile_f32_kernel(Args
     if constexpr (IN_TURN) {
         f32x4 part[TI][TJ];
         for_each_slice(a, slice_len, [&](const Args& s, bool first) {
-            f32_tile_product<C, A_KC, B_KC>(s, m0, n0, lds, wave_largest, flag, part);
+            f32_tile_product<C, A_KC, B_KC>(s, m0, n0, lds, flag, part);
 #pragma unroll
             for (int i = 0; i < TI; ++i)
 #pragma unroll
@@ -574,7 +544,7 @@ __global__ __launch_bounds__(C::NT, C::WAVES_PER_SIMD) void tile_f32_kernel(Args
                     for (int v = 0; v < 4; ++v) acc[i][j][v] = (first ? 0.0f : acc[i][j][v]) + part[i][j][v];
         });
     } else {
-        f32_tile_product<C, A_KC, B_KC>(a, m0, n0, lds, wave_largest, flag, acc);
+        f32_tile_product<C, A_KC, B_KC>(a, m0, n0, lds, flag, acc);
     }
     const int lane = threadIdx.x & 63, c16 = lane & 15, g4 = lane >> 4;
     tile_epilogue_bands<C>(

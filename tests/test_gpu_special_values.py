@@ -34,9 +34,9 @@ def store(x, dtype):
 # (kernel family, variant, split) to force; None = automatic
 def plans_for(M, dtype, ta):
     if dtype == wl.F32:
-        return [None, (lg.GEMM_KERNEL_MFMA_TILE, 11, 1), (lg.GEMM_KERNEL_MFMA_TILE, 13, 1), (lg.GEMM_KERNEL_GENERAL, 0, 1)]
+        return [None, (lg.GEMM_KERNEL_MFMA_TILE, 11, 1), (lg.GEMM_KERNEL_MFMA_TILE, 13, 1), (lg.GEMM_KERNEL_GENERAL, 0, 1), (lg.GEMM_KERNEL_GENERAL, 2, 1)]
     plans = [None, (lg.GEMM_KERNEL_MFMA_TILE, 10, 1), (lg.GEMM_KERNEL_MFMA_TILE, 5, 1), (lg.GEMM_KERNEL_MFMA_TILE, 0, 1),
-             (lg.GEMM_KERNEL_MFMA_TILE, 5, 2), (lg.GEMM_KERNEL_GENERAL, 0, 1)]
+             (lg.GEMM_KERNEL_MFMA_TILE, 5, 2), (lg.GEMM_KERNEL_GENERAL, 0, 1), (lg.GEMM_KERNEL_GENERAL, 1, 1), (lg.GEMM_KERNEL_GENERAL, 1, 2)]
     if M <= 64 and not ta:
         plans += [(lg.GEMM_KERNEL_SKINNY, -1, 1), (lg.GEMM_KERNEL_SKINNY, -1, 2)]
     if M <= 8 and not ta:        # few rows: both kernels for a weight stored N x K, by name (each refuses the other layout)
