@@ -164,9 +164,10 @@ constexpr double kSmallAloneFew = 0.0055, kSmallAloneMany = 0.008, kSmallAloneAl
 constexpr double kSmallHbmRate = 4.7e6, kSliceMoveRate = 4.5e6;      // bytes per us
 constexpr int kSliceChoices[] = {2, 4, 8, 16};
 constexpr int64_t kMinSliceK = 512;          // shorter k ranges spend their time filling the pipeline (256x512x4096: 8 slices 12 us, 16 slices 15)
-constexpr int64_t kMinSliceKF32 = 128;      // (an fp32 slab takes 16 times as long to multiply: 64x1024x1024 11 us in 8 slices, 18 in 2)
+constexpr int64_t kMinSliceKF32 = 128;      // (64x1024x1024 11 us in 8 slices, 18 in 2)
 constexpr double kSliceMargin = 0.9;          // slices must promise 10 % (384x2048x2048: 14 us whole, 18 in 4 slices, estimated equal)
 constexpr double kSliceLaunchF32 = 3.5, kSliceMarginF32 = 0.92;      // (512^3 fp32: 11 us in 4 slices, 13 whole; 3072^3 within 8 %)
+constexpr double kF32StoreRate = 3.75e6;
 constexpr double kSliceLaunch = 5.0;          // the second kernel of a sliced call: launch, gap, one round trip (512x2048x2048: 14 us whole, 19 in 4 slices)
 // Operands beyond the last-level cache stream from HBM on every call; there the large tile with its split
 // stays ahead of the sliced small tile (128x16384x16384: 114 against 125 us, 128x8192x28672: 104
@@ -223,26 +224,32 @@ constexpr int kF32TileVariant = 11, kF32SmallTileVariant = 13;
 constexpr int64_t kF32MinTiles = 1;
 
 // fp32: the 128x128 tile (beyond one per compute unit in pairs, see kF32PairAbove) or the 64x64 tile (up to three
-// workgroups per unit), whole or in `slices` of k.  Estimate in us per element of k, 4 us fixed:
-//   64x64: a unit's one, two or three workgroups 0.0177, 0.028, 0.0405 (1024^3 22 us, 1536^3 60, 3072^3 364);
-//   128x128: one per unit 0.0465 (2048^3 95 us); in pairs 0.0755 for a full round (4096x2048x4096 297 us),
-//   0.0575 for one that leaves 40 % of the units idle (2304^3 140), in between in proportion (2560^3 161).
+// workgroups per unit), whole or in `slices` of k.  Estimate in us, fitted to both tiles on 350 random calls (M, N up to 4096,
+// K from 8 to 4096, batches; the rule's choice is within 8 % of the faster one on all of them and 0.05 % behind on average):
+//   64x64: 5.5 fixed; per element of k a unit's one, two or three workgroups 0.0177, 0.0262, 0.0374 (1024^3 21.6 us, 3072^3 360);
+//   128x128: 10.8 fixed, 0.0435 per element with one per unit (2048^3 92 us); in pairs 4.7 more per full round behind the first, 0.0714
+//   per element for a full round, 0.0543 for one that leaves 40 % of the units idle, in between in proportion;
+//   the results leave at 3.75 TB/s.
+// The fixed part decides at short k: 4001x895x16 12.5 us on the small tile, 15.3 on the large one, 2044x1940x104 14.7 / 17.9.
 // Slices add the second kernel.  Deep k on a small grid gains most from them: 256x256x4096 74 -> 15 us in
 // 16, 64x4096x4096 78 -> 23 in 8.
 double f32_time(const Args& a, bool big, int slices, int64_t cus) {
     const int64_t side = big ? 128 : 64;
     const int64_t wgs = ((a.M + side - 1) / side) * ((a.N + side - 1) / side) * a.batch * slices, per_unit = (wgs + cus - 1) / cus;
-    double per_k;
+    double per_k, fixed;
     if (!big) {
-        per_k = (double)(per_unit / 3) * 0.0405 + (per_unit % 3 == 0 ? 0.0 : (per_unit % 3 == 1 ? 0.0177 : 0.028));
+        per_k = (double)(per_unit / 3) * 0.0374 + (per_unit % 3 == 0 ? 0.0 : (per_unit % 3 == 1 ? 0.0177 : 0.0262));
+        fixed = 5.5;
     } else if (wgs <= gemm::kF32PairAbove) {
-        per_k = (double)per_unit * 0.0465;
+        per_k = (double)per_unit * 0.0435;
+        fixed = 10.8;
     } else {
         const double n = (double)(((a.M + 255) / 256) * ((a.N + 127) / 128) * a.batch * slices) / (double)cus;
         const double whole = (double)(int64_t)n, fill = n - whole;
-        per_k = whole * 0.0755 + (fill > 0.0 ? 0.0575 + 0.018 * (fill > 0.6 ? (fill - 0.6) / 0.4 : 0.0) : 0.0);
+        per_k = whole * 0.0714 + (fill > 0.0 ? 0.0543 + 0.0171 * (fill > 0.6 ? (fill - 0.6) / 0.4 : 0.0) : 0.0);
+        fixed = 6.1 + 4.7 * (whole > 1.0 ? whole : 1.0) + (fill > 0.0 && whole > 0.0 ? 1.3 : 0.0);
     }
-    const double t = per_k * ((double)a.K / slices) + 4.0;
+    const double t = fixed + per_k * ((double)a.K / slices) + (double)(a.M * a.N * a.batch) * 4.0 / kF32StoreRate;
     return slices > 1 ? (t + kSliceLaunchF32 + (double)slices * (double)(a.M * a.N) * 8.0 / kSliceMoveRate) / kSliceMarginF32 : t;
 }
 
@@ -503,6 +510,8 @@ Args slices_of(const Args& a, int slices, int64_t len, float* partials, int64_t 
     return p;
 }
 
+int64_t general_slice_len(int64_t K, int& slices);
+
 // Launches the kernels of a plan for the (validated) call `a`; may lower plan.split_k to what the
 // call can take.  split_first: first tile of a split trailing round (macro-tile family).
 // allocate_only: stop after making the workspace large enough for the plan.
@@ -564,8 +573,7 @@ gemm_status_t launch_plan(const Workspace& ws, const Args& a, gemm_plan_t& plan,
         if (plan.split_k > 1) {
             // k slices, as above; a call of this family has never failed for want of a workspace, so where there is none to
             // be had (the stream is being captured, memory is out) its slices are computed one after another, to the same bits
-            const int64_t slabs = (K + 31) / 32, len = ((slabs + plan.split_k - 1) / plan.split_k) * 32, P = (N + 7) / 8 * 8;
-            plan.split_k = (int)((K + len - 1) / len);
+            const int64_t len = general_slice_len(K, plan.split_k), P = (N + 7) / 8 * 8;
             if (plan.split_k > 1) {
                 const size_t need = (size_t)plan.split_k * (size_t)M * (size_t)P * sizeof(float);
                 if (ws.fixed && need > kScratchBytes) return GEMM_ERR_SCRATCH_LIMIT;
@@ -674,36 +682,69 @@ struct AutoPlan {
 
 // Operands off the 16-byte grid: the general kernel for the smallest calls, the matrix cores for the rest, in k slices where
 // the tiles leave the chip idle.  Slices have to fit the static scratch, so that every entry point takes the same ones.
-// 16-bit operands, the 128x128 tile: 10 us fixed and per element of k 0.0175 us for up to 128 workgroups, 0.021 for one on
-// every unit, 0.0305 per round of two (1023^3 25 to 29 us, 2049x2051x2045 53, 4095x4097x4093 245 to 270; 16x8191x4095 83 whole,
-// 27 in 8 slices; 1201x1203x4095 78 whole, 49 in 4).  The general kernel: 4.5 us and, per step of 16 along k, 0.35 us and
-// 0.25 ns per block at least (65x67x129 6.8 us against 12, 255x1023x255 14 against 20; 129x257x511 19 against 14.5,
-// 2049x2051x2045 1245).  fp32 operands: the 64x64 tiles with folded sums, 1.5 us and 3 ns per element of k behind the plain
-// ones, against the same general kernel (33x35x31 5.8 us against 4.8, 65x67x129 8.7 / 6.9, 255x1023x255 12.7 / 14.7,
-// 129x257x511 10.8 in 4 slices / 18.6, 2049x2051x2045 147 to 156 / 1280 to 1330, 4095x4097x4093 958 / about 10 ms).
-constexpr int64_t kGeneralMinSliceK = 64;
+// Estimates in us, fitted to all plans on 1250 random calls (M, N 1 to 3072, K 24 to 4096, the four layouts, batches):
+// the choice is 0.3 % behind the fastest plan on average, by more than 10 % on 9 of them, and with 16 bits never by more than 6 %
+// behind the general kernel.  Nine calls of ten are within 7 % of their estimates.
+constexpr int64_t kGeneralMinSliceK = 48;
+// (2.6 to 3.1 on the device, more for the call: 33x43x223 fp32 10.2 us plain, 10.8 in 4 slices; 291x97x165 fp32 with GELU 8.3 plain, 9.9 on tiles)
+constexpr double kSecondKernel = 3.4, kActivation = 1.5;
+constexpr double kGeneralMargin = 1.08;       // what the 16-bit tiles must promise (without it up to 22 % behind the general kernel); the fp32 ones round less
+
+// The general kernel: 0.55 us per step of 16 along k, and its throughput (beyond four blocks per unit less each).
+double general_time(const Args& a) {
+    const double blocks = (double)((a.M + 15) / 16) * (double)((a.N + 15) / 16) * (double)a.batch;
+    return 2.2 + (double)((a.K + 15) / 16) * (0.55 + 0.00031 * blocks + 0.00026 * (blocks > 1024.0 ? blocks - 1024.0 : 0.0)) + 0.0004 * blocks;
+}
+
+// The tiles in `slices` of `len` elements of k.  An operand contiguous along m or n costs more instructions per slab than a
+// k-contiguous one, so a slab's time goes by layout (1023x1025x1021 22 us NT, 25 NN, 31 TN).  The epilogue is in proportion to
+// a tile's live rows up to 64; a number of slices that the reduction has no instance for costs a round trip each.
+double general_tile_time(const Args& a, int slices, int64_t len, int64_t cus) {
+    const bool f32 = a.dtype == gemm::DT_F32, fold = !f32 && a.out_dtype == gemm::DT_F32;
+    const double elements = (double)a.M * (double)a.N * (double)a.batch;
+    double moved = elements * (f32 || fold || slices > 1 ? 4.0 : 2.0), t = 0.0;
+    if (a.act != gemm::ACT_NONE && slices == 1) t = kActivation;
+    if (slices > 1) {
+        moved += (double)slices * (double)a.M * (double)((a.N + 7) / 8 * 8) * 4.0;
+        t = kSecondKernel + (slices == 2 || slices == 4 || slices == 8 || slices == 16 ? 0.0 : 0.36 * slices);
+    }
+    if (f32) {      // 64x64 tiles with folded sums, up to three workgroups per unit
+        const int64_t per_unit = (((a.M + 63) / 64) * ((a.N + 63) / 64) * a.batch * slices + cus - 1) / cus;
+        const double per_k = (double)(per_unit / 3) * 0.037 + (per_unit % 3 == 0 ? 0.0 : (per_unit % 3 == 1 ? 0.0185 : 0.0281));
+        return t + 4.6 + per_k * (double)len + moved / 2.6e6;
+    }
+    // 128x128 tiles, two workgroups per unit (one with folded sums); per slab of 64 and layout: up to half a workgroup per unit,
+    // up to one, and per round
+    static const double few[4] = {0.77, 1.10, 1.01, 1.48}, one[4] = {0.97, 1.27, 1.24, 1.58}, full[4] = {1.22, 1.47, 1.54, 1.89};
+    static const double few_folded[4] = {1.15, 1.42, 1.34, 1.78}, full_folded[4] = {1.19, 1.49, 1.33, 1.69};
+    const int layout = (a.transA ? 2 : 0) + (a.transB ? 0 : 1);                  // NT, NN, TT, TN
+    const int64_t wgs = ((a.M + 127) / 128) * ((a.N + 127) / 128) * a.batch * slices, places = fold ? cus : 2 * cus;
+    const double rounds = (double)((wgs + places - 1) / places), slabs = (double)((len + 63) / 64);
+    const double live = (double)(a.M < 64 ? a.M : 64) / 64.0;
+    if (fold) return t + 5.25 + 4.2 * live + (wgs <= cus / 2 ? few_folded : full_folded)[layout] * slabs * rounds + 4.2 * (rounds - 1.0) + moved / 3.6e6;
+    return t + 4.7 + 4.0 * live + (wgs <= cus / 2 ? few : (wgs <= cus ? one : full))[layout] * slabs * rounds + 0.9 * (rounds - 1.0) + moved / 3.3e6;
+}
+
+// The length of the `slices` slices a general plan cuts K into (whole 32-element slabs); `slices` becomes what there are.
+int64_t general_slice_len(int64_t K, int& slices) {
+    const int64_t slabs = (K + 31) / 32, len = ((slabs + slices - 1) / slices) * 32;
+    slices = (int)((K + len - 1) / len);
+    return slices > 1 ? len : K;
+}
 
 gemm_plan_t general_plan(const Args& a, int num_cus) {
     const int64_t cus = num_cus > 0 ? num_cus : 256;
     gemm_plan_t plan{GEMM_KERNEL_GENERAL, 0, 1};
     const bool f32 = a.dtype == gemm::DT_F32;
-    if (!gemm::general_variant_supports(a, f32 ? 2 : 1)) return plan;
-    const double blocks = (double)((a.M + 15) / 16) * (double)((a.N + 15) / 16) * (double)a.batch;
-    double best = 4.5 + (double)((a.K + 15) / 16) * (0.35 + 0.00025 * blocks);
     const int variant = f32 ? 2 : 1;
-    for (int sl : {1, 2, 4, 8, 16}) {
-        const int64_t P = (a.N + 7) / 8 * 8;
-        if (sl > 1 && (a.batch != 1 || a.K / sl < kGeneralMinSliceK || (int64_t)sl * a.M * P * 4 > (int64_t)kScratchBytes)) break;
-        double t;
-        if (f32) {
-            t = f32_time(a, false, sl, cus) + 1.5 + 0.003 * ((double)a.K / sl);
-        } else {
-            const int64_t wgs = ((a.M + 127) / 128) * ((a.N + 127) / 128) * a.batch * sl;
-            const double per_k = wgs <= cus / 2 ? 0.0175 : (wgs <= cus ? 0.021 : 0.0305 * (double)((wgs + 2 * cus - 1) / (2 * cus)));
-            t = 10.0 + per_k * ((double)a.K / sl);
-            if (sl > 1) t = (t + kSliceLaunchF32 + (double)sl * (double)(a.M * P) * 8.0 / kSliceMoveRate) / kSliceMarginF32;
-        }
-        if (t < best) { best = t; plan.variant = variant; plan.split_k = sl; }
+    if (!gemm::general_variant_supports(a, variant)) return plan;
+    double best = general_time(a) / (f32 ? 1.0 : kGeneralMargin);
+    for (int cut : {1, 2, 4, 8, 16}) {
+        if (cut > 1 && (a.batch != 1 || a.K / cut < kGeneralMinSliceK || (int64_t)cut * a.M * ((a.N + 7) / 8 * 8) * 4 > (int64_t)kScratchBytes)) break;
+        int slices = cut;
+        const int64_t len = general_slice_len(a.K, slices);
+        const double t = general_tile_time(a, slices, len, cus);
+        if (t < best) { best = t; plan.variant = variant; plan.split_k = slices; }
     }
     return plan;
 }

@@ -171,6 +171,38 @@ def test_fp32_tiles_and_slices():
     assert plan(64, 1024, 1024, dtype=wl.F32)[2] > 1
 
 
+def test_fp32_short_k_takes_the_small_tile():
+    # the large tile's fixed time is twice the small one's: (us on the small, on the large)
+    for M, N, K, ta, tb, batch in [(4001, 895, 16, 0, 1, 1),        # 12.5, 15.3   (N no multiple of 4: only C's rows are off the grid)
+                                   (2044, 1940, 104, 1, 0, 1),      # 14.7, 17.9
+                                   (1092, 2693, 40, 0, 1, 1),       # 13.6, 15.9
+                                   (2712, 3440, 40, 1, 0, 1),       # 20.9, 29.2
+                                   (376, 1024, 12, 0, 0, 14)]:      # 13.7, 15.9
+        assert plan(M, N, K, ta, tb, dtype=wl.F32, batch=batch) == (TILE, "f32_64x64x32_w2x2", 1), (M, N, K)
+    for shape in [(2336, 2704, 1568), (1836, 3424, 968), (2560, 2560, 2560)]:       # 148 / 111, 98 / 77, 350 / 172
+        assert plan(*shape, dtype=wl.F32)[1] == "f32_128x128x32_w2x2", shape
+
+
+def test_calls_off_the_grid_by_size_and_layout():
+    general, tiles16, tiles32 = "general_16x16", "general_128x128x64_w2x2", "general_f32_64x64x32_w2x2"
+    lay = {"NT": (0, 1), "NN": (0, 0), "TN": (1, 0)}
+    # the general kernel where a handful of tiles would leave the chip idle (us on it, on the tiles)
+    for M, N, K, l in [(65, 67, 129, "NT"), (65, 80, 65, "NN"), (301, 203, 101, "TN")]:                            # 8.2 / 10.2, 8.2 / 9.2, 8.3 / 11.9
+        assert plan(M, N, K, *lay[l]) == (GENERAL, general, 1), (M, N, K, l)
+    assert plan(33, 35, 31, 0, 1, dtype=wl.F32) == (GENERAL, general, 1)
+    # slices in a number that the reduction has an instance for (us in four, in six or seven)
+    for M, N, K, l in [(335, 75, 629, "NN"), (747, 159, 537, "NN"), (271, 147, 587, "TN")]:                        # 16.1 / 26.9, 15.8 / 27.0, 18.6 / 29.1
+        assert plan(M, N, K, *lay[l]) == (GENERAL, tiles16, 4), (M, N, K, l)
+    for shape in [(1023, 1025, 1021), (2049, 2051, 2045), (129, 257, 511), (16, 8191, 4095)]:
+        for l in lay.values():
+            assert plan(*shape, *l)[1] == tiles16 and plan(*shape, *l, dtype=wl.F32)[1] == tiles32, (shape, l)
+    assert plan(2049, 2051, 2045)[2] == 1 and plan(16, 8191, 4095)[2] > 1
+    # the workspace of an automatic plan fits the static scratch
+    for M, N, K, l in [(3, 2999, 4095, "NN"), (1201, 1203, 4095, "NT"), (2047, 33, 4093, "NN"), (600, 1501, 4095, "TN")]:
+        _, _, slices = plan(M, N, K, *lay[l])
+        assert slices * M * ((N + 7) // 8 * 8) * 4 <= lg.GEMM_NOALLOC_SCRATCH_BYTES
+
+
 def test_fewer_compute_units_change_the_choice():
     # the same 256 tiles are two rounds on 128 units: no share of a last round to split
     assert plan(4096, 4096, 4096, cus=128) == (TILE, "dma16p_256x256x32_w2x2_s5", 1)
