@@ -58,7 +58,9 @@ def measured_traffic(name: str):
 def classify(cfg) -> str:
     """The paper's roofline rule (Section 4.3): left of the ridge of the slowest unit (fp32
     vector ALUs) is memory-bound, right of the ridge of the fastest unit that can do the work (the
-    matrix cores for the operand type) is compute-bound, in between is the middle zone."""
+    matrix cores for the operand type) is compute-bound, in between is the middle zone.  (fp32: the ridge is the
+    fp32 instruction's, as in the library, which places the end of streaming on the vector ALUs; the roof that a
+    compute-bound fp32 row is held against below is the bf16 rate over six, what its kernel can reach.)"""
     import workloads as wl
     ai = cfg.flops() / cfg.algorithmic_bytes()
     low = FP32_VECTOR_PEAK_TFLOPS * 1e12 / (HBM_PEAK_GBPS * 1e9)

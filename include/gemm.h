@@ -15,7 +15,7 @@
  *   transB = GEMM_OP_T : B is stored N x K ("column-major B"), op(B)(k,j) = B[j*ldb + k], ldb >= K
  *   C is M x N, C(i,j) = C[i*ldc + j], ldc >= N.
  * Products are accumulated in fp32 (bf16 x bf16 and fp16 x fp16 products are exact; an fp32 product is formed from
- * exact bf16 pieces of its factors to within 2^-23 of itself, typically 2^-26, or by the fp32 instruction), the
+ * exact bf16 pieces of its factors to within 2^-24 of itself, or by the fp32 instruction), the
  * epilogue runs in fp32, and the result is rounded once, to nearest-even, into the type of C.
  * IEEE special values behave as in that arithmetic: subnormal inputs are multiplied (not flushed
  * to zero), fp32 results below the normal range stay subnormal, a result beyond the largest
@@ -187,7 +187,7 @@ gemm_status_t gemm_run_noalloc(gemm_handle_t h, int64_t M, int64_t N, int64_t K,
  * by the whole batch.  strideA or strideB may be 0 (one operand shared by all products);
  * strideC must be at least (M-1)*ldc + N so that no two results overlap.  batch == 0 does
  * nothing.  The fast kernels additionally need strideA and strideB to be multiples of 16 bytes;
- * other strides run the general kernel.  One launch covers up to 65535 matrices; a longer batch
+ * other strides run the general family.  One launch covers up to 65535 matrices; a longer batch
  * is enqueued as consecutive launches.
  *
  * Errors: as gemm_run, and GEMM_ERR_INVALID_ARG for a negative batch or stride or an
@@ -213,7 +213,8 @@ const char* gemm_status_string(gemm_status_t s);
 typedef enum {
     GEMM_KERNEL_AUTO = 0,      /* let the library choose (default) */
     GEMM_KERNEL_GENERAL = 1,   /* any shape and alignment.  Variant 0: one thread per output element.  Variant 1 (bf16 / fp16):
-                                  128x128 MFMA tiles; variant 2 (fp32): 64x64 fp32 tiles.  A forced variant that
+                                  128x128 MFMA tiles, with folded sums where C is fp32; variant 2 (fp32): 64x64 fp32
+                                  tiles with folded sums.  A forced variant that
                                   cannot serve the call (and -1) falls back to 0 */
     GEMM_KERNEL_MFMA_TILE = 2, /* LDS-staged macro-tile kernel on MFMA */
     GEMM_KERNEL_SKINNY = 3     /* streaming kernels with split-K for few rows of C.  bf16 / fp16, M <= 64: variant 0
@@ -251,7 +252,8 @@ typedef struct {
  * GEMM_ERR_UNSUPPORTED.  Errors: GEMM_ERR_INVALID_ARG for a null handle or out-of-range fields. */
 gemm_status_t gemm_set_plan(gemm_handle_t h, const gemm_plan_t* plan);
 
-/* Reports the plan the most recent successful gemm_run on this handle used.  (An automatic plan may
+/* Reports the plan the most recent successful gemm_run on this handle used, whether its slices ran side by side or, for want of
+ * a workspace, one after another.  (An automatic plan may
  * run a C with a thin last strip of columns or rows as two products, the whole tiles and the strip;
  * the plan of the whole tiles is the one reported.)
  * Errors: GEMM_ERR_INVALID_ARG for null arguments. */
@@ -274,7 +276,8 @@ gemm_status_t gemm_plan_query(int32_t compute_units, int64_t batch, int64_t M, i
  * operand (A, B, C written, C read if `reads_c`, the bias if `has_bias`), against two ridge points of
  * the MI355X roofline at 8 TB/s: 19.7 flop/byte, where the fp32 vector ALUs (157.3 TFLOP/s) meet the
  * memory roof, and the ridge of the matrix cores for the operand type (bf16, fp16: 2.5 PFLOP/s ->
- * 312.5; fp32: 157.3 TFLOP/s -> 19.7).  Left of the first: memory-bound, the streaming kernels are
+ * 312.5; fp32: the fp32 instruction's 157.3 TFLOP/s -> 19.7, where streaming on the vector ALUs ends, although products of
+ * bf16 pieces go beyond it).  Left of the first: memory-bound, the streaming kernels are
  * candidates and bytes per second is the objective; right of the second: compute-bound, matrix-core
  * tiles only; in between: middle zone, both families compete and measured thresholds decide.
  * Host arithmetic only.  `intensity` may be NULL.

@@ -639,6 +639,9 @@ bool peel_remainder(const Args& a, int num_cus, double whole_time, Args* main_pa
 // to optimise for: memory-bound and middle-zone calls are candidates for the streaming (skinny)
 // family, whose objective is bytes per second on one pass over B; compute-bound calls go to the
 // macro-tile family, whose objective is matrix-core occupancy, and never to the streaming family.
+// For fp32 that unit's roof is taken at the fp32 instruction's rate, which is the vector ALUs' too, although products of bf16 pieces
+// reach up to 417 TFLOP/s (2.5e15 / 6): the streaming fp32 kernels multiply on the vector ALUs, so where those meet the
+// memory roof is where streaming ends, and fp32 has no middle zone.
 constexpr double kPeakVectorFlops = 157.3e12, kPeakMatrixFlops16 = 2.5e15, kPeakMatrixFlops32 = 157.3e12, kPeakMemoryBytes = 8.0e12;
 
 struct Roofline { double intensity; gemm_roofline_t cls; };

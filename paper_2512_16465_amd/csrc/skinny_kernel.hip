@@ -773,6 +773,7 @@ int skinny_variant_of(const Args& a) {
 // tiles at K = 8192 (16 x 515 x 7936 13.2 / 14.0) and loses beyond (16 x 515 x 16384 22.1 / 17.4, 4 x 259 x 16384 16.3 / 15.4,
 // 4 x 259 x 32768 29.0 / 18.1), with a single row, whose trips cost a third, at twice that (1 x 31 x 16384 8.1 / 14.3,
 // 1 x 31 x 65536 25.4 / 20.9).
+// (The sums of variant 5 are folded for these N, see skinny_nt_narrow_kernel.)
 constexpr int64_t SK_RAGGED_MAX_K = 8192, SK_RAGGED_MAX_K_ONE_ROW = 16384;
 int skinny_ragged_columns_variant(const Args& a) {
     if (a.N % 8 == 0 || a.batch != 1 || !a.transB || a.transA || a.dtype == DT_F32) return -1;
@@ -915,8 +916,8 @@ hipError_t launch_skinny(const Args& call, int split_k, float* workspace, hipStr
 }
 
 // The kernel is one trip to memory long.  Few threads are spread over the chip, a wave per workgroup: with 256 threads
-// each, 8 x 8192 gave 32 workgroups on 256 units (8 x 8192 x 8192 34.5 -> 33.7 to 34.2 us, fp32 64 x 264 x 2504 in 16 slices 14.4 ->
-// 12.3); from 256 such workgroups on every unit has one either way.
+// each, 8 x 8192 gave 32 workgroups on 256 units (8 x 8192 x 8192 28.6 -> 28.0 us in both orders of timing, the runs of one side
+// 0.3 apart; fp32 64 x 264 x 2504 in 16 slices 13.1 to 13.9 -> 11.3 to 12.3); from 256 such workgroups on every unit has one either way.
 constexpr int64_t kReduceSpread = 65536;
 
 hipError_t launch_splitk_reduce(const Args& a, int split_k, const float* partials, hipStream_t stream) {

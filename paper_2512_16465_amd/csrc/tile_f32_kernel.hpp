@@ -6,8 +6,9 @@
 // (8 significant bits each and the signs of the remainders: 24 bits), and of the nine products of the pieces the
 // six largest are summed,
 //   hi*hi + hi*mid + mid*hi + mid*mid + hi*lo + lo*hi,
-// each exact in fp32 and added in the fp32 accumulators of v_mfma_f32_16x16x32_bf16.  The three left out are below
-// 2^-23 |a b| together at the very worst and 2^-27 each as a rule.  Against 64-bit sums the results are closer than the
+// each exact in fp32 and added in the fp32 accumulators of v_mfma_f32_16x16x32_bf16.  The three left out are at most
+// 2^-24 |a b| together (|mid| <= 2^-8 |x|, |lo| <= 2^-17 |x|).  (Sums of products of an exact split in shorter floats: Dekker 1971;
+// three bf16 for one fp32: Henry, Tang and Heinecke 2019.)  Against 64-bit sums the results are closer than the
 // fp32 instruction's, which rounds an accumulator once per two products where this one does six times per 32 (2-norm, Gaussian data: K = 4
 // 3.2e-8 against 4.0e-8, K = 32 3.7e-8 against 1.0e-7, K = 256 2.3e-7 against 2.9e-7, K = 4096 1.0e-6 against 1.1e-6).
 //
@@ -17,13 +18,12 @@
 // the matrix pipe has work on both sides of the barrier.  Everything is placed by slots, one behind each matrix
 // instruction.
 //
-// Bound: the issue port.  Next to a matrix instruction (16 cycles) there is room for about two vector
-// instructions; beyond, each costs 4.7 cycles (measured: 17.9 cycles per matrix instruction alone, 19.3 with two vector ones, 23.6
-// with three, 28.4 with four, from one wave or from two alike).  Taking an element apart costs six, so a tile's ratio of
-// staged elements to products decides: 1.5 vector instructions per matrix instruction with 256x128, two with 128x128.
-// Beyond that the power limit: the pairs run at 1.88 GHz with the matrix pipe 68 % busy.  Measured, this kernel / the fp32
-// instruction before: 4096^3 600 us (229 TFLOP/s) / 1072, 2048^3 93 / 147, 1024^3 22 / 27, 256^3 8.6 / 8.9,
-// 4096x4096x64 27 / 30.
+// Bound: the issue port.  Next to a matrix instruction (16 cycles) there is room for about two vector instructions, and taking
+// an element apart costs 6.5, so a tile's ratio of staged elements to products decides: 1.6 vector instructions per
+// matrix instruction with 256x128, 2.2 with 128x128.  Beyond that the power limit: at 4096^3 the pairs run at 2.0 GHz with the
+// matrix pipe 67 % busy and 1.84 vector instructions per matrix instruction over the whole kernel.  Measured, this kernel / one
+// on the fp32 instruction before: 4096^3 580 to 616 us (237 to 223 TFLOP/s) / 1054 to 1209, 2048^3 86 to 93 / 137 to 146, 1024^3 20.5 to
+// 22.3 / 27.2 to 27.8, 512^3 11.1 / 11.5, 256^3 8.1 / 8.9, 4096x4096x64 27.2 to 28.1 / 30.
 //
 // What the split cannot take.  The pieces of an element are multiples of its last bit, 2^-149 for the smallest floats, and a bf16
 // number's last bit is 2^-133 at least: both operands are multiplied by 2^16 first (one instruction per element, exact), which
@@ -32,7 +32,8 @@
 // (results from 2^96 on), and infinities and NaN themselves.  All of these end in a sum that is not finite, whatever comes
 // after, so a tile with such a sum is computed again, unscaled, the slabs that hold an element above 2^40 or below
 // 2^-110 by v_mfma_f32_16x16x4_f32.  Only elements of the operands count there, not what lies past their edges and is
-// loaded with them.
+// loaded with them.  Such a tile takes about three times its time (every one, 4096^3: 1714 us); the same time for all other data
+// (a zero row, triangular, ternary, one element of 2^50, all of them 1e15, subnormal elements: 1024^3 21.6 to 23.5 us).
 //
 // Edges: loads past the end of an operand return zero dword by dword through the buffer descriptor's range check;
 // elements of a k-contiguous operand past K are cleared when they are staged.  Nothing needs more than the natural
@@ -48,7 +49,7 @@ namespace tile {
 // ALUs, which rounds a sum once per 32 elements of k at full magnitude (without: six times, on the matrix unit).  The general
 // family takes it, whose plain kernel sums sixteen at a time: 2-norm error against 64 bits, Gaussian data, K = 128 / 1024 /
 // 4095, plain kernel 9.3e-8 / 1.65e-7 / 2.98e-7, folded 5.6e-8 / 1.18e-7 / 2.21e-7, not folded 1.5e-7 / 4.9e-7 / 1.0e-6
-// (the fp32 instruction is behind all three).  2049x2051x2045 145 us against 120 without the folds.
+// (the fp32 instruction is behind all three).  2049x2051x2045 143 us, a sixth less without the folds.
 template <int BM_, int BN_, int WM_, int WN_, bool FOLD_ = false>
 struct F32CfgT {
     static constexpr bool FOLD = FOLD_;

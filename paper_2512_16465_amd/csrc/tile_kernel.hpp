@@ -323,7 +323,7 @@ __device__ __forceinline__ void tile_epilogue_bands(Dump dump, char* lds, const 
             constexpr int TRIPS = 32 / EL::RPI;
             constexpr int GROUP = TRIPS % 4 == 0 ? 4 : 1;
             if (interior) {
-                // Whole tile inside C and rows aligned for vector access: no per-lane conditions at
+                // Whole tile inside C (its rows may start on any element): no per-lane conditions at
                 // all, only wave-uniform branches on beta and the activation; four rows in flight
                 // per trip so that the LDS and C_in latencies overlap.
                 typename OV::elem* p0 = Cp + (m0 + wm * C::WTM + i * 32 + lane / EL::LPR) * a.ldc + col;

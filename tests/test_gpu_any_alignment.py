@@ -72,7 +72,7 @@ def test_odd_batch(handle, dtype, variant):
 
 
 @pytest.mark.parametrize("dtype", [wl.BF16, wl.F16])
-@pytest.mark.parametrize("M,N,K", [(1, 9, 8), (1, 4097, 520), (3, 1031, 1032), (4, 12301, 264), (5, 4095, 256), (8, 4099, 1288), (16, 1025, 776)])
+@pytest.mark.parametrize("M,N,K", [(1, 1, 8), (4, 3, 520), (6, 5, 512), (16, 7, 1032), (1, 9, 8), (1, 4097, 520), (3, 1031, 1032), (4, 12301, 264), (5, 4095, 256), (8, 4099, 1288), (16, 1025, 776)])
 def test_few_rows_and_columns_that_are_no_multiple_of_eight(handle, M, N, K, dtype):
     cfg = wl.Config("ragged", M, N, K, 0, 1, dtype, wl.F32 if N % 4 == 1 else dtype, alpha=1.0, beta=1.0, bias_dist=("normal", 1.0),
                     bias_dtype=wl.F32, lda=K + 8, ldb=K + 24, ldc=N + 3)
