@@ -689,8 +689,10 @@ struct AutoPlan {
 // the choice is 0.3 % behind the fastest plan on average, by more than 10 % on 9 of them, and with 16 bits never by more than 6 %
 // behind the general kernel.  Nine calls of ten are within 7 % of their estimates.
 constexpr int64_t kGeneralMinSliceK = 48;
-// (2.6 to 3.1 on the device, more for the call: 33x43x223 fp32 10.2 us plain, 10.8 in 4 slices; 291x97x165 fp32 with GELU 8.3 plain, 9.9 on tiles)
-constexpr double kSecondKernel = 3.4, kActivation = 1.5;
+// (2.6 to 3.1 on the device, more for the call: 33x43x223 fp32 10.2 us plain, 10.8 in 4 slices; none / SiLU / GELU on the 16-bit tile 215x127x181
+// 11.7 / 12.4 / 13.8, 335x75x629 20.3 / 21.1 / 22.4; on the fp32 one 0.1 to 0.4 more than none; 1.5 there too left 65x23x223 with GELU at 11.3
+// in 4 slices where one takes 8.9 and the general kernel 10.2)
+constexpr double kSecondKernel = 3.4, kActivation = 1.5, kActivationF32 = 0.3;
 constexpr double kGeneralMargin = 1.08;       // what the 16-bit tiles must promise (without it up to 22 % behind the general kernel); the fp32 ones round less
 
 // The general kernel: 0.55 us per step of 16 along k, and its throughput (beyond four blocks per unit less each).
@@ -706,7 +708,7 @@ double general_tile_time(const Args& a, int slices, int64_t len, int64_t cus) {
     const bool f32 = a.dtype == gemm::DT_F32, fold = !f32 && a.out_dtype == gemm::DT_F32;
     const double elements = (double)a.M * (double)a.N * (double)a.batch;
     double moved = elements * (f32 || fold || slices > 1 ? 4.0 : 2.0), t = 0.0;
-    if (a.act != gemm::ACT_NONE && slices == 1) t = kActivation;
+    if (a.act != gemm::ACT_NONE && slices == 1) t = f32 ? kActivationF32 : kActivation;
     if (slices > 1) {
         moved += (double)slices * (double)a.M * (double)((a.N + 7) / 8 * 8) * 4.0;
         t = kSecondKernel + (slices == 2 || slices == 4 || slices == 8 || slices == 16 ? 0.0 : 0.36 * slices);

@@ -350,10 +350,11 @@ __device__ __forceinline__ void tile_epilogue_bands(Dump dump, char* lds, const 
                 }
             } else {
                 // Code run for the first time waits for the instruction cache, and this is run once: jumps and second copies are
-                // dear.  One branch around the activations instead of one per element, and two forms of which a call runs
-                // one: N a multiple of four, where a lane's columns are inside C or all outside, and any other, where the
-                // lane at the edge loads and stores one by one.  192x80x192 fp16, batch of 14, 11.3 us with a branch per
-                // element, 8.5 so; 571x55x40 fp16 14.0 with the arithmetic in two copies, 10.2 in one, 8.0 so.
+                // dear.  The activation is chosen once for a lane's columns instead of once per element, behind one branch, and
+                // there are two forms of which a call runs one: N a multiple of four, where a lane's columns are inside C or
+                // all outside, and any other, where the lane at the edge loads and stores one by one.  192x80x192 fp16, batch
+                // of 14, 10.9 us with a branch per element, 8.5 so, with GELU 14.6 and 11.0; 571x55x40 fp16 14.0 with the
+                // arithmetic in two copies, 10.2 in one, 8.4 so; 1008x11448x1968 bf16 with GELU (tanh) 75 and 63.
                 auto rows = [&](auto ragged) {
                     constexpr bool RAGGED = decltype(ragged)::value;
 #pragma unroll 1
@@ -374,19 +375,16 @@ __device__ __forceinline__ void tile_epilogue_bands(Dump dump, char* lds, const 
                                         if (col + e < a.N) cin[e] = OV::load1(p + e);
                                 }
                             }
-                            f32x4 o;
+                            f32x4 o[1];
 #pragma unroll
-                            for (int e = 0; e < 4; ++e) o[e] = epilogue_value(s[e], alpha, beta, cin[e], bias4[e], ACT_NONE);
-                            if (act != ACT_NONE) {
-#pragma unroll
-                                for (int e = 0; e < 4; ++e) o[e] = apply_act(o[e], act);
-                            }
+                            for (int e = 0; e < 4; ++e) o[0][e] = epilogue_value(s[e], alpha, beta, cin[e], bias4[e], ACT_NONE);
+                            if (act != ACT_NONE) apply_act4(o, act);
                             if (whole) {
-                                OV::store4(p, o);
+                                OV::store4(p, o[0]);
                             } else {
 #pragma unroll
                                 for (int e = 0; e < 3; ++e)
-                                    if (col + e < a.N) OV::store1(p + e, o[e]);
+                                    if (col + e < a.N) OV::store1(p + e, o[0][e]);
                             }
                         }
                     }
