@@ -195,6 +195,10 @@ bool tile_variant_slices(int variant);
 // eight waves, two to a SIMD, fill each other's gaps (4096^3: 612 us against 727 with one tile per workgroup; 2560^3 171
 // against 222).  With fewer tiles it would leave units idle (2048^3: 124 against 98).
 constexpr int64_t kF32PairAbove = 256;
+// The tiles with the k range divided among a workgroup's waves (kind 6): the variant for a 16-bit call on a grid too small for the
+// 128x128 tile, -1 where that one is ahead, and its estimated time in us.  A whole call on the 128x128 tiles of variants 5
+// and 12 is launched on it (the plan names the tile, as with the pairs of variant 11).
+int wave_tile_for(const Args& a, int64_t cus, double* estimate);
 hipError_t launch_tile(const Args& a, int variant, int group_m, const TileSplit& split, hipStream_t stream);
 hipError_t launch_tile_split_reduce(const Args& a, int variant, int group_m, const TileSplit& split, hipStream_t stream);
 

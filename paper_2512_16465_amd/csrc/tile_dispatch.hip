@@ -77,9 +77,46 @@ bool shortk_call_fits(const Args& a) {
 bool tile_variant_splits(int variant) { return variant >= 0 && variant < kNum && kInfo[variant].kind == 3; }
 bool tile_variant_slices(int variant) { return variant >= 0 && variant < kNum && kInfo[variant].kind != 3 && kInfo[variant].kind != 5; }
 
+namespace {
+
+// Estimates in us of the wave tiles, fitted to 490 random calls (M 1 to 4000, N and K 64 to 16384, all layouts, batches; half
+// of the calls within 7 %, nine of ten within 20 %).  Per element of k: a workgroup alone on its unit, or each round of
+// them; both grow where an operand's rows start inside a 128-byte line, so that a slab's 128 bytes of a row lie in two.
+struct WaveTile { int variant, bm; double per_k_alone, per_k, straddling, fixed, per_round, store_rate, weight_rate; };
+constexpr WaveTile kWaveTiles[] = {{18, 64, 0.00255, 0.00258, 0.15, 4.2, 0.96, 6.7e6, 22e6}, {19, 16, 0.00131, 0.00143, 0.21, 4.1, 0.6, 22e6, 11e6}};
+// Up to two workgroups of 64x64 per unit: those are resident at once.  Beyond, the 128x128 tile reads half as much per product
+// (1392x2816x1024, 968 tiles of 64x64: 21.9 us against 17.5; 960x2048x1280, 480 tiles: 13.0 against 19.1).  Operands
+// of more than 128 MiB stream from memory, which few short-lived workgroups do not keep busy (14x3840x14336 60 us in 16-row tiles, 40 cut along k).
+constexpr int64_t kWaveTilesPerUnit = 2, kWaveTileBytes = (int64_t)128 << 20;
+
+}  // namespace
+
+int wave_tile_for(const Args& a, int64_t cus, double* estimate) {
+    if ((a.M + a.N) * a.K * a.batch * 2 > kWaveTileBytes) return -1;
+    if (((a.M + 63) / 64) * ((a.N + 63) / 64) * a.batch > kWaveTilesPerUnit * cus) return -1;
+    int best = -1;
+    double best_time = 0.0;
+    for (const WaveTile& t : kWaveTiles) {
+        if (!tile_variant_supports(a, t.variant) || (a.transA && t.bm != 64)) continue;
+        const int64_t rounds = (((a.M + t.bm - 1) / t.bm) * ((a.N + 63) / 64) * a.batch + cus - 1) / cus;
+        const int straddling = ((a.transA ? a.M : a.K) % 64 != 0) + ((a.transB ? a.K : a.N) % 64 != 0);
+        const double per_k = (rounds == 1 ? t.per_k_alone : t.per_k * (double)rounds) * (1.0 + t.straddling * straddling);
+        const double stored = (double)(a.M * a.N * a.batch) * (double)elem_bytes(a.out_dtype) * (a.beta != 0.0f ? 2.0 : 1.0);
+        const double time = t.fixed + t.per_round * (double)rounds + per_k * (double)a.K + stored / t.store_rate + (double)(a.N * a.K * a.batch) * 2.0 / t.weight_rate;
+        if (best < 0 || time < best_time) { best = t.variant; best_time = time; }
+    }
+    if (estimate) *estimate = best_time;
+    return best;
+}
+
 hipError_t launch_tile(const Args& a, int variant, int group_m, const TileSplit& split, hipStream_t stream) {
     if (variant < 0 || variant >= kNum) return hipErrorInvalidValue;
     if (split.parts > 1 && !tile_variant_splits(variant)) return hipErrorInvalidValue;
+    if ((variant == 5 || variant == 12) && a.k_total == 0) {
+        const int wave_tile = wave_tile_for(a, 256, nullptr);
+        if (wave_tile >= 0) variant = wave_tile;
+    }
+    if (variant == 19 && a.transA) variant = 18;      // (a k-row of A is moved in whole lines: 64 rows to a tile)
     return kLaunch[variant](a, group_m < 1 ? 1 : group_m, split, stream);
 }
 

@@ -1,0 +1,83 @@
+"""CPU checks of the tiles whose k range is divided among the waves: the loads of their movers stay inside the operand and put
+every element where the fragment reads look for it (the arithmetic of tile_wavek_kernel.hpp, restated), and the generated code
+touches no fragment register before its wait."""
+import os
+
+import numpy as np
+import pytest
+
+from asm_inflight import check_listing, check_wide_store_data
+
+LANES = np.arange(64)
+
+
+def kc_hash(r):
+    return (r ^ ((r >> 3) & 1)) & 7
+
+
+def mc_swizzle(k):
+    return (k & 2) | (((k >> 3) & 1) << 2)
+
+
+def slab_loads(kc, rows, valid, ld, K, slab):
+    """(byte offset in the operand, LDS byte, fetched) of every lane's 16 bytes of one slab."""
+    k_left = K - slab * 64
+    for q in range(rows // 8):
+        if kc:
+            row = 8 * q + (LANES >> 3)
+            c = (LANES & 7) ^ kc_hash(row)
+            off = np.minimum(row, valid - 1) * ld * 2 + c * 16 + slab * 128
+            k = c * 8
+        else:
+            k = 8 * (q % 8) + (LANES >> 3)
+            c = ((LANES & 7) ^ mc_swizzle(k)) + 8 * (q // 8)
+            off = (k * ld + np.where(c * 8 + 8 <= valid, c * 8, valid - 8)) * 2 + slab * 128 * ld
+        yield off, q * 1024 + LANES * 16, k < k_left
+
+
+@pytest.mark.parametrize("kc,rows", [(True, 64), (True, 16), (False, 64)])
+@pytest.mark.parametrize("K", [8, 64, 72, 136, 256])
+def test_loads_stay_inside_and_the_fragments_find_their_elements(kc, rows, K):
+    for valid in (8, 24, 56, 64) if not kc else (1, 7, 16, 63, 64):
+        if valid > rows:
+            continue
+        for ld in ((K if kc else valid), (K if kc else valid) + 8):
+            # the operand as its elements' own indices
+            n = (valid - 1) * ld + K if kc else (K - 1) * ld + valid
+            for slab in range((K + 63) // 64):
+                lds = np.full(rows * 64, -1, np.int64)          # element index held by every 16-bit place, -1: zero
+                for off, at, fetched in slab_loads(kc, rows, valid, ld, K, slab):
+                    assert np.all(off[fetched] + 16 <= n * 2)
+                    for o, a, f in zip(off, at, fetched):
+                        lds[a // 2: a // 2 + 8] = np.arange(8) + o // 2 if f else -1
+                r, g = LANES & 15, LANES >> 4
+                for tile in range(rows // 16):
+                    for ks in range(2):
+                        for e in range(8):
+                            k = 32 * ks + 8 * g + e
+                            row = 16 * tile + r
+                            if kc:
+                                place = tile * 2048 + r * 128 + (((4 * ks + g) ^ kc_hash(r)) << 4) + 2 * e
+                            else:
+                                # a transposing read: lane i of 16 receives column i of the four k-rows that lanes 4j .. 4j+3 address
+                                col = 16 * tile + 4 * (r >> 2)
+                                place = k * 128 + (((col >> 3) ^ mc_swizzle(k)) << 4) + (col & 7) * 2 + 2 * (r & 3)
+                            got = lds[place // 2]
+                            inside = (row < valid) & (slab * 64 + k < K)
+                            want = row * ld + slab * 64 + k if kc else (slab * 64 + k) * ld + row
+                            assert np.array_equal(got[inside], want[inside])
+                            past_k = slab * 64 + k >= K
+                            assert np.all(got[past_k] == -1)                   # zeros
+
+
+def test_no_fragment_register_is_touched_before_its_wait(tmp_path):
+    from paper_2512_16465_amd import build
+    if not os.path.exists(build.HIPCC):
+        pytest.skip("no hipcc")
+    for variant, kernels in ((18, 8), (19, 4)):
+        path = build.device_assembly(f"tile_variant_{variant}.hip", str(tmp_path / f"{variant}.s"))
+        with open(path) as f:
+            n, found = check_listing(f, only="tile_wavek_kernel")
+        assert n == kernels and not found, (n, found[:1])
+        with open(path) as f:
+            assert not check_wide_store_data(f)
