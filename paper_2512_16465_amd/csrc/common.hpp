@@ -246,6 +246,9 @@ bool general_variant_supports(const Args& a, int variant);
 // for an error no larger than that of variant 0, which adds sixteen elements at a time (a 16-bit result's own rounding is
 // three orders of magnitude above either).
 hipError_t launch_general(const Args& a, int variant, int group_m, hipStream_t stream, bool fold, int64_t slice_len = 0);
+// The 16-bit wave tiles (kind 6 of tile_variants.def) with movers that need no alignment, 64 or 16 rows to a tile: K >= 8 where k is
+// contiguous, M or N >= 8 where they are, operands below 2 GiB.
+hipError_t launch_wave_any(const Args& a, int rows, int group_m, hipStream_t stream);
 hipError_t launch_any_tile(const Args& a, int group_m, hipStream_t stream, int64_t slice_len, bool fold);
 hipError_t launch_any_f32_tile(const Args& a, int group_m, hipStream_t stream, int64_t slice_len);
 

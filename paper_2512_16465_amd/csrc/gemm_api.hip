@@ -536,6 +536,7 @@ Args slices_of(const Args& a, int slices, int64_t len, float* partials, int64_t 
 }
 
 int64_t general_slice_len(int64_t K, int& slices);
+int wave_any_rows(const Args& a, int slices, int num_cus);
 
 // Launches the kernels of a plan for the (validated) call `a`; may lower plan.split_k to what the
 // call can take.  split_first: first tile of a split trailing round (macro-tile family).
@@ -595,6 +596,7 @@ gemm_status_t launch_plan(const Workspace& ws, const Args& a, gemm_plan_t& plan,
         }
     } else {
         const bool fold = a.out_dtype == gemm::DT_F32;
+        const int wave_rows = plan.variant == 1 ? wave_any_rows(a, plan.split_k, ws.h->num_cus) : 0;
         if (plan.split_k > 1) {
             // k slices, as above; a call of this family has never failed for want of a workspace, so where there is none to
             // be had (the stream is being captured, memory is out) its slices are computed one after another, to the same bits
@@ -604,6 +606,10 @@ gemm_status_t launch_plan(const Workspace& ws, const Args& a, gemm_plan_t& plan,
                 if (ws.fixed && need > kScratchBytes) return GEMM_ERR_SCRATCH_LIMIT;
                 const bool side_by_side = ws.obtain(need, stream);
                 if (allocate_only) return GEMM_OK;
+                if (wave_rows) {      // (one launch, no partial results; the workspace is there for the calls of this size that need it)
+                    e = gemm::launch_wave_any(a, wave_rows, kTileBandRows, stream);
+                    return e == hipSuccess ? GEMM_OK : GEMM_ERR_HIP;
+                }
                 if (!side_by_side) {
                     e = gemm::launch_general(a, plan.variant, kTileBandRows, stream, fold, len);
                     return e == hipSuccess ? GEMM_OK : GEMM_ERR_HIP;
@@ -613,7 +619,8 @@ gemm_status_t launch_plan(const Workspace& ws, const Args& a, gemm_plan_t& plan,
                 return e == hipSuccess ? GEMM_OK : GEMM_ERR_HIP;
             }
         }
-        if (!allocate_only) e = gemm::launch_general(a, plan.variant, kTileBandRows, stream, fold);
+        if (!allocate_only && wave_rows) e = gemm::launch_wave_any(a, wave_rows, kTileBandRows, stream);
+        else if (!allocate_only) e = gemm::launch_general(a, plan.variant, kTileBandRows, stream, fold);
     }
     return e == hipSuccess ? GEMM_OK : GEMM_ERR_HIP;
 }
@@ -760,6 +767,35 @@ int64_t general_slice_len(int64_t K, int& slices) {
     const int64_t slabs = (K + 31) / 32, len = ((slabs + slices - 1) / slices) * 32;
     slices = (int)((K + len - 1) / len);
     return slices > 1 ? len : K;
+}
+
+// A call that a plan gives to the 16-bit tiles of the general family, in whatever slices, runs in one launch on the tiles whose waves
+// divide the k range, 64 or 16 (returned; 0: neither) rows by 64 columns, where those promise to be ahead.  Estimates in us, fitted to 210
+// random calls each (half within 5 %, nine of ten within 14 %); on 350 such calls the choice is 1.40 times as fast as before
+// on average (geometric), the faster of all three in hindsight 1.404 times.  At 2049x2051x2045 the three are level (53 to 54 us); at 4095^3 the large tile,
+// which reads half as many bytes, is ahead (255 us against 328), as are slices with few columns and a long k (9x979x4043 16.4 against 29.4).
+// Results of 16 bits only: for an fp32 C slices and folds have the smaller error.
+int wave_any_rows(const Args& a, int slices, int num_cus) {
+    const int64_t cus = num_cus > 0 ? num_cus : 256;
+    // (the movers start the last chunk of a row 8 elements ahead of its end, and mask with an offset of 2 GiB - 16)
+    if (a.dtype == gemm::DT_F32 || a.out_dtype == gemm::DT_F32 || (!a.transA && a.K < 8) || (a.transB && a.K < 8)) return 0;
+    if ((a.transA ? a.K : a.M) * a.lda * 2 >= 0x7ffffff0ll || (a.transB ? a.N : a.K) * a.ldb * 2 >= 0x7ffffff0ll) return 0;
+    struct Tile { int rows; double per_k_alone, per_k, fixed, per_round, store_rate, activation, weight_rate, layout[4]; };
+    static const Tile tiles[] = {{64, 0.0041, 0.0038, 5.1, 0.6, 3.4e6, 1.3, 41e6, {1.0, 1.12, 1.34, 1.37}},      // NT, NN, TT, TN
+                                 {16, 0.00256, 0.0024, 4.2, 0.0, 1.0e6, 0.6, 23e6, {1.0, 1.05, 0.0, 0.0}}};
+    const int layout = (a.transA ? 2 : 0) + (a.transB ? 0 : 1);
+    int sl = slices > 1 ? slices : 1, rows = 0;
+    const int64_t len = sl > 1 ? general_slice_len(a.K, sl) : a.K;
+    double best = general_tile_time(a, sl, len, cus);
+    for (const Tile& t : tiles) {
+        if (t.layout[layout] == 0.0) continue;      // (a k-row of 16 elements of an A stored K x M is no whole line)
+        const int64_t rounds = (((a.M + t.rows - 1) / t.rows) * ((a.N + 63) / 64) * a.batch + cus - 1) / cus;
+        const double time = t.fixed + t.per_round * (double)rounds + (rounds == 1 ? t.per_k_alone : t.per_k * (double)rounds) * t.layout[layout] * (double)a.K +
+                            (double)(a.M * a.N * a.batch) * 2.0 / t.store_rate + (a.act != gemm::ACT_NONE ? t.activation : 0.0) +
+                            (double)(a.N * a.K * a.batch) * 2.0 / t.weight_rate;
+        if (time < best) { best = time; rows = t.rows; }
+    }
+    return rows;
 }
 
 gemm_plan_t general_plan(const Args& a, int num_cus) {

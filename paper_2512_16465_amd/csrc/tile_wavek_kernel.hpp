@@ -24,8 +24,11 @@ namespace gemm {
 namespace tile {
 
 // ROWS x 64 tile, 64 of k per slab and wave, NS places for slabs per wave.  WGS: workgroups that share a unit.
-template <int ROWS, int NS_, int WGS_>
+// ANY: operands off the 16-byte grid.
+template <int ROWS, int NS_, int WGS_, bool ANY_ = false>
 struct WaveK {
+    static constexpr bool ANY = ANY_;
+    static_assert(!ANY || NS_ == 1, "the registers hold the slab behind");
     static constexpr int BM = ROWS, BN = 64, BK = 64, WAVES = 4, NT = WAVES * 64, NS = NS_, WGS = WGS_;
     static constexpr int TM = BM / 16;                                                        // blocks of 16 rows
     static constexpr int A_SLAB = BM * BK * 2, SLAB = A_SLAB + BN * BK * 2, RING = NS * SLAB;      // bytes, of one wave
@@ -127,6 +130,103 @@ __device__ __forceinline__ f32x4 wavek_mfma(u32x4 a, u32x4 b, f32x4 c) {
     if constexpr (IS_BF16) return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
     else return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
 }
+
+// ---- the same operands off the 16-byte grid: through registers, to the same places in LDS ----
+// A 16-byte buffer load takes any element's address.  Chunks that would cross the end of a row are loaded from 8 elements ahead of the
+// end and moved down by `s` elements (wave-uniform), so that nothing outside the operand is ever asked for.
+
+__device__ __forceinline__ u32x4 drop_elements(u32x4 v, int s) {
+    if (s & 1) {
+        v.x = __builtin_amdgcn_alignbit(v.y, v.x, 16);
+        v.y = __builtin_amdgcn_alignbit(v.z, v.y, 16);
+        v.z = __builtin_amdgcn_alignbit(v.w, v.z, 16);
+        v.w >>= 16;
+    }
+    if (s & 2) v = u32x4{v.y, v.z, v.w, 0u};
+    if (s & 4) v = u32x4{v.z, v.w, 0u, 0u};
+    return v;
+}
+
+template <int ROWS>
+struct WaveAnyKC : WaveKC<ROWS> {
+    using Base = WaveKC<ROWS>;
+    u32x4 r[Base::L];
+    static __device__ __forceinline__ const char* tile_base(const void* p, int64_t first_row, int64_t ld) { return Base::tile_base(p, first_row, ld); }
+    __device__ __forceinline__ void init(int lane, int64_t ld, int64_t /*first_row*/, int valid_rows) { Base::init(lane, ld, valid_rows); }
+    // slab `t`; `bytes`: from `base` to the end of the operand
+    __device__ __forceinline__ void load(const char* base, int64_t bytes, int64_t step, int t, int k_left, int lane) {
+        if (k_left >= 64) {
+            const __amdgpu_buffer_rsrc_t rsrc = make_rsrc(base, bytes);
+#pragma unroll
+            for (int q = 0; q < Base::L; ++q) r[q] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, Base::voff[q], (uint32_t)(t * step), 0);
+            return;
+        }
+        // the last slab: the chunk with the row's last element in it, zeros behind it (the matrix has at least 8 k, so only a later
+        // slab than the first can start a load ahead of itself)
+        const int s = -k_left & 7, ahead = t > 0 ? 16 : 0;
+        const __amdgpu_buffer_rsrc_t rsrc = make_rsrc(base + t * step - ahead, bytes - t * step + ahead);
+#pragma unroll
+        for (int q = 0; q < Base::L; ++q) {
+            const int k = (int)Base::chunk(q, lane) * 8;
+            const uint32_t off = Base::voff[q] + (uint32_t)(ahead - (k + 8 > k_left ? 2 * s : 0));
+            r[q] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, k < k_left ? off : 0x7ffffff0u, 0, 0);
+        }
+        if (s) {
+#pragma unroll
+            for (int q = 0; q < Base::L; ++q) {
+                const int k = (int)Base::chunk(q, lane) * 8;
+                const u32x4 moved = drop_elements(r[q], s);
+                r[q] = k + 8 > k_left ? moved : r[q];
+            }
+        }
+    }
+    __device__ __forceinline__ void store(char* slab, int lane) const {
+#pragma unroll
+        for (int q = 0; q < Base::L; ++q) *(u32x4*)(slab + q * 1024 + lane * 16) = r[q];
+    }
+};
+
+template <int ROWS>
+struct WaveAnyMC : WaveMC<ROWS> {
+    using Base = WaveMC<ROWS>;
+    static_assert(ROWS == 64, "one sub-slab");
+    u32x4 r[Base::L];
+    int edge;      // columns of the tile inside the operand where they end inside a chunk, 0: they do not
+    // the base of a later tile is 8 columns ahead of it
+    static __device__ __forceinline__ const char* tile_base(const void* p, int64_t first_row, int64_t /*ld*/) {
+        return (const char*)p + (first_row - (first_row > 0 ? 8 : 0)) * 2;
+    }
+    __device__ __forceinline__ void init(int lane, int64_t ld, int64_t first_row, int valid_rows) {
+        const int ahead = first_row > 0 ? 8 : 0;
+        const uint32_t ld_bytes = (uint32_t)ld * 2;
+        edge = valid_rows & 7 ? valid_rows : 0;
+#pragma unroll
+        for (int q = 0; q < Base::L; ++q) {
+            const uint32_t k = 8 * q + (lane >> 3);
+            const int c8 = (int)((uint32_t)(lane & 7) ^ Base::swizzle(k)) * 8;
+            Base::voff[q] = k * ld_bytes + (uint32_t)((c8 + 8 <= valid_rows ? c8 : valid_rows - 8) + ahead) * 2;
+        }
+    }
+    __device__ __forceinline__ void load(const char* base, int64_t bytes, int64_t step, int t, int k_left, int lane) {
+        const __amdgpu_buffer_rsrc_t rsrc = make_rsrc(base, bytes);
+        if (k_left < 64) Base::mask(lane, k_left);      // (the last slab that this wave asks for)
+#pragma unroll
+        for (int q = 0; q < Base::L; ++q) r[q] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, Base::voff[q], (uint32_t)(t * step), 0);
+    }
+    __device__ __forceinline__ void store(char* slab, int lane) {
+        if (edge) {
+            const int s = -edge & 7;
+#pragma unroll
+            for (int q = 0; q < Base::L; ++q) {
+                const int c8 = (int)((uint32_t)(lane & 7) ^ Base::swizzle(8 * q + (lane >> 3))) * 8;
+                const u32x4 moved = drop_elements(r[q], s);
+                r[q] = c8 == (edge & ~7) ? moved : r[q];
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < Base::L; ++q) *(u32x4*)(slab + q * 1024 + lane * 16) = r[q];
+    }
+};
 
 // The sums of the waves are added in the order of the waves: every wave parks its own in its ring as rows of 16 chunks, chunk c
 // of row r at place c xor (r mod 16), then adds its share of the rows.
@@ -263,12 +363,20 @@ __global__ __launch_bounds__(C::NT, C::WGS) void tile_wavek_kernel(Args a, int t
     const int64_t m0 = (int64_t)tm * C::BM, n0 = (int64_t)tn * C::BN;
     const int K = (int)a.K, slabs = (K + C::BK - 1) / C::BK;
 
-    using LA = typename std::conditional<A_KC, WaveKC<C::BM>, WaveMC<C::BM>>::type;
-    using LB = typename std::conditional<B_KC, WaveKC<C::BN>, WaveMC<C::BN>>::type;
+    using LA = typename std::conditional<C::ANY, typename std::conditional<A_KC, WaveAnyKC<C::BM>, WaveAnyMC<C::BM>>::type,
+                                         typename std::conditional<A_KC, WaveKC<C::BM>, WaveMC<C::BM>>::type>::type;
+    using LB = typename std::conditional<C::ANY, typename std::conditional<B_KC, WaveAnyKC<C::BN>, WaveAnyMC<C::BN>>::type,
+                                         typename std::conditional<B_KC, WaveKC<C::BN>, WaveMC<C::BN>>::type>::type;
     LA la;
     LB lb;
-    la.init(lane, a.lda, (int)(a.M - m0 < C::BM ? a.M - m0 : C::BM));
-    lb.init(lane, a.ldb, (int)(a.N - n0 < C::BN ? a.N - n0 : C::BN));
+    const int valid_m = (int)(a.M - m0 < C::BM ? a.M - m0 : C::BM), valid_n = (int)(a.N - n0 < C::BN ? a.N - n0 : C::BN);
+    if constexpr (C::ANY) {
+        la.init(lane, a.lda, m0, valid_m);
+        lb.init(lane, a.ldb, n0, valid_n);
+    } else {
+        la.init(lane, a.lda, valid_m);
+        lb.init(lane, a.ldb, valid_n);
+    }
     const char* const pa = LA::tile_base(a.A, m0, a.lda);
     const char* const pb = LB::tile_base(a.B, n0, a.ldb);
     const int64_t a_step = LA::k_step_bytes(a.lda), b_step = LB::k_step_bytes(a.ldb);
@@ -287,6 +395,13 @@ __global__ __launch_bounds__(C::NT, C::WGS) void tile_wavek_kernel(Args a, int t
     // fetches nothing but counts like any other, so the waits below can be exact.
     auto request = [&](int t, int p) {
         const int k_left = K - t * C::BK;
+        if constexpr (C::ANY) {
+            if (k_left > 0) {
+                la.load(pa, a_bytes, a_step, t, k_left, lane);
+                lb.load(pb, b_bytes, b_step, t, k_left, lane);
+            }
+            return;
+        } else {
         const __amdgpu_buffer_rsrc_t ra = make_rsrc(pa, k_left > 0 ? a_bytes : 0), rb = make_rsrc(pb, k_left > 0 ? b_bytes : 0);
         const uint32_t sa = (uint32_t)(t * a_step), sb = (uint32_t)(t * b_step);
         char* const dst = ring + p * C::SLAB;
@@ -298,6 +413,7 @@ __global__ __launch_bounds__(C::NT, C::WGS) void tile_wavek_kernel(Args a, int t
         for (int q = 0; q < LA::L; ++q) load_to_lds_b128(ra, dst + q * 1024, la.voff[q], sa);
 #pragma unroll
         for (int q = 0; q < LB::L; ++q) load_to_lds_b128(rb, dst + C::A_SLAB + q * 1024, lb.voff[q], sb);
+        }
     };
 
     WaveBias bias;
@@ -329,7 +445,13 @@ __global__ __launch_bounds__(C::NT, C::WGS) void tile_wavek_kernel(Args a, int t
     for (int i = -C::NS; i < mine; ++i) {      // (the first NS trips only ask: the code is there once)
         const int place = C::NS == 1 ? 0 : i & (C::NS - 1);
         if (i >= 0) {
-            asm volatile("s_waitcnt vmcnt(%0)" ::"n"((C::NS - 1) * C::LOADS) : "memory");
+            if constexpr (C::ANY) {
+                la.store(ring, lane);
+                lb.store(ring + C::A_SLAB, lane);
+                asm volatile("" ::: "memory");      // (a wave's LDS operations take effect in their order)
+            } else {
+                asm volatile("s_waitcnt vmcnt(%0)" ::"n"((C::NS - 1) * C::LOADS) : "memory");
+            }
             read(std::integral_constant<int, 0>{}, (uint32_t)(place * C::SLAB));
             read(std::integral_constant<int, 1>{}, (uint32_t)(place * C::SLAB));
             wait_frags(af[0]);

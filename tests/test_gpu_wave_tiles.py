@@ -86,3 +86,26 @@ def test_strided_batch(handle, name):
         p.check(name, exact=True)
     finally:
         lg.gemm_set_plan(handle)
+
+
+@pytest.mark.parametrize("ta,tb", [(0, 1), (0, 0), (1, 1), (1, 0)])
+@pytest.mark.parametrize("M,N,K", [(9, 200, 9), (65, 131, 63), (130, 73, 65), (200, 139, 201), (19, 67, 1031), (301, 453, 519), (8, 75, 127)])
+def test_off_the_grid(handle, ta, tb, M, N, K):
+    """The movers that need no alignment: rows that start on any element and end inside a chunk, the last slab of a k range, tiles with fewer
+    than eight columns or rows inside C.  What lies outside the operands is NaN; integer data, one right answer."""
+    M = max(M, 8) if ta else M
+    for dtype in (wl.BF16, wl.F16):
+        cfg = wl.Config("w", M, N, K, ta, tb, dtype, dtype, lda=(M if ta else K) + 3, ldb=(K if tb else N) + 1, ldc=N + 1)
+        inp, _ = wl.make_integer_inputs(cfg, M + K, -2, 2)
+        want = c_bits_as_uint(cfg, expected_bits_exact(cfg, inp).reshape(M, N))
+        for key, (rows, cols), ld in (("A", cfg.a_shape(), cfg.ld_a()), ("B", cfg.b_shape(), cfg.ld_b())):
+            x = inp[key].reshape(rows, ld).copy()
+            x[:, cols:] = wl.to_bits(np.full((1,), np.nan, dtype=np.float32), dtype)[0]
+            inp[key] = x.reshape(-1)
+        lg.gemm_set_plan(handle, lg.GEMM_KERNEL_GENERAL, 1, 1)
+        try:
+            p = DeviceProblem(cfg, inp, a_offset_elems=1, b_offset_elems=3)
+            p.run(handle)
+            assert np.array_equal(c_bits_as_uint(cfg, p.result_bits()), want)
+        finally:
+            lg.gemm_set_plan(handle)

@@ -70,12 +70,56 @@ def test_loads_stay_inside_and_the_fragments_find_their_elements(kc, rows, K):
                             assert np.all(got[past_k] == -1)                   # zeros
 
 
+def any_loads(kc, rows, first, valid, ld, K, slab):
+    """(element index relative to the operand, LDS byte, fetched, elements dropped) of every lane's load off the grid."""
+    k_left = K - slab * 64
+    for q in range(rows // 8):
+        if kc:
+            row = 8 * q + (LANES >> 3)
+            k = ((LANES & 7) ^ kc_hash(row)) * 8
+            drop = np.where((k + 8 > k_left) & (k_left < 64), -k_left % 8, 0)
+            off = (first + np.minimum(row, valid - 1)) * ld + slab * 64 + k - drop
+            yield off, q * 1024 + LANES * 16, k < k_left, drop
+        else:
+            k = 8 * q + (LANES >> 3)
+            c8 = ((LANES & 7) ^ mc_swizzle(k)) * 8
+            off = (slab * 64 + k) * ld + first + np.where(c8 + 8 <= valid, c8, valid - 8)
+            yield off, q * 1024 + LANES * 16, k < k_left, np.where((c8 == valid // 8 * 8) & (valid % 8 != 0), -valid % 8, 0)
+
+
+@pytest.mark.parametrize("kc,rows", [(True, 64), (True, 16), (False, 64)])
+@pytest.mark.parametrize("K", [9, 63, 65, 131])
+def test_loads_off_the_grid_stay_inside_and_land_in_place(kc, rows, K):
+    for total in (9, 63, 64, 67, 129):
+        ld = (K if kc else total) + 1
+        n = (total - 1) * ld + K if kc else (K - 1) * ld + total
+        for first in range(0, total, rows):
+            valid = min(rows, total - first)
+            for slab in range((K + 63) // 64):
+                lds = np.full(rows * 64, -1, np.int64)
+                for off, at, fetched, drop in any_loads(kc, rows, first, valid, ld, K, slab):
+                    assert np.all(off[fetched] >= 0) and np.all(off[fetched] + 8 <= n), (total, first, slab)
+                    for o, a, f, d in zip(off, at, fetched, drop):
+                        lds[a // 2: a // 2 + 8] = -1
+                        if f:
+                            lds[a // 2: a // 2 + 8 - d] = np.arange(d, 8) + o
+                for row in range(valid):
+                    for k in range(64):
+                        if kc:
+                            place = row * 128 + (((k // 8) ^ kc_hash(np.int64(row))) << 4) + k % 8 * 2
+                        else:
+                            place = k * 128 + (((row // 8) ^ mc_swizzle(np.int64(k))) << 4) + row % 8 * 2
+                        inside = slab * 64 + k < K
+                        want = ((first + row) * ld + slab * 64 + k if kc else (slab * 64 + k) * ld + first + row) if inside else -1
+                        assert lds[place // 2] == want, (total, first, slab, row, k)
+
+
 def test_no_fragment_register_is_touched_before_its_wait(tmp_path):
     from paper_2512_16465_amd import build
     if not os.path.exists(build.HIPCC):
         pytest.skip("no hipcc")
-    for variant, kernels in ((18, 8), (19, 4)):
-        path = build.device_assembly(f"tile_variant_{variant}.hip", str(tmp_path / f"{variant}.s"))
+    for unit, kernels in (("tile_variant_18", 8), ("tile_variant_19", 4), ("tile_wave_any", 12)):
+        path = build.device_assembly(unit + ".hip", str(tmp_path / (unit + ".s")))
         with open(path) as f:
             n, found = check_listing(f, only="tile_wavek_kernel")
         assert n == kernels and not found, (n, found[:1])
