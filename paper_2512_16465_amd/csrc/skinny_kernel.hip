@@ -98,15 +98,39 @@ __device__ __forceinline__ void sk_load_row_inputs(const Args& a, int64_t row, i
         for (int e = 0; e < 8; ++e) in.c_in[e] = 0.0f;
     }
 #pragma unroll
-    for (int e = 0; e < 8; ++e) in.bias[e] = a.bias && e < count ? load_elem(a.bias, a.bias_dtype, col + e) : 0.0f;
+    for (int e = 0; e < 8; ++e) in.bias[e] = 0.0f;
+    if (a.bias) {      // (one choice of type for all: the loads travel together)
+        const int64_t last = a.N - 1;
+        if (a.bias_dtype == DT_F32) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) in.bias[e] = ((const float*)a.bias)[col + e < last ? col + e : last];
+        } else {
+            uint16_t b[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) b[e] = ((const uint16_t*)a.bias)[col + e < last ? col + e : last];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) in.bias[e] = a.bias_dtype == DT_BF16 ? bf16_bits_to_f32(b[e]) : f16_bits_to_f32(b[e]);
+        }
+    }
 }
 
-// Stores 8 consecutive outputs of one row, after the epilogue, in the type of C.
+// Stores 8 consecutive outputs of one row, after the epilogue, in the type of C.  ACT_ONCE: the activation is chosen once for all
+// (less code, for a kernel that runs it once; in the unrolled rows of the kernel below it is the choice at each element that stays small).
+template <bool ACT_ONCE>
 __device__ __forceinline__ void sk_store_row(const Args& a, int64_t row, int64_t col, const float (&x)[8], const SkRowInputs& in, bool vec_ok, int count = 8) {
     float o[8];
     const int64_t idx = row * a.ldc + col;
+    if constexpr (ACT_ONCE) {
+        f32x4 v[2];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) o[e] = epilogue_value(x[e], a.alpha, a.beta, in.c_in[e], in.bias[e], a.act);
+        for (int e = 0; e < 8; ++e) v[e / 4][e % 4] = epilogue_value(x[e], a.alpha, a.beta, in.c_in[e], in.bias[e], ACT_NONE);
+        if (a.act != ACT_NONE) apply_act4(v, a.act);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[e] = v[e / 4][e % 4];
+    } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[e] = epilogue_value(x[e], a.alpha, a.beta, in.c_in[e], in.bias[e], a.act);
+    }
     if (a.out_dtype == DT_F32) {
         float* p = (float*)a.C + idx;
         if (vec_ok) {
@@ -279,7 +303,7 @@ __global__ __launch_bounds__(SK_WAVES * 64) void skinny_nn_kernel(Args a, int sp
                 } else {
                     SkRowInputs in;
                     sk_load_row_inputs(a, row, col0, c_vec_ok != 0, in);
-                    sk_store_row(a, row, col0, x, in, c_vec_ok != 0);
+                    sk_store_row<false>(a, row, col0, x, in, c_vec_ok != 0);
                 }
             }
         }
@@ -669,7 +693,9 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(Args a, int split_k,
     const int64_t groups_per_row = (a.N + 7) / 8;       // rows of a partial result are whole groups of eight
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (g >= a.M * groups_per_row) return;
-    const int64_t row = g / groups_per_row, col = (g % groups_per_row) * 8;
+    // (a 64-bit division is a hundred instructions, run once and cold)
+    const int64_t row = a.M * groups_per_row < (int64_t)1 << 31 ? (int64_t)((uint32_t)g / (uint32_t)groups_per_row) : g / groups_per_row;
+    const int64_t col = (g - row * groups_per_row) * 8;
     const int64_t slice = a.M * groups_per_row * 8;
     const float* p = ws + row * groups_per_row * 8 + col;
     const int count = a.N - col < 8 ? (int)(a.N - col) : 8;
@@ -696,7 +722,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(Args a, int split_k,
             for (int e = 0; e < 4; ++e) { x[e] += lo[e]; x[4 + e] += hi[e]; }
         }
     }
-    sk_store_row(a, row, col, x, in, vec_ok, count);
+    sk_store_row<true>(a, row, col, x, in, vec_ok, count);
 }
 
 // A stored K x M (transA): the few rows of op(A) are gathered once into a row-major M x K copy in the

@@ -137,8 +137,10 @@ __global__ __launch_bounds__(256) void tile_split_reduce_kernel(Args a, int tile
     if (row >= a.M || col >= a.N) return;
     const size_t tile_floats = (size_t)BM * BN;
     const float* p = partials + ((size_t)blockIdx.x * parts) * tile_floats + (size_t)r * BN + c;
-    float c_in[4] = {0.0f, 0.0f, 0.0f, 0.0f}, bj[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    float c_in[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    tile::RawBias bias;
     auto load_inputs = [&]() {
+        tile::ask_bias(a, col, bias);
         const bool vec = col + 3 < a.N;
         if (vec && a.beta != 0.0f) {
             const int64_t ci = row * a.ldc + col;
@@ -151,9 +153,8 @@ __global__ __launch_bounds__(256) void tile_split_reduce_kernel(Args a, int tile
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            if (col + e >= a.N) break;
-            if (!vec && a.beta != 0.0f) c_in[e] = load_elem(a.C, a.out_dtype, row * a.ldc + col + e);
-            if (a.bias) bj[e] = load_elem(a.bias, a.bias_dtype, col + e);
+            if (vec || col + e >= a.N) break;
+            if (a.beta != 0.0f) c_in[e] = load_elem(a.C, a.out_dtype, row * a.ldc + col + e);
         }
     };
     f32x4 s;
@@ -178,9 +179,12 @@ __global__ __launch_bounds__(256) void tile_split_reduce_kernel(Args a, int tile
         }
         for (; q < parts; ++q) s += *(const f32x4*)(p + (size_t)q * tile_floats);
     }
-    f32x4 o;
+    const f32x4 bj = tile::bias_values(a, bias);
+    f32x4 one[1];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) o[e] = epilogue_value(s[e], a.alpha, a.beta, c_in[e], bj[e], a.act);
+    for (int e = 0; e < 4; ++e) one[0][e] = epilogue_value(s[e], a.alpha, a.beta, c_in[e], bj[e], ACT_NONE);
+    if (a.act != ACT_NONE) apply_act4(one, a.act);
+    const f32x4 o = one[0];
     if (col + 3 < a.N) {          // four outputs in one store
         const int64_t ci = row * a.ldc + col;
         if (a.out_dtype == DT_F32) tile::OutVec<DT_F32>::store4((float*)a.C + ci, o);

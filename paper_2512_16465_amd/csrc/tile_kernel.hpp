@@ -253,6 +253,35 @@ template <> struct OutVec<DT_F16> {
     static __device__ __forceinline__ void store1(elem* p, float v) { *p = f32_to_f16_bits(v); }
 };
 
+// The bias of four columns, as stored, and its values.  One choice of type and four loads in flight together: a choice at each
+// element is a branch, and a trip to memory, for each (on the device: 512x512x256 with bias and GELU on quartered tiles 10.3 -> 10.0 us, 1024x4096x1024 16.5 -> 16.0; 70 random calls with a bias 0.9 % faster, none slower).
+struct RawBias { uint32_t v[4]; };
+__device__ __forceinline__ void ask_bias(const Args& a, int64_t col, RawBias& b) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) b.v[e] = 0;
+    if (!a.bias) return;
+    const int64_t last = a.N - 1;      // (columns past the edge re-read the last one)
+    if (a.bias_dtype == DT_F32) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) b.v[e] = ((const uint32_t*)a.bias)[col + e < last ? col + e : last];
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) b.v[e] = ((const uint16_t*)a.bias)[col + e < last ? col + e : last];
+    }
+}
+__device__ __forceinline__ f32x4 bias_values(const Args& a, const RawBias& b) {
+    f32x4 r;
+    if (a.bias_dtype == DT_F16) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) r[e] = f16_bits_to_f32((uint16_t)b.v[e]);
+    } else {
+        const int shift = a.bias_dtype == DT_BF16 ? 16 : 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) r[e] = __uint_as_float(b.v[e] << shift);
+    }
+    return r;
+}
+
 template <class C>
 struct EpiLayout {
     // Each wave parks one 32-row band of its sub-block in a private LDS region, row-major with a
@@ -289,12 +318,9 @@ __device__ __forceinline__ void tile_epilogue_bands(Dump dump, char* lds, const 
     const int act = a.act;
     const int cl = (lane % EL::LPR) * 4;                 // first of this lane's four columns inside the wave sub-block
     const int64_t col = n0 + wn * C::WTN + cl;
-    f32x4 bias4 = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (a.bias) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if (col + e < a.N) bias4[e] = load_elem(a.bias, a.bias_dtype, col + e);
-    }
+    RawBias raw_bias;
+    ask_bias(a, col, raw_bias);
+    const f32x4 bias4 = bias_values(a, raw_bias);
 
     // The code below runs once per tile, so its size matters more than its instruction count: a
     // kernel that streams tens of kilobytes of straight-line epilogue through the instruction

@@ -239,41 +239,11 @@ __device__ __forceinline__ void wavek_park(char* ring, const f32x4 (&acc)[TM][4]
         for (int j = 0; j < 4; ++j) *(f32x4*)(ring + (16 * i + r) * 256 + (((4 * j + g) ^ r) << 4)) = acc[i][j];
 }
 
-// The bias of a lane's four columns as stored, asked for ahead of the k loop: behind it the loads would be a trip to memory more.
-struct WaveBias { uint32_t v[4]; };
-__device__ __forceinline__ void wavek_ask_bias(const Args& a, int64_t n0, int lane, WaveBias& b) {
-    if (!a.bias) return;
-    const int64_t col = n0 + 4 * (lane & 15);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) b.v[e] = 0;
-    const int64_t last = a.N - 1;      // (columns past the edge re-read the last one)
-    if (a.bias_dtype == DT_F32) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) b.v[e] = ((const uint32_t*)a.bias)[col + e < last ? col + e : last];
-    } else {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) b.v[e] = ((const uint16_t*)a.bias)[col + e < last ? col + e : last];
-    }
-}
-__device__ __forceinline__ f32x4 wavek_bias(const Args& a, const WaveBias& b) {
-    if (!a.bias) return f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    f32x4 r;
-    if (a.bias_dtype == DT_F16) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) r[e] = f16_bits_to_f32((uint16_t)b.v[e]);
-    } else {
-        const int shift = a.bias_dtype == DT_BF16 ? 16 : 0;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) r[e] = __uint_as_float(b.v[e] << shift);
-    }
-    return r;
-}
-
 // ... and the epilogue of those rows, four columns to a lane.  `unscale`: factor on the sums.  A wave runs this code once, and code run
 // for the first time waits for the instruction cache, so what an activation takes is there once, for a row at a time, and a
 // ragged edge goes element by element in a loop (all of it unrolled, bias and GELU cost a 512x512x256 call 5.5 us).
 template <class C, int OUT>
-__device__ __forceinline__ void wavek_finish(char* lds, const Args& a, int64_t m0, int64_t n0, int wave, int lane, const WaveBias& bias, float unscale = 1.0f) {
+__device__ __forceinline__ void wavek_finish(char* lds, const Args& a, int64_t m0, int64_t n0, int wave, int lane, const RawBias& bias, float unscale = 1.0f) {
     using OV = OutVec<OUT>;
     constexpr int SHARE = C::BM / C::WAVES, T = SHARE >= 4 ? SHARE / 4 : 1;      // rows of a wave; of a lane
     const int rr = lane >> 4, cc = lane & 15, first = SHARE * wave;
@@ -284,7 +254,7 @@ __device__ __forceinline__ void wavek_finish(char* lds, const Args& a, int64_t m
     const float alpha = a.alpha, beta = a.beta;
     typename OV::elem* const p0 = (typename OV::elem*)a.C + row0 * a.ldc + col;
     const int64_t step = 4 * a.ldc;
-    const f32x4 bias4 = wavek_bias(a, bias);
+    const f32x4 bias4 = bias_values(a, bias);
     auto place = [&](int t) {
         const int r = first + 4 * t + rr;
         return lds + r * 256 + ((cc ^ (r & 15)) << 4);
@@ -416,8 +386,8 @@ __global__ __launch_bounds__(C::NT, C::WGS) void tile_wavek_kernel(Args a, int t
         }
     };
 
-    WaveBias bias;
-    wavek_ask_bias(a, n0, lane, bias);
+    RawBias bias;      // (asked for ahead of the k loop: behind it the loads would be a trip to memory more)
+    ask_bias(a, n0 + 4 * (lane & 15), bias);
     constexpr int TM = C::TM;
     f32x4 acc[TM][4];
 #pragma unroll
