@@ -1,4 +1,4 @@
-"""ctypes binding of libgemm's C ABI (include/gemm.h): same names, argument marshalling only.
+"""Binding of libgemm's C ABI (include/gemm.h) on ctypes: same names, argument marshalling only.
 
 Every step of a GEMM call runs in the HIP kernels of libgemm.so.  There is no fallback: if the
 shared library is missing or does not load, the first use raises.
@@ -221,6 +221,21 @@ def gemm_roofline_class(batch: int, M: int, N: int, K: int, dtype: int, out_dtyp
 def gemm_variant_name(kernel: int, variant: int) -> Optional[str]:
     s = load_library().gemm_variant_name(kernel, variant)
     return s.decode() if s else None
+
+
+def _addresses(lib):
+    return tuple(ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in ("gemm_run", "gemm_run_noalloc", "gemm_run_batched"))
+
+
+# The same three functions without ctypes' conversions (csrc/pycall.c), where that small extension is built for this Python.  They
+# hand every call that is not made of plain ints and floats, and the first one, to the functions above.
+try:
+    from . import _pycall
+except ImportError:
+    _pycall = None
+if _pycall is not None:
+    _pycall.setup(globals(), gemm_epilogue_t, GemmError, (gemm_run, gemm_run_noalloc, gemm_run_batched), _addresses)
+    gemm_run, gemm_run_noalloc, gemm_run_batched = _pycall.gemm_run, _pycall.gemm_run_noalloc, _pycall.gemm_run_batched
 
 
 def make_epilogue(out_dtype: int, bias: int = 0, bias_dtype: int = GEMM_F32, act: int = GEMM_ACT_NONE) -> gemm_epilogue_t:

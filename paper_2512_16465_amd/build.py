@@ -8,7 +8,8 @@
 
 Objects go to paper_2512_16465_amd/_build/ (not tracked); the shared library lands next to
 this file so that it travels with the source tree.  Every build also compiles
-diagnostics/*.hip into libceilings.so, measuring aids that only bench.py loads.
+diagnostics/*.hip into libceilings.so, measuring aids that only bench.py loads, and csrc/pycall.c into the
+extension through which the binding makes its gemm_run calls.
 """
 from __future__ import annotations
 
@@ -17,6 +18,7 @@ import os
 import re
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -94,6 +96,18 @@ def build_diagnostics(force: bool = False) -> str:
     return DIAG_LIB
 
 
+def build_python_calls(force: bool = False) -> str:
+    """_pycall: the binding's gemm_run functions as vector calls (host code, the C compiler; needs Python's headers)."""
+    src = os.path.join(CSRC, "pycall.c")
+    lib = os.path.join(HERE, "_pycall" + sysconfig.get_config_var("EXT_SUFFIX"))
+    if force or not os.path.exists(lib) or os.path.getmtime(lib) < os.path.getmtime(src):
+        cmd = ["gcc", "-O2", "-Wall", "-shared", "-fPIC", "-I" + sysconfig.get_paths()["include"], src, "-o", lib]
+        p = subprocess.run(cmd, capture_output=True, text=True)
+        if p.returncode != 0:
+            raise RuntimeError(f"gcc failed: {' '.join(cmd)}\n{p.stderr}")
+    return lib
+
+
 def build_library(force: bool = False, jobs: int = 8, verbose: bool = True, defines=(), output: str = "") -> str:
     global OBJ, LIB, FLAGS
     if output:
@@ -130,4 +144,5 @@ if __name__ == "__main__":
     outp = next((argv[i + 1] for i, x in enumerate(argv) if x == "--output" and i + 1 < len(argv)), "")
     if not outp:
         print(build_diagnostics(force="--force" in argv))
+        print(build_python_calls(force="--force" in argv))
     print(build_library(force="--force" in argv or bool(defs), defines=defs, output=outp))
