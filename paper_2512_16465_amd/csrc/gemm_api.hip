@@ -793,7 +793,8 @@ int wave_any_rows(const Args& a, int slices, int num_cus) {
         const double time = t.fixed + t.per_round * (double)rounds + (rounds == 1 ? t.per_k_alone : t.per_k * (double)rounds) * t.layout[layout] * (double)a.K +
                             (double)(a.M * a.N * a.batch) * 2.0 / t.store_rate + (a.act != gemm::ACT_NONE ? t.activation : 0.0) +
                             (double)(a.N * a.K * a.batch) * 2.0 / t.weight_rate;
-        if (time < best) { best = time; rows = t.rows; }
+        // (7 % promised beyond what is resident at once: 2049x2051x2045 NN 54.4 against 53.2 us, 2279x1369x2125 48.2 against 42.7)
+        if (time < best * (rounds > 2 ? 0.93 : 1.0)) { best = time; rows = t.rows; }
     }
     return rows;
 }
