@@ -342,6 +342,31 @@ TileChoice choose_shared_k_tile(const Args& a, int num_cus) {
     return TileChoice{slices == 1 && a.K <= kShortK ? kSmallTileShortK : kSmallTileVariant, 0, slices, t_small};
 }
 
+// An fp32 call that a plan gives to the 64x64 tiles, in whatever slices, runs in one launch on the tiles whose eight waves divide the k
+// range, 32x32 (variant 20) or 16x32 (21), where those promise to be ahead (-1: neither).  Estimates in us, fitted to 240 random calls each (half
+// within 4 %, nine of ten within 12 %).  On 600 random calls (M, N to 4096, K to 6000, batches) the choice is 1.31 times as fast on average
+// (geometric; in hindsight the fastest of all 1.34) and more than 3 % slower on none: 268x228x3592 TN 69 -> 18 us, 64x460x1152 23.7 -> 7.6 (N no multiple of 8, so never cut in
+// slices), 512^3 10.5 -> 7.0, 64x168x2752 16.8 -> 12.6, 256^3 8.2 -> 7.2.  Two workgroups of 32x32 to a unit are resident at once; beyond, the 64x64 tile
+// stages half as many elements per product (1016x2352x868 39 us against 48), and few columns with a long k are faster in slices.
+int wave_f32_variant(const Args& a, int slices, int num_cus) {
+    const int64_t cus = num_cus > 0 ? num_cus : 256;
+    constexpr int64_t kTwoSlabs = 64;      // (up to here one launch takes as long as another: 39x588x64 6.6 us on either)
+    constexpr double kSlicedMargin = 0.8; // (f32_time has a margin of its own against slices; 207x1328x3164: 27 us in 8 slices, 35 here)
+    if (a.dtype != gemm::DT_F32 || a.K <= kTwoSlabs || ((a.M + 31) / 32) * ((a.N + 31) / 32) * a.batch > 2 * cus) return -1;
+    struct Tile { int variant, rows; double per_k_half, per_k, per_k_more, fixed, per_round, weight_rate, activation, rows_of_a, rows_of_b; };
+    static const Tile tiles[] = {{20, 32, 0.00462, 0.00998, 0.00957, 3.4, 0.37, 19e6, 0.3, 0.056, 0.017}, {21, 16, 0.00294, 0.00702, 0.00597, 2.66, 1.21, 17e6, 0.18, 0.086, 0.0}};
+    double best = slices > 1 ? kSlicedMargin * f32_time(a, false, slices, cus) : f32_time(a, false, 1, cus);
+    int variant = -1;
+    for (const Tile& t : tiles) {
+        const double wgs = (double)(((a.M + t.rows - 1) / t.rows) * ((a.N + 31) / 32) * a.batch) / (double)(2 * cus), rounds = wgs > 1.0 ? wgs : 1.0;
+        const double per_k = (wgs <= 0.5 ? t.per_k_half : t.per_k + t.per_k_more * (rounds - 1.0)) * (1.0 + (a.transA ? t.rows_of_a : 0.0) + (a.transB ? 0.0 : t.rows_of_b));
+        const double time = t.fixed + t.per_round * rounds + per_k * (double)a.K + (double)(a.M * a.N * a.batch) * 4.0 / 1.0e6 +
+                            (double)(a.N * a.K * a.batch) * 4.0 / t.weight_rate + (a.act != gemm::ACT_NONE ? t.activation : 0.0);
+        if (time < best) { best = time; variant = t.variant; }
+    }
+    return variant;
+}
+
 TileChoice choose_tile(const Args& a, int num_cus) {
     TileChoice c = choose_shared_k_tile(a, num_cus);
     const int64_t cus = num_cus > 0 ? num_cus : 256;
@@ -565,6 +590,7 @@ gemm_status_t launch_plan(const Workspace& ws, const Args& a, gemm_plan_t& plan,
         }
     } else if (plan.kernel == GEMM_KERNEL_MFMA_TILE) {
         gemm::TileSplit split{0, 1, nullptr};
+        const int wave_tile = plan.variant == kF32SmallTileVariant ? wave_f32_variant(a, plan.split_k, ws.h->num_cus) : -1;
         if (plan.split_k > 1) {
             const int64_t slabs = (K + 31) / 32;
             if (plan.split_k > slabs) plan.split_k = (int)slabs;
@@ -580,6 +606,10 @@ gemm_status_t launch_plan(const Workspace& ws, const Args& a, gemm_plan_t& plan,
             const gemm_status_t st = ws.ensure((size_t)plan.split_k * (size_t)M * (size_t)N * sizeof(float));
             if (st != GEMM_OK) return st;
             const Args p = slices_of(a, plan.split_k, slice_len, ws.ptr(), N);
+            if (wave_tile >= 0) {      // (one launch, no partial results; the workspace is there for the calls of this size that need it)
+                if (!allocate_only) e = gemm::launch_tile(a, wave_tile, kTileBandRows, split, stream);
+                return e == hipSuccess ? GEMM_OK : GEMM_ERR_HIP;
+            }
             if (!allocate_only) e = gemm::launch_tile(p, plan.variant, kTileBandRows, split, stream);
             if (!allocate_only && e == hipSuccess) e = gemm::launch_splitk_reduce(a, plan.split_k, ws.ptr(), stream);
         } else if (plan.split_k > 1) {
@@ -592,7 +622,7 @@ gemm_status_t launch_plan(const Workspace& ws, const Args& a, gemm_plan_t& plan,
             if (!allocate_only) e = gemm::launch_tile(a, plan.variant, kTileBandRows, split, stream);
             if (!allocate_only && e == hipSuccess) e = gemm::launch_tile_split_reduce(a, plan.variant, kTileBandRows, split, stream);
         } else if (!allocate_only) {
-            e = gemm::launch_tile(a, plan.variant, kTileBandRows, split, stream);
+            e = gemm::launch_tile(a, wave_tile >= 0 ? wave_tile : plan.variant, kTileBandRows, split, stream);
         }
     } else {
         const bool fold = a.out_dtype == gemm::DT_F32;

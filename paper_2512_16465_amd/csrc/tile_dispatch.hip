@@ -56,8 +56,9 @@ bool tile_supports(const Args& a) {
 // fixed out-of-range offset of 2 GiB - 16.
 bool tile_variant_supports(const Args& a, int variant) {
     if (variant < 0 || variant >= kNum) return false;
-    if ((kInfo[variant].kind == 4) != (a.dtype == DT_F32)) return false;
-    if (kInfo[variant].kind == 0 || kInfo[variant].kind == 4) return true;
+    const bool fp32 = kInfo[variant].kind == 4 || kInfo[variant].kind == 7;
+    if (fp32 != (a.dtype == DT_F32)) return false;
+    if (kInfo[variant].kind == 0 || fp32) return true;
     if (kInfo[variant].kind == 5 && !shortk_call_fits(a)) return false;
     const int64_t a_bytes = ((a.transA ? a.K : a.M) * a.lda) * 2, b_bytes = ((a.transB ? a.N : a.K) * a.ldb) * 2;
     return a_bytes < 0x7ffffff0ll && b_bytes < 0x7ffffff0ll;

@@ -12,7 +12,7 @@ from gpu_harness import BatchedDeviceProblem, DeviceProblem, check_full, expecte
 pytestmark = pytest.mark.gpu
 
 TILE = lg.GEMM_KERNEL_MFMA_TILE
-WAVE = {n: v for v in range(64) if (n := lg.gemm_variant_name(TILE, v) or "").startswith("wavek")}
+WAVE = {n: v for v in range(64) if (n := lg.gemm_variant_name(TILE, v) or "").startswith("wavek_")}
 
 
 @pytest.fixture(scope="module")
@@ -109,3 +109,65 @@ def test_off_the_grid(handle, ta, tb, M, N, K):
             assert np.array_equal(c_bits_as_uint(cfg, p.result_bits()), want)
         finally:
             lg.gemm_set_plan(handle)
+
+
+WAVE_F32 = {n: v for v in range(64) if (n := lg.gemm_variant_name(TILE, v) or "").endswith("_wk8")}
+
+
+@pytest.mark.parametrize("name", sorted(WAVE_F32))
+@pytest.mark.parametrize("ta,tb", [(0, 1), (0, 0), (1, 1), (1, 0)])
+@pytest.mark.parametrize("K", [4, 32, 36, 100, 256, 324, 1000])
+def test_fp32_edges_of_tiles_and_of_the_k_range(handle, name, ta, tb, K):
+    for M, N in [(32, 32), (36, 68), (4, 8), (16, 100)] + ([] if ta else [(1, 36), (33, 32), (17, 64)]) + ([(32, 33), (16, 31)] if tb else []):
+        cfg = wl.Config("w", M, N, K, ta, tb, wl.F32, wl.F32, lda=(M if ta else K) + 4, ldb=(K if tb else N) + 4 + (0 if tb else -N % 4), ldc=N + 3)
+        inp, _ = wl.make_integer_inputs(cfg, 40 + K, -5, 5)
+        got, plan = run(handle, cfg, inp, (TILE, WAVE_F32[name], 1))
+        assert plan == (TILE, WAVE_F32[name], 1)
+        assert np.array_equal(c_bits_as_uint(cfg, got), c_bits_as_uint(cfg, expected_bits_exact(cfg, inp).reshape(M, N))), (M, N, K)
+        assert np.all(np.isnan(oracle.decode(wl.F32, np.ascontiguousarray(got[:-1, N:]))))
+
+
+@pytest.mark.parametrize("name", sorted(WAVE_F32) + ["f32_64x64x32_w2x2"])
+@pytest.mark.parametrize("M,N,K,tb,batch", [(45, 75, 333, 1, 1), (83, 100, 520, 0, 1), (1100, 1060, 72, 0, 1), (20, 44, 100, 0, 5)])
+def test_fp32_epilogues_batches_and_grids_that_stay_on_the_64x64_tile(handle, name, M, N, K, tb, batch):
+    K = K // 4 * 4
+    variant = next(v for v in range(64) if lg.gemm_variant_name(TILE, v) == name)
+    for act, bias_dtype, beta in [(wl.ACT_SILU, wl.F32, 1.0), (wl.ACT_NONE, wl.F32, 0.0)]:
+        cfg = wl.Config("w", M, N, K, 0, tb, wl.F32, wl.F32, alpha=0.75, beta=beta, a_dist=("normal", 1.0), b_dist=("normal", 0.05),
+                        c_dist=("normal", 1.0), bias_dist=("normal", 0.1) if batch == 1 else None, bias_dtype=bias_dtype, act=act, ldc=N + 5)
+        if batch > 1:
+            lg.gemm_set_plan(handle, TILE, variant, 1)
+            try:
+                p = BatchedDeviceProblem(cfg, batch, cfg.stride_a() + 4, cfg.stride_b(), cfg.stride_c() + 3, seed=5)
+                p.run(handle)
+                p.check(name)
+            finally:
+                lg.gemm_set_plan(handle)
+            continue
+        inp = wl.make_inputs(cfg, 9)
+        got, _ = run(handle, cfg, inp, (TILE, variant, 1))
+        check_full(cfg, inp, got, f"{name} act={act}")
+
+
+@pytest.mark.parametrize("name", sorted(WAVE_F32))
+@pytest.mark.parametrize("ta,tb", [(0, 1), (1, 0)])
+def test_fp32_values_outside_the_split(handle, name, ta, tb):
+    """Products and sums beyond the scaled range, infinities and NaN, in the share of one wave only or of all: computed again on the fp32
+    instruction.  Exact integers times powers of two, one right answer."""
+    rng = np.random.default_rng(3)
+    M, N, K = 36, 40, 300
+    a, b = rng.integers(-7, 8, (M, K)).astype(np.float64), rng.integers(-3, 4, (K, N)).astype(np.float64)
+    a[1] *= 2.0 ** 100
+    a[2, 70] = np.inf
+    a[3, K - 1] = np.nan
+    a[4] = rng.integers(-7, 8, K) * 2.0 ** -149
+    a[M - 1, :32] *= 2.0 ** 90
+    b[:, 1] *= 2.0 ** 12
+    A, B = (np.ascontiguousarray(x, dtype=np.float32) for x in (a.T if ta else a, b.T if tb else b))
+    cfg = wl.Config("w", M, N, K, ta, tb, wl.F32, wl.F32)
+    inp = {"A": wl.to_bits(A.reshape(-1), wl.F32), "B": wl.to_bits(B.reshape(-1), wl.F32), "C": None, "bias": None}
+    with np.errstate(invalid="ignore"):
+        want = oracle.decode(wl.F32, expected_bits_exact(cfg, inp)).reshape(M, N)
+    got, _ = run(handle, cfg, inp, (TILE, WAVE_F32[name], 1))
+    got = oracle.decode(wl.F32, np.ascontiguousarray(got[:, :N]))
+    assert np.array_equal(got, want, equal_nan=True), np.argwhere(~((got == want) | (np.isnan(got) & np.isnan(want))))[:4]

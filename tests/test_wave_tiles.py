@@ -6,7 +6,7 @@ import os
 import numpy as np
 import pytest
 
-from asm_inflight import check_listing, check_wide_store_data
+from asm_inflight import check_listing
 
 LANES = np.arange(64)
 
@@ -114,14 +114,61 @@ def test_loads_off_the_grid_stay_inside_and_land_in_place(kc, rows, K):
                         assert lds[place // 2] == want, (total, first, slab, row, k)
 
 
+def f32_mc_row(rows, q):
+    position = q * (256 // rows) + LANES // (rows // 4)
+    return position, 8 * (position & 3) + (position >> 2)
+
+
+def f32_loads(kc, rows, valid, ld, K, slab):
+    """(element in the operand, LDS dword, fetched) of every lane's 16 bytes of one fp32 slab."""
+    k_left = K - slab * 32
+    for q in range(rows // 8):
+        if kc:
+            row = 8 * q + (LANES >> 3)
+            k = ((LANES & 7) ^ kc_hash(row)) * 4
+            off = np.minimum(row, valid - 1) * ld + slab * 32 + k
+        else:
+            position, k = f32_mc_row(rows, q)
+            c = (LANES % (rows // 4)) ^ (((position & 2) << 1) if rows == 32 else 0)
+            off = (slab * 32 + k) * ld + np.where(c * 4 + 4 <= valid, c * 4, valid - 4)
+        yield off, q * 256 + LANES * 4, k < k_left
+
+
+@pytest.mark.parametrize("kc", [True, False])
+@pytest.mark.parametrize("rows", [16, 32])
+@pytest.mark.parametrize("K", [4, 32, 36, 100])
+def test_fp32_loads_stay_inside_and_the_fragments_find_their_elements(kc, rows, K):
+    for valid in (4, 12, 16, 28, 32) if not kc else (1, 7, 16, 31, 32):
+        if valid > rows:
+            continue
+        ld = (K if kc else valid) + 4
+        n = (valid - 1) * ld + K if kc else (K - 1) * ld + valid
+        for slab in range((K + 31) // 32):
+            lds = np.full(rows * 32, -1, np.int64)
+            for off, at, fetched in f32_loads(kc, rows, valid, ld, K, slab):
+                assert np.all(off[fetched] >= 0) and np.all(off[fetched] + 4 <= n)
+                for o, a, f in zip(off, at, fetched):
+                    lds[a: a + 4] = np.arange(4) + o if f else -1
+            r, g = LANES & 15, LANES >> 4
+            for tile in range(rows // 16):
+                for e in range(8):
+                    if kc:
+                        byte = tile * 2048 + r * 128 + (((2 * g + e // 4) ^ kc_hash(r)) << 4) + e % 4 * 4
+                    else:
+                        byte = g * rows * 4 + (((tile ^ (g >> 1)) << 6) if rows == 32 else 0) + r * 4 + e * (rows * 4 // 64) * 256
+                    k, row = slab * 32 + 8 * g + e, 16 * tile + r
+                    got = lds[byte // 4]
+                    inside = (row < valid) & (k < K)
+                    assert np.array_equal(got[inside], (row * ld + k if kc else k * ld + row)[inside])
+                    assert np.all(got[k >= K] == -1)
+
+
 def test_no_fragment_register_is_touched_before_its_wait(tmp_path):
     from paper_2512_16465_amd import build
     if not os.path.exists(build.HIPCC):
         pytest.skip("no hipcc")
-    for unit, kernels in (("tile_variant_18", 8), ("tile_variant_19", 4), ("tile_wave_any", 12)):
+    for unit, kernels in (("tile_variant_18", 8), ("tile_variant_19", 4), ("tile_wave_any", 12), ("tile_variant_20", 4), ("tile_variant_21", 4)):
         path = build.device_assembly(unit + ".hip", str(tmp_path / (unit + ".s")))
         with open(path) as f:
-            n, found = check_listing(f, only="tile_wavek_kernel")
+            n, found = check_listing(f, only="tile_wavek")
         assert n == kernels and not found, (n, found[:1])
-        with open(path) as f:
-            assert not check_wide_store_data(f)
