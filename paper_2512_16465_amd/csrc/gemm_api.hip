@@ -367,6 +367,51 @@ int wave_f32_variant(const Args& a, int slices, int num_cus) {
     return variant;
 }
 
+// Few rows whose plan is the narrow streaming kernel (one launch), a wide streaming kernel in slices or the quartered tile in
+// shares run, in one launch, on the 16x64 or 64x64 tile whose waves divide the k range, where that is ahead (-1: it isn't): a workgroup of it
+// reads 64 columns of the weight once, where the narrow kernel's has 16 (four times as many workgroups, the first products 5 us after the
+// launch) and slices and shares need a second launch.  A unit streams about 30 GB/s from memory however many waves ask, so what leaves units idle or
+// has more than one workgroup to a unit is left where it is, and so is K beyond 8192 (NN 5000), where four waves' walk is the longer one.  A
+// row-major weight with a pitch of whole 512 bytes is too: the k-rows of a slab fall on few memory channels (31x2560x4864 18.8 us here, 15 in shares).
+// - streaming kernels in slices, up to 16 rows: from 200 workgroups on, always (30 random calls, 1.13 to 1.20 times as fast on average; 7 % ahead at
+//   the least up to K = 7000: 16x16384x4096 NN 32.4 -> 29, 8x15296x5184 NN 35.7 -> 27.5, 12x12288x4096 NT 24.8 -> 24).
+// - the others by estimates in us, fitted to 423 random calls with 16-row tiles and 514 with 64-row tiles (half within 5 to 7 %, nine of ten within 11 to
+//   17 %), by a margin of 5 %.  On such calls 1.17 to 1.18 times as fast on average with 16 rows (the faster one in hindsight 1.18 to 1.19) and 1.06 to 1.10 with
+//   64: 12x8192x2048 12 -> 8, 7x9920x2176 15.9 -> 9.6, 46x8128x2944 NN 18.1 -> 13.3, 61x2624x4480 NN 16.2 -> 11; with fewer than 64 workgroups of
+//   a long k or a row-major weight a unit's own rate shows (26x3304x4544 NN 15.3 against 13.1).  Of 450 other random calls whose route this changed (1.25 times
+//   as fast on average) seven were more than 4 % slower, 12 % the worst (16x6696x4112).
+int few_rows_wave_tile(const Args& a, const gemm_plan_t& plan) {
+    constexpr int kQuarter = 16, kNarrow = 5, kWideRowMajor = 0, kWide = 1, kFewRows = 19, kManyRows = 18;
+    if (a.transA || a.batch != 1 || a.M > 64 || a.K > (a.transB ? 8192 : 5000 + 3192 * (plan.kernel == GEMM_KERNEL_SKINNY))) return -1;
+    if (a.dtype == gemm::DT_F32 || !gemm::tile_supports(a) || !gemm::tile_variant_supports(a, kManyRows)) return -1;
+    const int64_t columns = (a.N + 63) / 64, tiles = ((a.M + 15) / 16) * columns;
+    const bool pitch = !a.transB && a.ldb % 256 == 0;
+    const double weight = (double)(a.N * a.K) * 2e-6, k = (double)a.K;
+    if (plan.kernel == GEMM_KERNEL_SKINNY && (plan.variant == kWideRowMajor || plan.variant == kWide))
+        return plan.split_k > 1 && a.M <= 16 && tiles >= 200 && tiles <= 256 && a.K <= 7000 && !(pitch && a.K >= 5000) ? kFewRows : -1;
+    const bool narrow = plan.kernel == GEMM_KERNEL_SKINNY;
+    if (narrow ? plan.variant != kNarrow || plan.split_k != 1 || !a.transB : plan.variant != kQuarter || plan.split_k == 1) return -1;
+    if (pitch && a.K >= 3000) return -1;
+    const int straddling = (a.K % 64 != 0) + ((a.transB ? a.K : a.N) % 64 != 0);      // operands whose 128-byte pieces lie in two lines
+    const double beyond = weight > 30.0 ? weight - 30.0 : 0.0, uncached = weight > 72.0 ? weight - 72.0 : 0.0;
+    const double partial = (double)(a.M * a.N * plan.split_k) * 8e-6;
+    double time, wave;
+    if (tiles >= (a.transB && (!narrow || a.K <= 4096) ? 48 : 64) && tiles <= 256 && weight <= 100.0) {
+        const double grid = (double)tiles / 256.0;
+        time = narrow ? 4.96 + 0.00072 * k + 0.0311 * weight + 0.0776 * beyond + 6.98 * grid
+               : a.transB ? 10.3 + 0.00051 * k + 0.119 * beyond + 1.78 * grid + 0.109 * partial
+                          : 11.7 + 0.00027 * k + 0.159 * beyond + 0.276 * partial;
+        wave = a.transB ? 2.94 + 0.00143 * k * (1.0 + 0.25 * straddling) + 0.2 * uncached + 4.41 * grid
+                        : 3.10 + 0.00159 * k * (1.0 + 0.28 * straddling) + 0.2 * uncached + 2.09 * grid;
+        return wave < 0.95 * time ? kFewRows : -1;
+    }
+    if (a.M <= 16 || columns < 80 || columns > 256 || weight > 130.0) return -1;
+    const double grid = (double)columns / 256.0;
+    time = a.transB ? 10.7 + 3.3 * grid + 0.232 * partial + 0.234 * beyond : 12.1 + 1.2 * grid + 0.164 * partial + 0.209 * beyond;
+    wave = a.transB ? 4.3 + 0.00275 * k * (1.0 + 0.2 * straddling) + 0.25 * uncached + 0.5 * grid : 5.0 + 0.00272 * k * (1.0 + 0.19 * straddling) + 0.226 * uncached;
+    return wave < 0.93 * time ? kManyRows : -1;
+}
+
 TileChoice choose_tile(const Args& a, int num_cus) {
     TileChoice c = choose_shared_k_tile(a, num_cus);
     const int64_t cus = num_cus > 0 ? num_cus : 256;
@@ -579,6 +624,11 @@ gemm_status_t launch_plan(const Workspace& ws, const Args& a, gemm_plan_t& plan,
             const gemm_status_t st = ws.ensure(need);
             if (st != GEMM_OK) return st;
         }
+        const int wave_tile = few_rows_wave_tile(a, plan);
+        if (wave_tile >= 0) {
+            if (!allocate_only) e = gemm::launch_tile(a, wave_tile, kTileBandRows, gemm::TileSplit{0, 1, nullptr}, stream);
+            return e == hipSuccess ? GEMM_OK : GEMM_ERR_HIP;
+        }
         // one matrix per launch (the slices of a split share the workspace, in stream order)
         Args one = a;
         one.batch = 1;
@@ -618,6 +668,11 @@ gemm_status_t launch_plan(const Workspace& ws, const Args& a, gemm_plan_t& plan,
             const size_t need = (size_t)(tiles - split_first) * plan.split_k * info->BM * info->BN * sizeof(float);
             const gemm_status_t st = ws.ensure(need);
             if (st != GEMM_OK) return st;
+            const int few_rows = split_first == 0 ? few_rows_wave_tile(a, plan) : -1;
+            if (few_rows >= 0) {
+                if (!allocate_only) e = gemm::launch_tile(a, few_rows, kTileBandRows, gemm::TileSplit{0, 1, nullptr}, stream);
+                return e == hipSuccess ? GEMM_OK : GEMM_ERR_HIP;
+            }
             split = gemm::TileSplit{split_first, plan.split_k, ws.ptr()};
             if (!allocate_only) e = gemm::launch_tile(a, plan.variant, kTileBandRows, split, stream);
             if (!allocate_only && e == hipSuccess) e = gemm::launch_tile_split_reduce(a, plan.variant, kTileBandRows, split, stream);

@@ -171,3 +171,19 @@ def test_fp32_values_outside_the_split(handle, name, ta, tb):
     got, _ = run(handle, cfg, inp, (TILE, WAVE_F32[name], 1))
     got = oracle.decode(wl.F32, np.ascontiguousarray(got[:, :N]))
     assert np.array_equal(got, want, equal_nan=True), np.argwhere(~((got == want) | (np.isnan(got) & np.isnan(want))))[:4]
+
+
+SKINNY = lg.GEMM_KERNEL_SKINNY
+
+
+@pytest.mark.parametrize("plan,M,N,K,tb", [((SKINNY, 5, 1), 7, 4200, 520, 1), ((SKINNY, 5, 1), 16, 4093, 264, 1), ((SKINNY, 0, 2), 5, 12872, 264, 0),
+                                           ((SKINNY, 1, 2), 16, 13000, 328, 1), ((TILE, 16, 2), 40, 8200, 520, 1), ((TILE, 16, 2), 33, 5208, 328, 0),
+                                           ((TILE, 16, 2), 20, 2184, 1032, 0), ((TILE, 16, 3), 16, 4200, 520, 0)])
+def test_few_rows_whose_plan_runs_on_a_wave_tile(handle, plan, M, N, K, tb):
+    for dtype, out, act, bias_dtype, beta in [(wl.BF16, wl.F32, wl.ACT_NONE, wl.BF16, 1.0), (wl.F16, wl.F16, wl.ACT_GELU_ERF, wl.F32, 0.0)]:
+        cfg = wl.Config("w", M, N, K, 0, tb, dtype, out, alpha=0.5, beta=beta, a_dist=("normal", 1.0), b_dist=("normal", 0.05), c_dist=("normal", 1.0),
+                        bias_dist=("normal", 0.1), bias_dtype=bias_dtype, act=act, ldb=(K if tb else (N + 7) // 8 * 8) + 8, ldc=N + 3)
+        inp = wl.make_inputs(cfg, 21)
+        got, ran = run(handle, cfg, inp, plan)
+        assert ran == plan
+        check_full(cfg, inp, got, f"{plan} {M}x{N}x{K}")
