@@ -187,3 +187,14 @@ def test_few_rows_whose_plan_runs_on_a_wave_tile(handle, plan, M, N, K, tb):
         got, ran = run(handle, cfg, inp, plan)
         assert ran == plan
         check_full(cfg, inp, got, f"{plan} {M}x{N}x{K}")
+
+
+@pytest.mark.parametrize("K", [1272, 1280, 1304])
+def test_whole_128x128_tiles_of_a_long_k(handle, K):
+    M, N = 2085, 1051      # beyond two rounds of wave tiles, ragged on both sides
+    cfg = wl.Config("w", M, N, K, 0, 1, wl.BF16, wl.F32, lda=K + 8, ldb=K + 16, ldc=N + 3)
+    inp, _ = wl.make_integer_inputs(cfg, 77 + K, -5, 5)
+    got, plan = run(handle, cfg, inp, (TILE, 5, 1))
+    assert plan == (TILE, 5, 1)
+    assert np.array_equal(c_bits_as_uint(cfg, got), c_bits_as_uint(cfg, expected_bits_exact(cfg, inp).reshape(M, N)))
+    assert np.all(np.isnan(oracle.decode(wl.F32, np.ascontiguousarray(got[:-1, N:]))))
