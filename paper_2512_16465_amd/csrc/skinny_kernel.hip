@@ -44,6 +44,8 @@ constexpr int64_t SK_NARROW_BYTES = (int64_t)128 << 20, SK_NARROW_MAX_N = 4096, 
 // With 9 to 16 rows the partly filled last round shows: 16 x 5120 x 5120 18.2 against 15.4 on split tiles (320 workgroups
 // on 512 places), 16 x 9216 x 4608 22.7 against 20.1 (576 on 1024), but 16 x 11008 x 4096 22.0 against 23.3 (688 on 1024):
 // then the places must be 65 % full.  The places are those of a 256-unit part.
+// (Between 48 and 256 workgroups of 64 columns the call is launched on a tile whose waves divide k where that is ahead:
+// few_rows_wave_tile.)
 constexpr int64_t SK_NARROW_FAR_N = 12288, SK_NARROW_FAR_K = 1024, SK_NARROW_PLACES = 512;
 constexpr uint32_t SK_MASKED = 0x7ffffff0u;   // an offset past the end of any operand: the load returns zero
 

@@ -83,16 +83,16 @@ struct WaveKC {
 // block) are served together and fall on distinct places: two rows per 256-byte bank line, bits 1 and 3 of k spread the others.
 template <int ROWS>
 struct WaveMC {
-    static constexpr int SUBS = ROWS / 64, L = 8 * SUBS;      // 64 columns each, one sub-slab behind the other
-    static_assert(ROWS % 64 == 0, "whole lines of a k-row");
+    static constexpr int L = 8;
+    static_assert(ROWS == 64, "a whole line of a k-row");
     static __device__ __forceinline__ uint32_t swizzle(uint32_t k) { return (k & 2u) | (((k >> 3) & 1u) << 2); }
     uint32_t voff[L];
     __device__ __forceinline__ void init(int lane, int64_t ld, int valid_rows) {
         const uint32_t ld_bytes = (uint32_t)ld * 2;
 #pragma unroll
         for (int q = 0; q < L; ++q) {
-            const uint32_t k = 8 * (q % 8) + (lane >> 3);
-            const uint32_t c = ((uint32_t)(lane & 7) ^ swizzle(k)) + 8 * (q / 8);
+            const uint32_t k = 8 * q + (lane >> 3);
+            const uint32_t c = (uint32_t)(lane & 7) ^ swizzle(k);
             const uint32_t c8 = (int)(c * 8 + 8) <= valid_rows ? c * 8 : (uint32_t)(valid_rows - 8);      // past the edge: the last valid chunk, never stored
             voff[q] = k * ld_bytes + c8 * 2;
         }
@@ -100,7 +100,7 @@ struct WaveMC {
     __device__ __forceinline__ void mask(int lane, int k_left) {
 #pragma unroll
         for (int q = 0; q < L; ++q)
-            if (8 * (q % 8) + (lane >> 3) >= k_left) voff[q] = 0x7ffffff0u;
+            if (8 * q + (lane >> 3) >= k_left) voff[q] = 0x7ffffff0u;
     }
     static __device__ __forceinline__ const char* tile_base(const void* p, int64_t first_row, int64_t /*ld*/) { return (const char*)p + first_row * 2; }
     static __device__ __forceinline__ int64_t k_step_bytes(int64_t ld) { return 128 * ld; }
@@ -115,8 +115,8 @@ struct WaveMC {
     }
     template <int TILE, int KS>
     static __device__ __forceinline__ void read(const uint32_t (&addr)[ADDRESSES], uint32_t slab, Raw& r) {
-        asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(r.lo) : "v"(addr[TILE % 4] + slab), "n"(TILE / 4 * 8192 + KS * 4096));
-        asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(r.hi) : "v"(addr[TILE % 4] + slab), "n"(TILE / 4 * 8192 + KS * 4096 + 512));
+        asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(r.lo) : "v"(addr[TILE] + slab), "n"(KS * 4096));
+        asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(r.hi) : "v"(addr[TILE] + slab), "n"(KS * 4096 + 512));
     }
 };
 
