@@ -245,6 +245,11 @@ typedef struct {
                              * second kernel; this needs N to be a multiple of 8.  Batched calls, and
                              * calls that miss that condition, return GEMM_ERR_UNSUPPORTED.  Slices
                              * are added in a fixed order: results do not vary from run to run. */
+    /* Several plans are run in one launch on tiles whose waves divide the k range, or on another pipeline of the same tile, for
+     * the sizes at which that is faster, whatever their slices, automatic or forced: the whole 128x128 tiles (variants 5 and
+     * 12), the fp32 64x64 tiles (13), the 128x128 tiles in shares (16) and the streaming variants 0, 1 and 5 with up to 64
+     * rows, and the general family's variant 1.  The plan, its errors and the workspace it asks for stay as described; a plan
+     * and a shape always give the same bits. */
 } gemm_plan_t;
 
 /* Forces the plan used by later gemm_run calls on this handle; a NULL plan restores automatic
