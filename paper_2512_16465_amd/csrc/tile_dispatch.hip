@@ -116,6 +116,11 @@ int wave_tile_for(const Args& a, int64_t cus, double* estimate) {
 // 1648x1872x6224 80.8 -> 68, 2120x1376x3304 53.7 -> 44; 6 % slower on one of 58), 1.02 for K 512 to 768, 1.02 to 1.04 with a
 // row-major B (two of 32 4 % slower), 0.94 to 0.97 with A stored KxM.
 constexpr int64_t kLongK = 1280;
+// Up to 64 columns to a matrix the 128x128 tile is at least half empty, and the 64x64 wave tile is ahead at any number of tiles, with A row-major
+// and K from 768 on: 17 random calls, batches of attention's second product most of them, 1.09 times as fast on average (1160x64x1160 NN, batch of
+// 57, 59.4 -> 46.2 us, 1512x64x1512 NT, 26, 39.6 -> 32.2, 1864x64x1864 NN, 29, 65.4 -> 57.4; 2 % behind on one).  With A stored KxM 0.91 to 1.1, with a shorter k
+// 0.88 to 1.2.
+constexpr int64_t kNarrowK = 768;
 
 hipError_t launch_tile(const Args& a, int variant, int group_m, const TileSplit& split, hipStream_t stream) {
     if (variant < 0 || variant >= kNum) return hipErrorInvalidValue;
@@ -123,6 +128,7 @@ hipError_t launch_tile(const Args& a, int variant, int group_m, const TileSplit&
     if ((variant == 5 || variant == 12) && a.k_total == 0) {
         const int wave_tile = wave_tile_for(a, 256, nullptr);
         if (wave_tile >= 0) variant = wave_tile;
+        else if (variant == 5 && !a.transA && a.N <= 64 && a.K >= kNarrowK && tile_variant_supports(a, 18)) variant = 18;
         else if (!a.transA && a.transB && a.K >= kLongK && tile_variant_supports(a, 16)) variant = 16;
     }
     if (variant == 19 && a.transA) variant = 18;      // (a k-row of A is moved in whole lines: 64 rows to a tile)

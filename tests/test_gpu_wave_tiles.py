@@ -198,3 +198,17 @@ def test_whole_128x128_tiles_of_a_long_k(handle, K):
     assert plan == (TILE, 5, 1)
     assert np.array_equal(c_bits_as_uint(cfg, got), c_bits_as_uint(cfg, expected_bits_exact(cfg, inp).reshape(M, N)))
     assert np.all(np.isnan(oracle.decode(wl.F32, np.ascontiguousarray(got[:-1, N:]))))
+
+
+@pytest.mark.parametrize("K,N,tb", [(760, 64, 0), (768, 64, 0), (776, 48, 0), (776, 37, 1)])
+def test_batches_of_up_to_64_columns_beyond_two_rounds(handle, K, N, tb):
+    M, batch = 1093, 31
+    cfg = wl.Config("w", M, N, K, 0, tb, wl.BF16, wl.BF16, a_dist=("normal", 1.0), b_dist=("normal", 0.05), c_dist=("normal", 1.0), beta=0.5)
+    lg.gemm_set_plan(handle, TILE, 5, 1)
+    try:
+        p = BatchedDeviceProblem(cfg, batch, cfg.stride_a(), cfg.stride_b() + 8, cfg.stride_c() + 3, seed=5)
+        p.run(handle)
+        assert lg.gemm_get_last_plan(handle) == (TILE, 5, 1)
+        p.check("narrow batch")
+    finally:
+        lg.gemm_set_plan(handle)
