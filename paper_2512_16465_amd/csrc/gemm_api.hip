@@ -378,7 +378,8 @@ int wave_f32_variant(const Args& a, int slices, int num_cus) {
 // - the others by estimates in us, fitted to 423 random calls with 16-row tiles and 514 with 64-row tiles (half within 5 to 7 %, nine of ten within 11 to
 //   17 %), by a margin of 5 %.  On such calls 1.17 to 1.18 times as fast on average with 16 rows (the faster one in hindsight 1.18 to 1.19) and 1.06 to 1.10 with
 //   64: 12x8192x2048 12 -> 8, 7x9920x2176 15.9 -> 9.6, 46x8128x2944 NN 18.1 -> 13.3, 61x2624x4480 NN 16.2 -> 11; with fewer than 64 workgroups of
-//   a long k or a row-major weight a unit's own rate shows (26x3304x4544 NN 15.3 against 13.1).  Of 450 other random calls whose route this changed (1.25 times
+//   a long k or a row-major weight a unit's own rate shows (26x3304x4544 NN 15.3 against 13.1, 5x5120x5120 NT
+//   19.1 against 17.8 on 80).  Of 450 other random calls whose route this changed (1.25 times
 //   as fast on average) seven were more than 4 % slower, 12 % the worst (16x6696x4112).
 int few_rows_wave_tile(const Args& a, const gemm_plan_t& plan) {
     constexpr int kQuarter = 16, kNarrow = 5, kWideRowMajor = 0, kWide = 1, kFewRows = 19, kManyRows = 18;
@@ -396,7 +397,7 @@ int few_rows_wave_tile(const Args& a, const gemm_plan_t& plan) {
     const double beyond = weight > 30.0 ? weight - 30.0 : 0.0, uncached = weight > 72.0 ? weight - 72.0 : 0.0;
     const double partial = (double)(a.M * a.N * plan.split_k) * 8e-6;
     double time, wave;
-    if (tiles >= (a.transB && (!narrow || a.K <= 4096) ? 48 : 64) && tiles <= 256 && weight <= 100.0) {
+    if (tiles >= (a.K > 4096 && a.transB && columns < 96 ? 96 : a.transB ? 48 : 64) && tiles <= 256 && weight <= 100.0) {
         const double grid = (double)tiles / 256.0;
         time = narrow ? 4.96 + 0.00072 * k + 0.0311 * weight + 0.0776 * beyond + 6.98 * grid
                : a.transB ? 10.3 + 0.00051 * k + 0.119 * beyond + 1.78 * grid + 0.109 * partial
