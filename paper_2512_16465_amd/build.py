@@ -16,6 +16,7 @@ from __future__ import annotations
 import concurrent.futures as cf
 import os
 import re
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -97,11 +98,16 @@ def build_diagnostics(force: bool = False) -> str:
 
 
 def build_python_calls(force: bool = False) -> str:
-    """_pycall: the binding's gemm_run functions as vector calls (host code, the C compiler; needs Python's headers)."""
+    """_pycall: the binding's gemm_run functions as vector calls (host code).  The binding does without it, so a host that lacks the C
+    compiler or Python's headers gets a note and "" here; a compile error is an error."""
     src = os.path.join(CSRC, "pycall.c")
     lib = os.path.join(HERE, "_pycall" + sysconfig.get_config_var("EXT_SUFFIX"))
     if force or not os.path.exists(lib) or os.path.getmtime(lib) < os.path.getmtime(src):
-        cmd = ["gcc", "-O2", "-Wall", "-shared", "-fPIC", "-I" + sysconfig.get_paths()["include"], src, "-o", lib]
+        gcc, include = shutil.which("gcc"), sysconfig.get_paths()["include"]
+        if not gcc or not os.path.exists(os.path.join(include, "Python.h")):
+            print("_pycall not built (no %s): the binding makes its calls through ctypes" % ("gcc" if not gcc else include + "/Python.h"))
+            return ""
+        cmd = [gcc, "-O2", "-Wall", "-shared", "-fPIC", "-I" + include, src, "-o", lib]
         p = subprocess.run(cmd, capture_output=True, text=True)
         if p.returncode != 0:
             raise RuntimeError(f"gcc failed: {' '.join(cmd)}\n{p.stderr}")
@@ -142,7 +148,7 @@ if __name__ == "__main__":
     argv = sys.argv[1:]
     defs = [argv[i + 1] for i, x in enumerate(argv) if x == "--define" and i + 1 < len(argv)]
     outp = next((argv[i + 1] for i, x in enumerate(argv) if x == "--output" and i + 1 < len(argv)), "")
+    print(build_library(force="--force" in argv or bool(defs), defines=defs, output=outp))
     if not outp:
         print(build_diagnostics(force="--force" in argv))
         print(build_python_calls(force="--force" in argv))
-    print(build_library(force="--force" in argv or bool(defs), defines=defs, output=outp))
