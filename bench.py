@@ -382,7 +382,7 @@ def main():
         res = Resident(cfg, seed, copies=2 if bound == "hbm" and cfg.algorithmic_bytes() > (64 << 20) else 1)
         ok = None if args.no_verify else quick_verify(res, lg, handle)
         wall_ms, ev_mean, ev_min, ev_std, warm_done = time_config(lg, handle, res, args.steps, args.warmup, args.settle_ms)
-        kernel, variant, split = lg.gemm_get_last_plan(handle)
+        kernel, variant, split = lg.gemm_get_last_launch(handle)
         kname = lg.gemm_variant_name(kernel, variant)
         tflops = cfg.flops() / (wall_ms * 1e-3) / 1e12
         gbps = cfg.algorithmic_bytes() / (wall_ms * 1e-3) / 1e9

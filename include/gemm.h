@@ -214,8 +214,9 @@ typedef enum {
     GEMM_KERNEL_AUTO = 0,      /* let the library choose (default) */
     GEMM_KERNEL_GENERAL = 1,   /* any shape and alignment.  Variant 0: one thread per output element.  Variant 1 (bf16 / fp16):
                                   128x128 MFMA tiles, with folded sums where C is fp32; variant 2 (fp32): 64x64 fp32
-                                  tiles with folded sums.  A forced variant that
-                                  cannot serve the call (and -1) falls back to 0 */
+                                  tiles with folded sums; variants 3 and 4 (bf16 / fp16): 64x64 and 16x64 tiles whose waves
+                                  divide the k range, in one launch (K >= 8 where k is contiguous; 4 for a row-major A).  A
+                                  forced variant that cannot serve the call (and -1) falls back to 0 */
     GEMM_KERNEL_MFMA_TILE = 2, /* LDS-staged macro-tile kernel on MFMA */
     GEMM_KERNEL_SKINNY = 3     /* streaming kernels with split-K for few rows of C.  bf16 / fp16, M <= 64: variant 0
                                   for a row-major B (K x N), variant 1 for B stored N x K (an A stored K x M is first
@@ -238,23 +239,23 @@ typedef struct {
                              * the tiles of the last, partly filled round of workgroups (all tiles when
                              * there are fewer tiles than compute units) are cut, each into that many
                              * shares of the k range (at most one share per 32-element slab).
-                             * Every other tile variant, and the general family's variants but 0 (without the
+                             * Every other tile variant, and the general family's variants 1 and 2 (without the
                              * condition on N): the whole product is cut into that many
                              * ranges of K (whole 32-element slabs; fewer if K has not enough of
                              * them), computed side by side into fp32 partial results and added by a
                              * second kernel; this needs N to be a multiple of 8.  Batched calls, and
                              * calls that miss that condition, return GEMM_ERR_UNSUPPORTED.  Slices
                              * are added in a fixed order: results do not vary from run to run. */
-    /* Several plans are run in one launch on tiles whose waves divide the k range, or on another pipeline of the same tile, for
-     * the sizes at which that is faster, whatever their slices, automatic or forced: the whole 128x128 tiles (variants 5 and
-     * 12), the fp32 64x64 tiles (13), the 128x128 tiles in shares (16) and the streaming variants 0, 1 and 5 with up to 64
-     * rows, and the general family's variant 1.  The plan, its errors and the workspace it asks for stay as described; a plan
-     * and a shape always give the same bits. */
+    /* Several automatic plans are launched, whatever their slices, as one kernel whose waves divide the k range, or on another pipeline
+     * of the same tile, for the calls in which that is faster: the whole 128x128 tiles (variants 5 and 12), the fp32 64x64 tiles (13), the 128x128
+     * tiles in shares (16) and the streaming variants 0, 1 and 5 with up to 64 rows, and the general family's variant 1.  The
+     * plan, its errors and the workspace it asks for stay as described; gemm_get_last_launch names the kernel. */
 } gemm_plan_t;
 
 /* Forces the plan used by later gemm_run calls on this handle; a NULL plan restores automatic
- * choice.  A forced plan that cannot run a given call (alignment, shape) makes that call return
- * GEMM_ERR_UNSUPPORTED.  Errors: GEMM_ERR_INVALID_ARG for a null handle or out-of-range fields. */
+ * choice.  A forced plan runs the kernel that it names (tile variant 19 with A stored K x M: variant 18, the same with 64 rows to a
+ * tile); variant -1 leaves the choice within the family open.  A forced plan that cannot run a given call (alignment, shape)
+ * makes that call return GEMM_ERR_UNSUPPORTED.  Errors: GEMM_ERR_INVALID_ARG for a null handle or out-of-range fields. */
 gemm_status_t gemm_set_plan(gemm_handle_t h, const gemm_plan_t* plan);
 
 /* Reports the plan the most recent successful gemm_run on this handle used, whether its slices ran side by side or, for want of
@@ -263,6 +264,10 @@ gemm_status_t gemm_set_plan(gemm_handle_t h, const gemm_plan_t* plan);
  * the plan of the whole tiles is the one reported.)
  * Errors: GEMM_ERR_INVALID_ARG for null arguments. */
 gemm_status_t gemm_get_last_plan(gemm_handle_t h, gemm_plan_t* out);
+
+/* Reports the kernel that the most recent successful gemm_run on this handle was launched on, as a plan that can be forced: that
+ * of gemm_get_last_plan, or the kernel that took its place in one launch (see gemm_plan_t).  Errors: as gemm_get_last_plan. */
+gemm_status_t gemm_get_last_launch(gemm_handle_t h, gemm_plan_t* out);
 
 /* The plan an automatic call of this shape would take on a device with `compute_units` compute
  * units, for operands on 16-byte boundaries, matrices of a batch packed back to back, no epilogue
@@ -274,6 +279,12 @@ gemm_status_t gemm_get_last_plan(gemm_handle_t h, gemm_plan_t* out);
 gemm_status_t gemm_plan_query(int32_t compute_units, int64_t batch, int64_t M, int64_t N, int64_t K,
                               gemm_op_t transA, gemm_op_t transB, gemm_dtype_t dtype, gemm_dtype_t out_dtype,
                               int64_t lda, int64_t ldb, int64_t ldc, gemm_plan_t* out);
+
+/* What gemm_get_last_launch would report of that call, made with beta != 0 (`reads_c`) and the activation `act`, which weigh in where
+ * two kernels are close.  Host arithmetic only.  Errors: as gemm_plan_query; GEMM_ERR_INVALID_ARG for an unknown `act`. */
+gemm_status_t gemm_launch_query(int32_t compute_units, int64_t batch, int64_t M, int64_t N, int64_t K,
+                                gemm_op_t transA, gemm_op_t transB, gemm_dtype_t dtype, gemm_dtype_t out_dtype,
+                                int64_t lda, int64_t ldb, int64_t ldc, int32_t reads_c, gemm_act_t act, gemm_plan_t* out);
 
 /*
  * The roofline rule of the paper (Section 4.3) that the automatic choice starts from.  A call is

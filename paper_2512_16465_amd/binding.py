@@ -23,7 +23,7 @@ GEMM_MEMORY_BOUND, GEMM_MIDDLE_ZONE, GEMM_COMPUTE_BOUND = 0, 1, 2
 
 EXPORTED_SYMBOLS = (
     "gemm_create", "gemm_run", "gemm_run_batched", "gemm_destroy", "gemm_status_string",
-    "gemm_set_plan", "gemm_get_last_plan", "gemm_variant_name", "gemm_plan_query",
+    "gemm_set_plan", "gemm_get_last_plan", "gemm_get_last_launch", "gemm_variant_name", "gemm_plan_query", "gemm_launch_query",
     "gemm_reserve_workspace", "gemm_workspace_size", "gemm_run_noalloc", "gemm_roofline_class",
 )
 
@@ -80,6 +80,10 @@ def load_library() -> ctypes.CDLL:
     lib.gemm_plan_query.restype = ctypes.c_int
     lib.gemm_plan_query.argtypes = [ctypes.c_int32, i64, i64, i64, i64, ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int,
                                     i64, i64, i64, ctypes.POINTER(gemm_plan_t)]
+    lib.gemm_get_last_launch.restype = ctypes.c_int
+    lib.gemm_get_last_launch.argtypes = lib.gemm_get_last_plan.argtypes
+    lib.gemm_launch_query.restype = ctypes.c_int
+    lib.gemm_launch_query.argtypes = lib.gemm_plan_query.argtypes[:-1] + [ctypes.c_int32, ctypes.c_int, ctypes.POINTER(gemm_plan_t)]
     lib.gemm_reserve_workspace.restype = ctypes.c_int
     lib.gemm_reserve_workspace.argtypes = [vp, ctypes.c_size_t]
     lib.gemm_workspace_size.restype = ctypes.c_int
@@ -194,6 +198,14 @@ def gemm_get_last_plan(handle: int):
     return plan.kernel, plan.variant, plan.split_k
 
 
+def gemm_get_last_launch(handle: int):
+    plan = gemm_plan_t()
+    st = load_library().gemm_get_last_launch(ctypes.c_void_p(handle), ctypes.byref(plan))
+    if st != GEMM_OK:
+        raise GemmError(st, "gemm_get_last_launch")
+    return plan.kernel, plan.variant, plan.split_k
+
+
 def gemm_plan_query(compute_units: int, batch: int, M: int, N: int, K: int, transA: int, transB: int, dtype: int,
                     out_dtype: int, lda: int, ldb: int, ldc: int, check: bool = True):
     """(kernel, variant, split_k) of the automatic plan for this shape; host only, needs no GPU."""
@@ -203,6 +215,19 @@ def gemm_plan_query(compute_units: int, batch: int, M: int, N: int, K: int, tran
     if st != GEMM_OK:
         if check:
             raise GemmError(st, "gemm_plan_query")
+        return st
+    return plan.kernel, plan.variant, plan.split_k
+
+
+def gemm_launch_query(compute_units: int, batch: int, M: int, N: int, K: int, transA: int, transB: int, dtype: int,
+                      out_dtype: int, lda: int, ldb: int, ldc: int, reads_c: bool = False, act: int = GEMM_ACT_NONE, check: bool = True):
+    """(kernel, variant, split_k) of what an automatic call is launched on; host only, needs no GPU."""
+    plan = gemm_plan_t()
+    st = load_library().gemm_launch_query(compute_units, batch, M, N, K, transA, transB, dtype, out_dtype, lda, ldb, ldc,
+                                          int(bool(reads_c)), act, ctypes.byref(plan))
+    if st != GEMM_OK:
+        if check:
+            raise GemmError(st, "gemm_launch_query")
         return st
     return plan.kernel, plan.variant, plan.split_k
 

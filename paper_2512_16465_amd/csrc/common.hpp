@@ -195,10 +195,13 @@ bool tile_variant_slices(int variant);
 // eight waves, two to a SIMD, fill each other's gaps (4096^3: 612 us against 727 with one tile per workgroup; 2560^3 171
 // against 222).  With fewer tiles it would leave units idle (2048^3: 124 against 98).
 constexpr int64_t kF32PairAbove = 256;
-// The tiles with the k range divided among a workgroup's waves (kind 6): the variant for a 16-bit call on a grid too small for the
-// 128x128 tile, -1 where that one is ahead, and its estimated time in us.  A whole call on the 128x128 tiles of variants 5
-// and 12 is launched on it (the plan names the tile, as with the pairs of variant 11).
+// The tiles with the k range divided among a workgroup's waves (kind 6): the faster variant by their estimates, and its time in us, for
+// a 16-bit call on a grid too small for the 128x128 tile; -1 where the grid or the operands are too large for them.
 int wave_tile_for(const Args& a, int64_t cus, double* estimate);
+// The variant that an automatic call planned on whole 128x128 tiles (5 or 12) is launched on, -1: the planned one.
+int whole_tile_variant(const Args& a, int variant, int64_t cus);
+// `variant` but for 19 with A stored K x M, whose k-rows are moved in whole lines: 64 rows to a tile, variant 18.
+int tile_variant_for_layout(const Args& a, int variant);
 hipError_t launch_tile(const Args& a, int variant, int group_m, const TileSplit& split, hipStream_t stream);
 hipError_t launch_tile_split_reduce(const Args& a, int variant, int group_m, const TileSplit& split, hipStream_t stream);
 
@@ -236,8 +239,10 @@ hipError_t launch_gemv16(const Args& a, int split_k, float* workspace, hipStream
 
 // Operands off the 16-byte grid (any base address that suits the element type, any leading dimension, any sizes): the
 // general family.  Variant 0 takes everything; the others are the register-staged 128x128 macro-tile kernel with movers
-// that need no alignment (1, 16-bit operands) and the 64x64 fp32 tile kernel, which needs none (2).
-constexpr int kGeneralVariants = 3;
+// that need no alignment (1, 16-bit operands), the 64x64 fp32 tile kernel, which needs none (2), and the 16-bit wave tiles (kind 6 of
+// tile_variants.def) with movers that need none, 64 or 16 rows to a tile (3, and 4 with a row-major A): K >= 8 where k is
+// contiguous, M or N >= 8 where they are, operands below 2 GiB.
+constexpr int kGeneralVariants = 5, kGeneralWave64 = 3, kGeneralWave16 = 4;
 const char* general_variant_name(int variant);
 bool general_variant_supports(const Args& a, int variant);
 // slice_len: 0, or the length of the k slices in which variants 1 and 2 then compute the call without any workspace, one
@@ -246,8 +251,6 @@ bool general_variant_supports(const Args& a, int variant);
 // for an error no larger than that of variant 0, which adds sixteen elements at a time (a 16-bit result's own rounding is
 // three orders of magnitude above either).
 hipError_t launch_general(const Args& a, int variant, int group_m, hipStream_t stream, bool fold, int64_t slice_len = 0);
-// The 16-bit wave tiles (kind 6 of tile_variants.def) with movers that need no alignment, 64 or 16 rows to a tile: K >= 8 where k is
-// contiguous, M or N >= 8 where they are, operands below 2 GiB.
 hipError_t launch_wave_any(const Args& a, int rows, int group_m, hipStream_t stream);
 hipError_t launch_any_tile(const Args& a, int group_m, hipStream_t stream, int64_t slice_len, bool fold);
 hipError_t launch_any_f32_tile(const Args& a, int group_m, hipStream_t stream, int64_t slice_len);

@@ -30,6 +30,7 @@ struct gemm_handle_s {
     bool forced;
     gemm_plan_t plan;        // forced plan (valid when forced)
     gemm_plan_t last;        // plan of the last successful run
+    gemm_plan_t launched;    // ... and the kernel it was launched on
 };
 
 namespace {
@@ -517,6 +518,7 @@ GEMM_EXPORT gemm_status_t gemm_create(gemm_handle_t* out) {
     h->forced = false;
     h->plan = gemm_plan_t{GEMM_KERNEL_AUTO, -1, 0};
     h->last = gemm_plan_t{GEMM_KERNEL_AUTO, -1, 0};
+    h->launched = h->last;
     *out = h;
     return GEMM_OK;
 }
@@ -581,6 +583,12 @@ GEMM_EXPORT gemm_status_t gemm_get_last_plan(gemm_handle_t h, gemm_plan_t* out) 
     return GEMM_OK;
 }
 
+GEMM_EXPORT gemm_status_t gemm_get_last_launch(gemm_handle_t h, gemm_plan_t* out) {
+    if (!h || !out) return GEMM_ERR_INVALID_ARG;
+    *out = h->launched;
+    return GEMM_OK;
+}
+
 GEMM_EXPORT const char* gemm_variant_name(gemm_kernel_t kernel, int32_t variant) {
     if (kernel == GEMM_KERNEL_MFMA_TILE) {
         const gemm::TileVariantInfo* info = gemm::tile_variant_info(variant);
@@ -609,104 +617,102 @@ Args slices_of(const Args& a, int slices, int64_t len, float* partials, int64_t 
 int64_t general_slice_len(int64_t K, int& slices);
 int wave_any_rows(const Args& a, int slices, int num_cus);
 
+// The kernel that an automatic plan is launched on.  The plan says which family takes the call, in how many slices and with how much
+// workspace; several are launched, whatever their slices, as one kernel whose waves divide the k range, or on another pipeline
+// of the same tile, at the sizes at which that is faster.  A forced plan is launched as it stands.
+gemm_plan_t kernel_of(const Args& a, const gemm_plan_t& plan, int split_first, int num_cus) {
+    int variant = -1;
+    if (plan.kernel == GEMM_KERNEL_GENERAL) {
+        const int rows = plan.variant == 1 ? wave_any_rows(a, plan.split_k, num_cus) : 0;
+        return rows ? gemm_plan_t{GEMM_KERNEL_GENERAL, rows == 16 ? gemm::kGeneralWave16 : gemm::kGeneralWave64, 1} : plan;
+    }
+    if (plan.kernel == GEMM_KERNEL_MFMA_TILE && plan.variant == kF32SmallTileVariant) variant = wave_f32_variant(a, plan.split_k, num_cus);
+    else if (plan.kernel == GEMM_KERNEL_MFMA_TILE && plan.split_k == 1) variant = gemm::whole_tile_variant(a, plan.variant, num_cus);
+    else if (plan.kernel == GEMM_KERNEL_SKINNY || split_first == 0) variant = few_rows_wave_tile(a, plan);
+    return variant >= 0 ? gemm_plan_t{GEMM_KERNEL_MFMA_TILE, variant, 1} : plan;
+}
+
+bool same_plan(const gemm_plan_t& x, const gemm_plan_t& y) { return x.kernel == y.kernel && x.variant == y.variant && x.split_k == y.split_k; }
+
 // Launches the kernels of a plan for the (validated) call `a`; may lower plan.split_k to what the
 // call can take.  split_first: first tile of a split trailing round (macro-tile family).
-// allocate_only: stop after making the workspace large enough for the plan.
-gemm_status_t launch_plan(const Workspace& ws, const Args& a, gemm_plan_t& plan, int split_first, hipStream_t stream,
-                          bool allocate_only = false) {
+// automatic: the library chose the plan, and kernel_of it is launched.  `launched`: what was.
+// allocate_only: stop after making the workspace large enough for the plan (whatever kernel_of it is: another call of these
+// sizes, with another epilogue, may need it where nothing can be allocated).
+gemm_status_t launch_plan(const Workspace& ws, const Args& a, gemm_plan_t& plan, int split_first, hipStream_t stream, bool automatic,
+                          gemm_plan_t* launched, bool allocate_only = false) {
     const int64_t M = a.M, N = a.N, K = a.K, batch = a.batch;
     const int64_t in_bytes = gemm::elem_bytes(a.dtype);
+    const gemm_plan_t kernel = automatic ? kernel_of(a, plan, split_first, ws.h->num_cus) : plan;
+    const bool in_one_launch = !same_plan(kernel, plan);
+    const int variant = plan.kernel == GEMM_KERNEL_MFMA_TILE ? gemm::tile_variant_for_layout(a, plan.variant) : plan.variant;
     hipError_t e = hipSuccess;
+    gemm_status_t st = GEMM_OK;
+    bool side_by_side = true;
+    int64_t slice_len = 0;
+    // ---- the slices that there are, and the workspace ----
     if (plan.kernel == GEMM_KERNEL_SKINNY) {
         const int max_split = gemm::skinny_max_split(a, plan.variant);
         if (plan.split_k > max_split) plan.split_k = max_split;
         const size_t need = gemm::skinny_workspace_bytes(a, plan.split_k);
-        if (need) {
-            const gemm_status_t st = ws.ensure(need);
-            if (st != GEMM_OK) return st;
+        if (need) st = ws.ensure(need);
+    } else if (plan.kernel == GEMM_KERNEL_MFMA_TILE && plan.split_k > 1) {
+        const int64_t slabs = (K + 31) / 32;
+        if (plan.split_k > slabs) plan.split_k = (int)slabs;
+        if (plan.split_k > 1 && !gemm::tile_variant_splits(variant)) {
+            // k slices: ranges of whole 32-element slabs, all of one length but the last
+            slice_len = ((slabs + plan.split_k - 1) / plan.split_k) * 32;
+            plan.split_k = (int)((K + slice_len - 1) / slice_len);
+            if (plan.split_k > 1) st = ws.ensure((size_t)plan.split_k * (size_t)M * (size_t)N * sizeof(float));
+        } else if (plan.split_k > 1) {
+            const gemm::TileVariantInfo* info = gemm::tile_variant_info(variant);
+            const int64_t tiles = ((a.M + info->BM - 1) / info->BM) * ((a.N + info->BN - 1) / info->BN);
+            st = ws.ensure((size_t)(tiles - split_first) * plan.split_k * info->BM * info->BN * sizeof(float));
         }
-        const int wave_tile = few_rows_wave_tile(a, plan);
-        if (wave_tile >= 0) {
-            if (!allocate_only) e = gemm::launch_tile(a, wave_tile, kTileBandRows, gemm::TileSplit{0, 1, nullptr}, stream);
-            return e == hipSuccess ? GEMM_OK : GEMM_ERR_HIP;
+    } else if (plan.kernel == GEMM_KERNEL_GENERAL && plan.split_k > 1) {
+        // k slices, as above; a call of this family has never failed for want of a workspace, so where there is none to
+        // be had (the stream is being captured, memory is out) its slices are computed one after another, to the same bits
+        slice_len = general_slice_len(K, plan.split_k);
+        if (plan.split_k > 1) {
+            const size_t need = (size_t)plan.split_k * (size_t)M * (size_t)((N + 7) / 8 * 8) * sizeof(float);
+            if (ws.fixed && need > kScratchBytes) return GEMM_ERR_SCRATCH_LIMIT;
+            side_by_side = ws.obtain(need, stream);
         }
+    }
+    if (st != GEMM_OK || allocate_only) return st;
+    // ---- launch ----
+    *launched = in_one_launch ? kernel : gemm_plan_t{plan.kernel, variant, plan.split_k};
+    const gemm::TileSplit whole{0, 1, nullptr};
+    if (kernel.kernel == GEMM_KERNEL_MFMA_TILE && (in_one_launch || plan.split_k == 1)) {
+        e = gemm::launch_tile(a, launched->variant, kTileBandRows, whole, stream);
+    } else if (kernel.kernel == GEMM_KERNEL_MFMA_TILE && slice_len > 0) {
+        e = gemm::launch_tile(slices_of(a, plan.split_k, slice_len, ws.ptr(), N), variant, kTileBandRows, whole, stream);
+        if (e == hipSuccess) e = gemm::launch_splitk_reduce(a, plan.split_k, ws.ptr(), stream);
+    } else if (kernel.kernel == GEMM_KERNEL_MFMA_TILE) {
+        const gemm::TileSplit split{split_first, plan.split_k, ws.ptr()};
+        e = gemm::launch_tile(a, variant, kTileBandRows, split, stream);
+        if (e == hipSuccess) e = gemm::launch_tile_split_reduce(a, variant, kTileBandRows, split, stream);
+    } else if (kernel.kernel == GEMM_KERNEL_SKINNY) {
         // one matrix per launch (the slices of a split share the workspace, in stream order)
         Args one = a;
         one.batch = 1;
-        for (int64_t b = 0; b < batch && e == hipSuccess && !allocate_only; ++b) {
+        for (int64_t b = 0; b < batch && e == hipSuccess; ++b) {
             one.A = (const char*)a.A + b * a.strideA * in_bytes;
             one.B = (const char*)a.B + b * a.strideB * in_bytes;
             one.C = (char*)a.C + b * a.strideC * gemm::elem_bytes(a.out_dtype);
             e = gemm::launch_skinny(one, plan.split_k, ws.ptr(), stream, plan.variant);
         }
-    } else if (plan.kernel == GEMM_KERNEL_MFMA_TILE) {
-        gemm::TileSplit split{0, 1, nullptr};
-        const int wave_tile = plan.variant == kF32SmallTileVariant ? wave_f32_variant(a, plan.split_k, ws.h->num_cus) : -1;
-        if (plan.split_k > 1) {
-            const int64_t slabs = (K + 31) / 32;
-            if (plan.split_k > slabs) plan.split_k = (int)slabs;
-        }
-        int64_t slice_len = 0;
-        if (plan.split_k > 1 && !gemm::tile_variant_splits(plan.variant)) {
-            // k slices: ranges of whole 32-element slabs, all of one length but the last
-            const int64_t slabs = (K + 31) / 32;
-            slice_len = ((slabs + plan.split_k - 1) / plan.split_k) * 32;
-            plan.split_k = (int)((K + slice_len - 1) / slice_len);
-        }
-        if (plan.split_k > 1 && slice_len > 0) {
-            const gemm_status_t st = ws.ensure((size_t)plan.split_k * (size_t)M * (size_t)N * sizeof(float));
-            if (st != GEMM_OK) return st;
-            const Args p = slices_of(a, plan.split_k, slice_len, ws.ptr(), N);
-            if (wave_tile >= 0) {      // (one launch, no partial results; the workspace is there for the calls of this size that need it)
-                if (!allocate_only) e = gemm::launch_tile(a, wave_tile, kTileBandRows, split, stream);
-                return e == hipSuccess ? GEMM_OK : GEMM_ERR_HIP;
-            }
-            if (!allocate_only) e = gemm::launch_tile(p, plan.variant, kTileBandRows, split, stream);
-            if (!allocate_only && e == hipSuccess) e = gemm::launch_splitk_reduce(a, plan.split_k, ws.ptr(), stream);
-        } else if (plan.split_k > 1) {
-            const gemm::TileVariantInfo* info = gemm::tile_variant_info(plan.variant);
-            const int64_t tiles = ((a.M + info->BM - 1) / info->BM) * ((a.N + info->BN - 1) / info->BN);
-            const size_t need = (size_t)(tiles - split_first) * plan.split_k * info->BM * info->BN * sizeof(float);
-            const gemm_status_t st = ws.ensure(need);
-            if (st != GEMM_OK) return st;
-            const int few_rows = split_first == 0 ? few_rows_wave_tile(a, plan) : -1;
-            if (few_rows >= 0) {
-                if (!allocate_only) e = gemm::launch_tile(a, few_rows, kTileBandRows, gemm::TileSplit{0, 1, nullptr}, stream);
-                return e == hipSuccess ? GEMM_OK : GEMM_ERR_HIP;
-            }
-            split = gemm::TileSplit{split_first, plan.split_k, ws.ptr()};
-            if (!allocate_only) e = gemm::launch_tile(a, plan.variant, kTileBandRows, split, stream);
-            if (!allocate_only && e == hipSuccess) e = gemm::launch_tile_split_reduce(a, plan.variant, kTileBandRows, split, stream);
-        } else if (!allocate_only) {
-            e = gemm::launch_tile(a, wave_tile >= 0 ? wave_tile : plan.variant, kTileBandRows, split, stream);
-        }
     } else {
         const bool fold = a.out_dtype == gemm::DT_F32;
-        const int wave_rows = plan.variant == 1 ? wave_any_rows(a, plan.split_k, ws.h->num_cus) : 0;
-        if (plan.split_k > 1) {
-            // k slices, as above; a call of this family has never failed for want of a workspace, so where there is none to
-            // be had (the stream is being captured, memory is out) its slices are computed one after another, to the same bits
-            const int64_t len = general_slice_len(K, plan.split_k), P = (N + 7) / 8 * 8;
-            if (plan.split_k > 1) {
-                const size_t need = (size_t)plan.split_k * (size_t)M * (size_t)P * sizeof(float);
-                if (ws.fixed && need > kScratchBytes) return GEMM_ERR_SCRATCH_LIMIT;
-                const bool side_by_side = ws.obtain(need, stream);
-                if (allocate_only) return GEMM_OK;
-                if (wave_rows) {      // (one launch, no partial results; the workspace is there for the calls of this size that need it)
-                    e = gemm::launch_wave_any(a, wave_rows, kTileBandRows, stream);
-                    return e == hipSuccess ? GEMM_OK : GEMM_ERR_HIP;
-                }
-                if (!side_by_side) {
-                    e = gemm::launch_general(a, plan.variant, kTileBandRows, stream, fold, len);
-                    return e == hipSuccess ? GEMM_OK : GEMM_ERR_HIP;
-                }
-                e = gemm::launch_general(slices_of(a, plan.split_k, len, ws.ptr(), P), plan.variant, kTileBandRows, stream, fold);
-                if (e == hipSuccess) e = gemm::launch_splitk_reduce(a, plan.split_k, ws.ptr(), stream);
-                return e == hipSuccess ? GEMM_OK : GEMM_ERR_HIP;
-            }
+        if (in_one_launch || plan.split_k == 1) {
+            e = gemm::launch_general(a, kernel.variant, kTileBandRows, stream, fold);
+        } else if (!side_by_side) {
+            e = gemm::launch_general(a, plan.variant, kTileBandRows, stream, fold, slice_len);
+        } else {
+            const int64_t P = (N + 7) / 8 * 8;
+            e = gemm::launch_general(slices_of(a, plan.split_k, slice_len, ws.ptr(), P), plan.variant, kTileBandRows, stream, fold);
+            if (e == hipSuccess) e = gemm::launch_splitk_reduce(a, plan.split_k, ws.ptr(), stream);
         }
-        if (!allocate_only && wave_rows) e = gemm::launch_wave_any(a, wave_rows, kTileBandRows, stream);
-        else if (!allocate_only) e = gemm::launch_general(a, plan.variant, kTileBandRows, stream, fold);
     }
     return e == hipSuccess ? GEMM_OK : GEMM_ERR_HIP;
 }
@@ -863,9 +869,7 @@ int64_t general_slice_len(int64_t K, int& slices) {
 // Results of 16 bits only: for an fp32 C slices and folds have the smaller error.
 int wave_any_rows(const Args& a, int slices, int num_cus) {
     const int64_t cus = num_cus > 0 ? num_cus : 256;
-    // (the movers start the last chunk of a row 8 elements ahead of its end, and mask with an offset of 2 GiB - 16)
-    if (a.dtype == gemm::DT_F32 || a.out_dtype == gemm::DT_F32 || (!a.transA && a.K < 8) || (a.transB && a.K < 8)) return 0;
-    if ((a.transA ? a.K : a.M) * a.lda * 2 >= 0x7ffffff0ll || (a.transB ? a.N : a.K) * a.ldb * 2 >= 0x7ffffff0ll) return 0;
+    if (a.out_dtype == gemm::DT_F32 || !gemm::general_variant_supports(a, gemm::kGeneralWave64)) return 0;
     struct Tile { int rows; double per_k_alone, per_k, fixed, per_round, store_rate, activation, weight_rate, layout[4]; };
     static const Tile tiles[] = {{64, 0.0041, 0.0038, 5.1, 0.6, 3.4e6, 1.3, 41e6, {1.0, 1.12, 1.34, 1.37}},      // NT, NN, TT, TN
                                  {16, 0.00256, 0.0024, 4.2, 0.0, 1.0e6, 0.6, 23e6, {1.0, 1.05, 0.0, 0.0}}};
@@ -1021,6 +1025,8 @@ gemm_status_t run_batch(gemm_handle_t h, bool fixed_scratch, int64_t batch, int6
     // ---- plan ----
     gemm_plan_t plan{GEMM_KERNEL_GENERAL, 0, 1};
     int split_first = -1;          // first tile of a split trailing round (macro-tile family)
+    bool automatic = false;        // whether the library chose the kernel, not the caller
+    gemm_plan_t launched = plan;
     const bool product = (K > 0 && alpha != 0.0f);
     if (!product) {
         plan = gemm_plan_t{GEMM_KERNEL_GENERAL, 0, 1};      // only the epilogue is left
@@ -1029,6 +1035,7 @@ gemm_status_t run_batch(gemm_handle_t h, bool fixed_scratch, int64_t batch, int6
         if (plan.kernel == GEMM_KERNEL_MFMA_TILE) {
             if (!gemm::tile_supports(a) || !batch_aligned) return GEMM_ERR_UNSUPPORTED;
             if (plan.variant < 0) {
+                automatic = plan.split_k <= 1;
                 const TileChoice c = choose_tile(a, h->num_cus);
                 plan.variant = c.variant;
                 if (plan.split_k == 0) { plan.split_k = c.parts; split_first = c.first_split_tile; }
@@ -1055,31 +1062,35 @@ gemm_status_t run_batch(gemm_handle_t h, bool fixed_scratch, int64_t batch, int6
             if (plan.split_k == 0) plan.split_k = gemm::skinny_default_split(a, h->num_cus, plan.variant);
         } else if (plan.variant < 1 || !gemm::general_variant_supports(a, plan.variant) || plan.variant >= gemm::kGeneralVariants) {
             plan = gemm_plan_t{GEMM_KERNEL_GENERAL, 0, 1};      // (the one that takes everything)
-        } else if (plan.split_k < 1 || batch > 1) {
+        } else if (plan.split_k < 1 || batch > 1 || plan.variant >= gemm::kGeneralWave64) {
             plan.split_k = 1;
         }
     } else {
         const AutoPlan ap = automatic_plan(a, h->num_cus, batch_aligned);
         plan = ap.plan;
         split_first = ap.split_first;
+        automatic = true;
         if (ap.peeled) {
             gemm_plan_t pm = ap.plan, pr = ap.rest_plan;
             // the workspace of both parts first: a failed allocation must leave C untouched
-            gemm_status_t st = launch_plan(ws, ap.main_part, pm, ap.split_first, stream, true);
-            if (st == GEMM_OK) st = launch_plan(ws, ap.rest, pr, ap.rest_split_first, stream, true);
+            gemm_plan_t rest_launched = pr;
+            gemm_status_t st = launch_plan(ws, ap.main_part, pm, ap.split_first, stream, automatic, &launched, true);
+            if (st == GEMM_OK) st = launch_plan(ws, ap.rest, pr, ap.rest_split_first, stream, automatic, &rest_launched, true);
             if (st != GEMM_OK) return st;
-            st = launch_plan(ws, ap.main_part, pm, ap.split_first, stream);
-            if (st == GEMM_OK) st = launch_plan(ws, ap.rest, pr, ap.rest_split_first, stream);
+            st = launch_plan(ws, ap.main_part, pm, ap.split_first, stream, automatic, &launched);
+            if (st == GEMM_OK) st = launch_plan(ws, ap.rest, pr, ap.rest_split_first, stream, automatic, &rest_launched);
             if (st != GEMM_OK) return st;
             h->last = pm;         // the plan of the whole tiles
+            h->launched = launched;
             return GEMM_OK;
         }
     }
 
     // ---- launch ----
-    const gemm_status_t st = launch_plan(ws, a, plan, split_first, stream);
+    const gemm_status_t st = launch_plan(ws, a, plan, split_first, stream, automatic, &launched);
     if (st != GEMM_OK) return st;
     h->last = plan;
+    h->launched = launched;
     return GEMM_OK;
 }
 
@@ -1096,21 +1107,24 @@ GEMM_EXPORT gemm_status_t gemm_roofline_class(int64_t batch, int64_t M, int64_t 
     return GEMM_OK;
 }
 
-GEMM_EXPORT gemm_status_t gemm_plan_query(int32_t compute_units, int64_t batch, int64_t M, int64_t N, int64_t K,
-                                          gemm_op_t transA, gemm_op_t transB, gemm_dtype_t dtype, gemm_dtype_t out_dtype,
-                                          int64_t lda, int64_t ldb, int64_t ldc, gemm_plan_t* out) {
-    if (!out || compute_units < 1 || batch < 1 || M < 1 || N < 1 || K < 1) return GEMM_ERR_INVALID_ARG;
+namespace {
+
+// The automatic plan of a call on aligned operands that are never looked at; `call`: the call.
+gemm_status_t query(int32_t compute_units, int64_t batch, int64_t M, int64_t N, int64_t K, gemm_op_t transA, gemm_op_t transB, gemm_dtype_t dtype,
+                    gemm_dtype_t out_dtype, int64_t lda, int64_t ldb, int64_t ldc, bool reads_c, gemm_act_t act, Args* call, AutoPlan* plan) {
+    if (compute_units < 1 || batch < 1 || M < 1 || N < 1 || K < 1) return GEMM_ERR_INVALID_ARG;
     if ((transA != GEMM_OP_N && transA != GEMM_OP_T) || (transB != GEMM_OP_N && transB != GEMM_OP_T)) return GEMM_ERR_INVALID_ARG;
     if (!valid_dtype(dtype) || !valid_dtype(out_dtype)) return GEMM_ERR_INVALID_ARG;
+    if ((int)act < (int)GEMM_ACT_NONE || (int)act > (int)GEMM_ACT_GELU_TANH) return GEMM_ERR_INVALID_ARG;
     if (out_dtype != dtype && out_dtype != GEMM_F32) return GEMM_ERR_UNSUPPORTED;
     const int64_t a_cols = transA == GEMM_OP_N ? K : M, b_cols = transB == GEMM_OP_N ? N : K;
     if (lda < a_cols || ldb < b_cols || ldc < N) return GEMM_ERR_INVALID_ARG;
     if (batch > kMaxBatchPerLaunch) batch = kMaxBatchPerLaunch;      // larger batches run in parts of this size
-    Args a;
+    Args& a = *call;
     a.M = M; a.N = N; a.K = K;
     a.transA = transA == GEMM_OP_T; a.transB = transB == GEMM_OP_T;
-    a.dtype = (int)dtype; a.out_dtype = (int)out_dtype; a.bias_dtype = (int)dtype; a.act = gemm::ACT_NONE;
-    a.alpha = 1.0f; a.beta = 0.0f;
+    a.dtype = (int)dtype; a.out_dtype = (int)out_dtype; a.bias_dtype = (int)dtype; a.act = (int)act;
+    a.alpha = 1.0f; a.beta = reads_c ? 1.0f : 0.0f;
     // stand-ins for aligned operands (never dereferenced: nothing is launched)
     a.A = (const void*)(uintptr_t)0x100000; a.B = (const void*)(uintptr_t)0x100000; a.C = (void*)(uintptr_t)0x100000;
     a.lda = lda; a.ldb = ldb; a.ldc = ldc;
@@ -1121,8 +1135,32 @@ GEMM_EXPORT gemm_status_t gemm_plan_query(int32_t compute_units, int64_t batch, 
     a.strideA = batch > 1 ? rows_a * lda : 0; a.strideB = batch > 1 ? rows_b * ldb : 0; a.strideC = batch > 1 ? M * ldc : 0;
     const int64_t in_bytes = gemm::elem_bytes(a.dtype);
     const bool batch_aligned = batch == 1 || ((a.strideA * in_bytes) % 16 == 0 && (a.strideB * in_bytes) % 16 == 0);
-    *out = automatic_plan(a, compute_units, batch_aligned).plan;
+    *plan = automatic_plan(a, compute_units, batch_aligned);
     return GEMM_OK;
+}
+
+}  // namespace
+
+GEMM_EXPORT gemm_status_t gemm_plan_query(int32_t compute_units, int64_t batch, int64_t M, int64_t N, int64_t K,
+                                          gemm_op_t transA, gemm_op_t transB, gemm_dtype_t dtype, gemm_dtype_t out_dtype,
+                                          int64_t lda, int64_t ldb, int64_t ldc, gemm_plan_t* out) {
+    if (!out) return GEMM_ERR_INVALID_ARG;
+    Args a;
+    AutoPlan ap;
+    const gemm_status_t st = query(compute_units, batch, M, N, K, transA, transB, dtype, out_dtype, lda, ldb, ldc, false, GEMM_ACT_NONE, &a, &ap);
+    if (st == GEMM_OK) *out = ap.plan;
+    return st;
+}
+
+GEMM_EXPORT gemm_status_t gemm_launch_query(int32_t compute_units, int64_t batch, int64_t M, int64_t N, int64_t K,
+                                            gemm_op_t transA, gemm_op_t transB, gemm_dtype_t dtype, gemm_dtype_t out_dtype,
+                                            int64_t lda, int64_t ldb, int64_t ldc, int32_t reads_c, gemm_act_t act, gemm_plan_t* out) {
+    if (!out) return GEMM_ERR_INVALID_ARG;
+    Args a;
+    AutoPlan ap;
+    const gemm_status_t st = query(compute_units, batch, M, N, K, transA, transB, dtype, out_dtype, lda, ldb, ldc, reads_c != 0, act, &a, &ap);
+    if (st == GEMM_OK) *out = kernel_of(ap.peeled ? ap.main_part : a, ap.plan, ap.split_first, compute_units);
+    return st;
 }
 
 GEMM_EXPORT gemm_status_t gemm_run(gemm_handle_t h, int64_t M, int64_t N, int64_t K,

@@ -61,7 +61,8 @@ __global__ __launch_bounds__(GT * GT) void general_kernel(Args a) {
 
 const char* general_variant_name(int variant) {
     static const char* const names[kGeneralVariants] = {"general_16x16", "general_128x128x64_w2x2",
-                                                        "general_f32_64x64x32_w2x2"};
+                                                        "general_f32_64x64x32_w2x2", "general_wavek_64x64x64_w4",
+                                                        "general_wavek_16x64x64_w4"};
     return variant >= 0 && variant < kGeneralVariants ? names[variant] : nullptr;
 }
 
@@ -74,6 +75,12 @@ bool general_variant_supports(const Args& a, int variant) {
     // 32-bit byte offsets inside a slab, a 32-bit workgroup count
     if (a.lda > (1 << 22) || a.ldb > (1 << 22) || a.K > (1 << 30)) return false;
     if (((a.M + 63) / 64) * ((a.N + 63) / 64) > (int64_t)1 << 30) return false;
+    // the wave tiles' movers start the last chunk of a row 8 elements ahead of its end and mask with an offset of 2 GiB - 16; a k-row of
+    // 16 elements of an A stored K x M is no whole line
+    if (variant >= kGeneralWave64) {
+        if (((!a.transA || a.transB) && a.K < 8) || (variant == kGeneralWave16 && a.transA)) return false;
+        if ((a.transA ? a.K : a.M) * a.lda * 2 >= 0x7ffffff0ll || (a.transB ? a.N : a.K) * a.ldb * 2 >= 0x7ffffff0ll) return false;
+    }
     // the 16-bit mover of an m/n-contiguous operand fetches eight rows at a time
     return a.dtype == DT_F32 || ((!a.transA || a.M >= 8) && (a.transB || a.N >= 8));
 }
@@ -82,6 +89,7 @@ hipError_t launch_general(const Args& a, int variant, int group_m, hipStream_t s
     if (!general_variant_supports(a, variant)) return hipErrorInvalidValue;
     if (variant == 1) return launch_any_tile(a, group_m, stream, slice_len, fold);
     if (variant == 2) return launch_any_f32_tile(a, group_m, stream, slice_len);
+    if (variant >= kGeneralWave64) return launch_wave_any(a, variant == kGeneralWave16 ? 16 : 64, group_m, stream);
     const int64_t tiles = ((a.M + GT - 1) / GT) * ((a.N + GT - 1) / GT);
     if (tiles == 0) return hipSuccess;
     const int64_t grid = tiles < (1 << 20) ? tiles : (1 << 20);

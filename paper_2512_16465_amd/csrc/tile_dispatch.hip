@@ -122,16 +122,19 @@ constexpr int64_t kLongK = 1280;
 // 0.88 to 1.2.
 constexpr int64_t kNarrowK = 768;
 
+int whole_tile_variant(const Args& a, int variant, int64_t cus) {
+    if (variant != 5 && variant != 12) return -1;
+    const int wave_tile = wave_tile_for(a, cus, nullptr);
+    if (wave_tile >= 0) return wave_tile;
+    if (variant == 5 && !a.transA && a.N <= 64 && a.K >= kNarrowK && tile_variant_supports(a, 18)) return 18;
+    return !a.transA && a.transB && a.K >= kLongK && tile_variant_supports(a, 16) ? 16 : -1;
+}
+
+int tile_variant_for_layout(const Args& a, int variant) { return variant == 19 && a.transA ? 18 : variant; }
+
 hipError_t launch_tile(const Args& a, int variant, int group_m, const TileSplit& split, hipStream_t stream) {
     if (variant < 0 || variant >= kNum) return hipErrorInvalidValue;
     if (split.parts > 1 && !tile_variant_splits(variant)) return hipErrorInvalidValue;
-    if ((variant == 5 || variant == 12) && a.k_total == 0) {
-        const int wave_tile = wave_tile_for(a, 256, nullptr);
-        if (wave_tile >= 0) variant = wave_tile;
-        else if (variant == 5 && !a.transA && a.N <= 64 && a.K >= kNarrowK && tile_variant_supports(a, 18)) variant = 18;
-        else if (!a.transA && a.transB && a.K >= kLongK && tile_variant_supports(a, 16)) variant = 16;
-    }
-    if (variant == 19 && a.transA) variant = 18;      // (a k-row of A is moved in whole lines: 64 rows to a tile)
     return kLaunch[variant](a, group_m < 1 ? 1 : group_m, split, stream);
 }
 

@@ -1,5 +1,6 @@
 """GPU parity of the tiles whose k range is divided among the waves (64x64 and 16x64): edges of a tile, k ranges that give some waves
-no slab or a partial one, every layout, type, epilogue and a strided batch, forced and as the automatic plan launches them."""
+no slab or a partial one, every layout, type, epilogue and a strided batch, forced and as an automatic call launches them; and
+that a forced plan runs the kernel it names."""
 import numpy as np
 import pytest
 import torch
@@ -61,19 +62,51 @@ def test_epilogues(handle, name, N, tb):
         check_full(cfg, inp, got, f"{name} act={act}")
 
 
-def test_automatic_calls_take_them_under_the_plan_of_the_128_tile_and_in_place_of_a_split(handle):
-    """A whole 128x128 tile plan, reported and forced, is launched on them; so is a call that used to be split."""
+def test_automatic_calls_take_them_in_place_of_whole_128_tiles_and_of_a_split(handle):
+    """What an automatic call is launched on is reported, and gives the same bits when forced."""
     for M, N, K, ta, tb in [(200, 264, 776, 0, 1), (520, 392, 136, 1, 0), (30, 1096, 2056, 0, 0)]:
         cfg = wl.Config("w", M, N, K, ta, tb, wl.BF16, wl.F32, beta=1.0, a_dist=("normal", 1.0), b_dist=("normal", 0.05), c_dist=("normal", 1.0))
         inp = wl.make_inputs(cfg, 3)
         got, plan = run(handle, cfg, inp, None)
-        assert plan[2] == 1
-        again, _ = run(handle, cfg, inp, plan)
+        launched = lg.gemm_get_last_launch(handle)
+        assert plan[2] == 1 and launched[0] == TILE and launched[1] in WAVE.values() and launched[2] == 1, (plan, launched)
+        again, _ = run(handle, cfg, inp, launched)
         check_full(cfg, inp, got, str(plan))
         assert np.array_equal(got.view(np.uint32), again.view(np.uint32))
-        if not (ta and M % 64):
-            tiles = [run(handle, cfg, inp, (TILE, v, 1))[0].view(np.uint32) for n, v in sorted(WAVE.items()) if not (ta and n.startswith("wavek_16"))]
-            assert any(np.array_equal(got.view(np.uint32), t) for t in tiles), plan
+
+
+# (the kernel, another of the same sums, one that adds in another order) on a call that an automatic plan would launch as a wave tile
+NAMED = [(200, 264, 776, 0, 1, wl.BF16, (TILE, 5, 1), (TILE, 12, 1), (TILE, 18, 1)), (520, 392, 136, 1, 0, wl.F16, (TILE, 12, 1), (TILE, 5, 1), (TILE, 18, 1)),
+         (196, 132, 100, 0, 1, wl.F32, (TILE, 13, 1), None, (TILE, 21, 1)), (64, 460, 1152, 0, 1, wl.F32, (TILE, 13, 2), None, (TILE, 21, 1)),
+         (16, 3032, 264, 0, 1, wl.BF16, (lg.GEMM_KERNEL_SKINNY, 5, 1), None, (TILE, 19, 1)), (58, 728, 688, 0, 1, wl.BF16, (TILE, 16, 4), None, (TILE, 19, 1))]
+
+
+@pytest.mark.parametrize("M,N,K,ta,tb,dtype,plan,same,other", NAMED)
+def test_a_forced_plan_runs_the_kernel_that_it_names(handle, M, N, K, ta, tb, dtype, plan, same, other):
+    """Gaussian data and a 32-bit result: another order of the sums shows in the bits."""
+    cfg = wl.Config("named", M, N + (-N % 8 if plan[2] > 1 else 0), K, ta, tb, dtype, wl.F32, a_dist=("normal", 1.0), b_dist=("normal", 0.05))
+    inp = wl.make_inputs(cfg, 7)
+    got, last = run(handle, cfg, inp, plan)
+    assert last == plan and not np.array_equal(got.view(np.uint32), run(handle, cfg, inp, other)[0].view(np.uint32)), (plan, other)
+    assert same is None or np.array_equal(got.view(np.uint32), run(handle, cfg, inp, same)[0].view(np.uint32)), (plan, same)
+    check_full(cfg, inp, got, str(plan))
+    run(handle, cfg, inp, plan)
+    assert lg.gemm_get_last_launch(handle) == plan
+
+
+def test_a_forced_plan_of_the_unaligned_tiles_runs_the_kernel_that_it_names(handle):
+    """16-bit results: of 90 000 elements a few round the other way when they are added in another order."""
+    cfg = wl.Config("named", 301, 303, 519, 0, 1, wl.F16, wl.F16, lda=520, ldb=521, ldc=303, a_dist=("normal", 1.0), b_dist=("normal", 0.05))
+    inp = wl.make_inputs(cfg, 7)
+    bits = {}
+    for variant in (1, 3, 4):
+        bits[variant], last = run(handle, cfg, inp, (lg.GEMM_KERNEL_GENERAL, variant, 1))
+        assert last == (lg.GEMM_KERNEL_GENERAL, variant, 1)
+        check_full(cfg, inp, bits[variant], str(variant))
+    assert not np.array_equal(bits[1], bits[3]) and not np.array_equal(bits[1], bits[4])
+    got, _ = run(handle, cfg, inp, None)
+    launched = lg.gemm_get_last_launch(handle)
+    assert launched[0] == lg.GEMM_KERNEL_GENERAL and launched[1] in (3, 4) and np.array_equal(got, bits[launched[1]])
 
 
 @pytest.mark.parametrize("name", sorted(WAVE))
@@ -102,13 +135,17 @@ def test_off_the_grid(handle, ta, tb, M, N, K):
             x = inp[key].reshape(rows, ld).copy()
             x[:, cols:] = wl.to_bits(np.full((1,), np.nan, dtype=np.float32), dtype)[0]
             inp[key] = x.reshape(-1)
-        lg.gemm_set_plan(handle, lg.GEMM_KERNEL_GENERAL, 1, 1)
-        try:
-            p = DeviceProblem(cfg, inp, a_offset_elems=1, b_offset_elems=3)
-            p.run(handle)
-            assert np.array_equal(c_bits_as_uint(cfg, p.result_bits()), want)
-        finally:
-            lg.gemm_set_plan(handle)
+        for variant in (1, 3, 4):                               # the 128x128 tile, the 64x64 and (row-major A) the 16x64 wave tile
+            if variant == 4 and ta:
+                continue
+            lg.gemm_set_plan(handle, lg.GEMM_KERNEL_GENERAL, variant, 1)
+            try:
+                p = DeviceProblem(cfg, inp, a_offset_elems=1, b_offset_elems=3)
+                p.run(handle)
+                assert lg.gemm_get_last_launch(handle) == (lg.GEMM_KERNEL_GENERAL, variant, 1)
+                assert np.array_equal(c_bits_as_uint(cfg, p.result_bits()), want), variant
+            finally:
+                lg.gemm_set_plan(handle)
 
 
 WAVE_F32 = {n: v for v in range(64) if (n := lg.gemm_variant_name(TILE, v) or "").endswith("_wk8")}
@@ -176,39 +213,37 @@ def test_fp32_values_outside_the_split(handle, name, ta, tb):
 SKINNY = lg.GEMM_KERNEL_SKINNY
 
 
-@pytest.mark.parametrize("plan,M,N,K,tb", [((SKINNY, 5, 1), 7, 4200, 520, 1), ((SKINNY, 5, 1), 16, 4093, 264, 1), ((SKINNY, 0, 2), 5, 12872, 264, 0),
-                                           ((SKINNY, 1, 2), 16, 13000, 328, 1), ((TILE, 16, 2), 40, 8200, 520, 1), ((TILE, 16, 2), 33, 5208, 328, 0),
-                                           ((TILE, 16, 2), 20, 2184, 1032, 0), ((TILE, 16, 3), 16, 4200, 520, 0)])
-def test_few_rows_whose_plan_runs_on_a_wave_tile(handle, plan, M, N, K, tb):
+@pytest.mark.parametrize("kernel,variant,M,N,K,tb,launched", [
+    (SKINNY, 5, 16, 3032, 264, 1, 19), (SKINNY, 5, 16, 4093, 264, 1, 19), (SKINNY, 0, 16, 13088, 5128, 0, 19), (SKINNY, 1, 14, 13128, 5112, 1, 19),
+    (TILE, 16, 58, 728, 688, 1, 19), (TILE, 16, 60, 884, 728, 1, 19), (TILE, 16, 54, 1000, 688, 0, 19), (TILE, 16, 38, 5552, 1200, 1, 18),
+    (TILE, 16, 34, 5584, 1192, 0, 18)])
+def test_few_rows_whose_plan_runs_on_a_wave_tile(handle, kernel, variant, M, N, K, tb, launched):
     for dtype, out, act, bias_dtype, beta in [(wl.BF16, wl.F32, wl.ACT_NONE, wl.BF16, 1.0), (wl.F16, wl.F16, wl.ACT_GELU_ERF, wl.F32, 0.0)]:
         cfg = wl.Config("w", M, N, K, 0, tb, dtype, out, alpha=0.5, beta=beta, a_dist=("normal", 1.0), b_dist=("normal", 0.05), c_dist=("normal", 1.0),
                         bias_dist=("normal", 0.1), bias_dtype=bias_dtype, act=act, ldb=(K if tb else (N + 7) // 8 * 8) + 8, ldc=N + 3)
         inp = wl.make_inputs(cfg, 21)
-        got, ran = run(handle, cfg, inp, plan)
-        assert ran == plan
+        got, plan = run(handle, cfg, inp, None)
+        assert plan[:2] == (kernel, variant) and lg.gemm_get_last_launch(handle) == (TILE, launched, 1), plan
         check_full(cfg, inp, got, f"{plan} {M}x{N}x{K}")
 
 
-@pytest.mark.parametrize("K", [1272, 1280, 1304])
-def test_whole_128x128_tiles_of_a_long_k(handle, K):
+@pytest.mark.parametrize("K,launched", [(1272, 5), (1280, 16), (1304, 16)])
+def test_whole_128x128_tiles_of_a_long_k(handle, K, launched):
     M, N = 2085, 1051      # beyond two rounds of wave tiles, ragged on both sides
     cfg = wl.Config("w", M, N, K, 0, 1, wl.BF16, wl.F32, lda=K + 8, ldb=K + 16, ldc=N + 3)
     inp, _ = wl.make_integer_inputs(cfg, 77 + K, -5, 5)
-    got, plan = run(handle, cfg, inp, (TILE, 5, 1))
-    assert plan == (TILE, 5, 1)
-    assert np.array_equal(c_bits_as_uint(cfg, got), c_bits_as_uint(cfg, expected_bits_exact(cfg, inp).reshape(M, N)))
-    assert np.all(np.isnan(oracle.decode(wl.F32, np.ascontiguousarray(got[:-1, N:]))))
+    for forced in (None, (TILE, 5, 1), (TILE, 16, 1)):
+        got, plan = run(handle, cfg, inp, forced)
+        assert plan == (forced or (TILE, 5, 1)) and lg.gemm_get_last_launch(handle) == (forced or (TILE, launched, 1))
+        assert np.array_equal(c_bits_as_uint(cfg, got), c_bits_as_uint(cfg, expected_bits_exact(cfg, inp).reshape(M, N)))
+        assert np.all(np.isnan(oracle.decode(wl.F32, np.ascontiguousarray(got[:-1, N:]))))
 
 
-@pytest.mark.parametrize("K,N,tb", [(760, 64, 0), (768, 64, 0), (776, 48, 0), (776, 37, 1)])
-def test_batches_of_up_to_64_columns_beyond_two_rounds(handle, K, N, tb):
+@pytest.mark.parametrize("K,N,tb,launched", [(760, 64, 0, 5), (768, 64, 0, 18), (776, 48, 0, 18), (776, 37, 1, 18)])
+def test_batches_of_up_to_64_columns_beyond_two_rounds(handle, K, N, tb, launched):
     M, batch = 1093, 31
     cfg = wl.Config("w", M, N, K, 0, tb, wl.BF16, wl.BF16, a_dist=("normal", 1.0), b_dist=("normal", 0.05), c_dist=("normal", 1.0), beta=0.5)
-    lg.gemm_set_plan(handle, TILE, 5, 1)
-    try:
-        p = BatchedDeviceProblem(cfg, batch, cfg.stride_a(), cfg.stride_b() + 8, cfg.stride_c() + 3, seed=5)
-        p.run(handle)
-        assert lg.gemm_get_last_plan(handle) == (TILE, 5, 1)
-        p.check("narrow batch")
-    finally:
-        lg.gemm_set_plan(handle)
+    p = BatchedDeviceProblem(cfg, batch, cfg.stride_a(), cfg.stride_b() + 8, cfg.stride_c() + 3, seed=5)
+    p.run(handle)
+    assert lg.gemm_get_last_plan(handle) == (TILE, 5, 1) and lg.gemm_get_last_launch(handle) == (TILE, launched, 1)
+    p.check("narrow batch")

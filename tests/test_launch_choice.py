@@ -1,0 +1,65 @@
+"""CPU-only: which kernel an automatic plan is launched on, through gemm_launch_query (host arithmetic, no device)."""
+import random
+
+import paper_2512_16465_amd as lg
+import workloads as wl
+
+TILE, SKINNY, GENERAL = lg.GEMM_KERNEL_MFMA_TILE, lg.GEMM_KERNEL_SKINNY, lg.GEMM_KERNEL_GENERAL
+LAYOUT = {"NT": (0, 1), "NN": (0, 0), "TT": (1, 1), "TN": (1, 0)}
+
+
+def both(M, N, K, layout="NN", dtype=wl.BF16, out=None, batch=1, pad=0, reads_c=False, act=wl.ACT_NONE, cus=256):
+    """Name and slices of the plan and of the kernel that it is launched on."""
+    ta, tb = LAYOUT[layout]
+    call = (cus, batch, M, N, K, ta, tb, dtype, dtype if out is None else out, (M if ta else K) + pad, (K if tb else N) + pad, N)
+    plan, launched = lg.gemm_plan_query(*call), lg.gemm_launch_query(*call, reads_c, act)
+    return tuple((lg.gemm_variant_name(k, v), s) for k, v, s in (plan, launched))
+
+
+def test_plans_that_are_launched_as_wave_tiles():
+    small, short, f32 = "dma_128x128x32_w2x2_s4", "dma_128x128x32_w2x2_s3", "f32_64x64x32_w2x2"
+    w64, w16 = ("wavek_64x64x64_w4", 1), ("wavek_16x64x64_w4", 1)
+    assert both(1024, 1024, 1024) == ((small, 1), w64) and both(200, 264, 776, "NT") == ((small, 1), w16)
+    assert both(520, 392, 136, "TN") == ((short, 1), w64)
+    assert both(8192, 8192, 256) == ((short, 1), (short, 1))                        # more than two 64x64 tiles to a unit
+    assert both(2085, 1051, 1280, "NT", pad=8) == ((small, 1), ("dma16p_128x128x32_w2x2_s5", 1))
+    assert both(1093, 64, 768, batch=31) == ((small, 1), w64) and both(1093, 64, 760, batch=31) == ((small, 1), (small, 1))
+    assert both(256, 256, 256, dtype=wl.F32) == ((f32, 1), ("f32_16x32x32_wk8", 1))
+    plan, launched = both(268, 228, 3592, "TN", dtype=wl.F32)
+    assert plan[0] == f32 and launched == ("f32_16x32x32_wk8", 1)
+    assert both(512, 512, 512, dtype=wl.F32)[1] == ("f32_32x32x32_wk8", 1)
+    assert both(1024, 1024, 1024, dtype=wl.F32) == ((f32, 1), (f32, 1))             # four 32x32 tiles to a unit
+    assert both(16, 3032, 264, "NT") == (("skinny_nt_16x16_w4", 1), w16)
+    plan, launched = both(38, 5552, 1200, "NT", pad=8)
+    assert plan[0] == "dma16p_128x128x32_w2x2_s5" and plan[1] > 1 and launched == w64
+    plan, launched = both(335, 75, 629, "NN")
+    assert plan == ("general_128x128x64_w2x2", 4) and launched[0].startswith("general_wavek_") and launched[1] == 1
+    assert both(335, 75, 629, "NN", out=wl.F32)[1][0] == "general_128x128x64_w2x2"      # a 32-bit result keeps slices and folds
+
+
+def test_query_argument_errors():
+    ok = (256, 1, 64, 64, 64, 0, 0, wl.BF16, wl.BF16, 64, 64, 64)
+    assert isinstance(lg.gemm_launch_query(*ok, check=False), tuple)
+    assert lg.gemm_launch_query(*ok, False, 9, check=False) == lg.GEMM_ERR_INVALID_ARG
+    assert lg.gemm_launch_query(0, *ok[1:], check=False) == lg.GEMM_ERR_INVALID_ARG
+    assert lg.gemm_launch_query(*ok[:8], wl.F16, *ok[9:], check=False) == lg.GEMM_ERR_UNSUPPORTED
+
+
+def test_invariants_over_random_calls():
+    """Either the plan itself or one launch of a kernel that serves the call: its operand types, a row-major A for the 16-row tiles."""
+    rng = random.Random(11)
+    dims = [1, 7, 8, 16, 24, 64, 100, 128, 136, 250, 520, 1024, 1368, 2056, 4096, 6696]
+    for _ in range(4000):
+        M, N, K = rng.choice(dims), rng.choice(dims), rng.choice(dims)
+        ta, tb = rng.randint(0, 1), rng.randint(0, 1)
+        dtype = rng.choice([wl.BF16, wl.F16, wl.F32])
+        out, batch, pad = rng.choice([dtype, wl.F32]), rng.choice([1, 1, 5]), rng.choice([0, 0, 8, 3])
+        call = (256, batch, M, N, K, ta, tb, dtype, out, (M if ta else K) + pad, (K if tb else N) + pad, N)
+        plan, launched = lg.gemm_plan_query(*call), lg.gemm_launch_query(*call)
+        if launched == plan:
+            continue
+        name = lg.gemm_variant_name(*launched[:2])
+        assert launched[2] == 1 and (plan[0] == GENERAL) == (launched[0] == GENERAL), call
+        assert name.startswith("f32_") == (dtype == wl.F32), call
+        assert not (ta and "wavek_16x" in name), call
+        assert launched[0] != GENERAL or (out != wl.F32 and (M >= 8 if ta else K >= 8) and (K >= 8 if tb else N >= 8)), call
