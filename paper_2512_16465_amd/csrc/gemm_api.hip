@@ -371,9 +371,10 @@ int wave_f32_variant(const Args& a, int slices, int num_cus) {
 // Few rows whose plan is the narrow streaming kernel (one launch), a wide streaming kernel in slices or the quartered tile in
 // shares run, in one launch, on the 16x64 or 64x64 tile whose waves divide the k range, where that is ahead (-1: it isn't): a workgroup of it
 // reads 64 columns of the weight once, where the narrow kernel's has 16 (four times as many workgroups, the first products 5 us after the
-// launch) and slices and shares need a second launch.  A unit streams about 30 GB/s from memory however many waves ask, so what leaves units idle or
-// has more than one workgroup to a unit is left where it is, and so is K beyond 8192 (NN 5000), where four waves' walk is the longer one.  A
-// row-major weight with a pitch of whole 512 bytes is too: the k-rows of a slab fall on few memory channels (31x2560x4864 18.8 us here, 15 in shares).
+// launch) and slices and shares need a second launch.  A unit streams about 30 GB/s from memory however many waves ask, so what has fewer than 48
+// workgroups (64 with a row-major weight, 96 with fewer than 96 columns of tiles and K beyond 4096; 80 of 64 rows, 200 for the wide kernels) or more than one to a unit
+// is left where it is, and so is K beyond 8192 (NN 5000), where four waves' walk is the longer one.  A
+// row-major weight with a pitch of whole 512 bytes is too, from K = 3000 on (the wide kernel's slices: 5000): the k-rows of a slab fall on few memory channels (31x2560x4864 18.8 us here, 15 in shares).
 // - streaming kernels in slices, up to 16 rows: from 200 workgroups on, always (30 random calls, 1.13 to 1.20 times as fast on average; 7 % ahead at
 //   the least up to K = 7000: 16x16384x4096 NN 32.4 -> 29, 8x15296x5184 NN 35.7 -> 27.5, 12x12288x4096 NT 24.8 -> 24).
 // - the others by estimates in us, fitted to 423 random calls with 16-row tiles and 514 with 64-row tiles (half within 5 to 7 %, nine of ten within 11 to
@@ -382,9 +383,11 @@ int wave_f32_variant(const Args& a, int slices, int num_cus) {
 //   a long k or a row-major weight a unit's own rate shows (26x3304x4544 NN 15.3 against 13.1, 5x5120x5120 NT
 //   19.1 against 17.8 on 80).  Of 450 other random calls whose route this changed (1.25 times
 //   as fast on average) seven were more than 4 % slower, 12 % the worst (16x6696x4112).
-int few_rows_wave_tile(const Args& a, const gemm_plan_t& plan) {
+// Workgroups are counted against the 256 units of the whole part, on which all of this was measured; on a partition of it the plan stays.
+constexpr int64_t kFewRowsUnits = 256;
+int few_rows_wave_tile(const Args& a, const gemm_plan_t& plan, int64_t cus) {
     constexpr int kQuarter = 16, kNarrow = 5, kWideRowMajor = 0, kWide = 1, kFewRows = 19, kManyRows = 18;
-    if (a.transA || a.batch != 1 || a.M > 64 || a.K > (a.transB ? 8192 : 5000 + 3192 * (plan.kernel == GEMM_KERNEL_SKINNY))) return -1;
+    if (cus != kFewRowsUnits || a.transA || a.batch != 1 || a.M > 64 || a.K > (a.transB ? 8192 : 5000 + 3192 * (plan.kernel == GEMM_KERNEL_SKINNY))) return -1;
     if (a.dtype == gemm::DT_F32 || !gemm::tile_supports(a) || !gemm::tile_variant_supports(a, kManyRows)) return -1;
     const int64_t columns = (a.N + 63) / 64, tiles = ((a.M + 15) / 16) * columns;
     const bool pitch = !a.transB && a.ldb % 256 == 0;
@@ -628,7 +631,7 @@ gemm_plan_t kernel_of(const Args& a, const gemm_plan_t& plan, int split_first, i
     }
     if (plan.kernel == GEMM_KERNEL_MFMA_TILE && plan.variant == kF32SmallTileVariant) variant = wave_f32_variant(a, plan.split_k, num_cus);
     else if (plan.kernel == GEMM_KERNEL_MFMA_TILE && plan.split_k == 1) variant = gemm::whole_tile_variant(a, plan.variant, num_cus);
-    else if (plan.kernel == GEMM_KERNEL_SKINNY || split_first == 0) variant = few_rows_wave_tile(a, plan);
+    else if (plan.kernel == GEMM_KERNEL_SKINNY || split_first == 0) variant = few_rows_wave_tile(a, plan, num_cus);
     return variant >= 0 ? gemm_plan_t{GEMM_KERNEL_MFMA_TILE, variant, 1} : plan;
 }
 

@@ -37,6 +37,20 @@ def test_plans_that_are_launched_as_wave_tiles():
     assert both(335, 75, 629, "NN", out=wl.F32)[1][0] == "general_128x128x64_w2x2"      # a 32-bit result keeps slices and folds
 
 
+def test_the_substitution_counts_the_units_of_the_device():
+    """The same tiles on half or an eighth of the part: more of them to a unit than the wave tiles are ahead with, and no few-row rule, whose
+    limits are workgroups on 256 units."""
+    assert both(1024, 1024, 1024, cus=128)[1] == ("wavek_64x64x64_w4", 1)                     # 256 tiles of 64x64, two to a unit
+    assert both(1536, 1024, 1024, cus=256)[1] == ("wavek_64x64x64_w4", 1)
+    for cus in (32, 128):
+        plan, launched = both(1536, 1024, 1024, cus=cus)
+        assert launched == plan, (cus, launched)
+        for call in [(16, 3032, 264, "NT"), (54, 1000, 688, "NN"), (38, 5552, 1200, "NT"), (14, 13128, 5112, "NT")]:
+            plan, launched = both(*call, cus=cus, pad=8)
+            assert launched == plan or plan[0].startswith("dma_"), (cus, call, plan, launched)
+    assert both(512, 512, 512, dtype=wl.F32, cus=64)[1] == ("f32_64x64x32_w2x2", both(512, 512, 512, dtype=wl.F32, cus=64)[0][1])
+
+
 def test_query_argument_errors():
     ok = (256, 1, 64, 64, 64, 0, 0, wl.BF16, wl.BF16, 64, 64, 64)
     assert isinstance(lg.gemm_launch_query(*ok, check=False), tuple)
