@@ -280,8 +280,8 @@ gemm_status_t gemm_plan_query(int32_t compute_units, int64_t batch, int64_t M, i
                               gemm_op_t transA, gemm_op_t transB, gemm_dtype_t dtype, gemm_dtype_t out_dtype,
                               int64_t lda, int64_t ldb, int64_t ldc, gemm_plan_t* out);
 
-/* What gemm_get_last_launch would report of that call, made with beta != 0 (`reads_c`) and the activation `act`, which weigh in where
- * two kernels are close.  Host arithmetic only.  Errors: as gemm_plan_query; GEMM_ERR_INVALID_ARG for an unknown `act`. */
+/* What gemm_get_last_launch would report of that call, made without a bias, with beta != 0 (`reads_c`) and the activation `act`: the
+ * epilogue weighs in where two kernels are close.  Host arithmetic only.  Errors: as gemm_plan_query; GEMM_ERR_INVALID_ARG for an unknown `act`. */
 gemm_status_t gemm_launch_query(int32_t compute_units, int64_t batch, int64_t M, int64_t N, int64_t K,
                                 gemm_op_t transA, gemm_op_t transB, gemm_dtype_t dtype, gemm_dtype_t out_dtype,
                                 int64_t lda, int64_t ldb, int64_t ldc, int32_t reads_c, gemm_act_t act, gemm_plan_t* out);

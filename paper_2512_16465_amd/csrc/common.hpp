@@ -198,6 +198,8 @@ constexpr int64_t kF32PairAbove = 256;
 // The tiles with the k range divided among a workgroup's waves (kind 6): the faster variant by their estimates, and its time in us, for
 // a 16-bit call on a grid too small for the 128x128 tile; -1 where the grid or the operands are too large for them.
 int wave_tile_for(const Args& a, int64_t cus, double* estimate);
+// Whether a call planned on whole 128x128 tiles stays on them where wave_tile_for gives a wave tile.
+bool whole_128_tiles_ahead(const Args& a, int64_t cus);
 // The variant that an automatic call planned on whole 128x128 tiles (5 or 12) is launched on, -1: the planned one.
 int whole_tile_variant(const Args& a, int variant, int64_t cus);
 // `variant` but for 19 with A stored K x M, whose k-rows are moved in whole lines: 64 rows to a tile, variant 18.

@@ -425,7 +425,10 @@ TileChoice choose_tile(const Args& a, int num_cus) {
     const int wave_tile = gemm::wave_tile_for(a, cus, &time);
     if (wave_tile < 0) return c;
     if (c.variant == kSmallTileVariant || c.variant == kSmallTileShortK) {
-        if (c.parts == 1) { c.time = time; return c; }                       // (launch_tile takes the wave tiles for it)
+        if (c.parts == 1) {      // (launched on the wave tile: kernel_of)
+            if (!gemm::whole_128_tiles_ahead(a, cus)) c.time = time;
+            return c;
+        }
         if (a.K >= kLongSlicedK) return c;
     } else if (c.variant != kQuarterTile.variant) {
         return c;

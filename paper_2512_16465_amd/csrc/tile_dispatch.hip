@@ -122,9 +122,20 @@ constexpr int64_t kLongK = 1280;
 // 0.88 to 1.2.
 constexpr int64_t kNarrowK = 768;
 
+// C = alpha op(A) op(B) and nothing else on whole 128x128 tiles leaves that kernel straight from its registers.  There the wave tiles, which add their sums through
+// LDS first, are level at best up to K = 128 (batch of 21 256x256x64 NT 4.8 us against 6.0, of 5 512x512x128 5.2 against 6.2), and beyond one of them to a unit up to
+// K = 1536 (batch of 17 512x128x512 NN 7.9 against 9.8, 3072x384x256 NT 6.0 against 6.6): 247 such random calls 1.03 times as long on them, up to 1.39.
+// Ragged tiles, a C that is read, a bias or an activation take the staged epilogue, and the wave tiles are ahead of it.
+constexpr int64_t kWholeShortK = 128, kWholeK = 1536;
+
+bool whole_128_tiles_ahead(const Args& a, int64_t cus) {
+    if (a.beta != 0.0f || a.bias || a.act != ACT_NONE || a.M % 128 || a.N % 128) return false;
+    return a.M / 64 * (a.N / 64) * a.batch > cus ? a.K < kWholeK : a.K <= kWholeShortK;
+}
+
 int whole_tile_variant(const Args& a, int variant, int64_t cus) {
     if (variant != 5 && variant != 12) return -1;
-    const int wave_tile = wave_tile_for(a, cus, nullptr);
+    const int wave_tile = whole_128_tiles_ahead(a, cus) ? -1 : wave_tile_for(a, cus, nullptr);
     if (wave_tile >= 0) return wave_tile;
     if (variant == 5 && !a.transA && a.N <= 64 && a.K >= kNarrowK && tile_variant_supports(a, 18)) return 18;
     return !a.transA && a.transB && a.K >= kLongK && tile_variant_supports(a, 16) ? 16 : -1;

@@ -37,13 +37,25 @@ def test_plans_that_are_launched_as_wave_tiles():
     assert both(335, 75, 629, "NN", out=wl.F32)[1][0] == "general_128x128x64_w2x2"      # a 32-bit result keeps slices and folds
 
 
+def test_whole_tiles_that_leave_straight_from_the_registers():
+    """C = alpha A B on whole 128x128 tiles: the wave tiles only with a k loop long enough to pay for the sums' way through LDS."""
+    w64 = ("wavek_64x64x64_w4", 1)
+    for call, batch in [((256, 256, 64, "NT"), 21), ((512, 512, 128, "NT"), 5), ((512, 128, 512, "NN"), 17), ((3072, 384, 256, "NT"), 1), ((512, 2560, 256, "NT"), 1)]:
+        plan, launched = both(*call, batch=batch)
+        assert launched == plan and plan[0].startswith("dma_128x128x32"), (call, plan, launched)
+        assert both(*call, batch=batch, act=wl.ACT_SILU)[1][0].startswith("wavek_") and both(*call, batch=batch, reads_c=True)[1][0].startswith("wavek_"), call
+    assert both(512, 512, 136, "NT", batch=4)[1] == w64 and both(512, 640, 128, "NT", batch=4)[1] != w64      # up to one tile to a unit: K > 128
+    assert both(1536, 1024, 1536)[1] == w64 and both(1536, 1024, 1528)[1] != w64                              # beyond: from 1536 on
+    assert both(504, 512, 64, "NT", batch=5)[1] == w64                                                        # ragged
+
+
 def test_the_substitution_counts_the_units_of_the_device():
     """The same tiles on half or an eighth of the part: more of them to a unit than the wave tiles are ahead with, and no few-row rule, whose
     limits are workgroups on 256 units."""
-    assert both(1024, 1024, 1024, cus=128)[1] == ("wavek_64x64x64_w4", 1)                     # 256 tiles of 64x64, two to a unit
-    assert both(1536, 1024, 1024, cus=256)[1] == ("wavek_64x64x64_w4", 1)
+    assert both(1016, 1024, 1024, cus=128)[1] == ("wavek_64x64x64_w4", 1)                     # 256 tiles of 64x64, two to a unit
+    assert both(1528, 1024, 1024, cus=256)[1] == ("wavek_64x64x64_w4", 1)
     for cus in (32, 128):
-        plan, launched = both(1536, 1024, 1024, cus=cus)
+        plan, launched = both(1528, 1024, 1024, cus=cus)
         assert launched == plan, (cus, launched)
         for call in [(16, 3032, 264, "NT"), (54, 1000, 688, "NN"), (38, 5552, 1200, "NT"), (14, 13128, 5112, "NT")]:
             plan, launched = both(*call, cus=cus, pad=8)
