@@ -381,8 +381,10 @@ int wave_f32_variant(const Args& a, int slices, int num_cus) {
 //   17 %), by a margin of 5 %.  On such calls 1.17 to 1.18 times as fast on average with 16 rows (the faster one in hindsight 1.18 to 1.19) and 1.06 to 1.10 with
 //   64: 12x8192x2048 12 -> 8, 7x9920x2176 15.9 -> 9.6, 46x8128x2944 NN 18.1 -> 13.3, 61x2624x4480 NN 16.2 -> 11; with fewer than 64 workgroups of
 //   a long k or a row-major weight a unit's own rate shows (26x3304x4544 NN 15.3 against 13.1, 5x5120x5120 NT
-//   19.1 against 17.8 on 80).  Of 450 other random calls whose route this changed (1.25 times
-//   as fast on average) seven were more than 4 % slower, 12 % the worst (16x6696x4112).
+//   19.1 against 17.8 on 80).  On a weight that
+//   the caches do not hold the narrow kernel's four times as many workgroups draw more: with fewer than 128 here and a long k (149 of 1010 random calls; with K
+//   no multiple of 64 each visit's lines are asked for twice) these tiles took 1.19 times as long from memory and 0.95 from the last-level cache, and it stays:
+//   9x6693x4656 19.7 us, 25.6 here, 13x4045x3840 12.2 / 16.6, 16x6696x4112 12 % longer here out of the caches too.
 // Workgroups are counted against the 256 units of the whole part, on which all of this was measured; on a partition of it the plan stays.
 constexpr int64_t kFewRowsUnits = 256;
 int few_rows_wave_tile(const Args& a, const gemm_plan_t& plan, int64_t cus) {
@@ -395,6 +397,7 @@ int few_rows_wave_tile(const Args& a, const gemm_plan_t& plan, int64_t cus) {
     if (plan.kernel == GEMM_KERNEL_SKINNY && (plan.variant == kWideRowMajor || plan.variant == kWide))
         return plan.split_k > 1 && a.M <= 16 && tiles >= 200 && tiles <= 256 && a.K <= 7000 && !(pitch && a.K >= 5000) ? kFewRows : -1;
     const bool narrow = plan.kernel == GEMM_KERNEL_SKINNY;
+    if (narrow && columns < 128 && (a.K % 64 ? a.K >= 1500 : columns < 64 && a.K >= 2500)) return -1;
     if (narrow ? plan.variant != kNarrow || plan.split_k != 1 || !a.transB : plan.variant != kQuarter || plan.split_k == 1) return -1;
     if (pitch && a.K >= 3000) return -1;
     const int straddling = (a.K % 64 != 0) + ((a.transB ? a.K : a.N) % 64 != 0);      // operands whose 128-byte pieces lie in two lines

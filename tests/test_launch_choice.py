@@ -49,6 +49,15 @@ def test_whole_tiles_that_leave_straight_from_the_registers():
     assert both(504, 512, 64, "NT", batch=5)[1] == w64                                                        # ragged
 
 
+def test_narrow_streams_of_a_long_k_on_few_units():
+    """5 to 16 rows on a weight stored N x K: fewer workgroups than half the units draw too little from memory for a long k."""
+    narrow, w16 = ("skinny_nt_16x16_w4", 1), ("wavek_16x64x64_w4", 1)
+    for call in [(16, 6696, 4112), (9, 6693, 4656), (13, 4045, 3848), (7, 7703, 2552), (8, 4000, 2560), (10, 3999, 3584)]:
+        assert both(*call, "NT") == (narrow, narrow), call
+    for call in [(16, 6696, 1496), (8, 8200, 3336), (8, 4096, 2560), (8, 4000, 2496), (10, 3999, 1032)]:
+        assert both(*call, "NT") == (narrow, w16), call
+
+
 def test_the_substitution_counts_the_units_of_the_device():
     """The same tiles on half or an eighth of the part: more of them to a unit than the wave tiles are ahead with, and no few-row rule, whose
     limits are workgroups on 256 units."""
