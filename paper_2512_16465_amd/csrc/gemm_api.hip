@@ -260,7 +260,14 @@ double f32_time(const Args& a, bool big, int slices, int64_t cus) {
 // (geometric), more than 3 % slower on three (960x512x4096 TN 18.2 against 16.8 us the worst).  Cut as before:
 // long k ranges in slices, which put them on more units than a tile's waves are (128x1024x8192: 15 against 19.8), and a single strip
 // or two of 33 to 64 rows, whose weights three or four tiles of 16 rows would each read.
-constexpr int64_t kLongSlicedK = 4096, kFewWaveTiles = 16;
+// With a row-major weight, fewer 16-row tiles than half the units and K beyond 5000 (4096 where rows start inside a line) the shares draw more from memory than these few
+// workgroups do (26 random calls: 1.24 times as long here from memory, 0.91 out of the last-level cache), and with A stored K x M the shares are ahead beyond 4096
+// (3584x256x6144 TN 21 us against 24.9, 904x1024x5632 TT 20.4 against 23.5).
+constexpr int64_t kLongSlicedK = 4096, kFewWaveTiles = 16, kLongRowMajorK = 5000;
+
+bool row_major_stream_on_few_units(const Args& a, int64_t tiles, int64_t cus) {
+    return !a.transB && 2 * tiles < cus && a.K > (a.K % 64 || a.N % 64 ? kLongSlicedK : kLongRowMajorK);
+}
 
 TileChoice choose_shared_k_tile(const Args& a, int num_cus) {
     const int64_t cus = num_cus > 0 ? num_cus : 256;
@@ -399,7 +406,7 @@ int few_rows_wave_tile(const Args& a, const gemm_plan_t& plan, int64_t cus) {
     const bool narrow = plan.kernel == GEMM_KERNEL_SKINNY;
     if (narrow && columns < 128 && (a.K % 64 ? a.K >= 1500 : columns < 64 && a.K >= 2500)) return -1;
     if (narrow ? plan.variant != kNarrow || plan.split_k != 1 || !a.transB : plan.variant != kQuarter || plan.split_k == 1) return -1;
-    if (pitch && a.K >= 3000) return -1;
+    if ((pitch && a.K >= 3000) || row_major_stream_on_few_units(a, tiles, cus)) return -1;
     const int straddling = (a.K % 64 != 0) + ((a.transB ? a.K : a.N) % 64 != 0);      // operands whose 128-byte pieces lie in two lines
     const double beyond = weight > 30.0 ? weight - 30.0 : 0.0, uncached = weight > 72.0 ? weight - 72.0 : 0.0;
     const double partial = (double)(a.M * a.N * plan.split_k) * 8e-6;
@@ -433,9 +440,10 @@ TileChoice choose_tile(const Args& a, int num_cus) {
             return c;
         }
         if (a.K >= kLongSlicedK) return c;
-    } else if (c.variant != kQuarterTile.variant) {
+    } else if (c.variant != kQuarterTile.variant || (c.parts > 1 && a.transA && a.K > kLongSlicedK)) {
         return c;
     }
+    if (c.parts > 1 && !a.transA && row_major_stream_on_few_units(a, ((a.M + 15) / 16) * ((a.N + 63) / 64), cus)) return c;
     if (c.parts > 1 && a.M > 32 && ((a.M + 63) / 64) * ((a.N + 63) / 64) <= kFewWaveTiles) return c;
     return c.parts == 1 || time < c.time ? TileChoice{wave_tile, 0, 1, time} : c;
 }

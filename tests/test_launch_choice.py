@@ -58,6 +58,15 @@ def test_narrow_streams_of_a_long_k_on_few_units():
         assert both(*call, "NT") == (narrow, w16), call
 
 
+def test_shares_of_a_long_k_stay():
+    """Where few workgroups would stream a row-major weight, and with A stored K x M."""
+    quarter, w64 = "dma16p_128x128x32_w2x2_s5", ("wavek_64x64x64_w4", 1)
+    for call in [(16, 1000, 4936, "NN"), (30, 2048, 5184, "NN"), (40, 2504, 4168, "NN"), (3584, 256, 6144, "TN"), (904, 1024, 5632, "TT")]:
+        plan, launched = both(*call)
+        assert plan[0] == quarter and plan[1] > 1 and launched == plan, (call, plan, launched)
+    assert both(30, 2048, 4096, "NN")[1] == ("wavek_16x64x64_w4", 1) and both(904, 1024, 4096, "TT")[1] == w64
+
+
 def test_the_substitution_counts_the_units_of_the_device():
     """The same tiles on half or an eighth of the part: more of them to a unit than the wave tiles are ahead with, and no few-row rule, whose
     limits are workgroups on 256 units."""
