@@ -67,6 +67,16 @@ def test_shares_of_a_long_k_stay():
     assert both(30, 2048, 4096, "NN")[1] == ("wavek_16x64x64_w4", 1) and both(904, 1024, 4096, "TT")[1] == w64
 
 
+def test_calls_off_the_grid_that_stay_on_the_128_tile():
+    tiles = "general_128x128x64_w2x2"
+    for call in [(2711, 1985, 131, "NN"), (1711, 2679, 157, "NT")]:                       # more than two rounds of 64x64 tiles, a promise of less than 10 %
+        assert both(*call) == ((tiles, 1), (tiles, 1)), call
+    for call in [(9, 6015, 4201, "NT"), (5, 5501, 4101, "NT"), (5, 6079, 5001, "NT")]:   # few workgroups on a long k
+        plan, launched = both(*call)
+        assert plan[0] == tiles and plan[1] > 1 and launched == plan, (call, plan, launched)
+    assert both(9, 6079, 4095, "NT")[1][0] == "general_wavek_16x64x64_w4" and both(5, 6145, 5001, "NT")[1][0] == "general_wavek_16x64x64_w4"
+
+
 def test_the_substitution_counts_the_units_of_the_device():
     """The same tiles on half or an eighth of the part: more of them to a unit than the wave tiles are ahead with, and no few-row rule, whose
     limits are workgroups on 256 units."""
