@@ -114,7 +114,8 @@ int wave_tile_for(const Args& a, int64_t cus, double* estimate) {
 // (variant 16, 16x16x32 products, its slabs requested in pairs), which waits less per slab and has the longer fill (1216x2752x1024 14.6 -> 15.3); the sums are the same to the bit.  Of 165 random calls of 512 to 1600
 // 64x64 tiles it is 1.07 times as fast on average for K 1024 to 1536 and 1.10 beyond (600x4024x4264 59.7 -> 51 us,
 // 1648x1872x6224 80.8 -> 68, 2120x1376x3304 53.7 -> 44; 6 % slower on one of 58), 1.02 for K 512 to 768, 1.02 to 1.04 with a
-// row-major B (two of 32 4 % slower), 0.94 to 0.97 with A stored KxM.
+// row-major B (two of 32 4 % slower), 0.94 to 0.97 with A stored KxM.  With more than two and up to two and a half tiles to a unit it is level (20
+// random calls) and loses where few of the third are there (1856x80x1856, batch of 39, 69.6 -> 80.7 us, of 43 1696x80x1696 65 -> 71): variant 5 stays.
 constexpr int64_t kLongK = 1280;
 // Up to 64 columns to a matrix the 128x128 tile is at least half empty, and the 64x64 wave tile is ahead at any number of tiles, with A row-major
 // and K from 768 on: 17 random calls, batches of attention's second product most of them, 1.09 times as fast on average (1160x64x1160 NN, batch of
@@ -138,7 +139,9 @@ int whole_tile_variant(const Args& a, int variant, int64_t cus) {
     const int wave_tile = whole_128_tiles_ahead(a, cus) ? -1 : wave_tile_for(a, cus, nullptr);
     if (wave_tile >= 0) return wave_tile;
     if (variant == 5 && !a.transA && a.N <= 64 && a.K >= kNarrowK && tile_variant_supports(a, 18)) return 18;
-    return !a.transA && a.transB && a.K >= kLongK && tile_variant_supports(a, 16) ? 16 : -1;
+    const int64_t tiles = ((a.M + 127) / 128) * ((a.N + 127) / 128) * a.batch;
+    const bool thin_third_round = tiles > 2 * cus && 2 * tiles <= 5 * cus;
+    return !a.transA && a.transB && a.K >= kLongK && !thin_third_round && tile_variant_supports(a, 16) ? 16 : -1;
 }
 
 int tile_variant_for_layout(const Args& a, int variant) { return variant == 19 && a.transA ? 18 : variant; }

@@ -23,6 +23,8 @@ def test_plans_that_are_launched_as_wave_tiles():
     assert both(520, 392, 136, "TN") == ((short, 1), w64)
     assert both(8192, 8192, 256) == ((short, 1), (short, 1))                        # more than two 64x64 tiles to a unit
     assert both(2085, 1051, 1280, "NT", pad=8) == ((small, 1), ("dma16p_128x128x32_w2x2_s5", 1))
+    assert both(1856, 80, 1856, "NT", batch=39) == ((small, 1), (small, 1))         # 585 tiles: a thin third round of them
+    assert both(1856, 80, 1856, "NT", batch=44) == ((small, 1), ("dma16p_128x128x32_w2x2_s5", 1))
     assert both(1093, 64, 768, batch=31) == ((small, 1), w64) and both(1093, 64, 760, batch=31) == ((small, 1), (small, 1))
     assert both(256, 256, 256, dtype=wl.F32) == ((f32, 1), ("f32_16x32x32_wk8", 1))
     plan, launched = both(268, 228, 3592, "TN", dtype=wl.F32)
