@@ -261,11 +261,14 @@ double f32_time(const Args& a, bool big, int slices, int64_t cus) {
 // long k ranges in slices, which put them on more units than a tile's waves are (128x1024x8192: 15 against 19.8), and a single strip
 // or two of 33 to 64 rows, whose weights three or four tiles of 16 rows would each read.
 // With a row-major weight, fewer 16-row tiles than half the units and K beyond 5000 (4096 where rows start inside a line) the shares draw more from memory than these few
-// workgroups do (26 random calls: 1.24 times as long here from memory, 0.91 out of the last-level cache), and with A stored K x M the shares are ahead beyond 4096
+// workgroups do (26 random calls: 1.24 times as long here from memory, 0.91 out of the last-level cache); so do they from K = 3000 on with fewer tiles than a
+// quarter of the units and a pitch of whole 512 bytes, the k-rows of a slab on few memory channels (23 calls: 1.25 and 0.87; 10x2560x3328 13.8 us against 22.5 from memory, 12.3
+// against 14.4).  With A stored K x M the shares are ahead beyond K = 4096
 // (3584x256x6144 TN 21 us against 24.9, 904x1024x5632 TT 20.4 against 23.5).
 constexpr int64_t kLongSlicedK = 4096, kFewWaveTiles = 16, kLongRowMajorK = 5000;
 
 bool row_major_stream_on_few_units(const Args& a, int64_t tiles, int64_t cus) {
+    if (!a.transB && 4 * tiles < cus && a.ldb % 256 == 0 && a.K >= 3000) return true;
     return !a.transB && 2 * tiles < cus && a.K > (a.K % 64 || a.N % 64 ? kLongSlicedK : kLongRowMajorK);
 }
 

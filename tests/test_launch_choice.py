@@ -66,7 +66,11 @@ def test_shares_of_a_long_k_stay():
     for call in [(16, 1000, 4936, "NN"), (30, 2048, 5184, "NN"), (40, 2504, 4168, "NN"), (3584, 256, 6144, "TN"), (904, 1024, 5632, "TT")]:
         plan, launched = both(*call)
         assert plan[0] == quarter and plan[1] > 1 and launched == plan, (call, plan, launched)
-    assert both(30, 2048, 4096, "NN")[1] == ("wavek_16x64x64_w4", 1) and both(904, 1024, 4096, "TT")[1] == w64
+    for call in [(10, 2560, 3328, "NN"), (6, 2560, 3072, "NN"), (5, 1024, 4864, "NN")]:                # rows of the weight 512 bytes apart, or a multiple
+        plan, launched = both(*call)
+        assert plan[0] == quarter and plan[1] > 1 and launched == plan, (call, plan, launched)
+    assert both(10, 2568, 3328, "NN")[1] == ("wavek_16x64x64_w4", 1) and both(10, 2560, 2944, "NN")[1] == ("wavek_16x64x64_w4", 1)
+    assert both(30, 2040, 4096, "NN")[1] == ("wavek_16x64x64_w4", 1) and both(904, 1024, 4096, "TT")[1] == w64
 
 
 def test_calls_off_the_grid_that_stay_on_the_128_tile():
