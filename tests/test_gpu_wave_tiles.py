@@ -239,6 +239,15 @@ def test_whole_128x128_tiles_of_a_long_k(handle, K, launched):
         assert np.all(np.isnan(oracle.decode(wl.F32, np.ascontiguousarray(got[:-1, N:]))))
 
 
+@pytest.mark.parametrize("M,N,K,dtype", [(2085, 1051, 1304, wl.BF16), (200, 328, 4104, wl.F16)])
+def test_the_two_pipelines_of_the_128x128_tile_give_the_same_bits(handle, M, N, K, dtype):
+    """The ring of four (variant 5, products of 16 along k) and the quartered kernel (16, of 32): Gaussian data and a 32-bit result."""
+    cfg = wl.Config("w", M, N, K, 0, 1, dtype, wl.F32, a_dist=("normal", 1.0), b_dist=("normal", 0.05), ldb=K + 16, ldc=N + 3)
+    inp = wl.make_inputs(cfg, K)
+    a, b = (np.ascontiguousarray(run(handle, cfg, inp, (TILE, v, 1))[0][:, :N]).view(np.uint32) for v in (5, 16))
+    assert np.array_equal(a, b), int((a != b).sum())
+
+
 @pytest.mark.parametrize("K,N,tb,launched", [(760, 64, 0, 5), (768, 64, 0, 18), (776, 48, 0, 18), (776, 37, 1, 18)])
 def test_batches_of_up_to_64_columns_beyond_two_rounds(handle, K, N, tb, launched):
     M, batch = 1093, 31
