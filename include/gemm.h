@@ -246,16 +246,18 @@ typedef struct {
                              * second kernel; this needs N to be a multiple of 8.  Batched calls, and
                              * calls that miss that condition, return GEMM_ERR_UNSUPPORTED.  Slices
                              * are added in a fixed order: results do not vary from run to run. */
-    /* Several automatic plans are launched, whatever their slices, as one kernel whose waves divide the k range, or on another pipeline
-     * of the same tile, for the calls in which that is faster: the whole 128x128 tiles (variants 5 and 12), the fp32 64x64 tiles (13), the 128x128
-     * tiles in shares (16) and the streaming variants 0, 1 and 5 with up to 64 rows, and the general family's variant 1.  The
-     * plan, its errors and the workspace it asks for stay as described; gemm_get_last_launch names the kernel. */
+    /* Several automatic plans are launched, whatever their slices, as one kernel whose waves divide the
+     * k range, or on another pipeline of the same tile, for the calls in which that is faster: the whole
+     * 128x128 tiles (variants 5 and 12), the fp32 64x64 tiles (13), the 128x128 tiles in shares (16) and
+     * the streaming variants 0, 1 and 5 with up to 64 rows, and the general family's variant 1.  The plan,
+     * its errors and the workspace it asks for stay as described; gemm_get_last_launch names the kernel. */
 } gemm_plan_t;
 
 /* Forces the plan used by later gemm_run calls on this handle; a NULL plan restores automatic
- * choice.  A forced plan runs the kernel that it names (tile variant 19 with A stored K x M: variant 18, the same with 64 rows to a
- * tile); variant -1 leaves the choice within the family open.  A forced plan that cannot run a given call (alignment, shape)
- * makes that call return GEMM_ERR_UNSUPPORTED.  Errors: GEMM_ERR_INVALID_ARG for a null handle or out-of-range fields. */
+ * choice.  A forced plan runs the kernel that it names (tile variant 19 with A stored K x M: variant
+ * 18, the same with 64 rows to a tile); variant -1 leaves the choice within the family open.  A forced
+ * plan that cannot run a given call (alignment, shape) makes that call return GEMM_ERR_UNSUPPORTED.
+ * Errors: GEMM_ERR_INVALID_ARG for a null handle or out-of-range fields. */
 gemm_status_t gemm_set_plan(gemm_handle_t h, const gemm_plan_t* plan);
 
 /* Reports the plan the most recent successful gemm_run on this handle used, whether its slices ran side by side or, for want of
@@ -265,8 +267,9 @@ gemm_status_t gemm_set_plan(gemm_handle_t h, const gemm_plan_t* plan);
  * Errors: GEMM_ERR_INVALID_ARG for null arguments. */
 gemm_status_t gemm_get_last_plan(gemm_handle_t h, gemm_plan_t* out);
 
-/* Reports the kernel that the most recent successful gemm_run on this handle was launched on, as a plan that can be forced: that
- * of gemm_get_last_plan, or the kernel that took its place in one launch (see gemm_plan_t).  Errors: as gemm_get_last_plan. */
+/* Reports the kernel that the most recent successful gemm_run on this handle was launched on, as a plan
+ * that can be forced: that of gemm_get_last_plan, or the kernel that took its place in one launch (see
+ * gemm_plan_t).  Errors: as gemm_get_last_plan. */
 gemm_status_t gemm_get_last_launch(gemm_handle_t h, gemm_plan_t* out);
 
 /* The plan an automatic call of this shape would take on a device with `compute_units` compute
@@ -280,8 +283,9 @@ gemm_status_t gemm_plan_query(int32_t compute_units, int64_t batch, int64_t M, i
                               gemm_op_t transA, gemm_op_t transB, gemm_dtype_t dtype, gemm_dtype_t out_dtype,
                               int64_t lda, int64_t ldb, int64_t ldc, gemm_plan_t* out);
 
-/* What gemm_get_last_launch would report of that call, made without a bias, with beta != 0 (`reads_c`) and the activation `act`: the
- * epilogue weighs in where two kernels are close.  Host arithmetic only.  Errors: as gemm_plan_query; GEMM_ERR_INVALID_ARG for an unknown `act`. */
+/* What gemm_get_last_launch would report of that call, made without a bias, with beta != 0
+ * (`reads_c`) and the activation `act`: the epilogue weighs in where two kernels are close.
+ * Host arithmetic only.  Errors: as gemm_plan_query; GEMM_ERR_INVALID_ARG for an unknown `act`. */
 gemm_status_t gemm_launch_query(int32_t compute_units, int64_t batch, int64_t M, int64_t N, int64_t K,
                                 gemm_op_t transA, gemm_op_t transB, gemm_dtype_t dtype, gemm_dtype_t out_dtype,
                                 int64_t lda, int64_t ldb, int64_t ldc, int32_t reads_c, gemm_act_t act, gemm_plan_t* out);

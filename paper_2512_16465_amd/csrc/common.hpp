@@ -214,8 +214,9 @@ const char* skinny_variant_name(int variant);
 // variant < 0 stands for skinny_variant_of(a) everywhere below
 int skinny_variant_of(const Args& a);
 bool skinny_variant_serves(const Args& a, int variant);
-// For a call that the family refuses only because N is no multiple of 8: the one-launch variant (4 or 5) that serves it
-// without a split, -1 if there is none.  (The automatic choice may take it, and the plan that it reports can be forced; any other of the family stays refused.)
+// For a call that the family refuses only because N is no multiple of 8: the one-launch variant (4 or 5) that serves it without
+// a split, -1 if there is none.  (The automatic choice may take it, and the plan that it reports can be forced; any other of
+// the family stays refused.)
 int skinny_ragged_columns_variant(const Args& a);
 int skinny_max_split(const Args& a, int variant = -1);
 // bytes of fp32 workspace the skinny kernel needs for this split factor (0 when split_k == 1)

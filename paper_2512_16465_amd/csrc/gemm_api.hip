@@ -255,16 +255,17 @@ double f32_time(const Args& a, bool big, int slices, int64_t cus) {
 }
 
 // Where the choice below comes to a 128x128 tile, the tiles with the k range divided among the waves (see wave_tile_for) are
-// compared with it, whole or in parts: by their own estimate against that of the split or the slices, and in place of a whole 128x128 tile wherever
-// wave_tile_for gives one.  On 800 random calls of the sizes that a 128x128 tile used to take they are 18 % faster on average
-// (geometric), more than 3 % slower on three (960x512x4096 TN 18.2 against 16.8 us the worst).  Cut as before:
-// long k ranges in slices, which put them on more units than a tile's waves are (128x1024x8192: 15 against 19.8), and a single strip
-// or two of 33 to 64 rows, whose weights three or four tiles of 16 rows would each read.
-// With a row-major weight, fewer 16-row tiles than half the units and K beyond 5000 (4096 where rows start inside a line) the shares draw more from memory than these few
-// workgroups do (26 random calls: 1.24 times as long here from memory, 0.91 out of the last-level cache); so do they from K = 3000 on with fewer tiles than a
-// quarter of the units and a pitch of whole 512 bytes, the k-rows of a slab on few memory channels (23 calls: 1.25 and 0.87; 10x2560x3328 13.8 us against 22.5 from memory, 12.3
-// against 14.4).  With A stored K x M the shares are ahead beyond K = 4096
-// (3584x256x6144 TN 21 us against 24.9, 904x1024x5632 TT 20.4 against 23.5).
+// compared with it, whole or in parts: by their own estimate against that of the split or the slices, and in place of a whole
+// 128x128 tile wherever wave_tile_for gives one and whole_128_tiles_ahead does not keep it.  On the device, on random calls of
+// the sizes that a 128x128 tile used to take, they are 1.7 times as fast on average (geometric) in place of whole tiles (4600
+// calls, eleven more than 5 % behind, 14 % the worst) and 1.3 to 1.7 in place of shares and slices (2260; eight, 11 %).  Cut as
+// before: long k ranges in slices, which put them on more units than a tile's waves are (128x1024x8192: 15 against 19.8), and a
+// single strip or two of 33 to 64 rows, whose weights three or four tiles of 16 rows would each read. With a row-major weight,
+// fewer 16-row tiles than half the units and K beyond 5000 (4096 where rows start inside a line) the shares draw more from
+// memory than these few workgroups do (26 random calls: 1.24 times as long here from memory, 0.91 out of the last-level cache);
+// so do they from K = 3000 on with fewer tiles than a quarter of the units and a pitch of whole 512 bytes, the k-rows of a slab
+// on few memory channels (23 calls: 1.25 and 0.87; 10x2560x3328 13.8 us against 22.5 from memory, 12.3 against 14.4).  With A
+// stored K x M the shares are ahead beyond K = 4096 (3584x256x6144 TN 21 us against 24.9, 904x1024x5632 TT 20.4 against 23.5).
 constexpr int64_t kLongSlicedK = 4096, kFewWaveTiles = 16, kLongRowMajorK = 5000;
 
 bool row_major_stream_on_few_units(const Args& a, int64_t tiles, int64_t cus) {
@@ -353,12 +354,14 @@ TileChoice choose_shared_k_tile(const Args& a, int num_cus) {
     return TileChoice{slices == 1 && a.K <= kShortK ? kSmallTileShortK : kSmallTileVariant, 0, slices, t_small};
 }
 
-// An fp32 call that a plan gives to the 64x64 tiles, in whatever slices, runs in one launch on the tiles whose eight waves divide the k
-// range, 32x32 (variant 20) or 16x32 (21), where those promise to be ahead (-1: neither).  Estimates in us, fitted to 240 random calls each (half
-// within 4 %, nine of ten within 12 %).  On 600 random calls (M, N to 4096, K to 6000, batches) the choice is 1.31 times as fast on average
-// (geometric; in hindsight the fastest of all 1.34) and more than 3 % slower on none: 268x228x3592 TN 69 -> 18 us, 64x460x1152 23.7 -> 7.6 (N no multiple of 8, so never cut in
-// slices), 512^3 10.5 -> 7.0, 64x168x2752 16.8 -> 12.6, 256^3 8.2 -> 7.2.  Two workgroups of 32x32 to a unit are resident at once; beyond, the 64x64 tile
-// stages half as many elements per product (1016x2352x868 39 us against 48), and few columns with a long k are faster in slices.
+// An fp32 call that a plan gives to the 64x64 tiles, in whatever slices, runs in one launch on the tiles whose eight waves
+// divide the k range, 32x32 (variant 20) or 16x32 (21), where those promise to be ahead (-1: neither).  Estimates in us, fitted
+// to 240 random calls each (half within 4 %, nine of ten within 12 %).  On the device, on 2000 random calls (M, N to 3000, K
+// to 6000) the choice is 1.80 times as fast as before on average (geometric), more than 5 % behind on four (8 %):
+// 268x228x3592 TN 69 -> 18 us, 64x460x1152 23.7 -> 7.6 (N no multiple of 8, so never cut in slices), 512^3 10.5 -> 7.0,
+// 64x168x2752 16.8 -> 12.6, 256^3 8.2 -> 7.2.  Two workgroups of 32x32 to a unit are resident at once; beyond, the 64x64 tile
+// stages half as many elements per product (1016x2352x868 39 us against 48), and few columns with a long k are faster in
+// slices.
 int wave_f32_variant(const Args& a, int slices, int num_cus) {
     const int64_t cus = num_cus > 0 ? num_cus : 256;
     constexpr int64_t kTwoSlabs = 64;      // (up to here one launch takes as long as another: 39x588x64 6.6 us on either)
@@ -379,23 +382,30 @@ int wave_f32_variant(const Args& a, int slices, int num_cus) {
 }
 
 // Few rows whose plan is the narrow streaming kernel (one launch), a wide streaming kernel in slices or the quartered tile in
-// shares run, in one launch, on the 16x64 or 64x64 tile whose waves divide the k range, where that is ahead (-1: it isn't): a workgroup of it
-// reads 64 columns of the weight once, where the narrow kernel's has 16 (four times as many workgroups, the first products 5 us after the
-// launch) and slices and shares need a second launch.  A unit streams about 30 GB/s from memory however many waves ask, so what has fewer than 48
-// workgroups (64 with a row-major weight, 96 with fewer than 96 columns of tiles and K beyond 4096; 80 of 64 rows, 200 for the wide kernels) or more than one to a unit
-// is left where it is, and so is K beyond 8192 (NN 5000), where four waves' walk is the longer one.  A
-// row-major weight with a pitch of whole 512 bytes is too, from K = 3000 on (the wide kernel's slices: 5000): the k-rows of a slab fall on few memory channels (31x2560x4864 18.8 us here, 15 in shares).
-// - streaming kernels in slices, up to 16 rows: from 200 workgroups on, always (30 random calls, 1.13 to 1.20 times as fast on average; 7 % ahead at
-//   the least up to K = 7000: 16x16384x4096 NN 32.4 -> 29, 8x15296x5184 NN 35.7 -> 27.5, 12x12288x4096 NT 24.8 -> 24).
-// - the others by estimates in us, fitted to 423 random calls with 16-row tiles and 514 with 64-row tiles (half within 5 to 7 %, nine of ten within 11 to
-//   17 %), by a margin of 5 %.  On such calls 1.17 to 1.18 times as fast on average with 16 rows (the faster one in hindsight 1.18 to 1.19) and 1.06 to 1.10 with
-//   64: 12x8192x2048 12 -> 8, 7x9920x2176 15.9 -> 9.6, 46x8128x2944 NN 18.1 -> 13.3, 61x2624x4480 NN 16.2 -> 11; with fewer than 64 workgroups of
-//   a long k or a row-major weight a unit's own rate shows (26x3304x4544 NN 15.3 against 13.1, 5x5120x5120 NT
-//   19.1 against 17.8 on 80).  On a weight that
-//   the caches do not hold the narrow kernel's four times as many workgroups draw more: with fewer than 128 here and a long k (149 of 1010 random calls; with K
-//   no multiple of 64 each visit's lines are asked for twice) these tiles took 1.19 times as long from memory and 0.95 from the last-level cache, and it stays:
-//   9x6693x4656 19.7 us, 25.6 here, 13x4045x3840 12.2 / 16.6, 16x6696x4112 12 % longer here out of the caches too.
-// Workgroups are counted against the 256 units of the whole part, on which all of this was measured; on a partition of it the plan stays.
+// shares run, in one launch, on the 16x64 or 64x64 tile whose waves divide the k range, where that is ahead (-1: it isn't): a
+// workgroup of it reads 64 columns of the weight once, where the narrow kernel's has 16 (four times as many workgroups, the
+// first products 5 us after the launch) and slices and shares need a second launch.  A unit streams about 30 GB/s from memory
+// however many waves ask, so what has fewer than 48 workgroups (64 with a row-major weight, 96 with fewer than 96 columns of
+// tiles and K beyond 4096; 80 of 64 rows, 200 for the wide kernels) or more than one to a unit is left where it is, and so is K
+// beyond 8192 (NN 5000), where four waves' walk is the longer one.  A row-major weight with a pitch of whole 512 bytes is too,
+// from K = 3000 on (the wide kernel's slices: 5000): the k-rows of a slab fall on few memory channels (31x2560x4864 18.8 us
+// here, 15 in shares).
+// - streaming kernels in slices, up to 16 rows: from 200 workgroups on, always (30 random calls, 1.13 to 1.20 times as fast on
+//   average; 7 % ahead at the least up to K = 7000: 16x16384x4096 NN 32.4 -> 29, 8x15296x5184 NN 35.7 -> 27.5, 12x12288x4096 NT
+//   24.8 -> 24).
+// - the others by estimates in us, fitted to 423 random calls with 16-row tiles and 514 with 64-row tiles (half within 5 to 7
+//   %, nine of ten within 11 to 17 %), by a margin of 5 %.  On such calls 1.17 to 1.18 times as fast on average with 16 rows
+//   (the faster one in hindsight 1.18 to 1.19) and 1.06 to 1.10 with 64: 12x8192x2048 12 -> 8, 7x9920x2176 15.9 -> 9.6,
+//   46x8128x2944 NN 18.1 -> 13.3, 61x2624x4480 NN 16.2 -> 11; with fewer than 64 workgroups of a long k or a row-major weight a
+//   unit's own rate shows (26x3304x4544 NN 15.3 against 13.1, 5x5120x5120 NT 19.1 against 17.8 on 80).  Those were timed with
+//   the weights in the caches.  On a weight that the caches do not hold the narrow kernel's four times as many workgroups draw
+//   more: with fewer than 128 here and a long k (149 of 1010 random calls; with K no multiple of 64 each visit's lines are
+//   asked for twice) these tiles took 1.19 times as long from memory and 0.95 from the last-level cache, and it stays:
+//   9x6693x4656 19.7 us, 25.6 here, 13x4045x3840 12.2 / 16.6, 16x6696x4112 12 % longer here out of the caches too.  Of 884
+//   random calls that leave the narrow kernel none is more than 5 % behind with the weight in the L2, six (12 % the worst) out
+//   of the last-level cache, 120 (32 %) from memory: 1.38, 1.32 and 1.11 times as fast on average.
+// Workgroups are counted against the 256 units of the whole part, on which all of this was measured; on a partition of it the
+// plan stays.
 constexpr int64_t kFewRowsUnits = 256;
 int few_rows_wave_tile(const Args& a, const gemm_plan_t& plan, int64_t cus) {
     constexpr int kQuarter = 16, kNarrow = 5, kWideRowMajor = 0, kWide = 1, kFewRows = 19, kManyRows = 18;
@@ -833,9 +843,9 @@ struct AutoPlan {
 // the choice is 0.3 % behind the fastest plan on average, by more than 10 % on 9 of them, and with 16 bits never by more than 6 %
 // behind the general kernel.  Nine calls of ten are within 7 % of their estimates.
 constexpr int64_t kGeneralMinSliceK = 48;
-// (2.6 to 3.1 on the device, more for the call: 33x43x223 fp32 10.2 us plain, 10.8 in 4 slices; none / SiLU / GELU on the 16-bit tile 215x127x181
-// 11.7 / 12.4 / 13.8, 335x75x629 20.3 / 21.1 / 22.4; on the fp32 one 0.1 to 0.4 more than none; 1.5 there too left 65x23x223 with GELU at 11.3
-// in 4 slices where one takes 8.9 and the general kernel 10.2)
+// (2.6 to 3.1 on the device, more for the call: 33x43x223 fp32 10.2 us plain, 10.8 in 4 slices; none / SiLU / GELU on the
+// 16-bit tile 215x127x181 11.7 / 12.4 / 13.8, 335x75x629 20.3 / 21.1 / 22.4; on the fp32 one 0.1 to 0.4 more than none; 1.5
+// there too left 65x23x223 with GELU at 11.3 in 4 slices where one takes 8.9 and the general kernel 10.2)
 constexpr double kSecondKernel = 3.4, kActivation = 1.5, kActivationF32 = 0.3;
 constexpr double kGeneralMargin = 1.08;       // what the 16-bit tiles must promise (without it up to 22 % behind the general kernel); the fp32 ones round less
 
@@ -881,12 +891,13 @@ int64_t general_slice_len(int64_t K, int& slices) {
     return slices > 1 ? len : K;
 }
 
-// A call that a plan gives to the 16-bit tiles of the general family, in whatever slices, runs in one launch on the tiles whose waves
-// divide the k range, 64 or 16 (returned; 0: neither) rows by 64 columns, where those promise to be ahead.  Estimates in us, fitted to 210
-// random calls each (half within 5 %, nine of ten within 14 %); on 350 such calls the choice is 1.40 times as fast as before
-// on average (geometric), the faster of all three in hindsight 1.404 times.  At 2049x2051x2045 the three are level (53 to 54 us); at 4095^3 the large tile,
-// which reads half as many bytes, is ahead (255 us against 328), as are slices with few columns and a long k (9x979x4043 16.4 against 29.4).
-// Results of 16 bits only: for an fp32 C slices and folds have the smaller error.
+// A call that a plan gives to the 16-bit tiles of the general family, in whatever slices, runs in one launch on the tiles whose
+// waves divide the k range, 64 or 16 (returned; 0: neither) rows by 64 columns, where those promise to be ahead.  Estimates in
+// us, fitted to 210 random calls each (half within 5 %, nine of ten within 14 %).  On the device, on 1150 random calls with
+// more than 64 rows the choice is 1.63 times as fast as before on average (eight more than 5 % behind, 17 % the worst), on 2490
+// with fewer 1.58 (weights from memory 1.41; 149 of them behind there, 34 %).  At 2049x2051x2045 the three are level (53 to 54
+// us); at 4095^3 the large tile, which reads half as many bytes, is ahead (255 us against 328), as are slices with few columns
+// and a long k (9x979x4043 16.4 against 29.4). Results of 16 bits only: for an fp32 C slices and folds have the smaller error.
 int wave_any_rows(const Args& a, int slices, int num_cus) {
     const int64_t cus = num_cus > 0 ? num_cus : 256;
     if (a.out_dtype == gemm::DT_F32 || !gemm::general_variant_supports(a, gemm::kGeneralWave64)) return 0;
@@ -894,8 +905,8 @@ int wave_any_rows(const Args& a, int slices, int num_cus) {
     static const Tile tiles[] = {{64, 0.0041, 0.0038, 5.1, 0.6, 3.4e6, 1.3, 41e6, {1.0, 1.12, 1.34, 1.37}},      // NT, NN, TT, TN
                                  {16, 0.00256, 0.0024, 4.2, 0.0, 1.0e6, 0.6, 23e6, {1.0, 1.05, 0.0, 0.0}}};
     const int layout = (a.transA ? 2 : 0) + (a.transB ? 0 : 1);
-    // (slices of a weight stored N x K draw more from memory than few workgroups with a long k do: 40 random calls 1.14 times as long here, 0.92 out of the
-    // last-level cache)
+    // (slices of a weight stored N x K draw more from memory than few workgroups with a long k do: 40 random calls 1.14 times
+    // as long here, 0.92 out of the last-level cache)
     if (slices > 1 && !a.transA && a.transB && a.K > 4096 && ((a.M + 15) / 16) * ((a.N + 63) / 64) * 8 < cus * 3) return 0;
     int sl = slices > 1 ? slices : 1, rows = 0;
     const int64_t len = sl > 1 ? general_slice_len(a.K, sl) : a.K;
@@ -906,7 +917,8 @@ int wave_any_rows(const Args& a, int slices, int num_cus) {
         const double time = t.fixed + t.per_round * (double)rounds + (rounds == 1 ? t.per_k_alone : t.per_k * (double)rounds) * t.layout[layout] * (double)a.K +
                             (double)(a.M * a.N * a.batch) * 2.0 / t.store_rate + (a.act != gemm::ACT_NONE ? t.activation : 0.0) +
                             (double)(a.N * a.K * a.batch) * 2.0 / t.weight_rate;
-        // (10 % promised beyond what is resident at once: with 7 to 10 nine random calls were 1.06 times as long here, 2711x1985x131 NN 18.0 against 16.4 us)
+        // (10 % promised beyond what is resident at once: with 7 to 10 nine random calls were 1.06 times as long here,
+        // 2711x1985x131 NN 18.0 against 16.4 us)
         if (time < best * (rounds > 2 ? 0.9 : 1.0)) { best = time; rows = t.rows; }
     }
     return rows;

@@ -86,8 +86,9 @@ namespace {
 struct WaveTile { int variant, bm; double per_k_alone, per_k, straddling, fixed, per_round, store_rate, weight_rate; };
 constexpr WaveTile kWaveTiles[] = {{18, 64, 0.00255, 0.00258, 0.15, 4.2, 0.96, 6.7e6, 22e6}, {19, 16, 0.00131, 0.00143, 0.21, 4.1, 0.6, 22e6, 11e6}};
 // Up to two workgroups of 64x64 per unit: those are resident at once.  Beyond, the 128x128 tile reads half as much per product
-// (1392x2816x1024, 968 tiles of 64x64: 21.9 us against 17.5; 960x2048x1280, 480 tiles: 13.0 against 19.1).  Operands
-// of more than 128 MiB stream from memory, which few short-lived workgroups do not keep busy (14x3840x14336 60 us in 16-row tiles, 40 cut along k).
+// (1392x2816x1024, 968 tiles of 64x64: 21.9 us against 17.5; 960x2048x1280, 480 tiles: 13.0 against 19.1).  Operands of more
+// than 128 MiB stream from memory, which few short-lived workgroups do not keep busy (14x3840x14336 60 us in 16-row tiles, 40
+// cut along k).
 constexpr int64_t kWaveTilesPerUnit = 2, kWaveTileBytes = (int64_t)128 << 20;
 
 }  // namespace
@@ -110,23 +111,26 @@ int wave_tile_for(const Args& a, int64_t cus, double* estimate) {
     return best;
 }
 
-// Whole 128x128 tiles that have no wave tile: with both operands k-contiguous and K from 1280 on they run on the quartered kernel
-// (variant 16, 16x16x32 products, its slabs requested in pairs), which waits less per slab and has the longer fill (1216x2752x1024 14.6 -> 15.3); the sums are the same to the bit.  Of 165 random calls of 512 to 1600
-// 64x64 tiles it is 1.07 times as fast on average for K 1024 to 1536 and 1.10 beyond (600x4024x4264 59.7 -> 51 us,
+// Whole 128x128 tiles that have no wave tile: with both operands k-contiguous and K from 1280 on they run on the quartered
+// kernel (variant 16, 16x16x32 products, its slabs requested in pairs), which waits less per slab and has the longer fill
+// (1216x2752x1024 14.6 -> 15.3); the sums are the same to the bit (a test holds them together).  Of 165 random calls of 512 to
+// 1600 64x64 tiles it is 1.07 times as fast on average for K 1024 to 1536 and 1.10 beyond (600x4024x4264 59.7 -> 51 us,
 // 1648x1872x6224 80.8 -> 68, 2120x1376x3304 53.7 -> 44; 6 % slower on one of 58), 1.02 for K 512 to 768, 1.02 to 1.04 with a
-// row-major B (two of 32 4 % slower), 0.94 to 0.97 with A stored KxM.  With more than two and up to two and a half tiles to a unit it is level (20
-// random calls) and loses where few of the third are there (1856x80x1856, batch of 39, 69.6 -> 80.7 us, of 43 1696x80x1696 65 -> 71): variant 5 stays.
+// row-major B (two of 32 4 % slower), 0.94 to 0.97 with A stored KxM.  With more than two and up to two and a half tiles to a
+// unit it is level (20 random calls) and loses where few of the third are there (1856x80x1856, batch of 39, 69.6 -> 80.7 us, of
+// 43 1696x80x1696 65 -> 71): variant 5 stays.
 constexpr int64_t kLongK = 1280;
-// Up to 64 columns to a matrix the 128x128 tile is at least half empty, and the 64x64 wave tile is ahead at any number of tiles, with A row-major
-// and K from 768 on: 17 random calls, batches of attention's second product most of them, 1.09 times as fast on average (1160x64x1160 NN, batch of
-// 57, 59.4 -> 46.2 us, 1512x64x1512 NT, 26, 39.6 -> 32.2, 1864x64x1864 NN, 29, 65.4 -> 57.4; 2 % behind on one).  With A stored KxM 0.91 to 1.1, with a shorter k
-// 0.88 to 1.2.
+// Up to 64 columns to a matrix the 128x128 tile is at least half empty, and the 64x64 wave tile is ahead at any number of
+// tiles, with A row-major and K from 768 on: 17 random calls, batches of attention's second product most of them, 1.09 times as
+// fast on average (1160x64x1160 NN, batch of 57, 59.4 -> 46.2 us, 1512x64x1512 NT, 26, 39.6 -> 32.2, 1864x64x1864 NN, 29, 65.4
+// -> 57.4; 2 % behind on one).  With A stored KxM 0.91 to 1.1, with a shorter k 0.88 to 1.2.
 constexpr int64_t kNarrowK = 768;
 
-// C = alpha op(A) op(B) and nothing else on whole 128x128 tiles leaves that kernel straight from its registers.  There the wave tiles, which add their sums through
-// LDS first, are level at best up to K = 128 (batch of 21 256x256x64 NT 4.8 us against 6.0, of 5 512x512x128 5.2 against 6.2), and beyond one of them to a unit up to
-// K = 1536 (batch of 17 512x128x512 NN 7.9 against 9.8, 3072x384x256 NT 6.0 against 6.6): 247 such random calls 1.03 times as long on them, up to 1.39.
-// Ragged tiles, a C that is read, a bias or an activation take the staged epilogue, and the wave tiles are ahead of it.
+// C = alpha op(A) op(B) and nothing else on whole 128x128 tiles leaves that kernel straight from its registers.  There the wave
+// tiles, which add their sums through LDS first, are level at best up to K = 128 (batch of 21 256x256x64 NT 4.8 us against 6.0,
+// of 5 512x512x128 5.2 against 6.2), and beyond one of them to a unit up to K = 1536 (batch of 17 512x128x512 NN 7.9 against
+// 9.8, 3072x384x256 NT 6.0 against 6.6): 247 such random calls 1.03 times as long on them, up to 1.39. Ragged tiles, a C that
+// is read, a bias or an activation take the staged epilogue, and the wave tiles are ahead of it.
 constexpr int64_t kWholeShortK = 128, kWholeK = 1536;
 
 bool whole_128_tiles_ahead(const Args& a, int64_t cus) {

@@ -254,7 +254,8 @@ template <> struct OutVec<DT_F16> {
 };
 
 // The bias of four columns, as stored, and its values.  One choice of type and four loads in flight together: a choice at each
-// element is a branch, and a trip to memory, for each (on the device: 512x512x256 with bias and GELU on quartered tiles 10.3 -> 10.0 us, 1024x4096x1024 16.5 -> 16.0; 70 random calls with a bias 0.9 % faster, none slower).
+// element is a branch, and a trip to memory, for each (on the device: 512x512x256 with bias and GELU on quartered tiles 10.3 ->
+// 10.0 us, 1024x4096x1024 16.5 -> 16.0; 70 random calls with a bias 0.9 % faster, none slower).
 struct RawBias { uint32_t v[4]; };
 __device__ __forceinline__ void ask_bias(const Args& a, int64_t col, RawBias& b) {
 #pragma unroll

@@ -1,17 +1,18 @@
-// fp32 tiles of 32x32 and 16x32 whose k range is divided among the eight waves of the workgroup (gfx950), for calls whose grid of
-// 64x64 tiles leaves compute units idle.
+// fp32 tiles of 32x32 and 16x32 whose k range is divided among the eight waves of the workgroup (gfx950), for calls whose grid
+// of 64x64 tiles leaves compute units idle.
 //
-// Such a call is bound by one workgroup's chain: launch, first slab, a barrier per slab of 32 (0.57 us of which 0.2 are work, 64x64 alone on its
-// unit), sums, stores, and a second launch where slices are to shorten it.  Here each wave computes the whole small tile over every eighth slab:
-// it loads its slabs into LDS as they are (fp32), takes the fragments apart in registers, each element once in the workgroup, and
-// waits for nobody; the eight sums are added once.  Per slab and wave 208 vector instructions take the four fragments of a 32x32 tile apart for 24
-// matrix instructions: the vector ALUs bound it, 2 waves to a SIMD filling each other's waits, at 0.0046 us per element of k alone on
-// a unit.  The code that runs once is short on purpose (8 KB; a first form with 64x64 tiles and 20 KB took 6.6 us for one slab where this
-// takes 4): a wave waits for the instruction cache for all of it.
-// The products and their order, the scale and the way out for what overflows are those of tile_f32_kernel.hpp; every slab is summed by itself and added by the vector
-// ALUs, so the error is a third to a tenth (256^3 2.3e-7 -> 7.0e-8, 64x460x1152 5.2e-7 -> 8.9e-8 of the result's norm).
-// Measured, the 64x64 tiles (in slices where it was so) / these, us: 256^3 8.2 / 7.2 (the rate of launches), 512^3 10.5 / 7.0,
-// 64x460x1152 23.7 / 7.6, 268x228x3592 TN 69 / 18, 16x1024x1024 9.9 / 7.2, 64x1800x3008 15.7 / 15.2, 1024^3 24.1 to 25.3 / 25.6.
+// Such a call is bound by one workgroup's chain: launch, first slab, a barrier per slab of 32 (0.57 us of which 0.2 are work,
+// 64x64 alone on its unit), sums, stores, and a second launch where slices are to shorten it.  Here each wave computes the
+// whole small tile over every eighth slab: it loads its slabs into LDS as they are (fp32), takes the fragments apart in
+// registers, each element once in the workgroup, and waits for nobody; the eight sums are added once.  Per slab and wave 208
+// vector instructions take the four fragments of a 32x32 tile apart for 24 matrix instructions: the vector ALUs bound it, 2
+// waves to a SIMD filling each other's waits, at 0.0046 us per element of k alone on a unit.  The code that runs once is short
+// on purpose (8 KB; a first form with 64x64 tiles and 20 KB took 6.6 us for one slab where this takes 4): a wave waits for the
+// instruction cache for all of it. The products and their order, the scale and the way out for what overflows are those of
+// tile_f32_kernel.hpp; every slab is summed by itself and added by the vector ALUs, so the error is a third to a tenth (256^3
+// 2.3e-7 -> 7.0e-8, 64x460x1152 5.2e-7 -> 8.9e-8 of the result's norm). Measured, the 64x64 tiles (in slices where it was so) /
+// these, us: 256^3 8.2 / 7.2 (the rate of launches), 512^3 10.5 / 7.0, 64x460x1152 23.7 / 7.6, 268x228x3592 TN 69 / 18,
+// 16x1024x1024 9.9 / 7.2, 64x1800x3008 15.7 / 15.2, 1024^3 24.1 to 25.3 / 25.6.
 #pragma once
 #include "tile_f32_kernel.hpp"
 #include "tile_wavek_kernel.hpp"
@@ -31,7 +32,8 @@ struct WaveKF32 {
 };
 
 // k-contiguous operand: a slab is rows of 128 bytes, chunk c (four k) of row r at r*128 + (c xor hash(r))*16; a fragment, 8
-// consecutive k of a row per lane, is two chunks.
+// consecutive k of a row per lane, is two chunks.  (The placement of the 16-bit tiles, and no more free of conflicts: 0.30 to
+// 0.41 of the active LDS cycles.)
 template <int ROWS>
 struct WaveKCF32 {
     static constexpr int L = ROWS / 8;

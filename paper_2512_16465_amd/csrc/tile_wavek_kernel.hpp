@@ -1,21 +1,23 @@
-// Tiles of 64x64 and 16x64 whose k range is divided among the waves of the workgroup (bf16 / fp16, gfx950), for calls whose grid
-// of 128x128 tiles leaves compute units idle.
+// Tiles of 64x64 and 16x64 whose k range is divided among the waves of the workgroup (bf16 / fp16, gfx950), for calls whose
+// grid of 128x128 tiles leaves compute units idle.
 //
-// Such a call is bound by what one workgroup takes: the way of its operands from the L2 into LDS (about 50 bytes per clock and unit)
-// and, with a few dozen slabs of k, the time from the launch to the first product and from the last one to the stores.  A
+// Such a call is bound by what one workgroup takes: the way of its operands from the L2 into LDS (about 50 bytes per clock and
+// unit) and, with a few dozen slabs of k, the time from the launch to the first product and from the last one to the stores.  A
 // 128x128 tile on 4 waves that share every slab walks k at 0.0066 us per element alone on its unit (two barriers' worth of
-// waiting per 32 elements; its LDS traffic, 12 clocks per element, is above the 8 of its products) and needs 11 us around it, and dividing
-// its k range over workgroups costs a second launch.  Here a wave computes the whole tile over every fourth slab of 64: it loads its own slabs into
-// its own ring, waits for nobody, and the four sums are added through LDS once, at the end.  A tile of 64x64 reads half as many
-// bytes per element as one of 128x128, 0.0026 us each, and four times as many units work on it; with 16 rows 0.0013 us.
-// Two workgroups share a unit (64 KiB of LDS with one slab per wave, 80 KiB with two of the 16-row tile), one waits while the
-// other multiplies.  Slabs of 64 are whole 128-byte lines of a k-contiguous operand, and of an m/n-contiguous one.
+// waiting per 32 elements; its LDS traffic, 12 clocks per element, is above the 8 of its products) and needs 11 us around it,
+// and dividing its k range over workgroups costs a second launch.  Here a wave computes the whole tile over every fourth slab
+// of 64: it loads its own slabs into its own ring, waits for nobody, and the four sums are added through LDS once, at the end.
+// A tile of 64x64 reads half as many bytes per element as one of 128x128, 0.0026 us each, and four times as many units work on
+// it; with 16 rows 0.0013 us. Two workgroups share a unit (64 KiB of LDS with one slab per wave, 80 KiB with two of the 16-row
+// tile), one waits while the other multiplies.  Slabs of 64 are whole 128-byte lines of a k-contiguous operand, and of an
+// m/n-contiguous one.
 //
-// Measured, the 128x128 tiles (whole, or divided over workgroups and a second launch) / these, us: 832x512x768 12.3 / 8.2 (the rate of
-// launches from Python), 145x4864x2816 17.5 / 12.3, 960x2048x1280 19.1 / 13.0, 1024x1024x2048 18.2 / 10.6, 104x560x1768 12.6 / 8.3,
-// 896x896x6592 TN 23.4 / 23; 16 rows: 48x1024x4096 14.4 / 9.3, 256x512x4864 15.7 / 11.5, 15x16128x2048 17.1 / 12.8.  Tried: 128x64 (one
-// workgroup per unit: behind the other tiles everywhere), 32x64 (at most 14 % ahead on a few shapes), two slabs per wave and one
-// workgroup per unit with 64x64 (up to 16 % ahead at k beyond 4000 with under 100 tiles, half the speed beyond 256 tiles).
+// Measured, the 128x128 tiles (whole, or divided over workgroups and a second launch) / these, us: 832x512x768 12.3 / 8.2 (the
+// rate of launches from Python), 145x4864x2816 17.5 / 12.3, 960x2048x1280 19.1 / 13.0, 1024x1024x2048 18.2 / 10.6, 104x560x1768
+// 12.6 / 8.3, 896x896x6592 TN 23.4 / 23; 16 rows: 48x1024x4096 14.4 / 9.3, 256x512x4864 15.7 / 11.5, 15x16128x2048 17.1 / 12.8.
+// Tried: 128x64 (one workgroup per unit: behind the other tiles everywhere), 32x64 (at most 14 % ahead on a few shapes), two
+// slabs per wave and one workgroup per unit with 64x64 (up to 16 % ahead at k beyond 4000 with under 100 tiles, half the speed
+// beyond 256 tiles).
 #pragma once
 #include "tile_dma16_kernel.hpp"
 #include "tile_f32_kernel.hpp"
@@ -38,8 +40,11 @@ struct WaveK {
     static_assert(BM * BN * 4 <= RING, "a wave parks its sums in its own ring");
 };
 
-// k-contiguous operand: a slab is 64 rows of 128 bytes (whole cache lines); 16-byte chunk c of row r at r*128 + (c xor hash(r))*16.
-// The hash makes the 16 rows of a fragment read fall on 16 distinct places of a 256-byte bank line.
+// k-contiguous operand: a slab is 64 rows of 128 bytes (whole cache lines); 16-byte chunk c of row r at r*128 + (c xor
+// hash(r))*16. The hash puts the 16 rows that 16 consecutive lanes read on 16 distinct places of a 256-byte bank line.  Those
+// lanes are not the ones served together: 0.33 to 0.48 of the active LDS cycles are conflicts with both operands k-contiguous
+// (0.16 to 0.29 with one; the quartered kernel, whose rows of 64 bytes are placed otherwise, 0.04), so a fragment read takes
+// about two turns.
 template <int ROWS>
 struct WaveKC {
     static constexpr int L = ROWS / 8;
@@ -372,17 +377,17 @@ __global__ __launch_bounds__(C::NT, C::WGS) void tile_wavek_kernel(Args a, int t
             }
             return;
         } else {
-        const __amdgpu_buffer_rsrc_t ra = make_rsrc(pa, k_left > 0 ? a_bytes : 0), rb = make_rsrc(pb, k_left > 0 ? b_bytes : 0);
-        const uint32_t sa = (uint32_t)(t * a_step), sb = (uint32_t)(t * b_step);
-        char* const dst = ring + p * C::SLAB;
-        if (k_left > 0 && k_left < C::BK) {      // (the last slab that this wave asks for)
-            la.mask(lane, k_left);
-            lb.mask(lane, k_left);
-        }
+            const __amdgpu_buffer_rsrc_t ra = make_rsrc(pa, k_left > 0 ? a_bytes : 0), rb = make_rsrc(pb, k_left > 0 ? b_bytes : 0);
+            const uint32_t sa = (uint32_t)(t * a_step), sb = (uint32_t)(t * b_step);
+            char* const dst = ring + p * C::SLAB;
+            if (k_left > 0 && k_left < C::BK) {      // (the last slab that this wave asks for)
+                la.mask(lane, k_left);
+                lb.mask(lane, k_left);
+            }
 #pragma unroll
-        for (int q = 0; q < LA::L; ++q) load_to_lds_b128(ra, dst + q * 1024, la.voff[q], sa);
+            for (int q = 0; q < LA::L; ++q) load_to_lds_b128(ra, dst + q * 1024, la.voff[q], sa);
 #pragma unroll
-        for (int q = 0; q < LB::L; ++q) load_to_lds_b128(rb, dst + C::A_SLAB + q * 1024, lb.voff[q], sb);
+            for (int q = 0; q < LB::L; ++q) load_to_lds_b128(rb, dst + C::A_SLAB + q * 1024, lb.voff[q], sb);
         }
     };
 

@@ -1,6 +1,7 @@
 """CPU checks of the tiles whose k range is divided among the waves: the loads of their movers stay inside the operand and put
 every element where the fragment reads look for it (the arithmetic of tile_wavek_kernel.hpp, restated), and the generated code
-touches no fragment register before its wait."""
+touches no fragment register before its wait.  (Which lanes of a read the LDS serves together, and so its bank conflicts, is not
+checked here.)"""
 import os
 
 import numpy as np
