@@ -8,7 +8,8 @@ fp32 output) with operands resident in HBM.  The protocol follows the paper's ev
 (Section 5.1): warm-up launches, then timed launches, mean latency reported.  Prints ONE JSON
 line; `value` is TFLOP/s on C3, `roofline` prices the dominant kernel of C3 against the dense
 bf16 MFMA peak, `cpu_baseline` times the CPU oracle on a bounded sample of the same workload,
-and `other_configs` carries the remaining configurations (C5 is priced against HBM bandwidth).
+and `other_configs` carries the main figures of the remaining configurations (C5 is priced against HBM
+bandwidth); `--detail FILE` writes the line with all that was measured of each.
 `mfma_ceiling` is context for the compute-bound rows: the rate and clock of register-only MFMA
 loops on values drawn like the headline's operands and on zeros, measured in the same process;
 `hbm_read_ceiling` is the same for the bandwidth-bound rows: what a kernel that only reads gets.
@@ -53,6 +54,19 @@ def measured_traffic(name: str):
     if not rec or rec.get("kernel_source_hash") != kernel_source_hash():
         return None
     return rec.get("hbm_bytes_per_launch")
+
+
+def rounded(v, digits: int = 5):
+    return float(f"{v:.{digits}g}") if isinstance(v, float) else v
+
+
+def in_short(r: dict) -> dict:
+    """A configuration's entry in the printed line: with everything that is measured of twenty of them the line has 20 KB, more
+    than a log of a run keeps of it."""
+    out = {k: rounded(r[k]) for k in ("kernel", "split_k", "ms_per_step", "tflops", "algorithmic_gbps", "verified_sample")}
+    if r["roofline"]:
+        out.update(bound=r["roofline"]["bound"], frac=rounded(r["roofline"]["frac"]))
+    return out
 
 
 def classify(cfg) -> str:
@@ -341,6 +355,7 @@ def main():
     ap.add_argument("--variant", type=int, default=-1, help="tile variant when --kernel is forced")
     ap.add_argument("--split-k", type=int, default=0, help="split-K factor when --kernel is forced; 0 = automatic")
     ap.add_argument("--library", default="", help="path of another build of libgemm.so to measure (see paper_2512_16465_amd/build.py --output)")
+    ap.add_argument("--detail", default="", help="file to write the line to with all that was measured of every configuration")
     ap.add_argument("--copy-calibration", action="store_true",
                     help="also run a plain 256 MiB device-to-device copy (3 times) so that a counter run can scale "
                          "FETCH_SIZE / WRITE_SIZE by what they read for a transfer of known size")
@@ -439,9 +454,12 @@ def main():
         "mfma_ceiling": ceiling,
         "hbm_read_ceiling": None if args.no_hbm_ceiling else hbm_read_ceiling(torch),
         "hbm_gbps_at_m32": results["C5"]["algorithmic_gbps"] if "C5" in results else None,
-        "other_configs": {k: v for k, v in results.items() if k != name},
+        "other_configs": {k: in_short(v) for k, v in results.items() if k != name},
         "headline_detail": results[name],
     }
+    if args.detail:
+        with open(args.detail, "w") as f:
+            json.dump(dict(line, other_configs={k: v for k, v in results.items() if k != name}), f, indent=1)
     print(json.dumps(line))
 
 
