@@ -442,9 +442,9 @@ int few_rows_wave_tile(const Args& a, const gemm_plan_t& plan, int64_t cus) {
 
 // Whether a call is cut along k does not depend on the epilogue (beta, bias, activation, the type of C), so the wave tiles are
 // estimated without one: a caller that made a call without reading C, so that the workspace is there, and then captures it
-// with beta = 1 must not find that the second one needs a workspace and the first did not (112x6664x2712 TT was such a call: one
-// launch with C written only, 4 shares with C read).   44 random calls whose choice this
-// moved took 0.85 of the time (1.05 at most; weights from memory 0.89 and 1.14).
+// with beta = 1 must not find that the second one needs a workspace and the first did not (112x6664x2712 TT was such a call:
+// one launch with C written only, 4 shares with C read).  44 random calls whose choice this moved took 0.85 of the time (1.05
+// at most; weights from memory 0.89 and 1.14).
 TileChoice choose_tile(const Args& call, int num_cus) {
     TileChoice c = choose_shared_k_tile(call, num_cus);      // (which asks the epilogue only whether the persistent kernel takes it)
     Args a = call;
