@@ -905,6 +905,8 @@ int64_t general_slice_len(int64_t K, int& slices) {
 // with fewer 1.58 (weights from memory 1.41; 149 of them behind there, 34 %).  At 2049x2051x2045 the three are level (53 to 54
 // us); at 4095^3 the large tile, which reads half as many bytes, is ahead (255 us against 328), as are slices with few columns
 // and a long k (9x979x4043 16.4 against 29.4). Results of 16 bits only: for an fp32 C slices and folds have the smaller error.
+constexpr int kMostSlices = 16;
+constexpr int64_t kSlicedLongK = 3600;
 int wave_any_rows(const Args& a, int slices, int num_cus) {
     const int64_t cus = num_cus > 0 ? num_cus : 256;
     if (a.out_dtype == gemm::DT_F32 || !gemm::general_variant_supports(a, gemm::kGeneralWave64)) return 0;
@@ -928,6 +930,10 @@ int wave_any_rows(const Args& a, int slices, int num_cus) {
         // 2711x1985x131 NN 18.0 against 16.4 us)
         if (time < best * (rounds > 2 ? 0.9 : 1.0)) { best = time; rows = t.rows; }
     }
+    // (sixteen slices of a long k, where the 16-row tiles would leave half of the units idle: those stay.  140 random calls 1.10 times
+    // as long here from memory, 1.01 out of the last-level cache: 57x982x3883 NT 16.8 us against 21.0 and 15.5 against 17.7)
+    const int64_t strips = ((a.M + 15) / 16) * ((a.N + 63) / 64);
+    if (rows == 16 && slices == kMostSlices && a.M <= 128 && a.K >= kSlicedLongK && 2 * strips <= cus) return 0;
     return rows;
 }
 

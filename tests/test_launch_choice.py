@@ -80,6 +80,10 @@ def test_calls_off_the_grid_that_stay_on_the_128_tile():
     for call in [(9, 6015, 4201, "NT"), (5, 5501, 4101, "NT"), (5, 6079, 5001, "NT")]:   # few workgroups on a long k
         plan, launched = both(*call)
         assert plan[0] == tiles and plan[1] > 1 and launched == plan, (call, plan, launched)
+    for call in [(57, 982, 3883, "NT"), (56, 1474, 5045, "NT"), (64, 330, 5030, "NN"), (125, 734, 3956, "NT"), (43, 1817, 4960, "NN")]:   # in sixteen slices
+        assert both(*call) == ((tiles, 16), (tiles, 16)), call
+    for call in [(57, 982, 3585, "NT"), (60, 3781, 3989, "NN"), (129, 500, 3989, "NN")]:
+        assert both(*call)[1][0] == "general_wavek_16x64x64_w4", call
     assert both(9, 6079, 4095, "NT")[1][0] == "general_wavek_16x64x64_w4" and both(5, 6145, 5001, "NT")[1][0] == "general_wavek_16x64x64_w4"
 
 
