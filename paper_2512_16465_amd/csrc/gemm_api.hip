@@ -258,14 +258,17 @@ double f32_time(const Args& a, bool big, int slices, int64_t cus) {
 // compared with it, whole or in parts: by their own estimate against that of the split or the slices, and in place of a whole
 // 128x128 tile wherever wave_tile_for gives one and whole_128_tiles_ahead does not keep it.  On the device, on random calls of
 // the sizes that a 128x128 tile used to take, they are 1.7 times as fast on average (geometric) in place of whole tiles (4600
-// calls, eleven more than 5 % behind, 14 % the worst) and 1.3 to 1.7 in place of shares and slices (2260; eight, 11 %).  Cut as
-// before: long k ranges in slices, which put them on more units than a tile's waves are (128x1024x8192: 15 against 19.8), and a
-// single strip or two of 33 to 64 rows, whose weights three or four tiles of 16 rows would each read. With a row-major weight,
-// fewer 16-row tiles than half the units and K beyond 5000 (4096 where rows start inside a line) the shares draw more from
-// memory than these few workgroups do (26 random calls: 1.24 times as long here from memory, 0.91 out of the last-level cache);
-// so do they from K = 3000 on with fewer tiles than a quarter of the units and a pitch of whole 512 bytes, the k-rows of a slab
-// on few memory channels (23 calls: 1.25 and 0.87; 10x2560x3328 13.8 us against 22.5 from memory, 12.3 against 14.4).  With A
-// stored K x M the shares are ahead beyond K = 4096 (3584x256x6144 TN 21 us against 24.9, 904x1024x5632 TT 20.4 against 23.5).
+// calls, eleven more than 5 % behind, 14 % the worst; with A stored K x M and more than one 64x64 tile to a unit 1.03 times on
+// 739, 117 behind) and 1.5 in place of shares and slices (2149; three, 9 %), with the weights from memory 1.32 (134, 33 %: a k
+// beyond 2800 with rows off the line or beyond 5500 on few units, the same calls level or ahead out of the last-level cache).
+// Cut as before: long k ranges in slices, which put them on more units than a tile's waves are (128x1024x8192: 15 against
+// 19.8), and a single strip or two of 33 to 64 rows, whose weights three or four tiles of 16 rows would each read. With a
+// row-major weight, fewer 16-row tiles than half the units and K beyond 5000 (4096 where rows start inside a line) the shares
+// draw more from memory than these few workgroups do (26 random calls: 1.24 times as long here from memory, 0.91 out of the
+// last-level cache); so do they from K = 3000 on with fewer tiles than a quarter of the units and a pitch of whole 512 bytes, the
+// k-rows of a slab on few memory channels (23 calls: 1.25 and 0.87; 10x2560x3328 13.8 us against 22.5 from memory, 12.3 against
+// 14.4).  With A stored K x M the shares are ahead beyond K = 4096 (3584x256x6144 TN 21 us against 24.9, 904x1024x5632 TT 20.4
+// against 23.5).
 constexpr int64_t kLongSlicedK = 4096, kFewWaveTiles = 16, kLongRowMajorK = 5000;
 
 bool row_major_stream_on_few_units(const Args& a, int64_t tiles, int64_t cus) {
@@ -901,10 +904,11 @@ int64_t general_slice_len(int64_t K, int& slices) {
 // A call that a plan gives to the 16-bit tiles of the general family, in whatever slices, runs in one launch on the tiles whose
 // waves divide the k range, 64 or 16 (returned; 0: neither) rows by 64 columns, where those promise to be ahead.  Estimates in
 // us, fitted to 210 random calls each (half within 5 %, nine of ten within 14 %).  On the device, on 1150 random calls with
-// more than 64 rows the choice is 1.63 times as fast as before on average (eight more than 5 % behind, 17 % the worst), on 2490
-// with fewer 1.58 (weights from memory 1.41; 149 of them behind there, 34 %).  At 2049x2051x2045 the three are level (53 to 54
-// us); at 4095^3 the large tile, which reads half as many bytes, is ahead (255 us against 328), as are slices with few columns
-// and a long k (9x979x4043 16.4 against 29.4). Results of 16 bits only: for an fp32 C slices and folds have the smaller error.
+// more than 64 rows the choice is 1.63 times as fast as before on average (eight more than 5 % behind, 17 % the worst), on 1556
+// with fewer 1.74 times out of the last-level cache (eight, 16 %) and 1.64 from memory (76, 39 %).  At 2049x2051x2045 the
+// three are level (53 to 54 us); at 4095^3 the large tile, which reads half as many bytes, is ahead (255 us against 328), as are
+// slices with few columns and a long k (9x979x4043 16.4 against 29.4).  Results of 16 bits only: for an fp32 C slices and folds
+// have the smaller error.
 constexpr int kMostSlices = 16;
 constexpr int64_t kSlicedLongK = 3600;
 int wave_any_rows(const Args& a, int slices, int num_cus) {

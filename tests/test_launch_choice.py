@@ -73,6 +73,16 @@ def test_shares_of_a_long_k_stay():
     assert both(30, 2040, 4096, "NN")[1] == ("wavek_16x64x64_w4", 1) and both(904, 1024, 4096, "TT")[1] == w64
 
 
+def test_straddling_rows_with_a_stored_k_by_m():
+    """A stored K x M, B row-major, rows of both inside a 128-byte line: more than one 64x64 tile to a unit and a long k
+    stay with a C of 16 bits that is only written."""
+    small, w64 = ("dma_128x128x32_w2x2_s4", 1), ("wavek_64x64x64_w4", 1)
+    for call in [(264, 5904, 2824, "TN"), (296, 4968, 2456, "TN"), (416, 4208, 3776, "TN")]:
+        assert both(*call) == (small, small) and both(*call, out=wl.F32, reads_c=True)[1] == w64, call
+    for call in [(264, 5888, 2824, "TN"), (264, 5904, 2392, "TN"), (264, 2600, 2824, "TN"), (264, 5904, 2824, "TT")]:
+        assert both(*call)[1] == w64, call
+
+
 def test_calls_off_the_grid_that_stay_on_the_128_tile():
     tiles = "general_128x128x64_w2x2"
     for call in [(2711, 1985, 131, "NN"), (1711, 2679, 157, "NT")]:                       # more than two rounds of 64x64 tiles, a promise of less than 10 %
