@@ -151,11 +151,31 @@ bool long_straddling_tn(const Args& a, int64_t cus) {
     return ((a.M + 63) / 64) * ((a.N + 63) / 64) > cus;
 }
 
+// The tiles of a matrix of a batch lie on as many XCDs as there are of them, and each XCD's L2 fetches the matrix's operands for
+// itself: 64x64 tiles spread a small matrix over more of them than 128x128 tiles do.  Beyond one wave tile to a unit, where that
+// is 90 MB more to fetch (or 93 MB in all with A stored K x M, B row-major and K beyond 700), the 128x128 tiles of at most a round
+// (three quarters of one) stay: 239 of 1708 random batches 1.22 times as long on the wave tiles with the operands in the
+// last-level cache and 1.10 from memory (42 x 360x120x1696 NN 22.0 us against 37.4, 29 x 120x264x1544 TN 18.9 against 30.6),
+// three of them ahead; of the others 90 are more than 5 % behind, 0.85 of the time on average.  Level, and left: both operands
+// k-contiguous (1.01 and 0.87), and a row-major B of up to 64 columns (0.93 and 0.90 as attention's second product).  A C that is
+// read or has 32 bits costs the 128x128 tiles more; three times its further bytes are taken off (66 of 428 batches with an fp32
+// C and beta = 1: 1.12 and 1.02).
+constexpr int64_t kXcds = 8, kSpreadBytes = 90000000, kSpreadBytesTN = 93000000, kSpreadKTN = 700;
+
+bool spread_batch(const Args& a, int64_t cus) {
+    const int64_t wave = ((a.M + 63) / 64) * ((a.N + 63) / 64), whole = ((a.M + 127) / 128) * ((a.N + 127) / 128);
+    if (a.batch == 1 || wave * a.batch <= cus || whole * a.batch > cus || (!a.transA && (a.transB || a.N <= 64))) return false;
+    const int64_t operands = (a.M + a.N) * a.K * a.batch * 2, on = wave < kXcds ? wave : kXcds, before = whole < kXcds ? whole : kXcds;
+    const int64_t more_of_c = (a.M * a.N * a.batch) * (elem_bytes(a.out_dtype) * (a.beta != 0.0f ? 2 : 1) - 2);
+    if (operands * (on - before) - 3 * more_of_c >= kSpreadBytes) return true;
+    return a.transA && !a.transB && a.K > kSpreadKTN && 4 * whole * a.batch <= 3 * cus && operands * on - 3 * more_of_c > kSpreadBytesTN;
+}
+
 }  // namespace
 
 int whole_tile_variant(const Args& a, int variant, int64_t cus) {
     if (variant != 5 && variant != 12) return -1;
-    const int wave_tile = whole_128_tiles_ahead(a, cus) || long_straddling_tn(a, cus) ? -1 : wave_tile_for(a, cus, nullptr);
+    const int wave_tile = whole_128_tiles_ahead(a, cus) || long_straddling_tn(a, cus) || spread_batch(a, cus) ? -1 : wave_tile_for(a, cus, nullptr);
     if (wave_tile >= 0) return wave_tile;
     if (variant == 5 && !a.transA && a.N <= 64 && a.K >= kNarrowK && tile_variant_supports(a, 18)) return 18;
     const int64_t tiles = ((a.M + 127) / 128) * ((a.N + 127) / 128) * a.batch;

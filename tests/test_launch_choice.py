@@ -153,3 +153,13 @@ def test_the_plan_does_not_depend_on_the_epilogue():
             assert in_f32[0] != TILE or in_f32[2] == 1, call
     plan, launched = both(2048, 2048, 128, "NT", batch=32, reads_c=True)      # (the persistent kernel, but for a C that is read)
     assert plan[0].startswith("shortk_") and launched == ("dma_128x128x32_w2x2_s3", 1)
+
+
+def test_batches_whose_matrices_the_wave_tiles_spread_over_more_l2s():
+    small, w64 = ("dma_128x128x32_w2x2_s4", 1), ("wavek_64x64x64_w4", 1)
+    for call, batch in [((360, 120, 1696, "NN"), 42), ((120, 264, 1544, "TN"), 29), ((240, 96, 736, "TT"), 48), ((80, 256, 1888, "NN"), 45),
+                        ((152, 176, 888, "TN"), 34)]:
+        assert both(*call, batch=batch) == (small, small), call
+    for call, batch in [((360, 120, 1696, "NN"), 20), ((360, 120, 256, "TT"), 42), ((568, 64, 568, "NN"), 51), ((592, 64, 1888, "NT"), 37),
+                        ((512, 512, 1696, "TT"), 6)]:
+        assert both(*call, batch=batch)[1][0].startswith("wavek_"), (call, both(*call, batch=batch))
