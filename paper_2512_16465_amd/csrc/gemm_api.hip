@@ -443,15 +443,14 @@ int few_rows_wave_tile(const Args& a, const gemm_plan_t& plan, int64_t cus) {
     return wave < 0.93 * time ? kManyRows : -1;
 }
 
-// Whether a call is cut along k does not depend on the epilogue (beta, bias, activation, the type of C), so the wave tiles are
-// estimated without one: a caller that made a call without reading C, so that the workspace is there, and then captures it
-// with beta = 1 must not find that the second one needs a workspace and the first did not (112x6664x2712 TT was such a call:
-// one launch with C written only, 4 shares with C read).  44 random calls whose choice this moved took 0.85 of the time (1.05
-// at most; weights from memory 0.89 and 1.14).
+// Whether a call is cut along k does not depend on beta, the bias or the activation, so the wave tiles are estimated for one
+// epilogue per type of C, a C of 32 bits as read and one of 16 as written only: a caller that made a call without reading C, so
+// that the workspace is there, and then captures it with beta = 1 must not find that the second one needs a workspace and the
+// first did not (112x6664x2712 TT was such a call: one launch with C written only, 4 shares with C read).
 TileChoice choose_tile(const Args& call, int num_cus) {
     TileChoice c = choose_shared_k_tile(call, num_cus);      // (which asks the epilogue only whether the persistent kernel takes it)
     Args a = call;
-    a.beta = 0.0f; a.bias = nullptr; a.act = gemm::ACT_NONE; a.out_dtype = a.dtype;
+    a.beta = a.out_dtype == gemm::DT_F32 ? 1.0f : 0.0f; a.bias = nullptr; a.act = gemm::ACT_NONE;
     const int64_t cus = num_cus > 0 ? num_cus : 256;
     if (a.dtype == gemm::DT_F32 || c.time <= 0.0 || c.variant == kPersistentShortK) return c;
     double time = 0.0;
