@@ -128,14 +128,17 @@ constexpr int64_t kNarrowK = 768;
 
 // C = alpha op(A) op(B) and nothing else on whole 128x128 tiles leaves that kernel straight from its registers.  There the wave
 // tiles, which add their sums through LDS first, are level at best up to K = 128 (batch of 21 256x256x64 NT 4.8 us against 6.0,
-// of 5 512x512x128 5.2 against 6.2), and beyond one of them to a unit up to K = 1536 (batch of 17 512x128x512 NN 7.9 against
-// 9.8, 3072x384x256 NT 6.0 against 6.6): 247 such random calls 1.03 times as long on them, up to 1.39. Ragged tiles, a C that
-// is read, a bias or an activation take the staged epilogue, and the wave tiles are ahead of it.
-constexpr int64_t kWholeShortK = 128, kWholeK = 1536;
+// of 5 512x512x128 5.2 against 6.2), and beyond one of them to a unit up to K = 1536 in a batch (of 17 512x128x512 NN 7.9 against
+// 9.8), up to 512 in a single matrix (168 random calls 1.02 times as long on them out of the last-level cache, 0.97 from memory;
+// with A stored K x M and B row-major up to 1024, 100 calls 1.07 and 1.02).  From there on the wave tiles are ahead (168 calls 0.94
+// and 0.80: 5632x256x1280 NN 14.6 us against 16.7).  Ragged tiles, a C that is read, a bias or an activation take the staged
+// epilogue, and the wave tiles are ahead of it.
+constexpr int64_t kWholeShortK = 128, kWholeK = 512, kWholeKTN = 1024, kWholeKBatch = 1536;
 
 bool whole_128_tiles_ahead(const Args& a, int64_t cus) {
     if (a.beta != 0.0f || a.bias || a.act != ACT_NONE || a.M % 128 || a.N % 128) return false;
-    return a.M / 64 * (a.N / 64) * a.batch > cus ? a.K < kWholeK : a.K <= kWholeShortK;
+    if (a.M / 64 * (a.N / 64) * a.batch <= cus) return a.K <= kWholeShortK;
+    return a.K < (a.batch > 1 ? kWholeKBatch : a.transA && !a.transB ? kWholeKTN : kWholeK);
 }
 
 namespace {
