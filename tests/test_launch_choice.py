@@ -49,7 +49,7 @@ def test_whole_tiles_that_leave_straight_from_the_registers():
     assert both(512, 512, 136, "NT", batch=4)[1] == w64 and both(512, 640, 128, "NT", batch=4)[1] != w64      # up to one tile to a unit: K > 128
     assert both(1536, 1024, 512)[1] == w64 and both(1536, 1024, 504)[1] != w64                                # beyond: from 512 on, TN 1024
     assert both(1536, 1024, 1024, "TN")[1] == w64 and both(1536, 1024, 1016, "TN")[1] != w64
-    assert both(512, 128, 1536, "NN", batch=17)[1] == w64 and both(512, 128, 1528, "NN", batch=17)[1] != w64  # a batch: 1536
+    assert both(512, 128, 1536, "NT", batch=17)[1] == w64 and both(512, 128, 1528, "NT", batch=17)[1] != w64  # a batch: 1536
     assert both(504, 512, 64, "NT", batch=5)[1] == w64                                                        # ragged
 
 
